@@ -2,25 +2,20 @@
 // the scan) on channel-major maps, over the channels of each position:
 //     layer norm: out = (x - mean_c x) / sqrt(var_c x + eps) * gamma[c] + beta[c]      (biased variance)
 //     RMS norm:   out = x / sqrt(mean_c x^2 + eps) * gamma[c] (+ beta[c])
-// HBM-bound (one read, one write per element; the second and third pass over a workgroup's tile come from L2).  A
-// workgroup owns 32 groups of E consecutive positions (E = 4 when H*W is a multiple of 4, else 1); its threads split the
-// channels eight ways (half-wavefront s takes channels s, s + 8, ...), so every load is a row segment of 32 vectors,
-// eight loads in flight per thread, and the per-position sums of the eight parts meet in LDS in a fixed order.  The
-// mean is taken first and the variance as the mean of squared deviations (no cancellation), then the tile is read a
-// third time and written.
+// Bound: HBM (one read, one write per element).  The mean is taken first and the variance as the mean of squared
+// deviations (no cancellation).
+// scan2d_norm_kernel, up to 512 channels: a workgroup owns 64 positions, 16 lanes x 4 consecutive ones, and its 16 rows of
+// lanes take every 16th channel (any alignment, any H*W of at least 4).  A thread keeps its C / 16 channels x 4 positions
+// in registers as they were loaded, all loads in flight at once, so the tensor is read once; the sums over the 16 parts
+// go over the lanes of a wavefront and then through LDS, in a fixed order.
+// scan2d_norm_any_kernel, any shape: 32 groups of E consecutive positions per workgroup, the channels split eight ways,
+// three passes over the tile (the second and third from L2).
 #include "scan2d_block.hpp"
 
-#include "scan2d_common.hpp"
+#include "scan2d_contract.hpp"
 
 namespace scan2d {
 namespace {
-
-typedef float float2v __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack2_bf16_norm(float lo, float hi) {  // nearest even, one v_cvt_pk_bf16_f32
-    const float2v v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2v));
-}
 
 struct NormArgs {
     const void* in; const float* gamma; const float* beta; void* out;
@@ -29,10 +24,78 @@ struct NormArgs {
     long long P, groups;            // positions per map, groups of E positions per map
 };
 
+// CPT: channels per thread, 16 CPT >= C
+template <typename T, int CPT>
+__global__ __launch_bounds__(256) void scan2d_norm_kernel(const NormArgs p) {
+    constexpr int XW = words_of<T, 4>();
+    __shared__ float red[2][4][64];
+    const int tid = threadIdx.x, n = tid & 15, part = tid >> 4, wv = tid >> 6;
+    const uint32_t P = (uint32_t)p.P, tiles = (P + 63u) / 64u;
+    const int b = (int)(blockIdx.x / tiles), C = p.C;
+    const LanePos pos((blockIdx.x % tiles) * 64u, n, P);
+    const T* src = static_cast<const T*>(p.in) + (size_t)b * C * P + pos.s;
+    uint32_t raw[CPT][XW];
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) load_words_any<XW>(src + (size_t)min(part + 16 * k, C - 1) * P, raw[k]);
+    const float invC = 1.0f / (float)C;
+    auto total = [&](int buf, float* v) {                 // sum over the 16 parts, every thread gets it
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            v[t] += __shfl_xor(v[t], 16);
+            v[t] += __shfl_xor(v[t], 32);
+        }
+        if ((tid & 48) == 0) *reinterpret_cast<float4*>(&red[buf][wv][4 * n]) = make_float4(v[0], v[1], v[2], v[3]);
+        __syncthreads();
+        float4 t = *reinterpret_cast<const float4*>(&red[buf][0][4 * n]);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) {
+            const float4 a = *reinterpret_cast<const float4*>(&red[buf][w][4 * n]);
+            t.x += a.x; t.y += a.y; t.z += a.z; t.w += a.w;
+        }
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    };
+    float mean[4] = {0.0f, 0.0f, 0.0f, 0.0f}, v[4] = {0.0f, 0.0f, 0.0f, 0.0f}, rstd[4];
+    if (!p.rms) {
+#pragma unroll
+        for (int k = 0; k < CPT; ++k)
+            if (part + 16 * k < C) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) mean[t] += get_elem<T, 4>(raw[k], t);
+            }
+        total(0, mean);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) mean[t] *= invC;
+    }
+#pragma unroll
+    for (int k = 0; k < CPT; ++k)
+        if (part + 16 * k < C) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float e = get_elem<T, 4>(raw[k], t) - mean[t];
+                v[t] = fmaf(e, e, v[t]);
+            }
+        }
+    total(1, v);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) rstd[t] = 1.0f / sqrtf(v[t] * invC + p.eps);
+    T* dst = static_cast<T*>(p.out) + (size_t)b * C * P;
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        const int c = part + 16 * k;
+        if (c < C) {
+            const float gm = p.gamma[c], bt = p.beta ? p.beta[c] : 0.0f;
+            float o[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) o[t] = fmaf((get_elem<T, 4>(raw[k], t) - mean[t]) * rstd[t], gm, bt);
+            pos.store(dst + (size_t)c * P, o);
+        }
+    }
+}
+
 constexpr int kNormGroups = 32, kNormSplit = 8, kNormDeep = 8;   // position groups and channel parts per workgroup, loads in flight
 static_assert(kNormGroups * kNormSplit == 256, "one thread per (position group, channel part)");
 template <typename T, int E>
-__global__ __launch_bounds__(256) void scan2d_norm_kernel(const NormArgs p) {
+__global__ __launch_bounds__(256) void scan2d_norm_any_kernel(const NormArgs p) {
     constexpr int EB = Elem<T>::kBytes;
     __shared__ float red[kNormSplit][kNormGroups][E];
     const int tid = threadIdx.x, q = tid % kNormGroups, cq = tid / kNormGroups;
@@ -116,7 +179,7 @@ __global__ __launch_bounds__(256) void scan2d_norm_kernel(const NormArgs p) {
                 T* d = dst + (size_t)c * p.P;
                 if constexpr (E == 4 && EB == 2) {
                     uint2 r;
-                    r.x = pack2_bf16_norm(o[0], o[1]); r.y = pack2_bf16_norm(o[2], o[3]);
+                    r.x = pack_bf16x2(o[0], o[1]); r.y = pack_bf16x2(o[2], o[3]);
                     *reinterpret_cast<uint2*>(d) = r;
                 } else if constexpr (E == 4) {
                     *reinterpret_cast<float4*>(d) = make_float4(o[0], o[1], o[2], o[3]);
@@ -137,18 +200,30 @@ int block_norm_launch(const scan2d_desc* d, int kind, float eps, const void* in,
     a.in = in; a.gamma = gamma; a.beta = beta; a.out = out;
     a.C = d->Dc; a.Bt = d->Bt; a.rms = kind; a.eps = eps;
     a.P = (long long)d->H * d->W;
+    const bool bf16 = d->dtype == SCAN2D_BF16;
+    (void)hipGetLastError();
+    if (a.P >= 4 && a.P < (1LL << 31) && a.C <= 512) {
+        const long long blocks = (a.P + 63) / 64 * d->Bt;
+        if (blocks > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+        using Kernel = void (*)(const NormArgs);
+        Kernel k;
+        if (a.C <= 64) k = bf16 ? scan2d_norm_kernel<bf16_t, 4> : scan2d_norm_kernel<float, 4>;
+        else if (a.C <= 128) k = bf16 ? scan2d_norm_kernel<bf16_t, 8> : scan2d_norm_kernel<float, 8>;
+        else if (a.C <= 256) k = bf16 ? scan2d_norm_kernel<bf16_t, 16> : scan2d_norm_kernel<float, 16>;
+        else k = bf16 ? scan2d_norm_kernel<bf16_t, 32> : scan2d_norm_kernel<float, 32>;
+        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+        return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
+    }
     const bool vec = a.P % 4 == 0;
     a.groups = vec ? a.P / 4 : a.P;
     const long long blocks = (a.groups + kNormGroups - 1) / kNormGroups * d->Bt;
     if (blocks > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
-    const bool bf16 = d->dtype == SCAN2D_BF16;
-    (void)hipGetLastError();
     if (bf16) {
-        if (vec) hipLaunchKernelGGL((scan2d_norm_kernel<bf16_t, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((scan2d_norm_kernel<bf16_t, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
+        if (vec) hipLaunchKernelGGL((scan2d_norm_any_kernel<bf16_t, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((scan2d_norm_any_kernel<bf16_t, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
     } else {
-        if (vec) hipLaunchKernelGGL((scan2d_norm_kernel<float, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((scan2d_norm_kernel<float, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
+        if (vec) hipLaunchKernelGGL((scan2d_norm_any_kernel<float, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((scan2d_norm_any_kernel<float, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
     }
     return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
 }

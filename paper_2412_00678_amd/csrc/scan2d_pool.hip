@@ -1,34 +1,27 @@
 // The aggregator behind the last 2DMamba block (Supp. A "Aggregator": attention pooling with two linear layers):
 //     s_k = sum_d w[d] * tanh(sum_m V[d,m] * h[m,k]),   a_k = softmax of s over the bag,   z = sum_k a_k h_k.
-// Three kernels:
+// Three kernels, no workspace (attn holds the scores in between):
 //   scan2d_pool_scores_kernel  : the scores.  V . h is a dense contraction (D x M x positions), so it runs on the matrix
-//                                cores; tanh, the product with w and the sum over the D hidden units are its epilogue.
+//                                cores (scan2d_contract.hpp); tanh, the product with w and the sum over the D hidden
+//                                units are its epilogue.  scan2d_pool_scores_any_kernel: maps of fewer than 4 positions
+//                                or beyond 2^25.
 //   scan2d_pool_softmax_kernel : per batch item, max and sum of exp over the bag in a fixed order, then the weights.
 //   scan2d_pool_sum_kernel     : z[b][m], one workgroup per channel, fixed order.
 #include "scan2d_block.hpp"
 
 #include <algorithm>
 
-#include "scan2d_common.hpp"
+#include "scan2d_contract.hpp"
 
 namespace scan2d {
 namespace {
 
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef float float4v __attribute__((ext_vector_type(4)));
-
-constexpr int kPoolTile = 64;        // positions per tile: 16 per wavefront
-constexpr int kPoolRows = 128;       // hidden units, zero-padded: 8 MFMA row blocks
-template <typename T> struct PoolTile;
-// kChunk channels of V and of the tile of h are in LDS at a time; row pitches: the 16 lanes of a k-group that read one
-// row each with a 64- or 128-bit load are 16 bytes apart mod 256, the four k-groups of the tile of h 64 bytes
-template <> struct PoolTile<bf16_t> { static constexpr int kChunk = 128, kVPitch = 128 + 8, kXPitch = 68; };
-template <> struct PoolTile<float>  { static constexpr int kChunk = 64,  kVPitch = 64 + 4,  kXPitch = 68; };
+constexpr int kPoolRows = 128;       // most hidden units
 
 struct PoolArgs {
     const void* h; const void* V; const float* w; const uint8_t* mask;
     float* attn; float* z;
-    int M, D, Bt, tiles;             // channels, hidden units, batch items, tiles per batch item
+    int M, D, Bt, tiles;             // channels, hidden units, batch items, tiles of 64 positions per batch item
     long long P;                     // positions per map
 };
 
@@ -36,165 +29,154 @@ __device__ __forceinline__ float fast_tanh(float v) {          // 1 - 2 / (1 + e
     return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * (2.0f * kLog2e)));
 }
 
-// Persistent workgroups of 4 wavefronts over tiles of 64 positions.  Everything the MFMA loop reads sits in LDS,
-// zero-filled past M channels, D hidden units and the last position, so the loop carries no guard.  With at most one
-// chunk of channels V goes to LDS once per workgroup.
-// VEC: H*W and M are multiples of 4, so every group of 4 positions (of h) or 4 channels (of V) is one aligned vector
-// that lies inside the tensor or outside it as a whole.
-template <typename T, bool VEC>
+// A workgroup of four wavefronts per tile of 64 positions; wavefront v takes hidden units 32 v .. 32 v + 31, the parts of
+// a score meet in LDS and are added in wavefront order.
+template <typename T>
 __global__ __launch_bounds__(256) void scan2d_pool_scores_kernel(const PoolArgs p) {
-    constexpr int KC = PoolTile<T>::kChunk, VP = PoolTile<T>::kVPitch, XP = PoolTile<T>::kXPitch, NG = KC / 16;
-    constexpr int EB = Elem<T>::kBytes;
-    using Raw = std::conditional_t<EB == 2, uint16_t, uint32_t>;
-    __shared__ __align__(16) Raw vL[kPoolRows * VP];
-    __shared__ __align__(16) Raw xs[KC * XP];
-    const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6, g = l >> 4, n = l & 15;
-    const int ncol = wv * 16 + n;
-    const int M = p.M, D = p.D;
-    const long long P = p.P;
-    const T* V = static_cast<const T*>(p.V);
-    const int NC = (M + KC - 1) / KC;
-
-    float wr[8][4];                                       // w of the hidden units this lane's accumulators belong to
+    __shared__ float part[4][64];
+    const int tid = threadIdx.x, l = tid & 63, g = l >> 4, n = l & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), d0 = 32 * wv;
+    const int b = blockIdx.x / p.tiles;
+    const uint32_t p0 = (uint32_t)(blockIdx.x % p.tiles) * 64u, P = (uint32_t)p.P;
+    const LanePos pos(p0, n, P);
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (d0 < p.D) {
+        f32x4 acc[2][4];
 #pragma unroll
-    for (int rb = 0; rb < 8; ++rb)
+        for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int d = rb * 16 + 4 * g + i;
-            const float v = p.w[min(d, D - 1)];
-            wr[rb][i] = d < D ? v : 0.0f;
-        }
-
-    auto load_v = [&](int chunk) {                        // V[:, chunk] -> LDS, zero past D rows and M channels
-        if constexpr (VEC) {
-            using Vec = std::conditional_t<EB == 2, uint2, uint4>;
-            constexpr int VPR = KC / 4, RPI = 256 / VPR;  // vectors per row, rows per iteration
-            const int vq = tid % VPR, r0 = tid / VPR;
-            const int c = chunk * KC + 4 * vq;
-            Vec v[kPoolRows / RPI];
+            for (int t = 0; t < 4; ++t) acc[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        contract<T, 2, 2>(static_cast<const T*>(p.h) + (size_t)b * p.M * P, P, pos.s, static_cast<const T*>(p.V), p.M, p.D, d0, 0, p.M, acc);
 #pragma unroll
-            for (int it = 0; it < kPoolRows / RPI; ++it) {
-                const int d = r0 + it * RPI;
-                const Vec t = *reinterpret_cast<const Vec*>(V + (size_t)min(d, D - 1) * M + min(c, M - 4));
-                v[it] = (d < D && c < M) ? t : Vec{};
+        for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int d = d0 + 16 * ot + 4 * g + i;
+                const float wd = p.w[min(d, p.D - 1)];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) s[t] = d < p.D ? fmaf(wd, fast_tanh(acc[ot][t][i]), s[t]) : s[t];
             }
-#pragma unroll
-            for (int it = 0; it < kPoolRows / RPI; ++it) *reinterpret_cast<Vec*>(vL + (size_t)(r0 + it * RPI) * VP + 4 * vq) = v[it];
-        } else {
-            constexpr int RPI = 256 / KC;                 // rows per iteration
-            const int col = tid % KC, r0 = tid / KC;
-            const int c = chunk * KC + col;
-#pragma unroll 8
-            for (int it = 0; it < kPoolRows / RPI; ++it) {
-                const int d = r0 + it * RPI;
-                const uint32_t bits = elem_bits(V + (size_t)min(d, D - 1) * M + min(c, M - 1));
-                vL[d * VP + col] = (Raw)((d < D && c < M) ? bits : 0u);
-            }
-        }
-    };
-    if (NC == 1) load_v(0);
-
-    const long long total = (long long)p.tiles * p.Bt;
-    for (long long tile = blockIdx.x; tile < total; tile += gridDim.x) {
-        const int b = (int)(tile / p.tiles);
-        const long long p0 = (tile % p.tiles) * kPoolTile;
-        const T* hb = static_cast<const T*>(p.h) + (size_t)b * M * P;
-        float4v acc[8];
-#pragma unroll
-        for (int rb = 0; rb < 8; ++rb) acc[rb] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-        for (int chunk = 0; chunk < NC; ++chunk) {
-            __syncthreads();                              // the previous products have read both regions
-            if (NC > 1) load_v(chunk);
-            if constexpr (VEC) {
-                using Vec = std::conditional_t<EB == 2, uint2, uint4>;
-                const int cr0 = tid >> 4, q = tid & 15;
-                const long long pp = p0 + 4 * q;
-                const bool pin = pp < P;
-                const T* src = hb + (size_t)min(pp, P - 4);
-                Vec v[KC / 16];
-#pragma unroll
-                for (int it = 0; it < KC / 16; ++it) {
-                    const int c = chunk * KC + cr0 + 16 * it;
-                    const Vec t = *reinterpret_cast<const Vec*>(src + (size_t)min(c, M - 1) * P);
-                    v[it] = (pin && c < M) ? t : Vec{};
-                }
-#pragma unroll
-                for (int it = 0; it < KC / 16; ++it) *reinterpret_cast<Vec*>(xs + (size_t)(cr0 + 16 * it) * XP + 4 * q) = v[it];
-            } else {
-                const int pos = tid & 63, c0 = tid >> 6;
-                const long long pp = p0 + pos;
-                const bool pin = pp < P;
-                const T* src = hb + (size_t)min(pp, P - 1);
-#pragma unroll 8
-                for (int it = 0; it < KC / 4; ++it) {
-                    const int c = chunk * KC + c0 + 4 * it;
-                    const uint32_t bits = elem_bits(src + (size_t)min(c, M - 1) * P);
-                    xs[(c0 + 4 * it) * XP + pos] = (Raw)((pin && c < M) ? bits : 0u);
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int kg = 0; kg < NG; ++kg) {
-                const Raw* col = xs + (size_t)(kg * 16 + 4 * g) * XP + ncol;
-                if constexpr (EB == 2) {
-                    short4v bf;
-                    bf.x = (short)col[0]; bf.y = (short)col[XP]; bf.z = (short)col[2 * XP]; bf.w = (short)col[3 * XP];
-#pragma unroll
-                    for (int rb = 0; rb < 8; ++rb) {
-                        const uint2 t = *reinterpret_cast<const uint2*>(vL + (size_t)(rb * 16 + n) * VP + kg * 16 + 4 * g);
-                        short4v af;
-                        af.x = (short)(t.x & 0xffffu); af.y = (short)(t.x >> 16); af.z = (short)(t.y & 0xffffu); af.w = (short)(t.y >> 16);
-                        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af, bf, acc[rb], 0, 0, 0);
-                    }
-                } else {
-                    // the 16 channels of the group are contracted in the order (k-group of the lane, step) on both operands
-                    const float b0 = __uint_as_float(col[0]), b1 = __uint_as_float(col[XP]);
-                    const float b2 = __uint_as_float(col[2 * XP]), b3 = __uint_as_float(col[3 * XP]);
-#pragma unroll
-                    for (int rb = 0; rb < 8; ++rb) {
-                        const float4 a = *reinterpret_cast<const float4*>(vL + (size_t)(rb * 16 + n) * VP + kg * 16 + 4 * g);
-                        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b0, acc[rb], 0, 0, 0);
-                        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b1, acc[rb], 0, 0, 0);
-                        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b2, acc[rb], 0, 0, 0);
-                        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b3, acc[rb], 0, 0, 0);
-                    }
-                }
-            }
-        }
-        // ---- s = w . tanh(.): this lane holds hidden units rb*16 + 4g + i of position ncol
-        float s = 0.0f;
-#pragma unroll
-        for (int rb = 0; rb < 8; ++rb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s = fmaf(wr[rb][i], fast_tanh(acc[rb][i]), s);
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        if (g == 0 && p0 + ncol < P) p.attn[(size_t)b * P + p0 + ncol] = s;
     }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        s[t] += __shfl_xor(s[t], 16);
+        s[t] += __shfl_xor(s[t], 32);
+    }
+    if (g == 0) *reinterpret_cast<float4*>(&part[wv][4 * n]) = make_float4(s[0], s[1], s[2], s[3]);
+    __syncthreads();
+    if (tid < 16) {
+        float4 v = *reinterpret_cast<const float4*>(&part[0][4 * n]);
+#pragma unroll
+        for (int q = 1; q < 4; ++q) {
+            const float4 a = *reinterpret_cast<const float4*>(&part[q][4 * n]);
+            v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+        }
+        const float o[4] = {v.x, v.y, v.z, v.w};
+        pos.store(p.attn + (size_t)b * P, o);
+    }
+}
+
+// Any map: one wavefront per position, lane d and d + 64.
+template <typename T>
+__global__ __launch_bounds__(64) void scan2d_pool_scores_any_kernel(const PoolArgs p) {
+    const long long b = blockIdx.x / p.P, pos = blockIdx.x % p.P;
+    const T* h = static_cast<const T*>(p.h) + (size_t)b * p.M * p.P + pos;
+    float s = 0.0f;
+    for (int d = threadIdx.x; d < p.D; d += 64) {
+        const T* v = static_cast<const T*>(p.V) + (size_t)d * p.M;
+        float acc = 0.0f;
+        for (int m = 0; m < p.M; ++m) acc = fmaf(widen_bits<T>(elem_bits(v + m)), widen_bits<T>(elem_bits(h + (size_t)m * p.P)), acc);
+        s = fmaf(p.w[d], fast_tanh(acc), s);
+    }
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1) s += __shfl_xor(s, step);
+    if (threadIdx.x == 0) p.attn[(size_t)b * p.P + pos] = s;
 }
 
 constexpr int kSoftThreads = 1024;
 // Sum or maximum over the workgroup in a fixed order; every thread gets the result.
 template <bool MAX>
 __device__ __forceinline__ float block_reduce(float v, float* red) {
-    const int tid = threadIdx.x;
-    red[tid] = v;
-    __syncthreads();
-    for (int step = kSoftThreads / 2; step > 0; step >>= 1) {
-        if (tid < step) red[tid] = MAX ? fmaxf(red[tid], red[tid + step]) : red[tid] + red[tid + step];
-        __syncthreads();
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1) {
+        const float o = __shfl_xor(v, step);
+        v = MAX ? fmaxf(v, o) : v + o;
     }
-    const float r = red[0];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float r = red[0];
+#pragma unroll
+    for (int w = 1; w < kSoftThreads / 64; ++w) r = MAX ? fmaxf(r, red[w]) : r + red[w];
     __syncthreads();
     return r;
 }
 
 // One workgroup per batch item, in place: scores -> attention weights.  Positions under the mask are not members of
-// the bag: they are skipped by the maximum and the sum and get weight 0; an empty bag gets all zeros.  Every thread
-// walks its positions four loads deep (VEC: four aligned groups of 4 positions), in an order fixed by the shape.
-template <bool VEC>
+// the bag: they are skipped by the maximum and the sum and get weight 0; an empty bag gets all zeros.
+// Maps of 4 to 16384 NV / 4 positions: a thread keeps its NV groups of 4 positions in registers (scores outside the bag
+// as -infinity), so the scores are read once and written once, all loads in flight together.  The one compute unit of a
+// batch item moves 8 bytes per position: 65536 positions took 14 us in three passes.
+template <int NV>
 __global__ __launch_bounds__(kSoftThreads) void scan2d_pool_softmax_kernel(const PoolArgs p) {
-    __shared__ float red[kSoftThreads];
+    __shared__ float red[kSoftThreads / 64];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const uint32_t P = (uint32_t)p.P;
+    float* a = p.attn + (size_t)b * P;
+    const uint8_t* mk = p.mask ? p.mask + (size_t)b * P : nullptr;
+    float sv[NV][4];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const uint32_t q = 4u * (uint32_t)(tid + k * kSoftThreads), s = min(q, P - 4u);
+        load4<float>(a + s, sv[k]);
+        uint32_t m = 0u;
+        if (mk) load_words_any<1>(mk + s, &m);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (s + e < q || ((m >> (8 * e)) & 0xffu) != 0u) sv[k][e] = -INFINITY;    // not this thread's, or not in the bag
+    }
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sv[k][e]);
+    mx = block_reduce<true>(mx, red);
+    float sum = 0.0f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float x = sv[k][e];
+            sv[k][e] = x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((x - mx) * kLog2e);
+            sum += sv[k][e];
+        }
+    sum = block_reduce<false>(sum, red);
+    const float inv = sum > 0.0f ? 1.0f / sum : 0.0f;     // a NaN score makes the sum NaN: the weights then are NaN too
+    const bool bad = sum != sum;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const uint32_t q = 4u * (uint32_t)(tid + k * kSoftThreads);
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = sv[k][e] * inv;
+        if (bad) {                                        // members only; the mask again
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (q + e < P && mk && mk[q + e] != 0) ? 0.0f : sum;
+        }
+        if (q + 4u <= P) store4<float>(a + q, o);
+        else if (q < P) {
+            const uint32_t s = P - 4u;
+#pragma unroll
+            for (int e = 1; e < 4; ++e)
+                if (s + e >= q) a[s + e] = bad ? ((mk && mk[s + e] != 0) ? 0.0f : sum) : o[e];
+        }
+    }
+}
+
+// The same for any map, in three passes: every thread walks its positions four loads deep (VEC: four aligned groups of 4
+// positions), in an order fixed by the shape.
+template <bool VEC>
+__global__ __launch_bounds__(kSoftThreads) void scan2d_pool_softmax_any_kernel(const PoolArgs p) {
+    __shared__ float red[kSoftThreads / 64];
     constexpr int E = VEC ? 4 : 1;                        // positions per load
     const int b = blockIdx.x, tid = threadIdx.x;
     const long long P = p.P, PV = P / E;
@@ -241,54 +223,38 @@ __global__ __launch_bounds__(kSoftThreads) void scan2d_pool_softmax_kernel(const
     });
 }
 
-// z[b][m] = sum over the bag of a_k * h[m][k]: grid (M, Bt), fixed order (strided partial sums four loads deep, then a
-// tree over the workgroup).
-template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void scan2d_pool_sum_kernel(const PoolArgs p) {
-    __shared__ float red[256];
-    constexpr int E = VEC ? 4 : 1, EB = Elem<T>::kBytes;
+// z[b][m] = sum over the bag of a_k * h[m][k]: grid (M, Bt), fixed order (strided partial sums of groups of 4 positions,
+// any alignment, four loads deep, then over the workgroup).  Maps of fewer than 4 positions: one position per thread.
+template <typename T>
+__global__ __launch_bounds__(kSoftThreads) void scan2d_pool_sum_kernel(const PoolArgs p) {
+    __shared__ float red[kSoftThreads / 64];
     const int m = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    const long long P = p.P, PV = P / E;
+    const long long P = p.P;
     const T* hr = static_cast<const T*>(p.h) + ((size_t)b * p.M + m) * P;
     const float* a = p.attn + (size_t)b * P;
     float acc = 0.0f;
-    for (long long base = 0; base < PV; base += 4 * 256) {
-        float av[4][E], hv[4][E];
+    if (P >= 4) {
+        for (long long base = 0; base < P; base += 16 * kSoftThreads) {
+            float av[4][4], hv[4][4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const long long idx = min(base + u * 256 + tid, PV - 1);
-            if constexpr (VEC) {
-                const float4 t = *reinterpret_cast<const float4*>(a + 4 * idx);
-                av[u][0] = t.x; av[u][1] = t.y; av[u][2] = t.z; av[u][3] = t.w;
-                if constexpr (EB == 2) {
-                    const uint2 r = *reinterpret_cast<const uint2*>(hr + 4 * idx);
-                    hv[u][0] = __uint_as_float(r.x << 16); hv[u][1] = __uint_as_float(r.x & 0xffff0000u);
-                    hv[u][2] = __uint_as_float(r.y << 16); hv[u][3] = __uint_as_float(r.y & 0xffff0000u);
-                } else {
-                    const float4 r = *reinterpret_cast<const float4*>(hr + 4 * idx);
-                    hv[u][0] = r.x; hv[u][1] = r.y; hv[u][2] = r.z; hv[u][3] = r.w;
-                }
-            } else {
-                av[u][0] = a[idx];
-                const uint32_t bits = elem_bits(hr + idx);
-                hv[u][0] = EB == 4 ? __uint_as_float(bits) : __uint_as_float(bits << 16);
+            for (int u = 0; u < 4; ++u) {
+                const long long s = min(base + 4 * (u * kSoftThreads + tid), P - 4);
+                load4<float>(a + s, av[u]);
+                load4<T>(hr + s, hv[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const long long q = base + 4 * (u * kSoftThreads + tid), s = min(q, P - 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)                // weight 0: outside the bag, never read into the sum
+                    acc += (s + e >= q && av[u][e] != 0.0f) ? av[u][e] * hv[u][e] : 0.0f;
             }
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (base + u * 256 + tid < PV) {
-#pragma unroll
-                for (int e = 0; e < E; ++e) acc += av[u][e] != 0.0f ? av[u][e] * hv[u][e] : 0.0f;   // weight 0: outside the bag, never read into the sum
-            }
-        }
+    } else if (tid < P) {
+        acc = a[tid] != 0.0f ? a[tid] * widen_bits<T>(elem_bits(hr + tid)) : 0.0f;
     }
-    red[tid] = acc;
-    __syncthreads();
-    for (int step = 128; step > 0; step >>= 1) {
-        if (tid < step) red[tid] += red[tid + step];
-        __syncthreads();
-    }
-    if (tid == 0) p.z[(size_t)b * p.M + m] = red[0];
+    acc = block_reduce<false>(acc, red);
+    if (tid == 0) p.z[(size_t)b * p.M + m] = acc;
 }
 
 }  // namespace
@@ -300,23 +266,25 @@ int block_attn_pool_launch(const scan2d_desc* d, int D, const void* h, const voi
     a.h = h; a.V = V; a.w = w; a.mask = mask; a.attn = attn; a.z = z;
     a.M = d->Dc; a.D = D; a.Bt = d->Bt;
     a.P = (long long)d->H * d->W;
-    const long long tiles = (a.P + kPoolTile - 1) / kPoolTile;
-    if (tiles * d->Bt > 2147483647LL || d->Bt > 65535) return SCAN2D_ERR_BAD_SHAPE;
+    const long long tiles = (a.P + 63) / 64;
+    const bool bf16 = d->dtype == SCAN2D_BF16, fits = contract_fits(a.P, D, a.M, bf16 ? 2 : 4);
+    if ((fits ? tiles : a.P) * d->Bt > 2147483647LL || d->Bt > 65535) return SCAN2D_ERR_BAD_SHAPE;
     a.tiles = (int)tiles;
-    const bool bf16 = d->dtype == SCAN2D_BF16;
     (void)hipGetLastError();
-    const long long grid = std::min<long long>(tiles * d->Bt, 2 * 256);       // persistent: V is staged once per workgroup
-    const bool vec = a.P % 4 == 0 && a.M % 4 == 0;
-    const dim3 g1((unsigned)grid), g2((unsigned)d->Bt), g3((unsigned)d->Dc, (unsigned)d->Bt);
-#define SCAN2D_POOL_LAUNCH(T, VEC)                                                                        \
-    do {                                                                                                  \
-        hipLaunchKernelGGL((scan2d_pool_scores_kernel<T, VEC>), g1, dim3(256), 0, stream, a);             \
-        hipLaunchKernelGGL(scan2d_pool_softmax_kernel<VEC>, g2, dim3(kSoftThreads), 0, stream, a);        \
-        hipLaunchKernelGGL((scan2d_pool_sum_kernel<T, VEC>), g3, dim3(256), 0, stream, a);                \
-    } while (0)
-    if (bf16) { if (vec) SCAN2D_POOL_LAUNCH(bf16_t, true); else SCAN2D_POOL_LAUNCH(bf16_t, false); }
-    else { if (vec) SCAN2D_POOL_LAUNCH(float, true); else SCAN2D_POOL_LAUNCH(float, false); }
-#undef SCAN2D_POOL_LAUNCH
+    const dim3 g1((unsigned)((fits ? tiles : a.P) * d->Bt)), g2((unsigned)d->Bt), g3((unsigned)d->Dc, (unsigned)d->Bt);
+    using Kernel = void (*)(const PoolArgs);
+    Kernel scores, soft;
+    if (fits) scores = bf16 ? scan2d_pool_scores_kernel<bf16_t> : scan2d_pool_scores_kernel<float>;
+    else scores = bf16 ? scan2d_pool_scores_any_kernel<bf16_t> : scan2d_pool_scores_any_kernel<float>;
+    if (a.P < 4) soft = scan2d_pool_softmax_any_kernel<false>;
+    else if (a.P <= 4 * kSoftThreads) soft = scan2d_pool_softmax_kernel<1>;
+    else if (a.P <= 16 * kSoftThreads) soft = scan2d_pool_softmax_kernel<4>;
+    else if (a.P <= 64 * kSoftThreads) soft = scan2d_pool_softmax_kernel<16>;
+    else soft = a.P % 4 == 0 ? scan2d_pool_softmax_any_kernel<true> : scan2d_pool_softmax_any_kernel<false>;
+    hipLaunchKernelGGL(scores, g1, dim3(fits ? 256 : 64), 0, stream, a);
+    hipLaunchKernelGGL(soft, g2, dim3(kSoftThreads), 0, stream, a);
+    if (bf16) hipLaunchKernelGGL(scan2d_pool_sum_kernel<bf16_t>, g3, dim3(kSoftThreads), 0, stream, a);
+    else hipLaunchKernelGGL(scan2d_pool_sum_kernel<float>, g3, dim3(kSoftThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
 }
 
