@@ -85,8 +85,9 @@ template <typename T> constexpr int contract_step() { return Elem<T>::kBytes == 
 
 // `in`: the batch item's map, wave-uniform; s: first position this lane reads; W: row 0, wave-uniform, ldw channels per
 // row; this lane supplies rows min(o0 + 16 ot + n, rows - 1).  DEPTH steps are in flight ahead of the products.
+// TAIL: the channels are not whole steps (a flag, because the element-wise loads of the last ones take many registers).
 // 32-bit byte offsets per lane: 25 rows of positions and the whole of W stay below 2^32 bytes (checked on the host).
-template <typename T, int NOT, int DEPTH>
+template <typename T, int NOT, int DEPTH, bool TAIL>
 __device__ __forceinline__ void contract(const T* __restrict__ in, uint32_t P, uint32_t s, const T* __restrict__ W, int ldw, int rows,
                                          int o0, int cbeg, int cend, f32x4 (&acc)[NOT][4]) {
     constexpr int EB = Elem<T>::kBytes, KS = contract_step<T>(), KL = KS / 4;        // channels per lane and step
@@ -144,6 +145,7 @@ __device__ __forceinline__ void contract(const T* __restrict__ in, uint32_t P, u
             for (int d = 0; d < DEPTH; ++d) {
                 products(d);
                 load(d, cbeg + min(k + d + DEPTH, steps - 1) * KS);
+                __builtin_amdgcn_sched_barrier(0);         // the compiler would gather the products of all buffers in front of the loads
             }
         }
 #pragma unroll
@@ -151,7 +153,7 @@ __device__ __forceinline__ void contract(const T* __restrict__ in, uint32_t P, u
             if (k + d < steps) products(d);
     }
     const int c0 = cbeg + steps * KS;
-    if (c0 < cend) {                      // the last channels: element by element, zero past the end on both operands
+    if (TAIL && c0 < cend) {                      // the last channels: element by element, zero past the end on both operands
         const int cl = c0 + KL * g;
 #pragma unroll
         for (int e = 0; e < KL; ++e) {

@@ -21,19 +21,20 @@ namespace {
 struct LinArgs {
     const void* in; const void* Wt; const float* bias; const void* res; void* out;
     int Cin, Cout, Bt, ogroups;     // ogroups: wavefronts per tile of positions
-    long long ptiles, P, waves;     // tiles of 64 positions per batch item, positions per map, wavefronts with work
+    long long ptiles, P, waves;     // tiles of 64 positions per batch item, positions per map, wavefronts (pieces) with work
 };
 
-template <typename T, int NOT, int DEPTH>
+template <typename T, int NOT, int DEPTH, bool TAIL>
 __global__ __launch_bounds__(256) void scan2d_linear_kernel(const LinArgs p) {
     const long long per = gridDim.x / kXcds;               // the grid is a multiple of 8: workgroups of one XCD follow each other
     const long long wg = (long long)(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-    const long long wave = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (wave >= p.waves) return;
-    const int og = (int)(wave % p.ogroups);
-    const long long rest = wave / p.ogroups;
-    const int b = (int)(rest / p.ptiles);
-    const uint32_t p0 = (uint32_t)(rest % p.ptiles) * 64u, P = (uint32_t)p.P;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int pairs = (p.ogroups + 1) / 2;                 // the workgroup: 2 tiles of positions x 2 groups of output channels
+    const int og = (int)(wg % pairs) * 2 + (wv & 1);
+    const long long tile = wg / pairs * 2 + (wv >> 1);
+    if (og >= p.ogroups || tile >= p.ptiles * p.Bt) return;
+    const int b = (int)(tile / p.ptiles);
+    const uint32_t p0 = (uint32_t)(tile % p.ptiles) * 64u, P = (uint32_t)p.P;
     const int l = threadIdx.x & 63, g = l >> 4, n = l & 15, o0 = og * 16 * NOT;
     const LanePos pos(p0, n, P);
 
@@ -42,7 +43,7 @@ __global__ __launch_bounds__(256) void scan2d_linear_kernel(const LinArgs p) {
     for (int ot = 0; ot < NOT; ++ot)
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    contract<T, NOT, DEPTH>(static_cast<const T*>(p.in) + (size_t)b * p.Cin * P, P, pos.s, static_cast<const T*>(p.Wt), p.Cin, p.Cout, o0,
+    contract<T, NOT, DEPTH, TAIL>(static_cast<const T*>(p.in) + (size_t)b * p.Cin * P, P, pos.s, static_cast<const T*>(p.Wt), p.Cin, p.Cout, o0,
                             0, p.Cin, acc);
 
     const T* res = static_cast<const T*>(p.res);
@@ -68,6 +69,202 @@ __global__ __launch_bounds__(256) void scan2d_linear_kernel(const LinArgs p) {
         }
 }
 
+// bf16, large maps, at most 32 KT input channels in whole steps of 32: a wavefront reads its 64 positions x all channels
+// once, holds them as MFMA operands (16 KT registers) and walks over the output channels, whose rows of Wt it reads from
+// L1 / L2 one block ahead.  With `in` shared by the four wavefronts of a workgroup (above) only 16 KB per compute unit
+// were in flight, two steps deep, and 128 -> 256 channels at 65536 positions took 23 us; here every wavefront has 16 or
+// 32 KB of its own in flight before its first product.
+template <int KT>
+__global__ __launch_bounds__(256) void scan2d_linear_resident_kernel(const LinArgs p, int oblocks) {
+    const long long per = gridDim.x / kXcds;
+    const long long wg = (long long)(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+    const long long wave = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave >= p.waves) return;
+    const int og = (int)(wave % p.ogroups);                // blocks of 16 output channels og * oblocks ..
+    const long long rest = wave / p.ogroups;
+    const int b = (int)(rest / p.ptiles);
+    const uint32_t p0 = (uint32_t)(rest % p.ptiles) * 64u, P = (uint32_t)p.P;
+    const int l = threadIdx.x & 63, g = l >> 4, n = l & 15;
+    const int Cin = p.Cin, steps = Cin / 32;
+    const LanePos pos(p0, n, P);
+    const char* in = reinterpret_cast<const char*>(static_cast<const bf16_t*>(p.in) + (size_t)b * Cin * P);
+    const uint32_t boff = ((uint32_t)(8 * g) * P + pos.s) * 2u;
+
+    bf16x8 bv[KT][4];
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+        const char* base = in + (size_t)min(k, steps - 1) * 64u * P;
+        uint32_t raw[8][2];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) load_words_any<2>(base + (size_t)e * P * 2u + boff, raw[e]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            u32x4_t v;
+#pragma unroll
+            for (int e2 = 0; e2 < 4; ++e2)
+                v[e2] = __builtin_amdgcn_perm(raw[2 * e2 + 1][t / 2], raw[2 * e2][t / 2], t % 2 ? 0x07060302u : 0x05040100u);
+            bv[k][t] = __builtin_bit_cast(bf16x8, v);
+        }
+    }
+    const char* Wt = static_cast<const char*>(p.Wt);
+    u32x4_t av[2][KT];
+    const int o16 = (p.Cout + 15) / 16, ob = og * oblocks, oe = min(ob + oblocks, o16);
+    auto load_a = [&](int buf, int blk) {
+        const uint32_t off = ((uint32_t)min(16 * min(blk, oe - 1) + n, p.Cout - 1) * (uint32_t)Cin + (uint32_t)(8 * g)) * 2u;
+#pragma unroll
+        for (int k = 0; k < KT; ++k) av[buf][k] = *reinterpret_cast<const u32x4_a1*>(Wt + off + (uint32_t)(64 * min(k, steps - 1)));
+    };
+    const bf16_t* res = static_cast<const bf16_t*>(p.res);
+    bf16_t* out = static_cast<bf16_t*>(p.out);
+    auto block = [&](int buf, int blk) {
+        uint32_t rr[4][2];
+        float bias[4];
+        size_t row[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int o = min(16 * blk + 4 * g + i, p.Cout - 1);
+            row[i] = ((size_t)b * p.Cout + o) * P;
+            bias[i] = p.bias ? p.bias[o] : 0.0f;
+            if (res) load_words_any<2>(res + row[i] + pos.s, rr[i]);
+        }
+        f32x4 acc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < KT; ++k)
+            if (k < steps) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[buf][k]), bv[k][t], acc[t], 0, 0, 0);
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = acc[t][i] + bias[i];
+            if (res) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[t] += get_elem<bf16_t, 4>(rr[i], t);
+            }
+            if (16 * blk + 4 * g + i < p.Cout) pos.store(out + row[i], v);
+        }
+    };
+    load_a(0, ob);
+    for (int blk = ob; blk < oe; blk += 2) {
+        load_a(1, blk + 1);
+        block(0, blk);
+        if (blk + 1 < oe) {
+            load_a(0, blk + 2);
+            block(1, blk + 1);
+        }
+    }
+}
+
+// fp32, enough work for every SIMD, input channels in whole steps of 16: the products bound the layer (157 TFLOP/s on
+// v_mfma_f32_16x16x4_f32), and the matrix pipe of a SIMD is best kept busy by ONE wavefront: a loop of 64 products and 8
+// loads ran at 134 TFLOP/s with one wavefront per SIMD, 120 with two and 113 with three (their streams alternate on the
+// pipe and leave gaps).  So the launch is one workgroup per compute unit; its wavefronts walk over (tile of positions,
+// 16 NOT output channels), DEPTH steps of loads ahead of the products, across the end of one piece of work into the next.
+// No load in a branch (the residual is a template flag, a missing bias reads Wt and is not used): the compiler's wait
+// counts would become "everything" at the head of the loop.
+template <int NOT, int DEPTH, bool RES>
+__global__ __launch_bounds__(256, 1) void scan2d_linear_stream_kernel(const LinArgs p) {
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t ptiles = (uint32_t)p.ptiles, ogroups = (uint32_t)p.ogroups;
+    const uint32_t items = (uint32_t)p.waves, stride = gridDim.x * 4;        // below 2^31 (checked on the host)
+    const uint32_t first = ((blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds) * 4 + wv;
+    if (first >= items) return;
+    const int l = threadIdx.x & 63, g = l >> 4, n = l & 15;
+    const int Cin = p.Cin, steps = Cin / 16;
+    const uint32_t P = (uint32_t)p.P;
+
+    struct Piece { const char* in; uint32_t boff, p0; int b, o0; uint32_t aoff[NOT]; };
+    auto piece = [&](uint32_t item) {
+        Piece w;
+        const uint32_t tile = item / ogroups;
+        w.o0 = (int)(item - tile * ogroups) * 16 * NOT;
+        w.b = (int)(tile / ptiles);
+        w.p0 = (tile - (uint32_t)w.b * ptiles) * 64u;
+        w.in = reinterpret_cast<const char*>(static_cast<const float*>(p.in) + (size_t)w.b * Cin * P);
+        w.boff = ((uint32_t)(4 * g) * P + LanePos(w.p0, n, P).s) * 4u;
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot) w.aoff[ot] = ((uint32_t)min(w.o0 + 16 * ot + n, p.Cout - 1) * (uint32_t)Cin + (uint32_t)(4 * g)) * 4u;
+        return w;
+    };
+    uint32_t braw[DEPTH][4][4], araw[DEPTH][NOT][4];
+    auto load = [&](int buf, const Piece& w, int k) {
+        const char* bb = w.in + (size_t)k * 64u * P;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) load_words_any<4>(bb + (size_t)e * P * 4u + w.boff, braw[buf][e]);
+        const char* aa = static_cast<const char*>(p.Wt) + (size_t)k * 64u;
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot) load_words_any<4>(aa + w.aoff[ot], araw[buf][ot]);
+    };
+    f32x4 acc[NOT][4];
+    auto products = [&](int buf) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int ot = 0; ot < NOT; ++ot)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[ot][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(araw[buf][ot][e]), __uint_as_float(braw[buf][e][t]),
+                                                                      acc[ot][t], 0, 0, 0);
+    };
+    const float* res = static_cast<const float*>(p.res);
+    const float* bsrc = p.bias ? p.bias : static_cast<const float*>(p.Wt);   // Wt has Cout rows: at least as many elements
+    float* out = static_cast<float*>(p.out);
+
+    Piece cur = piece(first);
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load(d, cur, d);       // steps is a multiple of DEPTH
+    for (uint32_t item = first; item < items; item += stride) {
+        const Piece next = piece(min(item + stride, items - 1));
+        const LanePos pos(cur.p0, n, P);
+        float add[RES ? NOT : 1][4][4], bias[NOT][4];                // residual and bias, requested in front of the products
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int o = min(cur.o0 + 16 * ot + 4 * g + i, p.Cout - 1);
+                if constexpr (RES) load4<float>(res + ((size_t)cur.b * p.Cout + o) * P + pos.s, add[ot][i]);
+                bias[ot][i] = bsrc[o];
+            }
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k = 0; k < steps - DEPTH; k += DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                products(d);
+                load(d, cur, k + d + DEPTH);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            products(d);
+            load(d, next, d);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int o = cur.o0 + 16 * ot + 4 * g + i;
+                float v[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    v[t] = acc[ot][t][i] + (p.bias ? bias[ot][i] : 0.0f);
+                    if constexpr (RES) v[t] += add[ot][i][t];
+                }
+                if (o < p.Cout) pos.store(out + ((size_t)cur.b * p.Cout + o) * P, v);
+            }
+        cur = next;
+    }
+}
+
 // Any shape: one thread per output, channels in ascending order.
 template <typename T>
 __global__ __launch_bounds__(256) void scan2d_linear_any_kernel(const LinArgs p) {
@@ -88,10 +285,10 @@ __global__ __launch_bounds__(256) void scan2d_linear_any_kernel(const LinArgs p)
 template <typename T, int NOT, int DEPTH>
 int launch(LinArgs a, hipStream_t stream) {
     a.ogroups = (a.Cout + 16 * NOT - 1) / (16 * NOT);
-    a.waves = a.ptiles * a.Bt * a.ogroups;
-    const long long grid = ((a.waves + 3) / 4 + kXcds - 1) / kXcds * kXcds;
+    const long long wgs = (a.ptiles * a.Bt + 1) / 2 * ((a.ogroups + 1) / 2), grid = (wgs + kXcds - 1) / kXcds * kXcds;
     if (grid > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
-    hipLaunchKernelGGL((scan2d_linear_kernel<T, NOT, DEPTH>), dim3((unsigned)grid), dim3(256), 0, stream, a);
+    auto kernel = a.Cin % contract_step<T>() == 0 ? scan2d_linear_kernel<T, NOT, DEPTH, false> : scan2d_linear_kernel<T, NOT, DEPTH, true>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, stream, a);
     return SCAN2D_OK;
 }
 
@@ -100,6 +297,35 @@ int launch(LinArgs a, hipStream_t stream) {
 template <typename T>
 int launch_sized(const LinArgs& a, hipStream_t stream) {
     const long long tiles = a.ptiles * a.Bt, o16 = (a.Cout + 15) / 16;
+    if constexpr (Elem<T>::kBytes == 2) {
+        if (tiles >= 512 && o16 >= 4 && a.Cin % 32 == 0 && a.Cin <= 256) {
+            LinArgs r = a;                                 // two wavefronts per tile until there are four per SIMD
+            r.ogroups = tiles < 4096 ? 2 : 1;
+            const int oblocks = (int)((o16 + r.ogroups - 1) / r.ogroups);
+            r.waves = tiles * r.ogroups;
+            const long long grid = ((r.waves + 3) / 4 + kXcds - 1) / kXcds * kXcds;
+            if (grid > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+            if (a.Cin <= 128) hipLaunchKernelGGL(scan2d_linear_resident_kernel<4>, dim3((unsigned)grid), dim3(256), 0, stream, r, oblocks);
+            else hipLaunchKernelGGL(scan2d_linear_resident_kernel<8>, dim3((unsigned)grid), dim3(256), 0, stream, r, oblocks);
+            return SCAN2D_OK;
+        }
+    }
+    if constexpr (Elem<T>::kBytes == 4) {
+        // 16 NOT output channels per piece: the fewest rounds of 1024 wavefronts, counted in their products
+        const auto cost = [&](long long n) { return (tiles * ((o16 + n - 1) / n) + 1023) / 1024 * n; };
+        if (a.Cin % 64 == 0 && tiles * o16 >= 2048 && tiles * o16 < (1LL << 30)) {
+            LinArgs r = a;
+            const bool four = cost(4) <= cost(2);
+            r.ogroups = (int)((o16 + (four ? 3 : 1)) / (four ? 4 : 2));
+            r.waves = tiles * r.ogroups;
+            using Kernel = void (*)(const LinArgs);
+            Kernel k;
+            if (four) k = a.res ? scan2d_linear_stream_kernel<4, 2, true> : scan2d_linear_stream_kernel<4, 2, false>;
+            else k = a.res ? scan2d_linear_stream_kernel<2, 4, true> : scan2d_linear_stream_kernel<2, 4, false>;
+            hipLaunchKernelGGL(k, dim3(256), dim3(256), 0, stream, r);
+            return SCAN2D_OK;
+        }
+    }
     if (o16 >= 4 && tiles * ((o16 + 3) / 4) >= 2048) return launch<T, 4, 2>(a, stream);
     if (o16 >= 2 && tiles * ((o16 + 1) / 2) >= 2048) return launch<T, 2, 2>(a, stream);
     return launch<T, 1, 4>(a, stream);

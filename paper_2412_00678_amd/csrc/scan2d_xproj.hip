@@ -29,8 +29,8 @@ struct XprojArgs {
 constexpr int kRowBlocks = 3;    // MFMA row blocks of Wx per pass
 
 // KR: low-rank rows per lane group, 4 KR >= R
-template <typename T, int KR>
-__global__ __launch_bounds__(256) void scan2d_xproj_kernel(const XprojArgs p) {
+template <typename T, int KR, bool TAIL>
+__global__ __launch_bounds__(256, 2) void scan2d_xproj_kernel(const XprojArgs p) {
     __shared__ float part[4][kRowBlocks * 16][64];
     __shared__ float low[4 * KR][64];
     const int tid = threadIdx.x, l = tid & 63, g = l >> 4, n = l & 15;
@@ -41,6 +41,17 @@ __global__ __launch_bounds__(256) void scan2d_xproj_kernel(const XprojArgs p) {
     const T* x = static_cast<const T*>(p.x) + (size_t)b * Dc * P;
     const LanePos pos(p0, n, P);
 
+    auto weights = [&](int c0, float* a) {                 // row c0 + n of Wdt, columns KR g ..
+        const float* row = p.Wdt + (size_t)min(c0 + n, Dc - 1) * R;
+#pragma unroll
+        for (int s = 0; s < KR; ++s) {
+            const float v = row[min(KR * g + s, R - 1)];
+            a[s] = KR * g + s < R ? v : 0.0f;
+        }
+    };
+    float a[KR];
+    weights(16 * wv, a);                                   // requested in front of everything else
+
     constexpr int KS = contract_step<T>();
     const int span = ((Dc + KS - 1) / KS + 3) / 4 * KS;    // channels of a wavefront: whole steps
     const int cbeg = min(wv * span, Dc), cend = min(cbeg + span, Dc);
@@ -50,7 +61,7 @@ __global__ __launch_bounds__(256) void scan2d_xproj_kernel(const XprojArgs p) {
         for (int mb = 0; mb < kRowBlocks; ++mb)
 #pragma unroll
             for (int t = 0; t < 4; ++t) acc[mb][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        contract<T, kRowBlocks, 2>(x, P, pos.s, static_cast<const T*>(p.Wx), Dc, M, m0, cbeg, cend, acc);
+        contract<T, kRowBlocks, 2, TAIL>(x, P, pos.s, static_cast<const T*>(p.Wx), Dc, M, m0, cbeg, cend, acc);
         if (m0 > 0) __syncthreads();                       // the sums of the previous rows have been read
 #pragma unroll
         for (int mb = 0; mb < kRowBlocks; ++mb)
@@ -85,16 +96,6 @@ __global__ __launch_bounds__(256) void scan2d_xproj_kernel(const XprojArgs p) {
         const float4 v = *reinterpret_cast<const float4*>(&low[r][4 * n]);
         bl[s][0] = r < R ? v.x : 0.0f; bl[s][1] = r < R ? v.y : 0.0f; bl[s][2] = r < R ? v.z : 0.0f; bl[s][3] = r < R ? v.w : 0.0f;
     }
-    auto weights = [&](int c0, float* a) {                 // row c0 + n of Wdt, columns KR g ..
-        const float* row = p.Wdt + (size_t)min(c0 + n, Dc - 1) * R;
-#pragma unroll
-        for (int s = 0; s < KR; ++s) {
-            const float v = row[min(KR * g + s, R - 1)];
-            a[s] = KR * g + s < R ? v : 0.0f;
-        }
-    };
-    float a[KR];
-    weights(16 * wv, a);
     for (int c0 = 16 * wv; c0 < Dc; c0 += 64) {
         float next[KR];
         weights(c0 + 64, next);
@@ -140,12 +141,17 @@ __global__ __launch_bounds__(256) void scan2d_xproj_any_kernel(const XprojArgs p
     }
 }
 
-template <typename T>
+template <typename T, bool TAIL>
 void launch(const XprojArgs& a, int Bt, hipStream_t stream) {
     const dim3 grid((unsigned)(a.tiles * Bt));
-    if (a.R <= 8) hipLaunchKernelGGL((scan2d_xproj_kernel<T, 2>), grid, dim3(256), 0, stream, a);
-    else if (a.R <= 16) hipLaunchKernelGGL((scan2d_xproj_kernel<T, 4>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((scan2d_xproj_kernel<T, 16>), grid, dim3(256), 0, stream, a);
+    if (a.R <= 8) hipLaunchKernelGGL((scan2d_xproj_kernel<T, 2, TAIL>), grid, dim3(256), 0, stream, a);
+    else if (a.R <= 16) hipLaunchKernelGGL((scan2d_xproj_kernel<T, 4, TAIL>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((scan2d_xproj_kernel<T, 16, TAIL>), grid, dim3(256), 0, stream, a);
+}
+template <typename T>
+void launch(const XprojArgs& a, int Bt, hipStream_t stream) {
+    if (a.Dc % contract_step<T>() == 0) launch<T, false>(a, Bt, stream);
+    else launch<T, true>(a, Bt, stream);
 }
 
 }  // namespace
