@@ -1,7 +1,8 @@
 """Builds the gfx950 shared library `libscan2d.so` (and the roofline probe) with hipcc.
 
 Every translation unit is compiled for gfx950 only, with packed-FP32 instruction selection
-switched off, then linked in-tree next to this file.  Run as `python -m paper_2412_00678_amd.build`.
+switched off, then linked in-tree next to this file.  The host side of the Python binding
+(`_scan2d_py.so`) is a C++ extension against torch's headers and that library.  Run as `python -m paper_2412_00678_amd.build`.
 """
 from __future__ import annotations
 
@@ -28,6 +29,22 @@ UNITS = ["scan2d_elementwise.hip", "scan2d_block.hip", "scan2d_xproj.hip", "scan
 API_UNIT = "scan2d_api.hip"
 REGS_UNITS = ("scan2d_fwd_f32.hip", "scan2d_fwd_bf16.hip", "scan2d_fwd_shared_f32.hip", "scan2d_fwd_shared_bf16.hip")
 REGS_INC = "scan2d_fwd_regs.inc"
+
+
+PY_UNIT, PY_LIB = "scan2d_py.cpp", os.path.join(HERE, "_scan2d_py.so")
+
+
+def _py_extension_cmd():
+    """The compiler line of the binding's extension: host code only, linked with torch and (next to it) libscan2d.so."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = [sysconfig.get_paths()["include"], *include_paths(), "/opt/rocm/include"]
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall", "-Wno-unknown-pragmas",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            *[a for i in inc for a in ("-isystem", i)], os.path.join(CSRC, PY_UNIT), "-o", PY_LIB, "-L" + lib, "-L" + HERE, "-l:libscan2d.so",
+            "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + lib]
 
 
 def _run(cmd):
@@ -150,6 +167,11 @@ def build(force: bool = True, jobs: int = 6, verbose: bool = True) -> str:
         print(out)
     objs = [os.path.join(OBJ, u.replace(".hip", ".o")) for u in UNITS + [API_UNIT]]
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    src = os.path.join(CSRC, PY_UNIT)
+    if force or not os.path.exists(PY_LIB) or os.path.getmtime(PY_LIB) < max(os.path.getmtime(src), os.path.getmtime(os.path.join(HERE, "..", "include", "scan2d.h"))):
+        out = _run(_py_extension_cmd())
+        if verbose and out.strip():
+            print(out)
     probe_src = os.path.join(CSRC, "roofprobe.hip")
     if os.path.exists(probe_src):
         _run([HIPCC, *FLAGS, "-o", PROBE, probe_src])

@@ -17,6 +17,7 @@
 #include "scan2d_bwd.hpp"
 #include "scan2d_elementwise.hpp"
 #include "scan2d_block.hpp"
+#include "scan2d_memo.hpp"
 #include "scan2d_tuning.hpp"
 
 namespace scan2d {
@@ -25,6 +26,7 @@ namespace scan2d {
 namespace {
 TuneSlot g_tune[kTuneKinds];
 std::once_flag g_tune_env_once;
+std::atomic<unsigned> g_tune_generation;
 
 void tune_read_env() {
     static const char* const names[kTuneKinds] = {"SCAN2D_FWD_VARIANT", "SCAN2D_FWD_SHARED", "SCAN2D_BWD_VARIANT"};
@@ -58,6 +60,12 @@ void tune_set(int kind, const int* values, int n) {
     g_tune[kind].n.store(0, std::memory_order_release);
     for (int i = 0; i < kTuneMaxValues; ++i) g_tune[kind].v[i].store(i < n ? values[i] : 0, std::memory_order_relaxed);
     g_tune[kind].n.store(n, std::memory_order_release);
+    g_tune_generation.fetch_add(1, std::memory_order_release);
+}
+
+unsigned tune_generation() {
+    std::call_once(g_tune_env_once, tune_read_env);
+    return g_tune_generation.load(std::memory_order_acquire);
 }
 
 namespace {
@@ -295,7 +303,7 @@ double fwd_cost(const scan2d_desc* d, const FwdChoice& c) {
 // sp: pick the instantiation that computes the step itself
 // cf: columns first inside the kernel; only the shared-producer form has such instantiations (SCAN2D_ERR_BAD_SHAPE
 //     when none of them takes the shape: the caller then runs columns first through transposes)
-int choose_fwd(const scan2d_desc* d, FwdChoice* out, bool sp = false, bool ma = true, bool cf = false) {
+int rank_fwd(const scan2d_desc* d, FwdChoice* out, bool sp, bool ma, bool cf) {
     const TuneValues tsh = tune_get(kTuneShared);
     if (tsh.n >= 5 && fill_shared(d, tsh.v[0], tsh.v[1], tsh.v[2], tsh.v[3], tsh.v[4], sp, out, cf, tsh.n >= 6 && tsh.v[5] != 0 && !cf)) return SCAN2D_OK;
     if (cf) {
@@ -339,6 +347,11 @@ int choose_fwd(const scan2d_desc* d, FwdChoice* out, bool sp = false, bool ma = 
             if (!found || cost < best) { best = cost; *out = c; found = true; }
         }
     return found ? SCAN2D_OK : SCAN2D_ERR_BAD_SHAPE;
+}
+
+int choose_fwd(const scan2d_desc* d, FwdChoice* out, bool sp = false, bool ma = true, bool cf = false) {
+    thread_local PlanMemo<FwdChoice> memo;
+    return memo.get(*d, (sp ? 1u : 0u) | (ma ? 2u : 0u) | (cf ? 4u : 0u), out, [&](FwdChoice* c) { return rank_fwd(d, c, sp, ma, cf); });
 }
 
 }  // namespace

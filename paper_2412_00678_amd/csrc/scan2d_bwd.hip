@@ -6,6 +6,7 @@
 #include <cstdlib>
 
 #include "scan2d_bwd_variants.hpp"
+#include "scan2d_memo.hpp"
 #include "scan2d_tuning.hpp"
 
 namespace scan2d {
@@ -214,7 +215,7 @@ bool shared_by_default(int LG, int K, int NW) { return LG == 16 || (LG == 64 && 
 bool allow_large_lds(const void* kernel, size_t bytes);   // scan2d_api.hip
 namespace {
 
-bool make_plan(const scan2d_desc* d, BwdPlan* out, bool sp = false, bool av = false) {
+bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     BwdPlan pl;
     pl.av = av;
     const int W = d->W, N = d->N;
@@ -374,6 +375,11 @@ bool make_plan(const scan2d_desc* d, BwdPlan* out, bool sp = false, bool av = fa
     pl.total = o;
     *out = pl;
     return true;
+}
+
+bool make_plan(const scan2d_desc* d, BwdPlan* out, bool sp = false, bool av = false) {
+    thread_local PlanMemo<BwdPlan> memo;
+    return memo.get(*d, (sp ? 1u : 0u) | (av ? 2u : 0u), out, [&](BwdPlan* p) { return rank_plan(d, p, sp, av) ? 0 : 1; }) == 0;
 }
 
 }  // namespace

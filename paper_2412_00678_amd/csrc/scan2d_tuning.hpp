@@ -25,6 +25,8 @@ struct TuneValues {
 };
 
 TuneValues tune_get(int kind);                   // reads the environment on first use
+// Counts the calls of tune_set: a plan made under another count may not hold any more.
+unsigned tune_generation();
 void tune_set(int kind, const int* values, int n);
 
 }  // namespace scan2d

@@ -1,8 +1,11 @@
-"""Thin ctypes binding of the C-ABI library `libscan2d.so` (see include/scan2d.h).
+"""Thin binding of the C-ABI library `libscan2d.so` (see include/scan2d.h).
 
 Argument marshalling only: every step of the scan runs in the HIP kernels.  PyTorch is used
-for device memory and the current stream, nothing else.  Importing this module loads the
-shared library and raises if it has not been built (there is no fallback path).
+for device memory and the current stream, nothing else.  The calls of a program's inner loop
+are checked and converted by the C++ extension `_scan2d_py` (csrc/scan2d_py.cpp), the others
+(diagnostics, the ablation variants, the no-allocation call) through ctypes.  Importing this
+module loads both shared libraries and raises if they have not been built (there is no
+fallback path).
 """
 from __future__ import annotations
 
@@ -102,6 +105,9 @@ def _load() -> ctypes.CDLL:
 
 
 lib = _load()
+from . import _scan2d_py as _native  # noqa: E402  (links against the library that _load has found)
+
+_native.set_error(Scan2dError)
 
 
 def strerror(code: int) -> str:
@@ -200,27 +206,7 @@ def _stream_ptr() -> int:
 
 def scan2d_fwd(x, delta, A, Bm, Cm, Dskip=None, mask=None, y=None, workspace=None, flags=0):
     """y = 2D selective scan; enqueued on torch's current stream.  Returns y (allocated if None)."""
-    desc = make_desc(x, A, flags)
-    Bt, Dc, H, W, N = desc.Bt, desc.Dc, desc.H, desc.W, desc.N
-    _check(x, "x", x.dtype, (Bt, Dc, H, W))
-    _check(delta, "delta", x.dtype, (Bt, Dc, H, W))
-    _check(A, "A", torch.float32, (Dc, N))
-    _check(Bm, "Bm", x.dtype, (Bt, N, H, W))
-    _check(Cm, "Cm", x.dtype, (Bt, N, H, W))
-    _check(Dskip, "Dskip", torch.float32, (Dc,), optional=True)
-    _check(mask, "mask", torch.uint8, (Bt, H, W), optional=True)
-    if y is None:
-        y = torch.empty_like(x)
-    _check(y, "y", x.dtype, (Bt, Dc, H, W))
-    if workspace is None:
-        workspace, wbytes = _workspace(desc, PASS_FWD, x.device)
-    else:
-        wbytes = workspace.numel() * workspace.element_size()
-    rc = lib.scan2d_fwd(ctypes.byref(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm),
-                        _ptr(Dskip), _ptr(mask), _ptr(y), _ptr(workspace), wbytes, _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_fwd")
-    return y
+    return _native.scan2d_fwd(x, delta, A, Bm, Cm, Dskip, mask, y, workspace, flags)
 
 
 class Prepared:
@@ -229,10 +215,11 @@ class Prepared:
     one short call after another, where checking and converting a dozen arguments costs more than the kernel."""
 
     def __init__(self, fn, name, args, keep):
-        self._fn, self._name, self._args, self._keep = fn, name, args, keep      # keep: the tensors stay alive
+        self._call = _native.Call(ctypes.cast(fn, ctypes.c_void_p).value, args)
+        self._name, self._keep = name, keep                                      # keep: the tensors stay alive
 
     def __call__(self):
-        rc = self._fn(*self._args, torch.cuda.current_stream().cuda_stream)
+        rc = self._call()
         if rc != 0:
             raise Scan2dError(rc, self._name)
 
@@ -253,7 +240,7 @@ def prepare_fwd(x, delta, A, Bm, Cm, Dskip, mask, y, workspace=None, flags=0) ->
         workspace, wbytes = _workspace(desc, PASS_FWD, x.device)
     else:
         wbytes = workspace.numel() * workspace.element_size()
-    args = (ctypes.byref(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(y), _ptr(workspace), wbytes)
+    args = (ctypes.addressof(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(y), _ptr(workspace), wbytes)
     return Prepared(lib.scan2d_fwd, "scan2d_fwd", args, (desc, x, delta, A, Bm, Cm, Dskip, mask, y, workspace))
 
 
@@ -274,7 +261,7 @@ def prepare_bwd(x, delta, A, Bm, Cm, Dskip, mask, dy, out, workspace=None, flags
         workspace, wbytes = _workspace(desc, PASS_BWD, x.device)
     else:
         wbytes = workspace.numel() * workspace.element_size()
-    args = (ctypes.byref(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(dy),
+    args = (ctypes.addressof(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(dy),
             _ptr(out[0]), _ptr(out[1]), _ptr(out[2]), _ptr(out[3]), _ptr(out[4]), _ptr(out[5]), _ptr(workspace), wbytes)
     return Prepared(lib.scan2d_bwd, "scan2d_bwd", args, (desc, x, delta, A, Bm, Cm, Dskip, mask, dy, out, workspace))
 
@@ -305,9 +292,9 @@ def prepare_training_pair(x, delta, A, Bm, Cm, Dskip, mask, y, dy, out, workspac
     if workspace_bwd is None:
         workspace_bwd, _ = _workspace(desc, PASS_BWD, x.device)
     nbytes = lambda t: 0 if t is None else t.numel() * t.element_size()
-    fargs = (ctypes.byref(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(y), _ptr(saved), nsaved,
+    fargs = (ctypes.addressof(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(y), _ptr(saved), nsaved,
              _ptr(workspace_fwd), nbytes(workspace_fwd))
-    bargs = (ctypes.byref(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(dy), _ptr(saved), nsaved,
+    bargs = (ctypes.addressof(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(dy), _ptr(saved), nsaved,
              _ptr(out[0]), _ptr(out[1]), _ptr(out[2]), _ptr(out[3]), _ptr(out[4]), _ptr(out[5]), _ptr(workspace_bwd), nbytes(workspace_bwd))
     keep = (desc, x, delta, A, Bm, Cm, Dskip, mask, y, dy, out, saved, workspace_fwd, workspace_bwd)
     return (Prepared(lib.scan2d_fwd_saving, "scan2d_fwd_saving", fargs, keep), Prepared(lib.scan2d_bwd_saved, "scan2d_bwd_saved", bargs, keep),
@@ -316,68 +303,13 @@ def prepare_training_pair(x, delta, A, Bm, Cm, Dskip, mask, y, dy, out, workspac
 
 def scan2d_fwd_softplus(x, delta_raw, delta_bias, A, Bm, Cm, Dskip=None, mask=None, y=None, workspace=None, flags=0):
     """y of the scan with delta = softplus(delta_raw + delta_bias[c]) computed in the kernels."""
-    desc = make_desc(x, A, flags)
-    Bt, Dc, H, W, N = desc.Bt, desc.Dc, desc.H, desc.W, desc.N
-    _check(x, "x", x.dtype, (Bt, Dc, H, W))
-    _check(delta_raw, "delta_raw", x.dtype, (Bt, Dc, H, W))
-    _check(delta_bias, "delta_bias", torch.float32, (Dc,), optional=True)
-    _check(A, "A", torch.float32, (Dc, N))
-    _check(Bm, "Bm", x.dtype, (Bt, N, H, W))
-    _check(Cm, "Cm", x.dtype, (Bt, N, H, W))
-    _check(Dskip, "Dskip", torch.float32, (Dc,), optional=True)
-    _check(mask, "mask", torch.uint8, (Bt, H, W), optional=True)
-    if y is None:
-        y = torch.empty_like(x)
-    _check(y, "y", x.dtype, (Bt, Dc, H, W))
-    if workspace is None:
-        workspace, wbytes = _workspace(desc, PASS_FWD, x.device)
-    else:
-        wbytes = workspace.numel() * workspace.element_size()
-    rc = lib.scan2d_fwd_softplus(ctypes.byref(desc), _ptr(x), _ptr(delta_raw), _ptr(delta_bias), _ptr(A), _ptr(Bm),
-                                 _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(y), _ptr(workspace), wbytes, _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_fwd_softplus")
-    return y
+    return _native.scan2d_fwd_softplus(x, delta_raw, delta_bias, A, Bm, Cm, Dskip, mask, y, workspace, flags)
 
 
 def scan2d_bwd(x, delta, A, Bm, Cm, Dskip, mask, dy, workspace=None, flags=0, out=None):
     """Gradients (dx, ddelta, dA, dBm, dCm, dDskip) of sum(dy * y); dDskip is None iff Dskip is.
     `out`: the six tensors to write into (nothing is allocated then when a workspace is given too)."""
-    desc = make_desc(x, A, flags)
-    Bt, Dc, H, W, N = desc.Bt, desc.Dc, desc.H, desc.W, desc.N
-    _check(x, "x", x.dtype, (Bt, Dc, H, W))
-    _check(delta, "delta", x.dtype, (Bt, Dc, H, W))
-    _check(dy, "dy", x.dtype, (Bt, Dc, H, W))
-    _check(A, "A", torch.float32, (Dc, N))
-    _check(Bm, "Bm", x.dtype, (Bt, N, H, W))
-    _check(Cm, "Cm", x.dtype, (Bt, N, H, W))
-    _check(Dskip, "Dskip", torch.float32, (Dc,), optional=True)
-    _check(mask, "mask", torch.uint8, (Bt, H, W), optional=True)
-    if out is not None:
-        dx, ddelta, dA, dBm, dCm, dDskip = out
-        _check(dx, "dx", x.dtype, (Bt, Dc, H, W))
-        _check(ddelta, "ddelta", x.dtype, (Bt, Dc, H, W))
-        _check(dA, "dA", torch.float32, (Dc, N))
-        _check(dBm, "dBm", torch.float32, (Bt, N, H, W))
-        _check(dCm, "dCm", torch.float32, (Bt, N, H, W))
-        _check(dDskip, "dDskip", torch.float32, (Dc,), optional=True)
-    else:
-        dx = torch.empty_like(x)
-        ddelta = torch.empty_like(x)
-        dA = torch.empty((Dc, N), dtype=torch.float32, device=x.device)
-        dBm = torch.empty((Bt, N, H, W), dtype=torch.float32, device=x.device)
-        dCm = torch.empty((Bt, N, H, W), dtype=torch.float32, device=x.device)
-        dDskip = None if Dskip is None else torch.empty((Dc,), dtype=torch.float32, device=x.device)
-    if workspace is None:
-        workspace, wbytes = _workspace(desc, PASS_BWD, x.device)
-    else:
-        wbytes = workspace.numel() * workspace.element_size()
-    rc = lib.scan2d_bwd(ctypes.byref(desc), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm),
-                        _ptr(Dskip), _ptr(mask), _ptr(dy), _ptr(dx), _ptr(ddelta), _ptr(dA),
-                        _ptr(dBm), _ptr(dCm), _ptr(dDskip), _ptr(workspace), wbytes, _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_bwd")
-    return dx, ddelta, dA, dBm, dCm, dDskip
+    return _native.scan2d_bwd(x, delta, A, Bm, Cm, Dskip, mask, dy, workspace, flags, out)
 
 
 def scan2d_fwd_variants(x, delta, A, Bm, Cm, Dskip, mask, A_v=None, pad=None):
@@ -434,169 +366,35 @@ def scan2d_bwd_static_scratch(x, delta, A, Bm, Cm, Dskip, mask, dy, out, flags=0
 
 def scan2d_bwd_softplus(x, delta_raw, delta_bias, A, Bm, Cm, Dskip, mask, dy, workspace=None, flags=0):
     """Gradients (dx, ddelta_raw, ddelta_bias, dA, dBm, dCm, dDskip) with the step computed in the kernels."""
-    desc = make_desc(x, A, flags)
-    Bt, Dc, H, W, N = desc.Bt, desc.Dc, desc.H, desc.W, desc.N
-    _check(x, "x", x.dtype, (Bt, Dc, H, W))
-    _check(delta_raw, "delta_raw", x.dtype, (Bt, Dc, H, W))
-    _check(delta_bias, "delta_bias", torch.float32, (Dc,), optional=True)
-    _check(dy, "dy", x.dtype, (Bt, Dc, H, W))
-    _check(A, "A", torch.float32, (Dc, N))
-    _check(Bm, "Bm", x.dtype, (Bt, N, H, W))
-    _check(Cm, "Cm", x.dtype, (Bt, N, H, W))
-    _check(Dskip, "Dskip", torch.float32, (Dc,), optional=True)
-    _check(mask, "mask", torch.uint8, (Bt, H, W), optional=True)
-    dx = torch.empty_like(x)
-    draw = torch.empty_like(x)
-    dbias = None if delta_bias is None else torch.empty((Dc,), dtype=torch.float32, device=x.device)
-    dA = torch.empty((Dc, N), dtype=torch.float32, device=x.device)
-    dBm = torch.empty((Bt, N, H, W), dtype=torch.float32, device=x.device)
-    dCm = torch.empty((Bt, N, H, W), dtype=torch.float32, device=x.device)
-    dDskip = None if Dskip is None else torch.empty((Dc,), dtype=torch.float32, device=x.device)
-    if workspace is None:
-        workspace, wbytes = _workspace(desc, PASS_BWD_SOFTPLUS, x.device)
-    else:
-        wbytes = workspace.numel() * workspace.element_size()
-    rc = lib.scan2d_bwd_softplus(ctypes.byref(desc), _ptr(x), _ptr(delta_raw), _ptr(delta_bias), _ptr(A), _ptr(Bm),
-                                 _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(dy), _ptr(dx), _ptr(draw), _ptr(dbias),
-                                 _ptr(dA), _ptr(dBm), _ptr(dCm), _ptr(dDskip), _ptr(workspace), wbytes, _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_bwd_softplus")
-    return dx, draw, dbias, dA, dBm, dCm, dDskip
+    return _native.scan2d_bwd_softplus(x, delta_raw, delta_bias, A, Bm, Cm, Dskip, mask, dy, workspace, flags)
 
 
 def scan2d_fwd_softplus_gated(x, delta_raw, delta_bias, A, Bm, Cm, Dskip, mask, z, want_y_scan=True, workspace=None,
                               y=None, y_scan=None, flags=0):
     """(y_scan or None, y) with y = y_scan * SiLU(z), step and gate computed in the kernel."""
-    desc = make_desc(x, A, flags)
-    Bt, Dc, H, W, N = desc.Bt, desc.Dc, desc.H, desc.W, desc.N
-    _check(x, "x", x.dtype, (Bt, Dc, H, W))
-    _check(delta_raw, "delta_raw", x.dtype, (Bt, Dc, H, W))
-    _check(delta_bias, "delta_bias", torch.float32, (Dc,), optional=True)
-    _check(z, "z", x.dtype, (Bt, Dc, H, W))
-    _check(A, "A", torch.float32, (Dc, N))
-    _check(Bm, "Bm", x.dtype, (Bt, N, H, W))
-    _check(Cm, "Cm", x.dtype, (Bt, N, H, W))
-    _check(Dskip, "Dskip", torch.float32, (Dc,), optional=True)
-    _check(mask, "mask", torch.uint8, (Bt, H, W), optional=True)
-    if y is None:
-        y = torch.empty_like(x)
-    else:
-        _check(y, "y", x.dtype, (Bt, Dc, H, W))
-    if not want_y_scan:
-        y_scan = None
-    elif y_scan is None:
-        y_scan = torch.empty_like(x)
-    else:
-        _check(y_scan, "y_scan", x.dtype, (Bt, Dc, H, W))
-    if workspace is None:
-        workspace, wbytes = _workspace(desc, PASS_FWD, x.device)
-    else:
-        wbytes = workspace.numel() * workspace.element_size()
-    rc = lib.scan2d_fwd_softplus_gated(ctypes.byref(desc), _ptr(x), _ptr(delta_raw), _ptr(delta_bias), _ptr(A), _ptr(Bm),
-                                       _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(z), _ptr(y_scan), _ptr(y),
-                                       _ptr(workspace), wbytes, _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_fwd_softplus_gated")
-    return y_scan, y
+    return _native.scan2d_fwd_softplus_gated(x, delta_raw, delta_bias, A, Bm, Cm, Dskip, mask, z, want_y_scan, workspace, y, y_scan, flags)
 
 
 def scan2d_bwd_softplus_gated(x, delta_raw, delta_bias, A, Bm, Cm, Dskip, mask, z, y_scan, dy, workspace=None, flags=0):
     """Gradients (dx, ddelta_raw, ddelta_bias, dA, dBm, dCm, dDskip, dz) of the gated operator."""
-    desc = make_desc(x, A, flags)
-    Bt, Dc, H, W, N = desc.Bt, desc.Dc, desc.H, desc.W, desc.N
-    _check(x, "x", x.dtype, (Bt, Dc, H, W))
-    _check(delta_raw, "delta_raw", x.dtype, (Bt, Dc, H, W))
-    _check(delta_bias, "delta_bias", torch.float32, (Dc,), optional=True)
-    _check(z, "z", x.dtype, (Bt, Dc, H, W))
-    _check(y_scan, "y_scan", x.dtype, (Bt, Dc, H, W))
-    _check(dy, "dy", x.dtype, (Bt, Dc, H, W))
-    _check(A, "A", torch.float32, (Dc, N))
-    _check(Bm, "Bm", x.dtype, (Bt, N, H, W))
-    _check(Cm, "Cm", x.dtype, (Bt, N, H, W))
-    _check(Dskip, "Dskip", torch.float32, (Dc,), optional=True)
-    _check(mask, "mask", torch.uint8, (Bt, H, W), optional=True)
-    dx = torch.empty_like(x)
-    draw = torch.empty_like(x)
-    dz = torch.empty_like(x)
-    dbias = None if delta_bias is None else torch.empty((Dc,), dtype=torch.float32, device=x.device)
-    dA = torch.empty((Dc, N), dtype=torch.float32, device=x.device)
-    dBm = torch.empty((Bt, N, H, W), dtype=torch.float32, device=x.device)
-    dCm = torch.empty((Bt, N, H, W), dtype=torch.float32, device=x.device)
-    dDskip = None if Dskip is None else torch.empty((Dc,), dtype=torch.float32, device=x.device)
-    if workspace is None:
-        workspace, wbytes = _workspace(desc, PASS_BWD_GATED, x.device)
-    else:
-        wbytes = workspace.numel() * workspace.element_size()
-    rc = lib.scan2d_bwd_softplus_gated(ctypes.byref(desc), _ptr(x), _ptr(delta_raw), _ptr(delta_bias), _ptr(A), _ptr(Bm),
-                                       _ptr(Cm), _ptr(Dskip), _ptr(mask), _ptr(z), _ptr(y_scan), _ptr(dy), _ptr(dx),
-                                       _ptr(draw), _ptr(dbias), _ptr(dA), _ptr(dBm), _ptr(dCm), _ptr(dDskip), _ptr(dz),
-                                       _ptr(workspace), wbytes, _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_bwd_softplus_gated")
-    return dx, draw, dbias, dA, dBm, dCm, dDskip, dz
+    return _native.scan2d_bwd_softplus_gated(x, delta_raw, delta_bias, A, Bm, Cm, Dskip, mask, z, y_scan, dy, workspace, flags)
 
 
 def block_conv_silu(u, w, bias=None, PH=None, PW=None, x=None):
     """x = SiLU(depth-wise correlation of u [Bt][Dc][H][W] with w [Dc][KH][KW] + bias [Dc]); PH, PW: offset of the
     filter's first tap (default: centred)."""
-    Bt, Dc, H, W = u.shape
-    KH, KW = int(w.shape[1]), int(w.shape[2])
-    desc = Desc(Bt, Dc, H, W, 1, _dtype_code(u), 0)
-    _check(u, "u", u.dtype, (Bt, Dc, H, W))
-    _check(w, "w", torch.float32, (Dc, KH, KW))
-    _check(bias, "bias", torch.float32, (Dc,), optional=True)
-    if x is None:
-        x = torch.empty_like(u)
-    else:
-        _check(x, "x", u.dtype, (Bt, Dc, H, W))
-    shape = ConvShape(KH, KW, KH // 2 if PH is None else PH, KW // 2 if PW is None else PW)
-    rc = lib.scan2d_block_conv_silu(ctypes.byref(desc), ctypes.byref(shape), _ptr(u), _ptr(w), _ptr(bias), _ptr(x), _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_block_conv_silu")
-    return x
+    return _native.block_conv_silu(u, w, bias, PH, PW, x)
 
 
 def block_xproj(x, Wx, Wdt, N, out=None):
     """(delta_raw, Bm, Cm) from x [Bt][Dc][H][W], Wx [(R + 2N)][Dc] (type of x) and Wdt [Dc][R] fp32."""
-    Bt, Dc, H, W = x.shape
-    R = int(Wdt.shape[1])
-    desc = Desc(Bt, Dc, H, W, N, _dtype_code(x), 0)
-    _check(x, "x", x.dtype, (Bt, Dc, H, W))
-    _check(Wx, "Wx", x.dtype, (R + 2 * N, Dc))
-    _check(Wdt, "Wdt", torch.float32, (Dc, R))
-    if out is None:
-        out = (torch.empty_like(x), torch.empty((Bt, N, H, W), dtype=x.dtype, device=x.device),
-               torch.empty((Bt, N, H, W), dtype=x.dtype, device=x.device))
-    else:
-        _check(out[0], "delta_raw", x.dtype, (Bt, Dc, H, W))
-        _check(out[1], "Bm", x.dtype, (Bt, N, H, W))
-        _check(out[2], "Cm", x.dtype, (Bt, N, H, W))
-    rc = lib.scan2d_block_xproj(ctypes.byref(desc), R, _ptr(x), _ptr(Wx), _ptr(Wdt), _ptr(out[0]), _ptr(out[1]), _ptr(out[2]), _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_block_xproj")
-    return out
+    return _native.block_xproj(x, Wx, Wdt, N, out)
 
 
 def block_linear(x, Wt, bias=None, residual=None, out=None):
     """out [Bt][Cout][H][W] = Wt [Cout][Cin] (type of x) applied at every position of x [Bt][Cin][H][W], plus
     bias [Cout] fp32 and residual [Bt][Cout][H][W] (type of x), both optional."""
-    Bt, Cin, H, W = x.shape
-    Cout = int(Wt.shape[0])
-    desc = Desc(Bt, Cin, H, W, 1, _dtype_code(x), 0)
-    _check(x, "x", x.dtype, (Bt, Cin, H, W))
-    _check(Wt, "Wt", x.dtype, (Cout, Cin))
-    if bias is not None:
-        _check(bias, "bias", torch.float32, (Cout,))
-    if residual is not None:
-        _check(residual, "residual", x.dtype, (Bt, Cout, H, W))
-    if out is None:
-        out = torch.empty((Bt, Cout, H, W), dtype=x.dtype, device=x.device)
-    else:
-        _check(out, "out", x.dtype, (Bt, Cout, H, W))
-    rc = lib.scan2d_block_linear(ctypes.byref(desc), Cout, _ptr(x), _ptr(Wt), _ptr(bias), _ptr(residual), _ptr(out), _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_block_linear")
-    return out
+    return _native.block_linear(x, Wt, bias, residual, out)
 
 
 LAYER_NORM, RMS_NORM = 0, 1
@@ -604,43 +402,13 @@ LAYER_NORM, RMS_NORM = 0, 1
 
 def block_norm(x, gamma, beta=None, eps=1e-5, kind=LAYER_NORM, out=None):
     """Layer norm or RMS norm over the channels of every position of x [Bt][C][H][W]; gamma, beta: [C] fp32."""
-    Bt, C, H, W = x.shape
-    desc = Desc(Bt, C, H, W, 1, _dtype_code(x), 0)
-    _check(x, "x", x.dtype, (Bt, C, H, W))
-    _check(gamma, "gamma", torch.float32, (C,))
-    if beta is not None:
-        _check(beta, "beta", torch.float32, (C,))
-    if out is None:
-        out = torch.empty_like(x)
-    else:
-        _check(out, "out", x.dtype, (Bt, C, H, W))
-    rc = lib.scan2d_block_norm(ctypes.byref(desc), int(kind), float(eps), _ptr(x), _ptr(gamma), _ptr(beta), _ptr(out), _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_block_norm")
-    return out
+    return _native.block_norm(x, gamma, beta, eps, kind, out)
 
 
 def block_attn_pool(h, V, w, mask=None, out=None):
     """(z [Bt][M] fp32, attn [Bt][H][W] fp32) from h [Bt][M][H][W], V [D][M] (type of h), w [D] fp32 and an optional
     mask [Bt][H][W] uint8 (non-zero = not in the bag)."""
-    Bt, M, H, W = h.shape
-    D = int(w.shape[0])
-    desc = Desc(Bt, M, H, W, 1, _dtype_code(h), 0)
-    _check(h, "h", h.dtype, (Bt, M, H, W))
-    _check(V, "V", h.dtype, (D, M))
-    _check(w, "w", torch.float32, (D,))
-    if mask is not None:
-        _check(mask, "mask", torch.uint8, (Bt, H, W))
-    if out is None:
-        out = (torch.empty((Bt, M), dtype=torch.float32, device=h.device), torch.empty((Bt, H, W), dtype=torch.float32, device=h.device))
-    else:
-        _check(out[0], "z", torch.float32, (Bt, M))
-        _check(out[1], "attn", torch.float32, (Bt, H, W))
-    rc = lib.scan2d_block_attn_pool(ctypes.byref(desc), D, _ptr(h), _ptr(V), _ptr(w), _ptr(mask) if mask is not None else None,
-                                    _ptr(out[1]), _ptr(out[0]), _stream_ptr())
-    if rc != 0:
-        raise Scan2dError(rc, "scan2d_block_attn_pool")
-    return out
+    return _native.block_attn_pool(h, V, w, mask, out)
 
 
 def to_device(arrs: dict, dtype_code: int, device="cuda:0") -> dict:
