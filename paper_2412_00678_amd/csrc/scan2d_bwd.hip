@@ -13,87 +13,83 @@ namespace scan2d {
 namespace {
 
 // ------------------------------------------------------------------------------ final sums
-// dBm/dCm[b,n,i,j] = sum over channel groups of the partials; one thread per element.
-__global__ void scan2d_bwd_reduce_groups_kernel(const float* __restrict__ pB, const float* __restrict__ pC,
-                                                float* __restrict__ dBm, float* __restrict__ dCm,
-                                                int Bt, int CG, size_t NHW) {
-    const size_t total = (size_t)Bt * NHW;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-        const size_t b = e / NHW, r = e - b * NHW;
-        const float* sB = pB + b * CG * NHW + r;
-        const float* sC = pC + b * CG * NHW + r;
+// What is left to add up behind the sweeps, in one launch: workgroups below `groups_wgs` form dBm / dCm (sums of the
+// partials over the channel groups), the ones behind them dA, dA_v, dDskip and the bias gradient (sums over the batch
+// items).
+struct SumArgs {
+    const float* pB; const float* pC; float* dBm; float* dCm;
+    int Bt, CG;
+    unsigned groups_wgs;              // 0: one channel group, nothing to add
+    size_t per_item;                  // elements of a partial of one batch item
+    // partials whose rows are LG*K floats in the lane order of the main sweep, [K/4][LG][4] (K = 0: plain rows): element q
+    // of a row is column (q / 4 % LG) * K + (q / (4 * LG)) * 4 + q % 4
+    int W, LG, K;
+    // sums over batch items (Bt > 1): [Bt][n] -> [n]
+    struct Batch { const float* src; float* dst; int n; } batch[4];
+};
+
+// S threads per element split the channel groups (thread s: groups s, s + S, ...), 8 loads of each tensor in flight, and
+// meet in LDS; the order is fixed.  Bound: HBM for large maps.  S > 1 where one thread per element would leave most of the
+// chip's memory path idle: 8 batch items of 14x14 maps and 128 channels took 37 us with S = 1.
+template <int S>
+__global__ __launch_bounds__(S == 1 ? 256 : 64 * S) void scan2d_bwd_sums_kernel(const SumArgs p) {
+    constexpr int THREADS = S == 1 ? 256 : 64 * S, E = THREADS / S;
+    __shared__ float sh[S == 1 ? 1 : 2][S][E];
+    const int tid = threadIdx.x;
+    if (blockIdx.x >= p.groups_wgs) {
+        long long e = (long long)(blockIdx.x - p.groups_wgs) * THREADS + tid;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const SumArgs::Batch& t = p.batch[k];
+            if (t.dst == nullptr) continue;
+            if (e >= 0 && e < t.n) {
+                float acc = 0.0f;
+                for (int b = 0; b < p.Bt; ++b) acc += t.src[(size_t)b * t.n + e];
+                t.dst[e] = acc;
+            }
+            e -= t.n;
+        }
+        return;
+    }
+    const size_t per = p.per_item, total = (size_t)p.Bt * per;
+    const int s = tid / E, CG = p.CG;
+    for (size_t base = (size_t)blockIdx.x * E; base < total; base += (size_t)p.groups_wgs * E) {
+        const size_t e = min(base + tid % E, total - 1);
+        const size_t b = e / per, r = e - b * per;
+        const float* sB = p.pB + b * CG * per + r;
+        const float* sC = p.pC + b * CG * per + r;
         float aB = 0.0f, aC = 0.0f;
-        for (int g = 0; g < CG; ++g) { aB += sB[(size_t)g * NHW]; aC += sC[(size_t)g * NHW]; }
-        dBm[e] = aB;
-        dCm[e] = aC;
-    }
-}
-
-// The same sum for partials whose rows are LG*K floats in the lane order of the main sweep, [K/4][LG][4]: element q of a
-// row is column (q / 4 % LG) * K + (q / (4 * LG)) * 4 + q % 4.  rows = N * H.
-__global__ void scan2d_bwd_reduce_groups_chunked_kernel(const float* __restrict__ pB, const float* __restrict__ pC,
-                                                        float* __restrict__ dBm, float* __restrict__ dCm,
-                                                        int Bt, int CG, size_t rows, int W, int LG, int K) {
-    const size_t panel = (size_t)LG * K, per_item = rows * panel, total = (size_t)Bt * per_item;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-        const size_t b = e / per_item, r = e - b * per_item;
-        const size_t row = r / panel;
-        const int q = (int)(r - row * panel);
-        const int col = (q / 4 % LG) * K + (q / (4 * LG)) * 4 + q % 4;
-        if (col >= W) continue;
-        const float* sB = pB + b * CG * per_item + r;
-        const float* sC = pC + b * CG * per_item + r;
-        float aB = 0.0f, aC = 0.0f;
-        for (int g = 0; g < CG; ++g) { aB += sB[(size_t)g * per_item]; aC += sC[(size_t)g * per_item]; }
-        const size_t o = (b * rows + row) * W + col;
-        dBm[o] = aB;
-        dCm[o] = aC;
-    }
-}
-
-// dA[c,n] = sum_b pA[b,c,n]; dDskip[c] = sum_b pD[b,c].
-__global__ void scan2d_bwd_reduce_batch_kernel(const float* __restrict__ pA, const float* __restrict__ pD,
-                                               float* __restrict__ dA, float* __restrict__ dDskip,
-                                               int Bt, int Dc, int N) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < Dc * N) {
-        float acc = 0.0f;
-        for (int b = 0; b < Bt; ++b) acc += pA[(size_t)b * Dc * N + e];
-        dA[e] = acc;
-    }
-    if (dDskip != nullptr && e < Dc) {
-        float acc = 0.0f;
-        for (int b = 0; b < Bt; ++b) acc += pD[(size_t)b * Dc + e];
-        dDskip[e] = acc;
-    }
-}
-
-// ddelta_bias: per map, the sum of the (already chain-ruled) ddelta_raw over positions, in a fixed
-// order (strided partial sums per thread, then a tree over the workgroup); summed over batch items
-// by scan2d_bwd_reduce_bias_batch_kernel.
-template <typename T>
-__global__ __launch_bounds__(256) void scan2d_bwd_reduce_bias_kernel(const T* __restrict__ ddelta_raw, float* __restrict__ pbias, size_t HW) {
-    __shared__ float sh[256];
-    const T* src = ddelta_raw + (size_t)blockIdx.x * HW;
-    float acc = 0.0f;
-    for (size_t e = threadIdx.x; e < HW; e += 256) {
-        if constexpr (Elem<T>::kBytes == 4) acc += __uint_as_float(elem_bits(src + e));
-        else acc += __uint_as_float(elem_bits(src + e) << 16);
-    }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) pbias[blockIdx.x] = sh[0];
-}
-__global__ void scan2d_bwd_reduce_bias_batch_kernel(const float* __restrict__ pbias, float* __restrict__ dbias, int Bt, int Dc) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < Dc) {
-        float acc = 0.0f;
-        for (int b = 0; b < Bt; ++b) acc += pbias[(size_t)b * Dc + c];
-        dbias[c] = acc;
+        int g = s;
+        for (; g + 7 * S < CG; g += 8 * S) {
+            float vB[8], vC[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { vB[u] = sB[(size_t)(g + u * S) * per]; vC[u] = sC[(size_t)(g + u * S) * per]; }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { aB += vB[u]; aC += vC[u]; }
+        }
+        for (; g < CG; g += S) { aB += sB[(size_t)g * per]; aC += sC[(size_t)g * per]; }
+        if constexpr (S > 1) {
+            sh[0][s][tid % E] = aB;
+            sh[1][s][tid % E] = aC;
+            __syncthreads();
+            if (s == 0) {
+#pragma unroll
+                for (int k = 1; k < S; ++k) { aB += sh[0][k][tid]; aC += sh[1][k][tid]; }
+            }
+            __syncthreads();
+            if (s != 0) continue;
+        }
+        if (base + tid % E >= total) continue;
+        size_t o = e;
+        if (p.K > 0) {
+            const size_t panel = (size_t)p.LG * p.K, row = e / panel;
+            const int q = (int)(e - row * panel);
+            const int col = (q / 4 % p.LG) * p.K + (q / (4 * p.LG)) * 4 + q % 4;
+            if (col >= p.W) continue;
+            o = row * p.W + col;
+        }
+        p.dBm[o] = aB;
+        p.dCm[o] = aC;
     }
 }
 
@@ -184,7 +180,7 @@ __global__ __launch_bounds__(256) void scan2d_bwd_tail_kernel(const T* __restric
 }
 
 struct BwdPlan {
-    bool small = false;                                    // one wavefront per map, no bands (scan2d_bwd_small.hpp)
+    bool small = false;                                    // one to four wavefronts per map, no bands (scan2d_bwd_small.hpp)
     int LG = 0, K = 0, NW = 0, waves = 0, RB = 0;
     int NG = 0, GS = 0, CG = 0, nb = 0;
     BwdKernels k;
@@ -225,18 +221,24 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     if (cf && av) return false;
     const TuneValues tb = av ? TuneValues() : tune_get(kTuneBwd);
     if (W <= 16 && d->H <= 16 && N <= 16 && tb.n == 0 && !av && !cf) {
-        // small maps: the whole map stays in registers; dBm/dCm partials per channel
+        // small maps: the whole map stays in registers
         pl.small = true;
-        pl.LG = 16; pl.K = 1; pl.NW = N <= 4 ? 1 : (N <= 8 ? 2 : 4); pl.waves = 4; pl.RB = d->H;
-        pl.NG = 4; pl.GS = 1; pl.CG = d->Dc; pl.nb = 1; pl.lds_bytes = 0;
-        pl.k.main = d->dtype == SCAN2D_BF16 ? bwd_small_kernel_bf16(pl.NW, sp) : bwd_small_kernel_f32(pl.NW, sp);
+        const int wpm = N <= 4 ? 1 : (N <= 8 ? 2 : 4);
+        pl.LG = 16; pl.K = 1; pl.NW = wpm; pl.waves = 4; pl.RB = d->H;       // NW: states per DPP row over a map's wavefronts
+        pl.NG = 4 * wpm; pl.nb = 1; pl.lds_bytes = 0;
+        // channels per workgroup: as few partial sums as leave every SIMD two wavefronts
+        const long long wgs1 = ((long long)d->Bt * d->Dc * wpm + 3) / 4;
+        pl.GS = (int)std::max(1LL, std::min({wgs1 / 512, 8LL, (long long)d->Dc}));
+        pl.CG = (d->Dc + pl.GS - 1) / pl.GS;
+        pl.k.main = d->dtype == SCAN2D_BF16 ? bwd_small_kernel_bf16(wpm, sp, false) : bwd_small_kernel_f32(wpm, sp, false);
+        if (sp) pl.k.main_gate = d->dtype == SCAN2D_BF16 ? bwd_small_kernel_bf16(wpm, true, true) : bwd_small_kernel_f32(wpm, true, true);
         if (pl.k.main == nullptr) return false;
         const size_t maps = (size_t)d->Bt * d->Dc;
-        const size_t NHW = (size_t)N * d->H * W;
+        const size_t parts = (size_t)d->Bt * pl.CG * N * d->H * W;
         size_t o = 0;
         pl.off_ck = o;
-        pl.off_pB = o; o += pl.CG > 1 ? align_up(maps * NHW * sizeof(float)) : 0;
-        pl.off_pC = o; o += pl.CG > 1 ? align_up(maps * NHW * sizeof(float)) : 0;
+        pl.off_pB = o; o += pl.CG > 1 ? align_up(parts * sizeof(float)) : 0;
+        pl.off_pC = o; o += pl.CG > 1 ? align_up(parts * sizeof(float)) : 0;
         pl.off_pA = o; o += d->Bt > 1 ? align_up(maps * N * sizeof(float)) : 0;
         pl.off_pD = o; o += d->Bt > 1 ? align_up(maps * sizeof(float)) : 0;
         pl.off_pb = o; o += align_up(maps * sizeof(float));
@@ -382,6 +384,9 @@ bool make_plan(const scan2d_desc* d, BwdPlan* out, bool sp = false, bool av = fa
     return memo.get(*d, (sp ? 1u : 0u) | (av ? 2u : 0u), out, [&](BwdPlan* p) { return rank_plan(d, p, sp, av) ? 0 : 1; }) == 0;
 }
 
+// Workgroups of the small-map kernel: pl.NG lane groups (DPP rows) per map, 16 per workgroup.
+long long small_wgs(const scan2d_desc* d, const BwdPlan& pl) { return ((long long)d->Bt * pl.CG * pl.NG + 15) / 16; }
+
 }  // namespace
 
 size_t bwd_workspace_bytes(const scan2d_desc* d, bool softplus, bool av) {
@@ -394,7 +399,7 @@ int bwd_check(const scan2d_desc* d, bool softplus, bool av) {
     BwdPlan pl;
     if (!make_plan(d, &pl, softplus, av)) return SCAN2D_ERR_BAD_SHAPE;
     const long long maps = (long long)d->Bt * d->Dc;
-    if (pl.small) return (maps + 3) / 4 > 2147483647LL ? SCAN2D_ERR_BAD_SHAPE : SCAN2D_OK;
+    if (pl.small) return small_wgs(d, pl) > 2147483647LL ? SCAN2D_ERR_BAD_SHAPE : SCAN2D_OK;
     const int MPW = (pl.waves * 64 / pl.LG) / pl.NG;
     const int ck_NG = (d->N + pl.k.ckpt_NW - 1) / pl.k.ckpt_NW;
     const int MPW1 = (pl.ck_waves * 64 / pl.ck_LG) / ck_NG;
@@ -444,9 +449,8 @@ int fwd_saving_launch(const scan2d_desc* d, const void* x, const void* delta, co
 bool bwd_describe(const scan2d_desc* d, char* text, size_t text_bytes) {
     BwdPlan pl;
     if (!make_plan(d, &pl)) return false;
-    const long long maps = (long long)d->Bt * d->Dc;
     long long wgs;
-    if (pl.small) wgs = (maps + 3) / 4;
+    if (pl.small) wgs = small_wgs(d, pl);
     else wgs = ((long long)d->Bt * pl.CG + (pl.waves * 64 / pl.LG) / pl.NG - 1) / ((pl.waves * 64 / pl.LG) / pl.NG);
     std::snprintf(text, text_bytes, "%sbwd form=%s LG=%d K=%d NW=%d waves=%d RB=%d GS=%d CG=%d bands=%d panels=%d wgs=%lld lds=%zu workspace=%zu",
                   (d->flags & SCAN2D_FLAG_COLUMNS_FIRST) != 0 ? "columns-first(in-kernel) " : "",
@@ -457,25 +461,39 @@ bool bwd_describe(const scan2d_desc* d, char* text, size_t text_bytes) {
 
 bool bwd_gate_in_sweep(const scan2d_desc* d) {
     BwdPlan pl;
-    return d->flags == 0u && make_plan(d, &pl, true, false) && pl.shared && pl.panels == 1 && !pl.step_outside &&
+    return d->flags == 0u && make_plan(d, &pl, true, false) && (pl.small || (pl.shared && pl.panels == 1 && !pl.step_outside)) &&
            pl.k.main_gate != nullptr;
 }
 
 namespace {
-// Sum of ddelta_raw over positions and batch items, per channel (softplus step only).
-void launch_bias_sums(const scan2d_desc* d, const BwdPlan& pl, const void* ddelta_raw, float* dbias, char* ws, hipStream_t stream) {
-    const long long maps = (long long)d->Bt * d->Dc;
-    const size_t HW = (size_t)d->H * d->W;
-    float* pb = d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pb) : dbias;
-    if (d->dtype == SCAN2D_BF16)
-        hipLaunchKernelGGL(scan2d_bwd_reduce_bias_kernel<bf16_t>, dim3((unsigned)maps), dim3(256), 0, stream,
-                           static_cast<const bf16_t*>(ddelta_raw), pb, HW);
-    else
-        hipLaunchKernelGGL(scan2d_bwd_reduce_bias_kernel<float>, dim3((unsigned)maps), dim3(256), 0, stream,
-                           static_cast<const float*>(ddelta_raw), pb, HW);
-    if (d->Bt > 1)
-        hipLaunchKernelGGL(scan2d_bwd_reduce_bias_batch_kernel, dim3((d->Dc + 255) / 256), dim3(256), 0, stream,
-                           pb, dbias, d->Bt, d->Dc);
+// The sums behind the sweeps (scan2d_bwd_sums_kernel): channel groups, if there are several, and batch items, if there
+// are several.
+void launch_sums(const scan2d_desc* d, const BwdPlan& pl, const BwdArgs& a, float* dBm, float* dCm, float* dA, float* dA_v, float* dDskip,
+                 float* dbias, const float* pbias, hipStream_t stream) {
+    SumArgs s;
+    s.pB = a.pB; s.pC = a.pC; s.dBm = dBm; s.dCm = dCm; s.Bt = d->Bt; s.CG = pl.CG; s.W = d->W;
+    s.LG = pl.part_chunked ? pl.LG : 0;
+    s.K = pl.part_chunked ? pl.K : 0;
+    s.per_item = (size_t)d->N * d->H * (pl.part_chunked ? (size_t)pl.LG * pl.K : (size_t)d->W);
+    const size_t total = (size_t)d->Bt * s.per_item;
+    // threads per element: until about 400000 threads read, with at least two groups each
+    int S = total >= 400000 || pl.CG < 8 ? 1 : (total >= 100000 || pl.CG < 32 ? 4 : 16);
+    const unsigned E = S == 1 ? 256 : 64, threads = S == 1 ? 256 : 64 * S;
+    s.groups_wgs = pl.CG > 1 ? (unsigned)std::min<size_t>((total + E - 1) / E, 16384) : 0;
+    size_t n = 0;
+    for (auto& t : s.batch) t = {nullptr, nullptr, 0};
+    if (d->Bt > 1) {
+        s.batch[0] = {a.pA, dA, d->Dc * d->N};
+        if (dDskip != nullptr) s.batch[1] = {a.pD, dDskip, d->Dc};
+        if (dbias != nullptr) s.batch[2] = {pbias, dbias, d->Dc};
+        if (dA_v != nullptr) s.batch[3] = {a.pAv, dA_v, d->Dc * d->N};
+        for (const auto& t : s.batch) n += (size_t)t.n;
+    }
+    const unsigned wgs = s.groups_wgs + (unsigned)((n + threads - 1) / threads);
+    if (wgs == 0) return;
+    if (S == 1) hipLaunchKernelGGL(scan2d_bwd_sums_kernel<1>, dim3(wgs), dim3(threads), 0, stream, s);
+    else if (S == 4) hipLaunchKernelGGL(scan2d_bwd_sums_kernel<4>, dim3(wgs), dim3(threads), 0, stream, s);
+    else hipLaunchKernelGGL(scan2d_bwd_sums_kernel<16>, dim3(wgs), dim3(threads), 0, stream, s);
 }
 }  // namespace
 
@@ -488,7 +506,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     BwdPlan pl;
     if (!make_plan(d, &pl, softplus, A_v != nullptr)) return SCAN2D_ERR_BAD_SHAPE;
     if (z != nullptr) {                                        // the output gate's backward inside the main sweep
-        if (!softplus || y_scan == nullptr || dz == nullptr || !pl.shared || pl.panels != 1 || pl.step_outside || pl.k.main_gate == nullptr)
+        if (!softplus || y_scan == nullptr || dz == nullptr || pl.k.main_gate == nullptr || !(pl.small || (pl.shared && pl.panels == 1 && !pl.step_outside)))
             return SCAN2D_ERR_BAD_SHAPE;
         pl.k.main = pl.k.main_gate;
     }
@@ -512,28 +530,16 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     a.part_chunked = pl.part_chunked ? 1 : 0;
     a.pAv = A_v == nullptr ? nullptr : (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pAv) : dA_v);
     // the sweeps that apply the softplus themselves also add up ddelta_raw per map
-    const bool bias_in_sweep = softplus && ddelta_bias != nullptr && pl.shared && !pl.step_outside && !pl.small;
-    if (bias_in_sweep) a.pBias = d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pb) : ddelta_bias;
+    float* const pbias = softplus && ddelta_bias != nullptr ? (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pb) : ddelta_bias) : nullptr;
+    if (!pl.step_outside) a.pBias = pbias;
 
     const long long maps = (long long)d->Bt * d->Dc;
     if (pl.small) {
-        const long long wgs = (maps + 3) / 4;
+        const long long wgs = small_wgs(d, pl);
         if (wgs > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
         (void)hipGetLastError();
         hipLaunchKernelGGL(pl.k.main, dim3((unsigned)wgs), dim3(256), 0, stream, a);
-        if (pl.CG > 1) {
-            const size_t NHW = (size_t)d->N * d->H * d->W;
-            const size_t total = (size_t)d->Bt * NHW;
-            const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 16384);
-            hipLaunchKernelGGL(scan2d_bwd_reduce_groups_kernel, dim3(blocks), dim3(256), 0, stream,
-                               a.pB, a.pC, dBm, dCm, d->Bt, pl.CG, NHW);
-        }
-        if (d->Bt > 1) {
-            const int n = d->Dc * d->N;
-            hipLaunchKernelGGL(scan2d_bwd_reduce_batch_kernel, dim3((n + 255) / 256), dim3(256), 0, stream,
-                               a.pA, a.pD, dA, dDskip, d->Bt, d->Dc, d->N);
-        }
-        if (softplus && ddelta_bias != nullptr) launch_bias_sums(d, pl, ddelta, ddelta_bias, ws, stream);
+        launch_sums(d, pl, a, dBm, dCm, dA, nullptr, dDskip, softplus ? ddelta_bias : nullptr, pbias, stream);
         return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
     }
     const int slots = pl.waves * 64 / pl.LG;
@@ -613,46 +619,16 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
         }
         hipLaunchKernelGGL(pl.k.main, dim3((unsigned)wg2), dim3(pl.waves * 64), pl.lds_bytes, stream, a);
     }
-    if (pl.CG > 1 && pl.part_chunked) {
-        const size_t rows = (size_t)d->N * d->H;
-        const size_t total = (size_t)d->Bt * rows * pl.LG * pl.K;
-        const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 16384);
-        hipLaunchKernelGGL(scan2d_bwd_reduce_groups_chunked_kernel, dim3(blocks), dim3(256), 0, stream,
-                           a.pB, a.pC, dBm, dCm, d->Bt, pl.CG, rows, d->W, pl.LG, pl.K);
-    } else if (pl.CG > 1) {
-        const size_t NHW = (size_t)d->N * d->H * d->W;
-        const size_t total = (size_t)d->Bt * NHW;
-        const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 16384);
-        hipLaunchKernelGGL(scan2d_bwd_reduce_groups_kernel, dim3(blocks), dim3(256), 0, stream,
-                           a.pB, a.pC, dBm, dCm, d->Bt, pl.CG, NHW);
-    }
-    if (d->Bt > 1) {
-        const int n = d->Dc * d->N;
-        hipLaunchKernelGGL(scan2d_bwd_reduce_batch_kernel, dim3((n + 255) / 256), dim3(256), 0, stream,
-                           a.pA, a.pD, dA, dDskip, d->Bt, d->Dc, d->N);
-        if (A_v != nullptr)
-            hipLaunchKernelGGL(scan2d_bwd_reduce_batch_kernel, dim3((n + 255) / 256), dim3(256), 0, stream,
-                               a.pAv, static_cast<const float*>(nullptr), dA_v, static_cast<float*>(nullptr), d->Bt, d->Dc, d->N);
-    }
     if (pl.step_outside) {
-        float* pb = ddelta_bias == nullptr ? nullptr : (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pb) : ddelta_bias);
         const float* dstep = reinterpret_cast<const float*>(ws + pl.off_step);
         if (d->dtype == SCAN2D_BF16)
             hipLaunchKernelGGL(scan2d_bwd_chain_kernel<bf16_t>, dim3((unsigned)maps), dim3(256), 0, stream, dstep,
-                               static_cast<const bf16_t*>(delta), delta_bias, static_cast<bf16_t*>(ddelta), pb, HW, d->Dc);
+                               static_cast<const bf16_t*>(delta), delta_bias, static_cast<bf16_t*>(ddelta), pbias, HW, d->Dc);
         else
             hipLaunchKernelGGL(scan2d_bwd_chain_kernel<float>, dim3((unsigned)maps), dim3(256), 0, stream, dstep,
-                               static_cast<const float*>(delta), delta_bias, static_cast<float*>(ddelta), pb, HW, d->Dc);
-        if (ddelta_bias != nullptr && d->Bt > 1)
-            hipLaunchKernelGGL(scan2d_bwd_reduce_bias_batch_kernel, dim3((d->Dc + 255) / 256), dim3(256), 0, stream,
-                               pb, ddelta_bias, d->Bt, d->Dc);
-    } else if (bias_in_sweep) {
-        if (d->Bt > 1)
-            hipLaunchKernelGGL(scan2d_bwd_reduce_bias_batch_kernel, dim3((d->Dc + 255) / 256), dim3(256), 0, stream,
-                               a.pBias, ddelta_bias, d->Bt, d->Dc);
-    } else if (softplus && ddelta_bias != nullptr) {
-        launch_bias_sums(d, pl, ddelta, ddelta_bias, ws, stream);
+                               static_cast<const float*>(delta), delta_bias, static_cast<float*>(ddelta), pbias, HW, d->Dc);
     }
+    launch_sums(d, pl, a, dBm, dCm, dA, dA_v, dDskip, softplus ? ddelta_bias : nullptr, pbias, stream);
     return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
 }
 

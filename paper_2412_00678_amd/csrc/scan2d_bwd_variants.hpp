@@ -130,15 +130,15 @@ inline BwdKernels lookup_bwd_kernels_av(int NW, bool fast) {
     return r;
 }
 
-// Small maps (W, H, N <= 16): one wavefront per map, NW = states per lane group of its four.
-BwdKernel bwd_small_kernel_f32(int NW, bool sp);
-BwdKernel bwd_small_kernel_bf16(int NW, bool sp);
+// Small maps (W, H, N <= 16), WPM wavefronts per map; gate: with the output gate's backward (softplus step only).
+BwdKernel bwd_small_kernel_f32(int WPM, bool sp, bool gate);
+BwdKernel bwd_small_kernel_bf16(int WPM, bool sp, bool gate);
 
 template <typename T, bool SP>
-inline BwdKernel lookup_bwd_small_kernel(int NW) {
-    if (NW == 1) return scan2d_bwd_small_kernel<T, 1, SP>;
-    if (NW == 2) return scan2d_bwd_small_kernel<T, 2, SP>;
-    if (NW == 4) return scan2d_bwd_small_kernel<T, 4, SP>;
+inline BwdKernel lookup_bwd_small_kernel(int WPM, bool gate) {
+    if (WPM == 1) return gate ? scan2d_bwd_small_kernel<T, 1, SP, SP> : scan2d_bwd_small_kernel<T, 1, SP, false>;
+    if (WPM == 2) return gate ? scan2d_bwd_small_kernel<T, 2, SP, SP> : scan2d_bwd_small_kernel<T, 2, SP, false>;
+    if (WPM == 4) return gate ? scan2d_bwd_small_kernel<T, 4, SP, SP> : scan2d_bwd_small_kernel<T, 4, SP, false>;
     return nullptr;
 }
 
