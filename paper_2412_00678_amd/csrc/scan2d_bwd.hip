@@ -289,7 +289,8 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     pl.step_outside = sp;
     pl.fast = fast;
     // the main sweep that shares the per-position work through LDS, where it exists for this tiling (N = NG * NW)
-    if (want_shared != 0 && N % NW == 0 && !av) {              // (its kernels take column panels too)
+    // (its kernels take column panels too; their 32-bit offsets span one item's state planes)
+    if (want_shared != 0 && N % NW == 0 && !av && (double)N * d->H * std::max(W, LG * K) * 4.0 < 2147483648.0) {
         BwdKernels ks;
         if (cf) ks = d->dtype == SCAN2D_BF16 ? bwd_shared_kernels_bf16_cf(LG, K, NW, N / NW, waves, W, sp)
                                              : bwd_shared_kernels_f32_cf(LG, K, NW, N / NW, waves, W, sp);
@@ -322,11 +323,7 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     // partial sums to write and add up)
     const size_t T = (size_t)waves * 64;
     size_t fixed = 4 * T * K, per = T * ((size_t)NW * K + NW + 1);
-    if (pl.shared) {             // see the LDS layout in scan2d_bwd_shared.hpp
-        fixed = 4 * T * K + (T / (size_t)pl.NG / LG) * ((size_t)pl.RB * 5 * LG * K);
-        per = T * (size_t)NW * K + (T / LG) * NW + (size_t)waves;
-        if (sp && !pl.step_outside) per += (size_t)waves;     // the bias gradient per wavefront
-    }
+    if (pl.shared) { fixed = pl.k.lds_fixed; per = pl.k.lds_per_channel; }
     const int gs_lds = (int)std::max<size_t>(1, (40960 - std::min<size_t>(fixed, 40960)) / per);
     const int JPW = slots / pl.NG;
     const int gs_max = av ? 1 : std::min({gs_lds, 8, d->Dc});   // av: one channel per workgroup (its dA_v partial stays in registers)
@@ -451,7 +448,10 @@ bool bwd_describe(const scan2d_desc* d, char* text, size_t text_bytes) {
     if (!make_plan(d, &pl)) return false;
     long long wgs;
     if (pl.small) wgs = small_wgs(d, pl);
-    else wgs = ((long long)d->Bt * pl.CG + (pl.waves * 64 / pl.LG) / pl.NG - 1) / ((pl.waves * 64 / pl.LG) / pl.NG);
+    else {
+        const int per_wg = (pl.waves * 64 / pl.LG) / pl.NG;
+        wgs = ((long long)d->Bt * pl.CG + per_wg - 1) / per_wg;
+    }
     std::snprintf(text, text_bytes, "%sbwd form=%s LG=%d K=%d NW=%d waves=%d RB=%d GS=%d CG=%d bands=%d panels=%d wgs=%lld lds=%zu workspace=%zu",
                   (d->flags & SCAN2D_FLAG_COLUMNS_FIRST) != 0 ? "columns-first(in-kernel) " : "",
                   pl.small ? "small" : (pl.shared ? "banded-shared" : "banded"), pl.LG, pl.K, pl.NW, pl.waves, pl.RB, pl.GS, pl.CG, pl.nb,
@@ -542,8 +542,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
         launch_sums(d, pl, a, dBm, dCm, dA, nullptr, dDskip, softplus ? ddelta_bias : nullptr, pbias, stream);
         return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
     }
-    const int slots = pl.waves * 64 / pl.LG;
-    const int MPW = slots / pl.NG;
+    const int MPW = (pl.waves * 64 / pl.LG) / pl.NG;
     BwdArgs ac = a;                                            // the checkpoint sweep may hold more states per lane
     ac.NG = (d->N + pl.k.ckpt_NW - 1) / pl.k.ckpt_NW;
     const int MPW1 = (pl.ck_waves * 64 / pl.ck_LG) / ac.NG;

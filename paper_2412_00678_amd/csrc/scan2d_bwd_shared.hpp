@@ -1,33 +1,34 @@
 // Backward main sweep, the form whose lane groups share the per-position work of a map through LDS
 // (2DMamba Supp. B: two forward scans rebuild the states, a reverse column scan and a reverse row scan carry
 // the gradients).  Same banded organisation as scan2d_bwd_main_kernel (scan2d_bwd_kernels.hpp): bands of RB
-// rows walked bottom-up, per band and channel the states h[i-1,j] and hhor[i,j-1] are rebuilt into registers
-// from the band's checkpoint, then the band's rows are walked upwards with g (reverse column recurrence, an
-// FMA on a register that persists from row to row) and q (reverse row recurrence: serial over the lane's
-// columns plus a leftward lane-group scan); dBm/dCm accumulate in registers over the GS channels of a
-// workgroup; a*g of every channel waits in LDS between two bands.
+// rows walked bottom-up, per band and channel the states h[i-1,j] are rebuilt into registers from the band's
+// checkpoint, then the band's rows are walked upwards with g (reverse column recurrence, an FMA on a register
+// that persists from row to row) and q (reverse row recurrence: serial over the lane's columns plus a leftward
+// lane-group scan); dBm/dCm accumulate in registers over the GS channels of a workgroup; a*g of every channel
+// waits in LDS between two bands.
 //
-// What differs: with one state per lane, the N lane groups of a map each repeated everything that depends on
-// the position and the channel only - unpacking x, step, dy and the mask, the selects, step*x, Dskip*dy - in
-// both passes over a band: 17 of the 55 instructions per (position, channel, state).  Here the threads of a
-// job produce those values once per (band, channel) - each thread a few cells, loaded one (band, channel)
-// ahead - and leave them in LDS as fp32:
-//     dl = step       xe = mask ? 0 : x       dxe = dl * xe       dyv = dy       and the mask flag itself.
-// The scanning lanes read their K columns with wide LDS loads; only Bm and Cm still come from global memory.
-// The sums over the states of ddelta and dx go through LDS (double-buffered per row); the threads of the job add
-// them up over the lane groups, add the skip term Dskip * dy and write +0 under the mask.  Where a row has more
-// (column, tensor) pairs than the job has threads, the two sums are those of the decay gradients times a * A and of
-// the gradients of u times B, one thread per column forms both and only then applies the factors that depend on the
-// position alone (ddelta = first sum + x * second sum, dx = step * second sum): two instructions per state less.
-// dA is summed over the lane group once per (band, channel) (DPP) and accumulated by one lane in LDS; dDskip
-// is accumulated by the producing threads and summed per wavefront: both in a fixed order, so results are
-// bit-reproducible.  K only has to be even here (the scanning lanes load no mask bytes), which allows
-// half-wave groups of 6 columns on 192-wide maps: band state of 96 registers, two waves per SIMD.
-// MP instantiations - column panels (maps wider than LG*K columns, one launch per panel, right to left; the other
-// instantiations carry none of this code or its registers): p.cb is the panel's first column;
-// the row-scan state entering from the left panel (p.hc_in, left by the checkpoint sweeps) starts lane 0's rebuilt
-// row recurrence, a*q entering from the right panel (p.qc_in) joins the last lane's reverse recurrence, a*q of the
-// panel's first column goes to p.qc_out, and dA / dDskip add to what the panels to the right have left (p.accum).
+// A (band, channel) has two barriers:
+//   produce   the job's threads form what depends on the position and the channel only (step, step * x, dy), a few cells
+//             each, loaded one (band, channel) ahead, and leave it in LDS as fp32;
+//   sweep     the lane groups rebuild the states of the band's rows and walk back up.  Bm and Cm of the band stay in
+//             registers for all channels (BCR; the widest fp32 tilings read them per row), the checkpoint of the next
+//             channel is requested one channel ahead.  Per row and column two sums over the states are needed: of (gradient
+//             of the decay) * a * A and of (gradient of u) * B.  A wavefront adds its own states with
+//             v_permlane32_swap / v_permlane16_swap, so that one value per column, tensor and WAVEFRONT goes to LDS;
+//   finish    the thread that produced a cell adds the wavefronts' parts in a fixed order, applies the factors that
+//             depend on the position (ddelta = first sum + x * second sum, dx = step * second sum + Dskip * dy, +0
+//             under the mask; softplus: the logistic factor from the step) and stores.
+// What it replaced had a barrier and 2 NG LDS reads per column in every row: 128x192 fp32 waited 43 % of the time.
+// The row-scan states hhor[i,j-1] are not kept from the rebuild to the reverse sweep but formed again there from the
+// column states, which are kept anyway (RECOMP): Eq. 6 read backwards, hhor[i,j] = h[i,j] - a[i,j] * h[i-1,j].
+// dA is summed over the lane group once per (band, channel) (DPP) and accumulated by one lane in LDS; dDskip and the bias
+// gradient are accumulated by the producing threads and summed per wavefront: all in a fixed order, so results are
+// bit-reproducible.
+// MP instantiations - column panels (maps wider than LG*K columns, one launch per panel, right to left): p.cb is the
+// panel's first column; the row-scan state entering from the left panel (p.hc_in, left by the checkpoint sweeps) starts
+// lane 0's rebuilt row recurrence, a*q entering from the right panel (p.qc_in) joins the last lane's reverse recurrence,
+// a*q of the panel's first column goes to p.qc_out, and dA / dDskip / the bias gradient add to what the panels to the
+// right have left (p.accum).
 #pragma once
 
 #include "scan2d_bwd_kernels.hpp"
@@ -79,23 +80,35 @@ __device__ __forceinline__ float group_sum_last(float v) {
     return v;
 }
 
-// Mirror of a value inside its lane group (lane l <-> lane LG-1-l), through the LDS crossbar.
-template <int LG>
-__device__ __forceinline__ float group_mirror(float v) {
-    const int lane = (int)(threadIdx.x & 63u);
-    const int src = (lane & ~(LG - 1)) | (LG - 1 - (lane & (LG - 1)));
-    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(src << 2, __builtin_bit_cast(int, v)));
-}
-// Leftward scan of one recurrence over a lane group of any width (see group_scan_left): half-wave groups
-// mirror the pair inside the group, scan rightwards and mirror the carry back.
-template <int LG>
+// Leftward scan of S recurrences over a lane group of any width (see group_scan_left); half-wave groups: inside the two
+// DPP rows as for 16-lane groups, then the even row takes the value at the first lane of the odd row.
+template <int LG, int S>
 __device__ __forceinline__ void group_scan_left_any(float* P, float* Q, float* C) {
     if constexpr (LG == 32) {
-        float Pm[1] = {group_mirror<32>(P[0])}, Qm[1] = {group_mirror<32>(Q[0])}, Cm[1];
-        group_scan<32, 1>(Pm, Qm, Cm);
-        C[0] = group_mirror<32>(Cm[0]);
+        static_assert(S <= 2, "half-wave groups: one or two recurrences");
+        if constexpr (S == 1) {
+            asm volatile("s_nop 1\n\t"
+                         SCAN2D_S1_STEP(SCAN2D_SHL(1)) SCAN2D_S1_STEP(SCAN2D_SHL(2))
+                         SCAN2D_S1_STEP(SCAN2D_SHL(4)) SCAN2D_S1_STEP(SCAN2D_SHL(8))
+                         : "+v"(Q[0]), "+v"(P[0]));
+        } else {
+            asm volatile("s_nop 1\n\t"
+                         SCAN2D_S2_STEP(SCAN2D_SHL(1)) SCAN2D_S2_STEP(SCAN2D_SHL(2))
+                         SCAN2D_S2_STEP(SCAN2D_SHL(4)) SCAN2D_S2_STEP(SCAN2D_SHL(8))
+                         : "+v"(Q[0]), "+v"(Q[1]), "+v"(P[0]), "+v"(P[1]));
+        }
+#pragma unroll
+        for (int t = 0; t < S; ++t) {
+            float f;
+            asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 row_newbcast:0 row_mask:0xf bank_mask:0xf" : "=&v"(f) : "v"(Q[t]));
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(f), __float_as_uint(f), false, false);
+            const bool even = (threadIdx.x & 16u) == 0u;
+            Q[t] = even ? fmaf(P[t], __uint_as_float(r[1]), Q[t]) : Q[t];
+            C[t] = from_right<64>(Q[t]);
+            C[t] = (threadIdx.x & 31u) == 31u ? 0.0f : C[t];
+        }
     } else {
-        group_scan_left<LG, 1>(P, Q, C);
+        group_scan_left<LG, S>(P, Q, C);
     }
 }
 // Value held by the lane to the right inside the lane group (0 for the group's last lane).
@@ -130,17 +143,83 @@ __device__ __forceinline__ float dsoftplus_from_value(float sp) {
     return sp < 0.015625f ? small : big;
 }
 
-#ifndef SCAN2D_BWD_RECOMPUTE_HHOR
-#define SCAN2D_BWD_RECOMPUTE_HHOR 1
-#endif
+template <typename P>
+__device__ __forceinline__ P* at_byte(P* base, uint32_t bytes) {
+    using B = std::conditional_t<std::is_const_v<P>, const char, char>;
+    return reinterpret_cast<P*>(reinterpret_cast<B*>(base) + bytes);      // (through an integer the loads would become flat ones)
+}
+// lanes 0..31: a summed over the wavefront's halves, lanes 32..63: b
+__device__ __forceinline__ float halves_sum(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// even DPP rows: a summed over the row pair, odd rows: b
+__device__ __forceinline__ float row_pairs_sum(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 
-// Dynamic LDS layout (floats), T = workgroup threads, SLOTS = T / LG, JPW = SLOTS / NG:
-//   part [2][2][SLOTS][PANEL]      per-lane partial sums over its states of ddelta and dx (double buffered per row)
-//   pp   [JPW][RB][5][PANEL]       the per-position values of the current (band, channel): dl, xe, dxe, dyv, mask flag
-//   gaL  [GS][T][NW*K]             a[i+1,j]*g[i+1,j] of every channel, kept between bands
-//   dAL  [GS][SLOTS][NW]           dA of every channel, accumulated over the bands
-//   dDL  [GS][WAVES]               dDskip of every channel per wavefront, accumulated over the bands
-//   dBL  [GS][WAVES]               (SPIN) the bias gradient, the sum of ddelta_raw, likewise
+// The LDS rows of a wavefront's two sums over its states: kTensor floats per tensor, column c = l * K + j at at(c).
+// Narrow groups: [j][LG] with the pitch that spreads a reader's consecutive columns over the banks; wave-wide groups:
+// chunks of 4 columns per lane.
+template <int LG, int K>
+struct PartRow {
+    static constexpr int kPitch = LG == 64 ? LG : LG + 1;
+    static constexpr int kTensor = LG == 64 ? LG * K : kPitch * K + (LG == 16 ? 16 : 0);
+    static constexpr int kRow = 2 * kTensor;
+    static __device__ __forceinline__ int at(int c) {
+        if constexpr (LG == 64) return lds_colk<LG, K>(c);
+        else return (c % K) * kPitch + c / K;
+    }
+    // columns j and j + 1 (j even)
+    static __device__ __forceinline__ void put2(float* row, int lane, int j, const float* s1, const float* s2) {
+        if constexpr (LG == 32) {
+            float* dst = row + (lane >> 5) * kTensor + (lane & 31);
+            dst[j * kPitch] = halves_sum(s1[j], s2[j]);
+            dst[(j + 1) * kPitch] = halves_sum(s1[j + 1], s2[j + 1]);
+        } else {
+            float* dst = row + (lane >> 5) * kTensor + ((lane >> 4) & 1) * kPitch + (lane & 15);
+            dst[j * kPitch] = row_pairs_sum(halves_sum(s1[j], s2[j]), halves_sum(s1[j + 1], s2[j + 1]));
+        }
+    }
+    static __device__ __forceinline__ void put(float* row, int lane, const float* s1, const float* s2) {
+        if constexpr (LG == 64) {
+            lds_write_k<LG, K>(row, lane, s1);
+            lds_write_k<LG, K>(row + kTensor, lane, s2);
+        } else {
+#pragma unroll
+            for (int j = K - 2; j >= 0; j -= 2) put2(row, lane, j, s1, s2);
+        }
+    }
+};
+
+// Bm and Cm of a band kept in registers: up to 32 of them.  Beyond, two rows at a time, each requested one row ahead
+// (128x192 fp32: 1855 us for the sweep when a row requested its own, 1494 us one row ahead).
+template <typename T, int K, int NW, int RB>
+constexpr bool bwd_bc_in_registers() { return 2 * RB * NW * words_of<T, (K + 3) / 4 * 4>() <= 32; }
+
+// Rows of a band whose decays stay in LDS from the rebuild to the reverse sweep (the others' are formed again).  The
+// widest tilings run one wavefront per SIMD and have LDS for two rows beside eight channels; with all four rows there are
+// four channels per workgroup and twice the partial sums (128x192 fp32: +160 us in their reduction).  Narrow tilings share
+// the LDS with a second workgroup and gain 1 %.
+template <int K, int NW>
+constexpr int bwd_decay_rows() { return K * NW >= 12 ? 2 : 0; }
+
+// Dynamic LDS layout (floats), TH = workgroup threads, SLOTS = TH / LG, JPW = SLOTS / NG, GS channels:
+//   part [RB][WAVES][PartRow::kRow]    the wavefronts' sums over their states of the current (band, channel)
+//   pp   [JPW][RB][3][PANEL]           the per-position values of the current (band, channel): step, step * x, dy
+//   aL   [ALR][NW*K/4][TH][4]          the decays of the band's first ALR rows in the current channel, each thread its own
+//   gaL  [GS][TH][NW*K]               a[i+1,j]*g[i+1,j] of every channel, kept between bands
+//   dAL  [GS][SLOTS][NW]              dA of every channel, accumulated over the bands
+//   dDL  [GS][WAVES][2]               dDskip and (SPIN) the bias gradient of every channel per wavefront, likewise
+template <int LG, int K, int NW, int NG, int WAVES, int RB>
+constexpr size_t bwd_shared_lds_fixed() {                  // floats that do not depend on GS
+    constexpr size_t TH = WAVES * 64, JPW = TH / LG / NG;
+    return (size_t)RB * WAVES * PartRow<LG, K>::kRow + JPW * RB * 3 * LG * K + (size_t)bwd_decay_rows<K, NW>() * TH * NW * K;
+}
+template <int LG, int K, int NW, int WAVES>
+constexpr size_t bwd_shared_lds_per_channel() { return (size_t)WAVES * 64 * NW * K + (size_t)WAVES * 64 / LG * NW + 2 * WAVES; }
+
 // CF: columns first (v = a * v[i-1,j] + u, then h = a * h[i,j-1] + v).  The checkpoints then hold v, the band
 // arrays hold v[i-1,j] (in `hprev`) and h[i,j-1] (in `hhl`), the reverse row scan q runs on dy * Cm alone and the
 // reverse column recurrence on its result (gv = q + a[i+1,j] * gv[i+1,j], kept in `ga` as a * gv); the gradient of u
@@ -149,59 +228,45 @@ __device__ __forceinline__ float dsoftplus_from_value(float sp) {
 // produces a cell also loads z and y_scan there, stores dz = dy * y_scan * s (1 + z (1 - s)), s the logistic function of
 // z, and hands dy * SiLU(z), unrounded, to the sweeps in place of dy.
 template <typename T, int LG, int K, int NW, int NG, int WAVES, int RB, bool FAST, bool SP, bool CF = false, bool MP = false, bool GATE = false>
-__global__ __launch_bounds__(WAVES * 64) void scan2d_bwd_shared_kernel(const BwdArgs p) {
+__global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kernel(const BwdArgs p) {
     static_assert(!MP || !CF, "column panels: rows first only");
     static_assert(!GATE || (SP && !MP), "the gate goes with the softplus step, single panel");
-    // RECOMP: the row-scan states hhor[i,j-1] of a band are not kept from the rebuild to the reverse sweep (RB*NW*K
-    // registers) but formed again there from the column states, which are kept anyway: Eq. 6 read backwards,
-    // hhor[i,j] = h[i,j] - a[i,j] * h[i-1,j], one multiply-add per cell and one lane shift per row instead of a register
-    // (in practice: a copy into and out of an accumulation register) per cell.  The difference to the kept value is one
-    // rounding of h[i,j].
-    constexpr bool RECOMP = SCAN2D_BWD_RECOMPUTE_HHOR != 0 && !CF && !MP;
+    constexpr bool RECOMP = !CF;
     const int cb = MP ? p.cb : 0;                         // first column of this launch's panel
     constexpr int THREADS = WAVES * 64, SLOTS = THREADS / LG, JPW = SLOTS / NG, PANEL = LG * K, TMJ = NG * LG;
-    static_assert(SLOTS % NG == 0 && JPW >= 1, "whole jobs per workgroup");
+    static_assert(SLOTS % NG == 0 && JPW >= 1 && TMJ % 64 == 0, "whole jobs per workgroup, whole wavefronts per job");
+    constexpr int WPJ = TMJ / 64;                         // wavefronts of a job
     constexpr int CELLS = RB * PANEL, CT = (CELLS + TMJ - 1) / TMJ;     // cells of a band per producing thread
-    // Sums over the states of a row: where the job has fewer threads than (column, tensor) pairs, one thread per column
-    // forms both sums and the factors that depend on the position alone (x, the step) are applied after them (LATEF);
-    // otherwise one thread per (column, tensor) pair, the factors applied per state
-    constexpr bool LATEF = 2 * PANEL > TMJ;
-    constexpr int TASKS = LATEF ? PANEL : 2 * PANEL, TT = (TASKS + TMJ - 1) / TMJ;
-    constexpr int XW = words_of<T, K>();
+    using Part = PartRow<LG, K>;
+    constexpr int XW = words_of<T, (K + 3) / 4 * 4>();
+    static_assert(bwd_decay_rows<K, NW>() == 0 || K % 4 == 0, "decays move in pieces of four");
+    constexpr bool BCR = bwd_bc_in_registers<T, K, NW, RB>();
+    constexpr int ALR = bwd_decay_rows<K, NW>();
     // SP: p.delta is the raw projection.  Single-panel instantiations (SPIN) apply the softplus where the cells are
     // produced and the chain rule where ddelta is summed (the logistic factor comes from the step kept in LDS), so
     // ddelta receives the gradient of the raw projection directly; the column-panel instantiations read the step from a
     // buffer a kernel of its own has filled (fp32, p.delta) and write the step's gradient back over it.
     constexpr bool SPIN = SP && !MP;
     using DT = std::conditional_t<SP && !SPIN, float, T>;               // element type of what p.delta holds
-    constexpr int PP_ROW = 5 * PANEL, PP_JOB = RB * PP_ROW;
-    // Bm / Cm of the next row are requested before the current row is processed only where the registers allow it
-    // (two waves per SIMD hide the latency otherwise)
-#ifndef SCAN2D_BWD_SHARED_PF_LIMIT
-#define SCAN2D_BWD_SHARED_PF_LIMIT 4
-#endif
-    constexpr bool PF = K * NW <= SCAN2D_BWD_SHARED_PF_LIMIT;
-    constexpr int NB = PF ? 2 : 1;
+    constexpr int PP_ROW = 3 * PANEL, PP_JOB = RB * PP_ROW;
     extern __shared__ float lds[];
     const int GS = p.GS;
     float* const part = lds;
-    float* const pp = part + 4 * THREADS * K;
-    float* const gaL = pp + JPW * PP_JOB;
+    float* const pp = part + RB * WAVES * Part::kRow;
+    float* const gaL = lds + bwd_shared_lds_fixed<LG, K, NW, NG, WAVES, RB>();
+    float* const aL = gaL - ALR * THREADS * NW * K;
     float* const dAL = gaL + (size_t)GS * THREADS * NW * K;
     float* const dDL = dAL + (size_t)GS * SLOTS * NW;
-    float* const dBL = dDL + (size_t)GS * WAVES;             // SPIN instantiations only
 
-    const int tid = threadIdx.x, slot = tid / LG, l = tid % LG, wave = tid / 64;
-    int job_local = slot / NG;
-    const int sg = slot - job_local * NG;
-    const int tm = sg * LG + l;                           // thread index inside the job
-    const long long jobs = (long long)p.Bt * p.CG;
-    const long long job0 = (long long)blockIdx.x * JPW;
-    const bool live = job0 + job_local < jobs;
-    const int job_slot = job_local;
-    if (!live) job_local = 0;
-    const long long job = job0 + job_local;
-    const int b = (int)(job / p.CG), cg = (int)(job % p.CG);
+    const int tid = threadIdx.x, slot = tid / LG, l = tid % LG, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int job_slot = wave / WPJ;
+    const int sg = slot - job_slot * NG;
+    const int tm = tid - job_slot * TMJ;                  // thread index inside the job
+    const long long groups = (long long)p.Bt * p.CG;
+    const long long job = (long long)blockIdx.x * JPW + job_slot;
+    const bool live = job < groups;
+    const int b = live ? (int)(job / p.CG) : 0, cg = live ? (int)(job % p.CG) : 0;
     const int c_first = cg * GS;
     const int nch = live ? min(GS, p.Dc - c_first) : 0;
 
@@ -218,14 +283,16 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_bwd_shared_kernel(const Bwd
     for (int s = 0; s < NW; ++s) lastB[s] = lastm && (n0 + s == N - 1);
     const int nv = FAST ? (inside ? K : 0) : max(0, min(K, W - col0));   // cells of this lane inside the map
     const uint8_t* mm = p.mask ? p.mask + (size_t)b * HW : nullptr;
-    const T* Bs[NW];
-    const T* Cs[NW];
+    // Addresses are a wave-uniform base (scalar registers) plus one 32-bit byte offset per lane: as 64-bit pointers per row
+    // and tensor the compiler keeps them all in vector registers across the band loop.
+    constexpr uint32_t EB = Elem<T>::kBytes;
+    const T* const Bb = reinterpret_cast<const T*>(p.Bm) + (size_t)b * N * HW;
+    const T* const Cb = reinterpret_cast<const T*>(p.Cm) + (size_t)b * N * HW;
+    uint32_t soff[NW];                                    // state plane and column of this lane
 #pragma unroll
-    for (int s = 0; s < NW; ++s) {
-        Bs[s] = reinterpret_cast<const T*>(p.Bm) + ((size_t)b * N + n0 + s) * HW;
-        Cs[s] = reinterpret_cast<const T*>(p.Cm) + ((size_t)b * N + n0 + s) * HW;
-    }
+    for (int s = 0; s < NW; ++s) soff[s] = ((uint32_t)(n0 + s) * (uint32_t)HW + lcol) * EB;
     float* const ppj = pp + job_slot * PP_JOB;
+    const float* const partj = part + (size_t)job_slot * WPJ * Part::kRow;
 
     for (int ch = 0; ch < GS; ++ch) {
 #pragma unroll
@@ -234,13 +301,10 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_bwd_shared_kernel(const Bwd
 #pragma unroll
             for (int s = 0; s < NW; ++s) dAL[((size_t)ch * SLOTS + slot) * NW + s] = 0.0f;
         }
-        if ((tid & 63) == 63) {
-            dDL[ch * WAVES + wave] = 0.0f;
-            if constexpr (SPIN) dBL[ch * WAVES + wave] = 0.0f;
-        }
+        if ((lane & 31) == 31) dDL[(ch * WAVES + wave) * 2 + (lane >> 5)] = 0.0f;
     }
-    // gaL entries are private to a thread, dAL entries to the last lane of a lane group, dDL entries to the last
-    // lane of a wavefront: no barrier needed for them until the final sums
+    // gaL entries are private to a thread, dAL entries to the last lane of a lane group, dDL entries to lanes 31 and 63 of
+    // a wavefront: no barrier needed for them until the final sums
 
     // ---- the cells this thread produces: index inside the band -> (row, column), fixed for the whole kernel
     int cell_r[CT], cell_c[CT];
@@ -252,13 +316,23 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_bwd_shared_kernel(const Bwd
         cell_c[v] = id - cell_r[v] * PANEL;
         cell_ok[v] = id < CELLS && live;
         if (!cell_ok[v]) { cell_r[v] = 0; cell_c[v] = 0; }
+        cell_ok[v] = cell_ok[v] && cb + cell_c[v] < W;
     }
+    // Every access below runs unconditionally, in straight-line code: what does not exist is addressed past the end of its
+    // buffer descriptor (loads then return 0, stores are dropped).  With loads and stores in branches the compiler has to
+    // wait for ALL outstanding accesses wherever it needs one, the partial sums' stores of the previous band among them
+    // (a panel sweep of 211x397 bf16 spent two thirds of its time there).
+    constexpr uint32_t kNowhere = 0x80000000u;            // past every descriptor (at most 2^31 - 1 bytes)
     uint32_t rawx[CT], rawd[CT], rawy[CT], rawm[CT], rawz[GATE ? CT : 1], raws[GATE ? CT : 1];
-    // Loads of the cells of (band, channel): clamped to a valid element, so that no load sits in a branch; what
-    // lies outside the map is zeroed where the cell is produced.
+    float ckn[NW][K], An_next[NW];                        // of the next (band, channel): checkpoint, A
+    float hcn[MP ? RB : 1][NW], qcn[MP ? RB : 1][NW];     // and the carries from the neighbouring panels (lane 0, last lane; else 0)
+    auto map_of = [&](int ch) { return (size_t)b * p.Dc + c_first + min(ch, max(nch - 1, 0)); };
+    const uint32_t ck_row = p.ck_chunked ? (uint32_t)PANEL : (uint32_t)W;
+    const uint32_t ck_lane = p.ck_chunked ? (uint32_t)l * 16u : lcol * 4u, ck_step = p.ck_chunked ? LG * 16u : 16u;
+    const rsrc_t rs_m = make_rsrc(mm, mm != nullptr ? HW : 0);
+    // Loads of (band, channel): clamped to a valid element; what lies outside the map is zeroed where the cell is produced.
     auto request = [&](int band, int ch) {
-        const int c = c_first + min(ch, max(nch - 1, 0));
-        const size_t map = (size_t)b * p.Dc + c;
+        const size_t map = map_of(ch);
         const T* xm = reinterpret_cast<const T*>(p.x) + map * HW;
         const DT* dm = reinterpret_cast<const DT*>(p.delta) + map * HW;
         const T* dym = reinterpret_cast<const T*>(p.dy) + map * HW;
@@ -266,13 +340,35 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_bwd_shared_kernel(const Bwd
         const T* ysm = reinterpret_cast<const T*>(p.y_scan) + map * HW;    // GATE only
 #pragma unroll
         for (int v = 0; v < CT; ++v) {
-            const int i = min(band * RB + cell_r[v], H - 1);
-            const size_t o = (size_t)i * W + (size_t)min(cb + cell_c[v], W - 1);
-            if constexpr (GATE) { rawz[v] = elem_bits(zm + o); raws[v] = elem_bits(ysm + o); }
-            rawx[v] = elem_bits(xm + o);
-            rawd[v] = elem_bits(dm + o);
-            rawy[v] = elem_bits(dym + o);
-            rawm[v] = mm != nullptr ? (uint32_t)mm[o] : 0u;
+            const uint32_t o = (uint32_t)min(band * RB + cell_r[v], H - 1) * (uint32_t)W + (uint32_t)min(cb + cell_c[v], W - 1);
+            if constexpr (GATE) { rawz[v] = elem_bits(at_byte(zm, o * EB)); raws[v] = elem_bits(at_byte(ysm, o * EB)); }
+            rawx[v] = elem_bits(at_byte(xm, o * EB));
+            rawd[v] = elem_bits(at_byte(dm, o * (uint32_t)Elem<DT>::kBytes));
+            rawy[v] = elem_bits(at_byte(dym, o * EB));
+        }
+        // the checkpoint (band 0 starts from zero and reads what band 1 reads); past the row end: the next row or the region behind
+        const float* ck = p.ck + (map * p.nb + min(max(band, 1), p.nb - 1)) * N * ck_row;
+        const float* Am = p.A + (map - (size_t)b * p.Dc) * N;
+#pragma unroll
+        for (int s = 0; s < NW; ++s) {
+            const float* src = at_byte(ck, (uint32_t)(n0 + s) * ck_row * 4u + ck_lane);
+#pragma unroll
+            for (int j4 = 0; j4 < K / 4; ++j4) load_f32s<4>(at_byte(src, j4 * ck_step), &ckn[s][4 * j4]);
+            if constexpr (K % 4 == 2) load_f32s<2>(src + K - 2, &ckn[s][K - 2]);
+            An_next[s] = *at_byte(Am, (uint32_t)(n0 + s) * 4u);
+        }
+        if constexpr (MP) {
+            const size_t rows = (size_t)N * H;
+            const rsrc_t rh = make_rsrc(p.hc_in + map * rows, p.hc_in != nullptr ? rows * 4 : 0);
+            const rsrc_t rq = make_rsrc(p.qc_in + map * rows, p.qc_in != nullptr ? rows * 4 : 0);
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int s = 0; s < NW; ++s) {
+                    const uint32_t o = band * RB + r < H ? ((uint32_t)(n0 + s) * H + band * RB + r) * 4u : kNowhere;
+                    hcn[r][s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rh, l == 0 ? o : kNowhere, 0, 0));
+                    qcn[r][s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rq, l == LG - 1 ? o : kNowhere, 0, 0));
+                }
         }
     };
     auto widen = [](uint32_t bits, auto tag) -> float {
@@ -280,390 +376,347 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_bwd_shared_kernel(const Bwd
         if constexpr (Elem<E>::kBytes == 4) return __uint_as_float(bits);
         else return __uint_as_float(bits << 16);
     };
+    auto put_elem_at = [&](rsrc_t rs, uint32_t elem, bool ok, float v, auto tag) {      // one element, or nothing
+        using E = decltype(tag);
+        const uint32_t o = ok ? elem * (uint32_t)Elem<E>::kBytes : kNowhere;
+        if constexpr (Elem<E>::kBytes == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs, o, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b16((uint16_t)f32_to_bf16_bits(v), rs, o, 0, 0);
+    };
+    auto put_row = [&](uint32_t* r, const T* rowp, uint32_t off, bool last, const T* tail_row) {
+        const T* q = at_byte(rowp, off);
+        if constexpr (!FAST) q = last ? tail_row + lcol : q;
+        load_words_any<words_of<T, K>()>(q, r);
+    };
+    // Bm / Cm: of all rows of a band (BCR), or of the row at hand and the one after it
+    constexpr int BR = BCR ? RB : 2;                      // rows held: all, or the current and the next one
+    uint32_t bB[BR][NW][XW], bC[BR][NW][XW];
+    auto load_B = [&](int k, int i) {
+#pragma unroll
+        for (int s = 0; s < NW; ++s) put_row(bB[k][s], Bb + (size_t)min(i, H - 1) * W, soff[s], lastB[s] && i >= H - 1, tl.B);
+    };
+    auto load_C = [&](int k, int i) {
+#pragma unroll
+        for (int s = 0; s < NW; ++s) put_row(bC[k][s], Cb + (size_t)min(i, H - 1) * W, soff[s], lastB[s] && i >= H - 1, tl.C);
+    };
+    auto load_band = [&](int band) {
+        if constexpr (BCR) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r) { load_B(r, band * RB + r); load_C(r, band * RB + r); }
+        } else {
+            load_B(0, band * RB);
+        }
+#pragma unroll
+        for (int v = 0; v < CT; ++v)
+            rawm[v] = __builtin_amdgcn_raw_buffer_load_b8(rs_m, (uint32_t)min(band * RB + cell_r[v], H - 1) * (uint32_t)W + (uint32_t)min(cb + cell_c[v], W - 1), 0, 0);
+    };
 
-    int step = 0;                                         // rows reduced so far: parity picks the `part` buffer
-    request(p.nb - 1, 0);
-    for (int band = p.nb - 1; band >= 0; --band) {
+    float dBacc[RB][NW][K], dCacc[RB][NW][K];
+    // The partial sums of a band over this workgroup's channels (past the last band: nothing).
+    const uint32_t part_row = p.part_chunked ? (uint32_t)PANEL : (uint32_t)W;
+    const size_t part_bytes = (size_t)N * H * part_row * 4;
+    const rsrc_t rs_B = make_rsrc(p.pB + ((size_t)b * p.CG + cg) * N * H * part_row, part_bytes);
+    const rsrc_t rs_C = make_rsrc(p.pC + ((size_t)b * p.CG + cg) * N * H * part_row, part_bytes);
+    auto store_band = [&](int band) {
+        const uint32_t lane_at = p.part_chunked ? (uint32_t)l * 16u : (uint32_t)col0 * 4u, step = p.part_chunked ? LG * 16u : 16u;
+        const bool whole = live && (p.part_chunked || nv == K);      // chunked: every lane stores; the reduction drops the columns past W
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int i = band * RB + r;
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const uint32_t o = (((uint32_t)(n0 + s) * H + i) * part_row) * 4u + lane_at;
+                const uint32_t ow = whole && i < H ? o : kNowhere;
+#pragma unroll
+                for (int j = 0; j + 4 <= K; j += 4) {
+                    const u32x4_t vB = {__float_as_uint(dBacc[r][s][j]), __float_as_uint(dBacc[r][s][j + 1]), __float_as_uint(dBacc[r][s][j + 2]), __float_as_uint(dBacc[r][s][j + 3])};
+                    const u32x4_t vC = {__float_as_uint(dCacc[r][s][j]), __float_as_uint(dCacc[r][s][j + 1]), __float_as_uint(dCacc[r][s][j + 2]), __float_as_uint(dCacc[r][s][j + 3])};
+                    __builtin_amdgcn_raw_buffer_store_b128(vB, rs_B, ow, (j / 4) * step, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(vC, rs_C, ow, (j / 4) * step, 0);
+                }
+                if constexpr (K % 4 == 2) {
+                    const u32x2_t vB = {__float_as_uint(dBacc[r][s][K - 2]), __float_as_uint(dBacc[r][s][K - 1])};
+                    const u32x2_t vC = {__float_as_uint(dCacc[r][s][K - 2]), __float_as_uint(dCacc[r][s][K - 1])};
+                    __builtin_amdgcn_raw_buffer_store_b64(vB, rs_B, ow, (K - 2) * 4, 0);
+                    __builtin_amdgcn_raw_buffer_store_b64(vC, rs_C, ow, (K - 2) * 4, 0);
+                }
+                if constexpr (!FAST) {                     // the lane across the row end
+#pragma unroll
+                    for (int j = 0; j + 1 < K; ++j) {
+                        const uint32_t oe = live && !p.part_chunked && nv < K && j < nv && i < H ? o + 4u * j : kNowhere;
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dBacc[r][s][j]), rs_B, oe, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dCacc[r][s][j]), rs_C, oe, 0, 0);
+                    }
+                }
+            }
+        }
+    };
+
+    // One (band, channel).
+    auto sweep = [&](int band, int ch) {
         const int r0 = band * RB;
-        const int ilast = min(r0 + RB, H) - 1;            // bottom row of the band
-        float dBacc[RB][NW][K], dCacc[RB][NW][K];
+        const bool act = ch < nch;
+        const size_t map = map_of(ch);                     // idle iterations re-read a valid channel
+        const int c = (int)(map - (size_t)b * p.Dc);
+        const float dbc = (SPIN && p.delta_bias != nullptr) ? p.delta_bias[c] : 0.0f;
+        float An[NW], Ap[NW], hcv[MP ? RB : 1][NW], qcv[MP ? RB : 1][NW];
+#pragma unroll
+        for (int s = 0; s < NW; ++s) {
+            An[s] = An_next[s];
+            Ap[s] = An[s] * kLog2e;
+            if constexpr (MP) {
+#pragma unroll
+                for (int r = 0; r < RB; ++r) { hcv[r][s] = hcn[r][s]; qcv[r][s] = qcn[r][s]; }
+            }
+        }
+        const float dsk = p.Dskip != nullptr ? p.Dskip[c] : 0.0f;
+
+        // ---- produce the per-position values of this (band, channel)
+        float xe[CT], dDb = 0.0f, dBb = 0.0f;              // dBb (SPIN): sum of the ddelta_raw this thread stores
+#pragma unroll
+        for (int v = 0; v < CT; ++v) {
+            const bool in = cell_ok[v] && act && r0 + cell_r[v] < H;
+            const bool m = rawm[v] != 0u;
+            float dl = widen(rawd[v], DT{});
+            if constexpr (SPIN) dl = softplus_f32(dl + dbc);
+            dl = in ? dl : 0.0f;
+            xe[v] = (in && !m) ? widen(rawx[v], T{}) : 0.0f;         // select: nothing under the mask leaks
+            float dyv = in ? widen(rawy[v], T{}) : 0.0f;
+            if constexpr (GATE) {
+                const float zv = widen(rawz[v], T{}), sgm = logistic_f32(zv);
+                put_elem_at(make_rsrc(reinterpret_cast<T*>(p.dz) + map * HW, HW * EB), (uint32_t)(r0 + cell_r[v]) * (uint32_t)W + (uint32_t)(cb + cell_c[v]), in,
+                            dyv * widen(raws[v], T{}) * (sgm * fmaf(zv, 1.0f - sgm, 1.0f)), T{});
+                dyv = in ? dyv * (zv * sgm) : 0.0f;
+            }
+            if (v + 1 < CT || CELLS % TMJ == 0 || tm + v * TMJ < CELLS) {
+                float* row = ppj + cell_r[v] * PP_ROW + lds_colk<LG, K>(cell_c[v]);
+                row[0] = dl;
+                row[PANEL] = dl * xe[v];
+                row[2 * PANEL] = dyv;
+            }
+            dDb = fmaf(dyv, xe[v], dDb);
+        }
+        float hcur[NW][K];                                 // the band's checkpoint
+#pragma unroll
+        for (int s = 0; s < NW; ++s)
+#pragma unroll
+            for (int j = 0; j < K; ++j) hcur[s][j] = band > 0 && j < nv ? ckn[s][j] : 0.0f;
+        request(ch + 1 < GS ? band : max(band - 1, 0), ch + 1 < GS ? ch + 1 : 0);      // of the next (band, channel)
+        __syncthreads();
+        if constexpr (BCR && EB == 2) {                    // keep them packed: the compiler would widen them once, outside the channel loop
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int s = 0; s < NW; ++s)
+#pragma unroll
+                    for (int w = 0; w < XW; ++w) asm volatile("" : "+v"(bB[r][s][w]), "+v"(bC[r][s][w]));
+        }
+
+        // ---- scans 1 and 2: rebuild h[i-1,j] (CF: v[i-1,j] and h[i,j-1]) for the rows of the band.  Rows past H have step 0
+        // and x 0: they change nothing.  A row recurrence runs twice over the lane's columns: first for the lane's own
+        // (decay product, state) pair that the lanes scan, then from the state that enters the lane - as many
+        // multiply-adds as adding the carry to stored partial results, without the arrays that hold them
+        float hprev[RB][NW][K], hhl[RECOMP ? 1 : RB][NW][K];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            if constexpr (!BCR) {                          // row 0 is there: from the band's first request, then from the row sweep
+                if (r + 1 < RB) load_B((r + 1) % BR, r0 + r + 1);
+                else load_C(r % BR, r0 + r);
+            }
+            float dl[K], dxe[K], a[NW][K], u[NW][K], P[NW], Hh[NW], cin[NW];
+            lds_read_k<LG, K>(ppj + r * PP_ROW, l, dl);
+            lds_read_k<LG, K>(ppj + r * PP_ROW + PANEL, l, dxe);
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const uint32_t* Br = bB[r % BR][s];
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    a[s][j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
+                    if (r < ALR && j % 4 == 3) *reinterpret_cast<float4*>(aL + ((r * NW * K + s * K + j - 3) / 4 * THREADS + tid) * 4) = make_float4(a[s][j - 3], a[s][j - 2], a[s][j - 1], a[s][j]);
+                    u[s][j] = dxe[j] * get_elem<T, K>(Br, j);
+                    if constexpr (CF) {
+                        hprev[r][s][j] = hcur[s][j];                                   // v[i-1,j]
+                        u[s][j] = hcur[s][j] = fmaf(a[s][j], hcur[s][j], u[s][j]);
+                    }
+                    P[s] = j == 0 ? a[s][0] : P[s] * a[s][j];
+                    Hh[s] = j == 0 ? u[s][0] : fmaf(a[s][j], Hh[s], u[s][j]);
+                }
+                if constexpr (MP) Hh[s] = fmaf(P[s], hcv[r][s], Hh[s]);                // state entering from the panel to the left
+            }
+            group_scan<LG, NW>(P, Hh, cin);
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                float left = cin[s];                       // hhor[i, j-1] (CF: h[i, j-1])
+                if constexpr (MP) left += hcv[r][s];       // one of them is 0
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    if constexpr (!RECOMP) hhl[r][s][j] = left;
+                    if (!CF || j + 1 < K) left = fmaf(a[s][j], left, u[s][j]);
+                    if constexpr (!CF) {
+                        hprev[r][s][j] = hcur[s][j];
+                        hcur[s][j] = fmaf(a[s][j], hcur[s][j], left);
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);             // rows stay apart: merged, their temporaries would not fit the registers
+        }
+
+        // the compiler would keep step, step * x and the decays of all rows from here to the reverse sweep (3 RB NW K registers)
+        asm volatile("" ::: "memory");
+        // ---- scans 3 and 4, bottom row of the band first
+        float ga[NW][K], dAb[NW];
+#pragma unroll
+        for (int s = 0; s < NW; ++s) {
+            dAb[s] = 0.0f;
+#pragma unroll
+            for (int j = 0; j < K; ++j) ga[s][j] = gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j];
+        }
+#pragma unroll
+        for (int r = RB - 1; r >= 0; --r) {
+            if constexpr (!BCR) {
+                if (r > 0) { load_B((r - 1) % BR, r0 + r - 1); load_C((r - 1) % BR, r0 + r - 1); }
+            }
+            const float* prow = ppj + r * PP_ROW;
+            float dl[K], dxe[K], dyv[K], s1[K], s2[K], a[NW][K], g[NW][K], P[NW], Q[NW], qin[NW], edge[NW];
+            lds_read_k<LG, K>(prow, l, dl);
+            lds_read_k<LG, K>(prow + PANEL, l, dxe);
+            lds_read_k<LG, K>(prow + 2 * PANEL, l, dyv);
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                const uint32_t* Cr = bC[r % BR][s];
+                if (r < ALR) {
+#pragma unroll
+                    for (int j = 0; j < K; j += 4) {
+                        const float4 v = *reinterpret_cast<const float4*>(aL + ((r * NW * K + s * K + j) / 4 * THREADS + tid) * 4);
+                        a[s][j] = v.x; a[s][j + 1] = v.y; a[s][j + 2] = v.z; a[s][j + 3] = v.w;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    if (r >= ALR) a[s][j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
+                    float hv;
+                    if constexpr (CF) {                // v[i,j], then h[i,j]
+                        hv = fmaf(a[s][j], hprev[r][s][j], dxe[j] * get_elem<T, K>(bB[r % BR][s], j));
+                        hv = fmaf(a[s][j], hhl[r][s][j], hv);
+                    } else {                           // h[i,j] is what the row below started from
+                        hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
+                    }
+                    dCacc[r][s][j] = fmaf(dyv[j], hv, dCacc[r][s][j]);
+                    const float Cv = get_elem<T, K>(Cr, j);
+                    if constexpr (CF) {
+                        g[s][j] = dyv[j] * Cv;
+                    } else {
+                        g[s][j] = fmaf(dyv[j], Cv, ga[s][j]);                                       // scan 3
+                        ga[s][j] = a[s][j] * g[s][j];
+                    }
+                }
+                // scan 4: q[j] = g[j] + a[j+1] * q[j+1]
+                edge[s] = from_right_any<LG>(a[s][0]);
+                if constexpr (MP) g[s][K - 1] += qcv[r][s];        // a*q entering from the panel to the right (last lane)
+                P[s] = edge[s];
+                Q[s] = g[s][K - 1];
+#pragma unroll
+                for (int j = K - 2; j >= 0; --j) {
+                    Q[s] = fmaf(a[s][j + 1], Q[s], g[s][j]);
+                    P[s] *= a[s][j + 1];
+                }
+            }
+            group_scan_left_any<LG, NW>(P, Q, qin);
+#pragma unroll
+            for (int s = 0; s < NW; ++s) {
+                float q = qin[s], first = 0.0f;                    // first: hhor[i,j-1] of the lane's first column
+                const auto hh = [&](int j) {                       // hhor[i,j]
+                    const float hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
+                    return fmaf(-a[s][j], hprev[r][s][j], hv);
+                };
+                if constexpr (RECOMP) {
+                    first = from_left_any<LG>(hh(K - 1));
+                    if constexpr (MP) first += hcv[r][s];          // one of them is 0
+                }
+#pragma unroll
+                for (int j = K - 1; j >= 0; --j) {
+                    q = fmaf(j == K - 1 ? edge[s] : a[s][j + 1], q, g[s][j]);
+                    const float aq = a[s][j] * q;
+                    if constexpr (MP) {
+                        if (j == 0) put_elem_at(make_rsrc(p.qc_out + map * N * H, p.qc_out != nullptr ? (size_t)N * H * 4 : 0), (uint32_t)(n0 + s) * H + r0 + r,
+                                                l == 0 && act && r0 + r < H, aq, float{});
+                    }
+                    float left;                                    // hhor[i,j-1] (CF: h[i,j-1])
+                    if constexpr (RECOMP) left = j == 0 ? first : hh(j - 1);
+                    else left = hhl[r][s][j];
+                    float du = q;                                  // gradient of u
+                    if constexpr (CF) {
+                        du = q + ga[s][j];
+                        ga[s][j] = a[s][j] * du;
+                    }
+                    const float t = fmaf(aq, left, ga[s][j] * hprev[r][s][j]);   // gradient of the decay, times the decay
+                    dAb[s] = fmaf(t, dl[j], dAb[s]);
+                    s1[j] = s == 0 ? t * An[s] : fmaf(t, An[s], s1[j]);
+                    const float Bv = get_elem<T, K>(bB[r % BR][s], j);
+                    s2[j] = s == 0 ? du * Bv : fmaf(du, Bv, s2[j]);
+                    dBacc[r][s][j] = fmaf(du, dxe[j], dBacc[r][s][j]);
+                }
+            }
+            Part::put(part + (size_t)(r * WAVES + wave) * Part::kRow, lane, s1, s2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int s = 0; s < NW; ++s) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j] = ga[s][j];
+            const float tot = group_sum_last<LG>(inside ? dAb[s] : 0.0f);
+            if (l == LG - 1) dAL[((size_t)ch * SLOTS + slot) * NW + s] += tot;
+        }
+        __syncthreads();
+
+        // ---- finish: the sums over the states of this thread's cells
+#pragma unroll
+        for (int v = 0; v < CT; ++v) {
+            const bool in = cell_ok[v] && act && r0 + cell_r[v] < H;
+            const float* src = partj + (size_t)cell_r[v] * WAVES * Part::kRow + Part::at(cell_c[v]);
+            float sA = src[0], sB = src[Part::kTensor];
+#pragma unroll
+            for (int w = 1; w < WPJ; ++w) { sA += src[w * Part::kRow]; sB += src[w * Part::kRow + Part::kTensor]; }
+            const float* cell = ppj + cell_r[v] * PP_ROW + lds_colk<LG, K>(cell_c[v]);     // written by this thread
+            const float dl = cell[0], dyv = cell[2 * PANEL];
+            const uint32_t o = (uint32_t)(r0 + cell_r[v]) * (uint32_t)W + (uint32_t)(cb + cell_c[v]);
+            float dd = fmaf(xe[v], sB, sA);
+            if constexpr (SP && !SPIN)         // over the step of this cell, which nobody reads again
+                put_elem_at(make_rsrc(reinterpret_cast<const float*>(p.delta) + map * HW, HW * 4), o, in, dd, float{});
+            else {
+                if constexpr (SPIN) { dd = in ? dd * dsoftplus_from_value(dl) : 0.0f; dBb += dd; }
+                put_elem_at(make_rsrc(reinterpret_cast<T*>(p.ddelta) + map * HW, HW * EB), o, in, dd, T{});
+            }
+            // skip term; exactly +0 under the mask
+            put_elem_at(make_rsrc(reinterpret_cast<T*>(p.dx) + map * HW, HW * EB), o, in, rawm[v] != 0u ? 0.0f : fmaf(dsk, dyv, dl * sB), T{});
+        }
+        {
+            const float tot = group_sum_last<32>(halves_sum(dDb, dBb));   // lane 31: dDskip, lane 63: the bias gradient
+            if ((lane & 31) == 31) dDL[(ch * WAVES + wave) * 2 + (lane >> 5)] += tot;
+        }
+    };
+
+    request(p.nb - 1, 0);
+    load_band(p.nb - 1);
+    for (int band = p.nb - 1; band >= 0; --band) {
+        store_band(band + 1);                              // of the band below (first: rows past H, nothing is stored)
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
             for (int s = 0; s < NW; ++s)
 #pragma unroll
                 for (int j = 0; j < K; ++j) { dBacc[r][s][j] = 0.0f; dCacc[r][s][j] = 0.0f; }
-
-        for (int ch = 0; ch < GS; ++ch) {
-            const bool act = ch < nch;
-            const int c = act ? c_first + ch : c_first;      // idle iterations re-read a valid channel
-            const size_t map = (size_t)b * p.Dc + c;
-            float* ddw = (SP && !SPIN) ? const_cast<float*>(reinterpret_cast<const float*>(p.delta)) + map * HW : nullptr;
-            const float dbc = (SPIN && p.delta_bias != nullptr) ? p.delta_bias[c] : 0.0f;
-            T* dxm = reinterpret_cast<T*>(p.dx) + map * HW;
-            T* ddm = reinterpret_cast<T*>(p.ddelta) + map * HW;
-            float An[NW], Ap[NW];
-#pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                An[s] = p.A[(size_t)c * N + n0 + s];
-                Ap[s] = An[s] * kLog2e;
-            }
-            const float dsk = p.Dskip != nullptr ? p.Dskip[c] : 0.0f;
-
-            // ---- the per-position values of this (band, channel).  The threads that sum the last row of the previous
-            // (band, channel) still read its dy and mask flags: wait for them
-            __syncthreads();
-            float dDb = 0.0f, dBb = 0.0f;                      // dBb (SPIN): sum of the ddelta_raw this thread stores
-#pragma unroll
-            for (int v = 0; v < CT; ++v) {
-                const bool in = cell_ok[v] && act && r0 + cell_r[v] < H && cb + cell_c[v] < W;
-                const bool m = rawm[v] != 0u;
-                float dl = widen(rawd[v], DT{});
-                if constexpr (SPIN) dl = softplus_f32(dl + dbc);
-                dl = in ? dl : 0.0f;
-                const float xv = widen(rawx[v], T{});
-                const float xe = (in && !m) ? xv : 0.0f;                 // select: nothing under the mask leaks
-                float dyv = in ? widen(rawy[v], T{}) : 0.0f;
-                if constexpr (GATE) {
-                    const float zv = widen(rawz[v], T{}), sg = logistic_f32(zv);
-                    if (in) store_elem(reinterpret_cast<T*>(p.dz) + map * HW + (size_t)(r0 + cell_r[v]) * W + (size_t)(cb + cell_c[v]),
-                                       dyv * widen(raws[v], T{}) * (sg * fmaf(zv, 1.0f - sg, 1.0f)));
-                    dyv *= zv * sg;
-                }
-                if (cell_ok[v]) {
-                    float* row = ppj + cell_r[v] * PP_ROW + lds_colk<LG, K>(cell_c[v]);
-                    row[0] = dl;
-                    row[PANEL] = xe;
-                    row[2 * PANEL] = dl * xe;
-                    row[3 * PANEL] = dyv;
-                    row[4 * PANEL] = m ? 1.0f : 0.0f;
-                }
-                dDb = fmaf(dyv, xe, dDb);
-            }
-            // the cells of the next (band, channel)
-            if (ch + 1 < GS) request(band, ch + 1);
-            else request(max(band - 1, 0), 0);
-            __syncthreads();
-
-            // ---- scans 1 and 2: rebuild h[i-1,j] and hhor[i,j-1] for the rows of the band
-            float hprev[RB][NW][K], hhl[RECOMP ? 1 : RB][NW][K];
-            float hcur[NW][K];                                 // after scans 1 and 2: the state of the band's bottom row
-            {
-                uint32_t fB[NB][NW][XW];
-                auto issue = [&](int buf, int i) {
-                    const size_t ro = (size_t)i * W;
-                    const bool bottom = i == H - 1;
-#pragma unroll
-                    for (int s = 0; s < NW; ++s) ld_elems<T, K, FAST>(Bs[s] + ro, lcol, lastB[s] && bottom, tl.B, fB[buf][s]);
-                };
-                if constexpr (PF) issue(0, r0);
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    const float* src = p.ck + ((map * p.nb + band) * N + n0 + s) * W;
-                    if (band == 0) {
-#pragma unroll
-                        for (int j = 0; j < K; ++j) hcur[s][j] = 0.0f;
-                    } else {
-                        if (p.ck_chunked) {
-                            const float* cs = p.ck + ((map * p.nb + band) * N + n0 + s) * PANEL + l * 4;
-#pragma unroll
-                            for (int j4 = 0; j4 < K / 4; ++j4) {
-                                const float4 v = *reinterpret_cast<const float4*>(cs + j4 * (LG * 4));
-                                hcur[s][4 * j4] = v.x; hcur[s][4 * j4 + 1] = v.y; hcur[s][4 * j4 + 2] = v.z; hcur[s][4 * j4 + 3] = v.w;
-                            }
-                        } else {
-                            load_f32s<K>(src + lcol, hcur[s]);           // past the row end: the next checkpoint row or the region behind
-                        }
-                        if constexpr (!FAST) {
-#pragma unroll
-                            for (int j = 0; j < K; ++j)
-                                if (j >= nv) hcur[s][j] = 0.0f;
-                        }
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < RB; ++r) {
-                    const int i = r0 + r;
-                    if (i < H) {
-                        if constexpr (PF) { if (r + 1 < RB && i + 1 < H) issue((r + 1) & 1, i + 1); }
-                        else issue(0, i);
-                        float dl[K], dxe[K];
-                        lds_read_k<LG, K>(ppj + r * PP_ROW, l, dl);
-                        lds_read_k<LG, K>(ppj + r * PP_ROW + 2 * PANEL, l, dxe);
-#pragma unroll
-                        for (int s = 0; s < NW; ++s) {
-                            float a[K], hl[K], pl[K];
-#pragma unroll
-                            for (int j = 0; j < K; ++j) a[j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
-                            if constexpr (CF) {
-#pragma unroll
-                                for (int j = 0; j < K; ++j) {
-                                    hprev[r][s][j] = hcur[s][j];                                   // v[i-1,j]
-                                    hcur[s][j] = fmaf(a[j], hcur[s][j], dxe[j] * get_elem<T, K>(fB[PF ? (r & 1) : 0][s], j));
-                                }
-                                hl[0] = hcur[s][0];
-                            } else {
-                                hl[0] = dxe[0] * get_elem<T, K>(fB[PF ? (r & 1) : 0][s], 0);
-                            }
-                            float hcv = 0.0f;                             // state entering from the panel to the left
-                            if constexpr (MP) {
-                                if (p.hc_in != nullptr && l == 0) {
-                                    hcv = p.hc_in[(map * N + n0 + s) * H + i];
-                                    hl[0] = fmaf(a[0], hcv, hl[0]);
-                                }
-                            }
-                            pl[0] = a[0];
-#pragma unroll
-                            for (int j = 1; j < K; ++j) {
-                                hl[j] = fmaf(a[j], hl[j - 1], CF ? hcur[s][j] : dxe[j] * get_elem<T, K>(fB[PF ? (r & 1) : 0][s], j));
-                                pl[j] = pl[j - 1] * a[j];
-                            }
-                            float P[1] = {pl[K - 1]}, Hh[1] = {hl[K - 1]}, cin[1];
-                            group_scan<LG, 1>(P, Hh, cin);
-                            float left = cin[0];                          // hhor[i, j-1] (CF: h[i, j-1])
-                            if constexpr (MP) {
-                                if (p.hc_in != nullptr && l == 0) left = hcv;
-                            }
-#pragma unroll
-                            for (int j = 0; j < K; ++j) {
-                                const float hh = (j == K - 1) ? Hh[0] : fmaf(pl[j], cin[0], hl[j]);
-                                if constexpr (!RECOMP) hhl[r][s][j] = left;
-                                if constexpr (!CF) {
-                                    hprev[r][s][j] = hcur[s][j];
-                                    hcur[s][j] = fmaf(a[j], hcur[s][j], hh);
-                                }
-                                left = hh;
-                            }
-                        }
-                    } else if constexpr (!CF) {                  // below the map: the row above finds the bottom state here
-#pragma unroll
-                        for (int s = 0; s < NW; ++s)
-#pragma unroll
-                            for (int j = 0; j < K; ++j) hprev[r][s][j] = hcur[s][j];
-                    }
-                }
-            }
-
-            // ---- scans 3 and 4, bottom row of the band first
-            float ga[NW][K], dAb[NW];
-#pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                dAb[s] = 0.0f;
-#pragma unroll
-                for (int j = 0; j < K; ++j) ga[s][j] = gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j];
-            }
-            uint32_t bB[NB][NW][XW], bC[NB][NW][XW];
-            auto issue_r = [&](int buf, int i) {
-                const size_t ro = (size_t)i * W;
-                const bool bottom = i == H - 1;
-#pragma unroll
-                for (int s = 0; s < NW; ++s) {
-                    ld_elems<T, K, FAST>(Bs[s] + ro, lcol, lastB[s] && bottom, tl.B, bB[buf][s]);
-                    ld_elems<T, K, FAST>(Cs[s] + ro, lcol, lastB[s] && bottom, tl.C, bC[buf][s]);
-                }
-            };
-#pragma unroll
-            for (int r = RB - 1; r >= 0; --r) {
-                const int i = r0 + r;
-                if (i < H) {                                               // uniform over the workgroup
-                    if constexpr (PF) {
-                        if (i == ilast) issue_r(r & 1, i);
-                        if (r > 0) issue_r((r - 1) & 1, i - 1);
-                    } else {
-                        issue_r(0, i);
-                    }
-                    const size_t ro = (size_t)i * W;
-                    const float* prow = ppj + r * PP_ROW;
-                    // ddl: sum over this lane's states of (gradient of the decay) * a * A; dxl: of (gradient of u) * B.  The
-                    // factors that depend on the position only (x and the step) are applied after the sum over all states
-                    float dl[K], xe[LATEF ? 1 : K], dxe[K], dyv[K], ddl[K], dxl[K];
-                    lds_read_k<LG, K>(prow, l, dl);
-                    if constexpr (!LATEF) lds_read_k<LG, K>(prow + PANEL, l, xe);
-                    lds_read_k<LG, K>(prow + 2 * PANEL, l, dxe);
-                    lds_read_k<LG, K>(prow + 3 * PANEL, l, dyv);
-#pragma unroll
-                    for (int j = 0; j < K; ++j) { ddl[j] = 0.0f; dxl[j] = 0.0f; }
-#pragma unroll
-                    for (int s = 0; s < NW; ++s) {
-                        float a[K], Bv[K], g[K], hrow[RECOMP ? K : 1];
-#pragma unroll
-                        for (int j = 0; j < K; ++j) {
-                            a[j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
-                            Bv[j] = get_elem<T, K>(bB[PF ? (r & 1) : 0][s], j);
-                            float hv;
-                            if constexpr (CF) {                // v[i,j], then h[i,j]
-                                const float hh = fmaf(a[j], hprev[r][s][j], dxe[j] * Bv[j]);
-                                hv = fmaf(a[j], hhl[r][s][j], hh);
-                            } else {                           // h[i,j] is what the row below started from
-                                hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
-                            }
-                            dCacc[r][s][j] = fmaf(dyv[j], hv, dCacc[r][s][j]);
-                            if constexpr (RECOMP) hrow[j] = fmaf(-a[j], hprev[r][s][j], hv);           // hhor[i,j]
-                            const float dyC = dyv[j] * get_elem<T, K>(bC[PF ? (r & 1) : 0][s], j);
-                            if constexpr (CF) {
-                                g[j] = dyC;
-                            } else {
-                                g[j] = dyC + ga[s][j];                                                  // scan 3
-                                ga[s][j] = a[j] * g[j];
-                            }
-                        }
-                        if constexpr (RECOMP) {                  // hhor[i,j-1]: the left neighbour's last column for j = 0
-                            hhl[0][s][0] = from_left_any<LG>(hrow[K - 1]);
-#pragma unroll
-                            for (int j = 1; j < K; ++j) hhl[0][s][j] = hrow[j - 1];
-                        }
-                        // scan 4: q[j] = g[j] + a[j+1] * q[j+1]
-                        float ar[K], ql[K], pr[K];
-#pragma unroll
-                        for (int j = 0; j + 1 < K; ++j) ar[j] = a[j + 1];
-                        ar[K - 1] = from_right_any<LG>(a[0]);
-                        ql[K - 1] = g[K - 1];
-                        if constexpr (MP) {
-                            if (p.qc_in != nullptr && l == LG - 1)        // a*q entering from the panel to the right
-                                ql[K - 1] += p.qc_in[(map * N + n0 + s) * H + i];
-                        }
-                        pr[K - 1] = ar[K - 1];
-#pragma unroll
-                        for (int j = K - 2; j >= 0; --j) {
-                            ql[j] = fmaf(ar[j], ql[j + 1], g[j]);
-                            pr[j] = ar[j] * pr[j + 1];
-                        }
-                        float P[1] = {pr[0]}, Q[1] = {ql[0]}, qin[1];
-                        group_scan_left_any<LG>(P, Q, qin);
-#pragma unroll
-                        for (int j = 0; j < K; ++j) {
-                            const float q = fmaf(pr[j], qin[0], ql[j]);
-                            if constexpr (MP) {
-                                if (j == 0 && p.qc_out != nullptr && l == 0 && act) p.qc_out[(map * N + n0 + s) * H + i] = a[0] * q;
-                            }
-                            float gc, du;                                  // gradient along the column recurrence, gradient of u
-                            if constexpr (CF) {
-                                gc = q + ga[s][j];
-                                ga[s][j] = a[j] * gc;
-                                du = gc;
-                            } else {
-                                gc = g[j];
-                                du = q;
-                            }
-                            const float da = fmaf(gc, hprev[r][s][j], q * hhl[RECOMP ? 0 : r][s][j]);
-                            const float t = da * a[j];
-                            const float qB = du * Bv[j];
-                            dAb[s] = fmaf(t, dl[j], dAb[s]);
-                            if constexpr (LATEF) {
-                                ddl[j] = fmaf(t, An[s], ddl[j]);
-                                dxl[j] += qB;
-                            } else {
-                                ddl[j] = fmaf(t, An[s], fmaf(qB, xe[j], ddl[j]));
-                                dxl[j] = fmaf(qB, dl[j], dxl[j]);
-                            }
-                            dBacc[r][s][j] = fmaf(du, dxe[j], dBacc[r][s][j]);
-                        }
-                    }
-                    // sums over the states held by the other lane groups of this job
-                    float* mine = part + (size_t)(step & 1) * 2 * THREADS * K + (size_t)slot * PANEL;
-                    lds_write_k<LG, K>(mine, l, ddl);
-                    lds_write_k<LG, K>(mine + THREADS * K, l, dxl);
-                    __syncthreads();
-                    if (act) {
-                        const float* base = part + (size_t)(step & 1) * 2 * THREADS * K + (size_t)(slot - sg) * PANEL;
-#pragma unroll
-                        for (int v = 0; v < TT; ++v) {
-                            if constexpr (!LATEF) {
-                                const int t = tm + v * TMJ;
-                                const int tens = t / PANEL, lc = t - tens * PANEL, col = cb + lc;
-                                if (t < TASKS && col < W) {
-                                    const float sum = sum_partials_fixed<PANEL, NG>(base + tens * (THREADS * K) + lds_colk<LG, K>(lc));
-                                    if (tens == 0) {
-                                        if constexpr (SP && !SPIN) ddw[ro + col] = sum;  // over the step of this cell, which nobody reads again
-                                        else if constexpr (SPIN) {
-                                            const float v = sum * dsoftplus_from_value(prow[lds_colk<LG, K>(lc)]);
-                                            store_elem(ddm + ro + col, v);
-                                            dBb += v;
-                                        }
-                                        else store_elem(ddm + ro + col, sum);
-                                    } else {                                    // skip term; exactly +0 under the mask
-                                        const float* cell = prow + lds_colk<LG, K>(lc);
-                                        store_elem(dxm + ro + col, cell[4 * PANEL] != 0.0f ? 0.0f : fmaf(dsk, cell[3 * PANEL], sum));
-                                    }
-                                }
-                                continue;
-                            }
-                            const int lc = tm + v * TMJ, col = cb + lc;
-                            if (lc < PANEL && col < W) {
-                                const int at = lds_colk<LG, K>(lc);
-                                const float sA = sum_partials_fixed<PANEL, NG>(base + at);
-                                const float sB = sum_partials_fixed<PANEL, NG>(base + THREADS * K + at);
-                                const float* cell = prow + at;                  // dl, xe, dl*xe, dy, mask flag of this cell
-                                const float dd = fmaf(cell[PANEL], sB, sA);
-                                if constexpr (SP && !SPIN) ddw[ro + col] = dd;  // over the step of this cell, which nobody reads again
-                                else if constexpr (SPIN) {
-                                    const float v = dd * dsoftplus_from_value(cell[0]);
-                                    store_elem(ddm + ro + col, v);
-                                    dBb += v;
-                                }
-                                else store_elem(ddm + ro + col, dd);
-                                // skip term; exactly +0 under the mask
-                                store_elem(dxm + ro + col, cell[4 * PANEL] != 0.0f ? 0.0f : fmaf(dsk, cell[3 * PANEL], cell[0] * sB));
-                            }
-                        }
-                    }
-                    ++step;
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < NW; ++s) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j] = ga[s][j];
-                const float tot = group_sum_last<LG>(inside ? dAb[s] : 0.0f);
-                if (l == LG - 1) dAL[((size_t)ch * SLOTS + slot) * NW + s] += tot;
-            }
-            {
-                const float tot = group_sum_last<64>(dDb);
-                if ((tid & 63) == 63) dDL[ch * WAVES + wave] += tot;
-            }
-            if constexpr (SPIN) {
-                const float tot = group_sum_last<64>(dBb);
-                if ((tid & 63) == 63) dBL[ch * WAVES + wave] += tot;
-            }
-        }
-
-        // partial sums over this workgroup's channels, one write per band
-        if (live) {
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                const int i = r0 + r;
-                if (i < H) {
-#pragma unroll
-                    for (int s = 0; s < NW; ++s) {
-                        if (p.part_chunked) {                          // every lane stores; the reduction drops the columns past W
-                            const size_t oc = ((((size_t)b * p.CG + cg) * N + n0 + s) * H + i) * PANEL + l * 4;
-#pragma unroll
-                            for (int j4 = 0; j4 < K / 4; ++j4) {
-                                *reinterpret_cast<float4*>(p.pB + oc + j4 * (LG * 4)) =
-                                    make_float4(dBacc[r][s][4 * j4], dBacc[r][s][4 * j4 + 1], dBacc[r][s][4 * j4 + 2], dBacc[r][s][4 * j4 + 3]);
-                                *reinterpret_cast<float4*>(p.pC + oc + j4 * (LG * 4)) =
-                                    make_float4(dCacc[r][s][4 * j4], dCacc[r][s][4 * j4 + 1], dCacc[r][s][4 * j4 + 2], dCacc[r][s][4 * j4 + 3]);
-                            }
-                            continue;
-                        }
-                        const size_t o = ((((size_t)b * p.CG + cg) * N + n0 + s) * H + i) * W;
-                        if (nv == K) {
-                            store_f32s<K>(p.pB + o + col0, dBacc[r][s]);
-                            store_f32s<K>(p.pC + o + col0, dCacc[r][s]);
-                        } else {
-#pragma unroll
-                            for (int j = 0; j < K; ++j)
-                                if (col0 + j < W) { p.pB[o + col0 + j] = dBacc[r][s][j]; p.pC[o + col0 + j] = dCacc[r][s][j]; }
-                        }
-                    }
-                }
-            }
-        }
+        // The first channel is a copy of its own: behind it are a known number of accesses, which lets its waits leave the
+        // stores above in flight.  (One channel per workgroup: there is no other.)
+        sweep(band, 0);
+        for (int ch = 1; ch < GS; ++ch) sweep(band, ch);
+        load_band(max(band - 1, 0));
     }
+    store_band(0);
 
-    // dA[b,c,n]: already summed over the lane group; dDskip[b,c]: the sum over the job's wavefronts, in index order
+    // dA[b,c,n]: already summed over the lane group; dDskip[b,c] and the bias gradient: the sums over the job's wavefronts,
+    // in index order
     __syncthreads();
-    if (live && l == LG - 1) {
+    if (l == LG - 1) {
         for (int ch = 0; ch < nch; ++ch) {
 #pragma unroll
             for (int s = 0; s < NW; ++s)
@@ -674,24 +727,14 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_bwd_shared_kernel(const Bwd
             }
         }
     }
-    if (live && tm == 0 && p.pD != nullptr) {
-        constexpr int WPJ = TMJ >= 64 ? TMJ / 64 : 1;     // wavefronts of a job
-        const int w0 = (job_slot * TMJ) / 64;
-        for (int ch = 0; ch < nch; ++ch) {
-            float acc = 0.0f;
-            for (int w = 0; w < WPJ; ++w) acc += dDL[ch * WAVES + w0 + w];
-            float* dst = p.pD + (size_t)b * p.Dc + c_first + ch;
-            *dst = (MP && p.accum) ? *dst + acc : acc;
-        }
-    }
-    if constexpr (SPIN) {
-        if (live && tm == 0 && p.pBias != nullptr) {
-            constexpr int WPJ = TMJ >= 64 ? TMJ / 64 : 1;
-            const int w0 = (job_slot * TMJ) / 64;
+    if (tm < 2) {
+        float* const base = tm == 0 ? p.pD : (SPIN ? p.pBias : nullptr);
+        if (base != nullptr) {
             for (int ch = 0; ch < nch; ++ch) {
                 float acc = 0.0f;
-                for (int w = 0; w < WPJ; ++w) acc += dBL[ch * WAVES + w0 + w];
-                p.pBias[(size_t)b * p.Dc + c_first + ch] = acc;
+                for (int w = 0; w < WPJ; ++w) acc += dDL[(ch * WAVES + job_slot * WPJ + w) * 2 + tm];
+                float* dst = base + (size_t)b * p.Dc + c_first + ch;
+                *dst = (MP && p.accum) ? *dst + acc : acc;
             }
         }
     }

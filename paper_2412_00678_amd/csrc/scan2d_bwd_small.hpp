@@ -18,21 +18,10 @@
 // every channel another 37.
 #pragma once
 
-#include "scan2d_bwd_shared.hpp"   // dsoftplus_from_value, group_sum_last
+#include "scan2d_bwd_shared.hpp"   // dsoftplus_from_value, group_sum_last, halves_sum, row_pairs_sum
 #include "scan2d_fwd_small.hpp"    // raw_to_float
 
 namespace scan2d {
-
-// lanes 0..31: a summed over the wavefront's halves, lanes 32..63: b
-__device__ __forceinline__ float halves_sum(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// even DPP rows: a summed over the row pair, odd rows: b
-__device__ __forceinline__ float row_pairs_sum(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 // SP: delta is the raw projection, the step its softplus; GATE: as in scan2d_bwd_shared_kernel.
 template <typename T, int WPM, bool SP, bool GATE>

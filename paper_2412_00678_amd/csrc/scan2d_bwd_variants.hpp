@@ -22,6 +22,7 @@ struct BwdKernels {
     int ckpt_LG = 0, ckpt_waves = 0;      // the checkpoint sweep may use another lane tiling than the main sweep
     bool ckpt_fast = true;                // W is a multiple of the checkpoint sweep's columns per lane
     bool shared = false;                  // main sweep of scan2d_bwd_shared.hpp
+    size_t lds_fixed = 0, lds_per_channel = 0;   // its LDS in floats: fixed + per channel that a job handles in turn
     BwdKernel main_panels = nullptr;      // its instantiation that takes column panels (wave-wide tiling of two states per lane)
     BwdKernel main_gate = nullptr;        // its instantiation with the output gate's backward inside (softplus step, rows first)
     // checkpoint sweep run by the shared-producer forward kernel in its checkpoint mode (FwdArgs), with its tiling
@@ -38,7 +39,7 @@ struct BwdKernels {
 // checkpoint sweep in its checkpoint mode.
 #define SCAN2D_BWD_SHARED_VARIANTS(X)                                                       \
     X(16, 4, 1, 16, 4, 4, 16, 4, 2, 16, 4, 2, 8, 4, 4) X(16, 8, 1, 16, 4, 4, 16, 8, 2, 16, 8, 2, 8, 4, 2)       \
-    X(16, 12, 1, 16, 4, 4, 16, 12, 2, 16, 12, 2, 8, 4, 2) X(32, 6, 1, 16, 8, 2, 16, 12, 2, 16, 12, 2, 8, 4, 2)  \
+    X(16, 12, 1, 16, 4, 4, 16, 12, 2, 16, 12, 2, 8, 4, 2) X(32, 6, 1, 16, 8, 4, 16, 12, 2, 16, 12, 2, 8, 4, 2)  \
     X(32, 4, 1, 16, 8, 4, 16, 8, 2, 16, 8, 2, 8, 4, 2) X(64, 4, 1, 16, 16, 2, 64, 4, 1, 64, 4, 2, 8, 8, 4) \
     X(64, 4, 2, 8, 8, 2, 64, 4, 2, 64, 4, 2, 8, 8, 4)
 
@@ -62,7 +63,9 @@ inline BwdKernels lookup_bwd_shared_kernels(int LG, int K, int NW, int NG, int w
         r.ckpt_NW = cnw; r.ckpt_LG = clg; r.ckpt_waves = cwv; r.ckpt_fast = cfast;                       \
         r.main = fast ? scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, true, SP, CF>                 \
                       : scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, false, SP, CF>;               \
-        r.RB = rb; r.shared = true;                                                                      \
+        r.RB = rb; r.shared = true;                                                           \
+        r.lds_fixed = bwd_shared_lds_fixed<lg, k, nw, ng, wv, rb>();                                  \
+        r.lds_per_channel = bwd_shared_lds_per_channel<lg, k, nw, wv>();                                 \
         if constexpr (SP && !CF)                                                                         \
             r.main_gate = fast ? scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, true, true, false, false, true>       \
                                : scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, false, true, false, false, true>;     \

@@ -445,6 +445,14 @@ def test_backward_of_wide_maps_in_column_panels(s2d, shape):
     check_bwd(s2d, wl.Workload("bwide", Bt, Dc, N, H, W, dtype, mask_frac=mf, backward=True), seed=14)
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("Bt,Dc,H,W", [(3, 5, 5, 17), (1, 9, 4, 64), (2, 3, 9, 65), (1, 7, 3, 128), (2, 2, 8, 131), (1, 11, 13, 189),
+                                       (1, 3, 1, 192), (2, 3, 6, 193), (1, 2, 7, 259)])
+def test_backward_sweeps_at_the_edges_of_bands_and_tiles(s2d, Bt, Dc, H, W, dtype):
+    """Rows that fill a band exactly, leave one over or fall short of one; first and last widths of the lane tilings."""
+    check_bwd(s2d, wl.Workload("edge", Bt, Dc, 16, H, W, dtype, mask_frac=0.3, backward=True), seed=3)
+
+
 @pytest.mark.parametrize("W", [72, 75, 190])
 def test_backward_is_reproducible_and_ignores_garbage_under_the_mask(s2d, W):
     w = wl.Workload("brep", 2, 12, 16, 20, W, wl.F32, mask_frac=0.4, backward=True)
