@@ -40,6 +40,28 @@ __device__ __forceinline__ float widen_bits(uint32_t bits) {
     else return __uint_as_float(bits << 16);
 }
 
+// WORDS dwords at a wave-uniform base plus a 32-bit byte offset per lane.  Both are opaque to the compiler: seen through,
+// they are merged into a 64-bit pointer per load, kept in two vector registers wherever a loop around the
+// loads lets it (48 pointers in the projection kernel).
+template <int WORDS>
+__device__ __forceinline__ void load_words_at(const void* base, uint32_t off, uint32_t* r) {
+    static_assert(WORDS == 1 || WORDS == 2 || WORDS == 4, "one load");
+    uint64_t b = reinterpret_cast<uint64_t>(base);
+    asm volatile("" : "+s"(b), "+v"(off));
+    typedef const __attribute__((address_space(1))) char* Global;
+    const Global q = reinterpret_cast<Global>(b) + off;
+    if constexpr (WORDS == 1) {
+        typedef uint32_t W __attribute__((aligned(2), may_alias));
+        r[0] = *reinterpret_cast<const __attribute__((address_space(1))) W*>(q);
+    } else {
+        typedef uint32_t V __attribute__((ext_vector_type(WORDS)));
+        typedef V W __attribute__((aligned(2), may_alias));
+        const V v = *reinterpret_cast<const __attribute__((address_space(1))) W*>(q);
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) r[w] = v[w];
+    }
+}
+
 // 4 consecutive elements as fp32 / from fp32, any alignment.
 template <typename T>
 __device__ __forceinline__ void load4(const T* p, float* v) {
@@ -61,21 +83,29 @@ __device__ __forceinline__ void store4(T* p, const float* v) {
 
 // The positions of a lane.  Loads always take 4 positions that exist: at the end of the map the group moves back and
 // overlaps its neighbour, and only the positions from `p` on belong to this lane.  Maps have at least 4 positions.
+template <int E = 4>
 struct LanePos {
     uint32_t s, p;                        // first position read, first position owned (p >= s)
-    bool whole, any;                      // all four are owned; at least one is
+    bool whole, any;                      // all E are owned; at least one is
     __device__ __forceinline__ LanePos(uint32_t tile0, int n, uint32_t P) {
-        p = tile0 + 4u * (uint32_t)n;
-        s = min(p, P - 4u);
+        p = tile0 + (uint32_t)(E * n);
+        s = min(p, P - (uint32_t)E);
         whole = p == s;
         any = p < P;
     }
     // v[t] belongs to position s + t of `row`
     template <typename T> __device__ __forceinline__ void store(T* row, const float* v) const {
-        if (whole) store4<T>(row + s, v);
-        else if (any) {
+        if (whole) {
+            if constexpr (E == 4) store4<T>(row + s, v);
+            else if constexpr (Elem<T>::kBytes == 2) {
+                const uint32_t w = pack_bf16x2(v[0], v[1]);
+                store_words_any<1>(row + s, &w);
+            } else {
+                row[s] = v[0]; row[s + 1] = v[1];
+            }
+        } else if (any) {
 #pragma unroll
-            for (int t = 1; t < 4; ++t)
+            for (int t = 1; t < E; ++t)
                 if (s + t >= p) store_elem(row + s + t, v[t]);
         }
     }
@@ -101,10 +131,10 @@ __device__ __forceinline__ void contract(const T* __restrict__ in, uint32_t P, u
     auto load = [&](int buf, int c0) {
         const char* bb = reinterpret_cast<const char*>(in + (size_t)c0 * P);
 #pragma unroll
-        for (int e = 0; e < KL; ++e) load_words_any<BW>(bb + (size_t)e * P * EB + boff, braw[buf][e]);
+        for (int e = 0; e < KL; ++e) load_words_at<BW>(bb + (size_t)e * P * EB, boff, braw[buf][e]);
         const char* aa = reinterpret_cast<const char*>(W + c0);
 #pragma unroll
-        for (int ot = 0; ot < NOT; ++ot) load_words_any<4>(aa + aoff[ot], araw[buf][ot]);
+        for (int ot = 0; ot < NOT; ++ot) load_words_at<4>(aa, aoff[ot], araw[buf][ot]);
     };
     auto products = [&](int buf) {
         if constexpr (EB == 2) {

@@ -4,10 +4,11 @@
 //     RMS norm:   out = x / sqrt(mean_c x^2 + eps) * gamma[c] (+ beta[c])
 // Bound: HBM (one read, one write per element).  The mean is taken first and the variance as the mean of squared
 // deviations (no cancellation).
-// scan2d_norm_kernel, up to 512 channels: a workgroup owns 64 positions, 16 lanes x 4 consecutive ones, and its 16 rows of
-// lanes take every 16th channel (any alignment, any H*W of at least 4).  A thread keeps its C / 16 channels x 4 positions
-// in registers as they were loaded, all loads in flight at once, so the tensor is read once; the sums over the 16 parts
-// go over the lanes of a wavefront and then through LDS, in a fixed order.
+// scan2d_norm_kernel, up to 512 channels: a workgroup owns 64 positions, E consecutive ones per thread, and its PARTS rows of
+// threads take every PARTS-th channel (any alignment, any H*W of at least 4).  A thread keeps its C / PARTS channels x E
+// positions in registers as they were loaded, all loads in flight at once, so the tensor is read once; the sums over the
+// parts meet in LDS and are added in the order of the parts.  Eight parts of two positions in bf16 (the order of sums of
+// the other kernel, so both round alike), sixteen of four in fp32 (registers).
 // scan2d_norm_any_kernel, any shape: 32 groups of E consecutive positions per workgroup, the channels split eight ways,
 // three passes over the tile (the second and third from L2).
 #include "scan2d_block.hpp"
@@ -24,69 +25,71 @@ struct NormArgs {
     long long P, groups;            // positions per map, groups of E positions per map
 };
 
-// CPT: channels per thread, 16 CPT >= C
-template <typename T, int CPT>
-__global__ __launch_bounds__(256) void scan2d_norm_kernel(const NormArgs p) {
-    constexpr int XW = words_of<T, 4>();
-    __shared__ float red[2][4][64];
-    const int tid = threadIdx.x, n = tid & 15, part = tid >> 4, wv = tid >> 6;
+// E: consecutive positions of a thread, PARTS: threads that share a position's channels, CPT: channels per thread (PARTS CPT >= C)
+template <typename T, int E, int PARTS, int CPT>
+__global__ __launch_bounds__(64 / E * PARTS) void scan2d_norm_kernel(const NormArgs p) {
+    constexpr int XW = words_of<T, E>(), LANES = 64 / E, TH = LANES * PARTS;
+    __shared__ float red[2][PARTS][64];
+    __shared__ float gb[2][PARTS * CPT];
+    const int tid = threadIdx.x, n = tid % LANES, part = tid / LANES;
     const uint32_t P = (uint32_t)p.P, tiles = (P + 63u) / 64u;
     const int b = (int)(blockIdx.x / tiles), C = p.C;
-    const LanePos pos((blockIdx.x % tiles) * 64u, n, P);
+    const LanePos<E> pos((blockIdx.x % tiles) * 64u, n, P);
     const T* src = static_cast<const T*>(p.in) + (size_t)b * C * P + pos.s;
     uint32_t raw[CPT][XW];
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) load_words_any<XW>(src + (size_t)min(part + 16 * k, C - 1) * P, raw[k]);
+    for (int k = 0; k < CPT; ++k) load_words_any<XW>(src + (size_t)min(part + PARTS * k, C - 1) * P, raw[k]);
+    for (int c = tid; c < PARTS * CPT; c += TH) {          // behind the first barrier
+        gb[0][c] = p.gamma[min(c, C - 1)];
+        gb[1][c] = p.beta ? p.beta[min(c, C - 1)] : 0.0f;
+    }
     const float invC = 1.0f / (float)C;
-    auto total = [&](int buf, float* v) {                 // sum over the 16 parts, every thread gets it
+    auto total = [&](int buf, float* v) {                 // sum over the parts in their order, every thread gets it
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            v[t] += __shfl_xor(v[t], 16);
-            v[t] += __shfl_xor(v[t], 32);
-        }
-        if ((tid & 48) == 0) *reinterpret_cast<float4*>(&red[buf][wv][4 * n]) = make_float4(v[0], v[1], v[2], v[3]);
+        for (int t = 0; t < E; ++t) red[buf][part][E * n + t] = v[t];
         __syncthreads();
-        float4 t = *reinterpret_cast<const float4*>(&red[buf][0][4 * n]);
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const float4 a = *reinterpret_cast<const float4*>(&red[buf][w][4 * n]);
-            t.x += a.x; t.y += a.y; t.z += a.z; t.w += a.w;
-        }
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        for (int t = 0; t < E; ++t) v[t] = red[buf][0][E * n + t];
+#pragma unroll
+        for (int w = 1; w < PARTS; ++w)
+#pragma unroll
+            for (int t = 0; t < E; ++t) v[t] += red[buf][w][E * n + t];
     };
-    float mean[4] = {0.0f, 0.0f, 0.0f, 0.0f}, v[4] = {0.0f, 0.0f, 0.0f, 0.0f}, rstd[4];
+    float mean[E], v[E], rstd[E];
+#pragma unroll
+    for (int t = 0; t < E; ++t) mean[t] = v[t] = 0.0f;
     if (!p.rms) {
 #pragma unroll
         for (int k = 0; k < CPT; ++k)
-            if (part + 16 * k < C) {
+            if (part + PARTS * k < C) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) mean[t] += get_elem<T, 4>(raw[k], t);
+                for (int t = 0; t < E; ++t) mean[t] += get_elem<T, E>(raw[k], t);
             }
         total(0, mean);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) mean[t] *= invC;
+        for (int t = 0; t < E; ++t) mean[t] *= invC;
     }
 #pragma unroll
     for (int k = 0; k < CPT; ++k)
-        if (part + 16 * k < C) {
+        if (part + PARTS * k < C) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float e = get_elem<T, 4>(raw[k], t) - mean[t];
+            for (int t = 0; t < E; ++t) {
+                const float e = get_elem<T, E>(raw[k], t) - mean[t];
                 v[t] = fmaf(e, e, v[t]);
             }
         }
     total(1, v);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) rstd[t] = 1.0f / sqrtf(v[t] * invC + p.eps);
+    for (int t = 0; t < E; ++t) rstd[t] = 1.0f / sqrtf(v[t] * invC + p.eps);
     T* dst = static_cast<T*>(p.out) + (size_t)b * C * P;
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
-        const int c = part + 16 * k;
+        const int c = part + PARTS * k;
         if (c < C) {
-            const float gm = p.gamma[c], bt = p.beta ? p.beta[c] : 0.0f;
-            float o[4];
+            const float gm = gb[0][c], bt = gb[1][c];
+            float o[E];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) o[t] = fmaf((get_elem<T, 4>(raw[k], t) - mean[t]) * rstd[t], gm, bt);
+            for (int t = 0; t < E; ++t) o[t] = fmaf((get_elem<T, E>(raw[k], t) - mean[t]) * rstd[t], gm, bt);
             pos.store(dst + (size_t)c * P, o);
         }
     }
@@ -207,10 +210,10 @@ int block_norm_launch(const scan2d_desc* d, int kind, float eps, const void* in,
         if (blocks > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
         using Kernel = void (*)(const NormArgs);
         Kernel k;
-        if (a.C <= 64) k = bf16 ? scan2d_norm_kernel<bf16_t, 4> : scan2d_norm_kernel<float, 4>;
-        else if (a.C <= 128) k = bf16 ? scan2d_norm_kernel<bf16_t, 8> : scan2d_norm_kernel<float, 8>;
-        else if (a.C <= 256) k = bf16 ? scan2d_norm_kernel<bf16_t, 16> : scan2d_norm_kernel<float, 16>;
-        else k = bf16 ? scan2d_norm_kernel<bf16_t, 32> : scan2d_norm_kernel<float, 32>;
+        if (a.C <= 64) k = bf16 ? scan2d_norm_kernel<bf16_t, 2, 8, 8> : scan2d_norm_kernel<float, 4, 16, 4>;
+        else if (a.C <= 128) k = bf16 ? scan2d_norm_kernel<bf16_t, 2, 8, 16> : scan2d_norm_kernel<float, 4, 16, 8>;
+        else if (a.C <= 256) k = bf16 ? scan2d_norm_kernel<bf16_t, 2, 8, 32> : scan2d_norm_kernel<float, 4, 16, 16>;
+        else k = bf16 ? scan2d_norm_kernel<bf16_t, 2, 8, 64> : scan2d_norm_kernel<float, 4, 16, 32>;
         hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, stream, a);
         return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
     }

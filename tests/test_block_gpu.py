@@ -487,3 +487,36 @@ def test_whole_block_and_aggregator_replay_from_a_hip_graph(s2d, dtype):
     _, yr = oracle.scan2d_fwd_softplus_gated(xr, dr, i0["delta_bias"], i0["A"], Br, Cr, i0["Dskip"], i0["mask"], block.linear(tnr, i0["Win_z"], dtype=dtype), dtype=dtype)
     tr = block.linear(yr, i0["Wout"], None, i0["t"], dtype=dtype)
     assert rel_err(wl.to_float(got[0], dtype), wl.to_float(tr, dtype)) <= {wl.F32: 2e-5, wl.BF16: 3e-2}[dtype]
+
+
+# ------------------------------------------------------------------------------------------------ edges of the kernels' ranges
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("Bt,Dc,H,W", [(1, 3, 5, 8), (2, 2, 1, 9), (1, 2, 9, 15), (1, 5, 33, 65)])
+def test_conv3_at_the_edges_of_rows(s2d, Bt, Dc, H, W, dtype):
+    test_conv_silu_matches_oracle(s2d, (Bt, Dc, H, W, dtype, 3, 3, 1, 1))
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("Bt,Dc,N,H,W,R", [(1, 15, 1, 2, 2, 1), (1, 33, 16, 5, 13, 9), (2, 176, 16, 1, 67, 16), (1, 49, 20, 3, 43, 17),
+                                           (1, 40, 16, 257, 255, 3), (4, 20, 4, 127, 129, 20)])
+def test_xproj_with_ragged_channels_and_positions(s2d, Bt, Dc, N, H, W, R, dtype):
+    """Channels that are not whole steps, tiles that end inside a lane's group, more than one group of 48 rows, and enough
+    tiles that each wavefront works on its own."""
+    test_xproj_matches_oracle(s2d, (Bt, Dc, N, H, W, dtype, R))
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("Bt,Cin,Cout,H,W", [(1, 33, 17, 1, 5), (2, 31, 47, 5, 13), (1, 64, 96, 181, 183), (2, 96, 40, 129, 130), (1, 128, 80, 7, 4681)])
+def test_linear_with_ragged_channels_and_many_positions(s2d, Bt, Cin, Cout, H, W, dtype):
+    test_linear_matches_oracle(s2d, (Bt, Cin, Cout, H, W, dtype, True, True))
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("C", [7, 8, 64, 65, 129, 257, 511, 513])
+def test_norm_at_the_edges_of_channel_counts(s2d, C, dtype):
+    test_norm_matches_oracle(s2d, (2, C, 3, 23, dtype, C % 2, True))
+
+
+@pytest.mark.parametrize("H,W", [(1, 4), (31, 33), (32, 32), (65, 63), (64, 257), (129, 128)])
+def test_attn_pool_at_the_edges_of_bag_sizes(s2d, H, W):
+    test_attn_pool_matches_oracle(s2d, (1, 33, H, W, wl.BF16, 128, 0.3))
