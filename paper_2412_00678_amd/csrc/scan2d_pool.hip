@@ -125,6 +125,7 @@ __global__ __launch_bounds__(kSoftThreads) void scan2d_pool_softmax_kernel(const
     const uint8_t* mk = p.mask ? p.mask + (size_t)b * P : nullptr;
     float sv[NV][4];
     float mx = -INFINITY;
+    bool members = false;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         const uint32_t q = 4u * (uint32_t)(tid + k * kSoftThreads), s = min(q, P - 4u);
@@ -132,15 +133,18 @@ __global__ __launch_bounds__(kSoftThreads) void scan2d_pool_softmax_kernel(const
         uint32_t m = 0u;
         if (mk) load_words_any<1>(mk + s, &m);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (s + e < q || ((m >> (8 * e)) & 0xffu) != 0u) sv[k][e] = -INFINITY;    // not this thread's, or not in the bag
+        for (int e = 0; e < 4; ++e) {
+            const bool member = s + e >= q && ((m >> (8 * e)) & 0xffu) == 0u;         // else not this thread's, or not in the bag
+            if (!member) sv[k][e] = -INFINITY;
+            members |= member;
+        }
     }
 #pragma unroll
     for (int k = 0; k < NV; ++k)
 #pragma unroll
         for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sv[k][e]);
     mx = block_reduce<true>(mx, red);
-    float sum = 0.0f;
+    float sum = members && mx == -INFINITY ? NAN : 0.0f;  // every score of the bag is -infinity: no weights exist
 #pragma unroll
     for (int k = 0; k < NV; ++k)
 #pragma unroll

@@ -520,3 +520,15 @@ def test_norm_at_the_edges_of_channel_counts(s2d, C, dtype):
 @pytest.mark.parametrize("H,W", [(1, 4), (31, 33), (32, 32), (65, 63), (64, 257), (129, 128)])
 def test_attn_pool_at_the_edges_of_bag_sizes(s2d, H, W):
     test_attn_pool_matches_oracle(s2d, (1, 33, H, W, wl.BF16, 128, 0.3))
+
+
+@pytest.mark.parametrize("P", [2, 4, 4097, 20000])
+def test_attn_pool_of_a_bag_whose_scores_are_all_minus_infinity(s2d, P):
+    """No weights exist: NaN for the members as torch.softmax gives it, 0 under the mask."""
+    import torch
+    h = torch.rand((1, 8, 1, P), device="cuda") + 0.1
+    V, w = torch.ones((1, 8), device="cuda"), torch.full((1,), -float("inf"), device="cuda")
+    mask = torch.zeros((1, 1, P), dtype=torch.uint8, device="cuda")
+    mask[0, 0, 1] = 1
+    z, attn = s2d.block_attn_pool(h, V, w, mask)
+    assert float(attn[0, 0, 1]) == 0.0 and int(torch.isnan(attn).sum()) == P - 1 and bool(torch.isnan(z).all())
