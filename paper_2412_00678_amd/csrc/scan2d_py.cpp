@@ -40,6 +40,16 @@ void check_rc(int rc, const char* where) {
     throw Raised{};
 }
 
+// The call without the interpreter's lock: it may wait (a full queue, code objects loaded by a first call), and other
+// threads run meanwhile.
+template <typename R, typename... P, typename... A>
+R unlocked(R (*fn)(P...), A... args) {
+    PyThreadState* const state = PyEval_SaveThread();
+    const R r = fn(args...);
+    PyEval_RestoreThread(state);
+    return r;
+}
+
 std::string describe(at::ScalarType t, at::IntArrayRef shape) {
     std::string name = c10::toString(t);
     if (t == at::kFloat) name = "float32";
@@ -193,7 +203,7 @@ PyObject* scan_fwd(Args a) {              // x, delta, A, Bm, Cm, Dskip, mask, y
     const Scan s(a[0], a[1], "delta", a[2], a[3], a[4], a[5], a[6], flags_of(a[9]));
     Out y = s.new_map(a[7], "y");
     const Workspace w(a[8], s.m, SCAN2D_PASS_FWD);
-    check_rc(scan2d_fwd(&s.m.d, s.x, s.delta, s.A, s.Bm, s.Cm, s.Dskip, s.mask, y.p, w.p, w.bytes, stream()), "scan2d_fwd");
+    check_rc(unlocked(scan2d_fwd, &s.m.d, s.x, s.delta, s.A, s.Bm, s.Cm, s.Dskip, s.mask, y.p, w.p, w.bytes, stream()), "scan2d_fwd");
     return y.release();
 }
 
@@ -202,7 +212,7 @@ PyObject* scan_fwd_softplus(Args a) {     // x, delta_raw, delta_bias, A, Bm, Cm
     const float* bias = maybef(a[2], "delta_bias", {s.m.C});
     Out y = s.new_map(a[8], "y");
     const Workspace w(a[9], s.m, SCAN2D_PASS_FWD);
-    check_rc(scan2d_fwd_softplus(&s.m.d, s.x, s.delta, bias, s.A, s.Bm, s.Cm, s.Dskip, s.mask, y.p, w.p, w.bytes, stream()), "scan2d_fwd_softplus");
+    check_rc(unlocked(scan2d_fwd_softplus, &s.m.d, s.x, s.delta, bias, s.A, s.Bm, s.Cm, s.Dskip, s.mask, y.p, w.p, w.bytes, stream()), "scan2d_fwd_softplus");
     return y.release();
 }
 
@@ -215,7 +225,7 @@ PyObject* scan_fwd_gated(Args a) {        // x, delta_raw, delta_bias, A, Bm, Cm
     Out y = s.new_map(a[11], "y");
     Out ys = want ? s.new_map(a[12], "y_scan") : Out();
     const Workspace w(a[10], s.m, SCAN2D_PASS_FWD);
-    check_rc(scan2d_fwd_softplus_gated(&s.m.d, s.x, s.delta, bias, s.A, s.Bm, s.Cm, s.Dskip, s.mask, z, ys.p, y.p, w.p, w.bytes, stream()),
+    check_rc(unlocked(scan2d_fwd_softplus_gated, &s.m.d, s.x, s.delta, bias, s.A, s.Bm, s.Cm, s.Dskip, s.mask, z, ys.p, y.p, w.p, w.bytes, stream()),
              "scan2d_fwd_softplus_gated");
     return tuple(ys, y);
 }
@@ -239,7 +249,7 @@ PyObject* scan_bwd(Args a) {              // x, delta, A, Bm, Cm, Dskip, mask, d
     Out dx = s.new_map(given[0], "dx"), dd = s.new_map(given[1], "ddelta"), dA = s.new_A(given[2]), dB = s.new_states(given[3], "dBm"),
         dC = s.new_states(given[4], "dCm"), dD = s.new_channels(own && s.Dskip != nullptr, given[5], "dDskip");
     const Workspace w(a[8], s.m, SCAN2D_PASS_BWD);
-    check_rc(scan2d_bwd(&s.m.d, s.x, s.delta, s.A, s.Bm, s.Cm, s.Dskip, s.mask, dy, dx.p, dd.p, dA.f(), dB.f(), dC.f(), dD.f(), w.p, w.bytes, stream()),
+    check_rc(unlocked(scan2d_bwd, &s.m.d, s.x, s.delta, s.A, s.Bm, s.Cm, s.Dskip, s.mask, dy, dx.p, dd.p, dA.f(), dB.f(), dC.f(), dD.f(), w.p, w.bytes, stream()),
              "scan2d_bwd");
     return tuple(dx, dd, dA, dB, dC, dD);
 }
@@ -251,7 +261,7 @@ PyObject* scan_bwd_softplus(Args a) {     // x, delta_raw, delta_bias, A, Bm, Cm
     Out dx = s.new_map(), dd = s.new_map(), db = s.new_channels(bias != nullptr), dA = s.new_A(), dB = s.new_states(), dC = s.new_states(),
         dD = s.new_channels(s.Dskip != nullptr);
     const Workspace w(a[9], s.m, SCAN2D_PASS_BWD_SOFTPLUS);
-    check_rc(scan2d_bwd_softplus(&s.m.d, s.x, s.delta, bias, s.A, s.Bm, s.Cm, s.Dskip, s.mask, dy, dx.p, dd.p, db.f(), dA.f(), dB.f(), dC.f(), dD.f(),
+    check_rc(unlocked(scan2d_bwd_softplus, &s.m.d, s.x, s.delta, bias, s.A, s.Bm, s.Cm, s.Dskip, s.mask, dy, dx.p, dd.p, db.f(), dA.f(), dB.f(), dC.f(), dD.f(),
                                  w.p, w.bytes, stream()), "scan2d_bwd_softplus");
     return tuple(dx, dd, db, dA, dB, dC, dD);
 }
@@ -263,7 +273,7 @@ PyObject* scan_bwd_gated(Args a) {        // x, delta_raw, delta_bias, A, Bm, Cm
     Out dx = s.new_map(), dd = s.new_map(), dz = s.new_map(), db = s.new_channels(bias != nullptr), dA = s.new_A(), dB = s.new_states(),
         dC = s.new_states(), dD = s.new_channels(s.Dskip != nullptr);
     const Workspace w(a[11], s.m, SCAN2D_PASS_BWD_GATED);
-    check_rc(scan2d_bwd_softplus_gated(&s.m.d, s.x, s.delta, bias, s.A, s.Bm, s.Cm, s.Dskip, s.mask, z, ys, dy, dx.p, dd.p, db.f(), dA.f(), dB.f(),
+    check_rc(unlocked(scan2d_bwd_softplus_gated, &s.m.d, s.x, s.delta, bias, s.A, s.Bm, s.Cm, s.Dskip, s.mask, z, ys, dy, dx.p, dd.p, db.f(), dA.f(), dB.f(),
                                        dC.f(), dD.f(), dz.p, w.p, w.bytes, stream()), "scan2d_bwd_softplus_gated");
     return tuple(dx, dd, db, dA, dB, dC, dD, dz);
 }
@@ -276,7 +286,7 @@ PyObject* block_conv_silu(Args a) {       // u, w, bias, PH, PW, x
     const scan2d_conv_shape cs{(int32_t)KH, (int32_t)KW, (int32_t)(a[3] == Py_None ? KH / 2 : int_of(a[3])),
                                (int32_t)(a[4] == Py_None ? KW / 2 : int_of(a[4]))};
     Out x(a[5], "x", m, m.t, {m.Bt, m.C, m.H, m.W});
-    check_rc(scan2d_block_conv_silu(&m.d, &cs, u, w, bias, x.p, stream()), "scan2d_block_conv_silu");
+    check_rc(unlocked(scan2d_block_conv_silu, &m.d, &cs, u, w, bias, x.p, stream()), "scan2d_block_conv_silu");
     return x.release();
 }
 
@@ -295,7 +305,7 @@ PyObject* block_xproj(Args a) {           // x, Wx, Wdt, N, out
         }
     Out dr(given[0], "delta_raw", m, m.t, {m.Bt, m.C, m.H, m.W}), B(given[1], "Bm", m, m.t, {m.Bt, N, m.H, m.W}),
         C(given[2], "Cm", m, m.t, {m.Bt, N, m.H, m.W});
-    check_rc(scan2d_block_xproj(&m.d, (int)R, x, Wx, Wdt, dr.p, B.p, C.p, stream()), "scan2d_block_xproj");
+    check_rc(unlocked(scan2d_block_xproj, &m.d, (int)R, x, Wx, Wdt, dr.p, B.p, C.p, stream()), "scan2d_block_xproj");
     if (a[4] != Py_None) {
         Py_INCREF(a[4]);
         return a[4];
@@ -310,7 +320,7 @@ PyObject* block_linear(Args a) {          // x, Wt, bias, residual, out
     const float* bias = maybef(a[2], "bias", {Cout});
     const void* res = maybe(a[3], "residual", m.t, {m.Bt, Cout, m.H, m.W});
     Out out(a[4], "out", m, m.t, {m.Bt, Cout, m.H, m.W});
-    check_rc(scan2d_block_linear(&m.d, (int)Cout, x, Wt, bias, res, out.p, stream()), "scan2d_block_linear");
+    check_rc(unlocked(scan2d_block_linear, &m.d, (int)Cout, x, Wt, bias, res, out.p, stream()), "scan2d_block_linear");
     return out.release();
 }
 
@@ -322,7 +332,7 @@ PyObject* block_norm(Args a) {            // x, gamma, beta, eps, kind, out
     if (PyErr_Occurred()) throw Raised{};
     const int64_t kind = int_of(a[4]);
     Out out(a[5], "out", m, m.t, {m.Bt, m.C, m.H, m.W});
-    check_rc(scan2d_block_norm(&m.d, (int)kind, (float)eps, x, gamma, beta, out.p, stream()), "scan2d_block_norm");
+    check_rc(unlocked(scan2d_block_norm, &m.d, (int)kind, (float)eps, x, gamma, beta, out.p, stream()), "scan2d_block_norm");
     return out.release();
 }
 
@@ -341,7 +351,7 @@ PyObject* block_attn_pool(Args a) {       // h, V, w, mask, out
             if (given[i] == Py_None) raise(PyExc_ValueError, "out: expected two tensors");
         }
     Out z(given[0], "z", m, at::kFloat, {m.Bt, m.C}), attn(given[1], "attn", m, at::kFloat, {m.Bt, m.H, m.W});
-    check_rc(scan2d_block_attn_pool(&m.d, (int)D, h, V, w, mask, attn.f(), z.f(), stream()), "scan2d_block_attn_pool");
+    check_rc(unlocked(scan2d_block_attn_pool, &m.d, (int)D, h, V, w, mask, attn.f(), z.f(), stream()), "scan2d_block_attn_pool");
     if (a[4] != Py_None) {
         Py_INCREF(a[4]);
         return a[4];
@@ -366,6 +376,8 @@ int dispatch(size_t n, void* fn, const uint64_t* v, std::index_sequence<N...>) {
     static constexpr F table[] = {invoke_n<N + 1>...};
     return table[n - 1](fn, v);
 }
+
+int dispatch_any(size_t n, void* fn, const uint64_t* v) { return dispatch(n, fn, v, std::make_index_sequence<kMostArgs>()); }
 
 struct Call {
     PyObject_HEAD
@@ -402,7 +414,7 @@ PyObject* call_call(PyObject* self, PyObject*, PyObject*) {
     uint64_t v[kMostArgs];
     for (size_t i = 0; i + 1 < c->n; ++i) v[i] = c->v[i];
     v[c->n - 1] = reinterpret_cast<uint64_t>(stream());
-    return PyLong_FromLong(dispatch(c->n, c->fn, v, std::make_index_sequence<kMostArgs>()));
+    return PyLong_FromLong(unlocked(dispatch_any, c->n, c->fn, static_cast<const uint64_t*>(v)));
     END_HANDLE_TH_ERRORS
 }
 PyTypeObject CallType = {PyVarObject_HEAD_INIT(nullptr, 0)};

@@ -1152,3 +1152,57 @@ def test_training_pair_rejects_flags_and_short_buffers(s2d):
     flagged = s2d.make_desc(d["x"], d["A"], s2d.FLAG_IDENTITY_CELLS)
     assert s2d.lib.scan2d_fwd_saving(ctypes.byref(flagged), *args, p(saved), need, None, 0, None) == -4
     assert s2d.lib.scan2d_fwd_saving(ctypes.byref(desc), *args, None, need, None, 0, None) == -1
+
+
+def test_threads_with_streams_of_their_own_and_more_shapes_than_plans_are_kept(s2d):
+    """Each thread remembers its own launch plans, fewer than it is given shapes here, and calls run side by side."""
+    import threading
+    import torch
+    dev, g = "cuda", torch.Generator(device="cuda").manual_seed(5)
+    cases = []
+    for k in range(24):
+        H, W, N, Dc = 3 + 2 * k, 5 + 3 * k, (4, 16)[k % 2], 6
+        dt = (torch.float32, torch.bfloat16)[k // 2 % 2]
+        r = lambda *s: torch.randn(s, device=dev, generator=g)
+        cases.append((r(1, Dc, H, W).to(dt), r(1, Dc, H, W).sub(2).exp().to(dt), -r(Dc, N).exp(), r(1, N, H, W).to(dt), r(1, N, H, W).to(dt), r(Dc), None,
+                      r(1, Dc, H, W).to(dt)))
+    both = lambda c: (s2d.scan2d_fwd(*c[:7]),) + tuple(s2d.scan2d_bwd(*c))
+    want = [both(c) for c in cases]
+    torch.cuda.synchronize()
+    got, failed = [{} for _ in range(3)], []
+
+    def work(t):
+        try:
+            st = torch.cuda.Stream()
+            with torch.cuda.stream(st):
+                for k in range(2 * len(cases)):
+                    k = (k * (1, 5, 7)[t] + t) % len(cases)
+                    got[t][k] = both(cases[k])
+            st.synchronize()
+        except Exception as e:                             # noqa: BLE001 (reported below, in the test's own thread)
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
+    for outs in got:
+        assert len(outs) == len(cases)
+        for k, o in outs.items():
+            assert all(torch.equal(a, b) for a, b in zip(o, want[k]))
+
+
+@pytest.mark.parametrize("wrong", ["host", "strided", "dtype", "shape", "missing", "rank"])
+def test_binding_refuses_what_does_not_fit(s2d, wrong):
+    import torch
+    x = torch.zeros((1, 4, 6, 8), device="cuda")
+    A, B = torch.zeros((4, 2), device="cuda"), torch.zeros((1, 2, 6, 8), device="cuda")
+    bad = {"host": x.cpu(), "strided": x.transpose(2, 3).contiguous().transpose(2, 3), "dtype": x.bfloat16(), "shape": x[:, :3].contiguous(),
+           "missing": None, "rank": x[0]}[wrong]
+    with pytest.raises(ValueError):
+        s2d.scan2d_fwd(x, bad, A, B, B)
+    if wrong == "rank":
+        with pytest.raises(ValueError):
+            s2d.scan2d_fwd(bad, bad, A, B, B)
