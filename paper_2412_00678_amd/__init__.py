@@ -2,7 +2,7 @@
 
 Sub-modules:
   workloads -- seeded synthetic inputs (no scan arithmetic; importable without a GPU)
-  scan2d    -- thin ctypes binding of the C-ABI library built from csrc/ (HIP, gfx950)
+  scan2d    -- binding of the C-ABI library built from csrc/ (HIP, gfx950)
   build     -- compiles csrc/ with hipcc
 
 Importing the package itself loads nothing; `scan2d` loads the shared library on import and
