@@ -18,7 +18,7 @@
 // every channel another 37.
 #pragma once
 
-#include "scan2d_bwd_shared.hpp"   // dsoftplus_from_value, group_sum_last, halves_sum, row_pairs_sum
+#include "scan2d_bwd_shared.hpp"   // group_sum_last, halves_sum, row_pairs_sum
 #include "scan2d_fwd_small.hpp"    // raw_to_float
 
 namespace scan2d {
@@ -98,12 +98,15 @@ __global__ __launch_bounds__(256) void scan2d_bwd_small_kernel(const BwdArgs p) 
         const float dsk = p.Dskip != nullptr ? p.Dskip[c] : 0.0f;
         const float bias = (SP && p.delta_bias != nullptr) ? p.delta_bias[c] : 0.0f;
 
-        float dl_[CPT], xe_[CPT], dy_[CPT];
+        float dl_[CPT], xe_[CPT], dy_[CPT], lg_[SP ? CPT : 1];
 #pragma unroll
         for (int v = 0; v < CPT; ++v) {
             const bool ok = in[v] && act;
             float dl = raw_to_float(T{}, rd[v]);
-            if constexpr (SP) dl = softplus_f32(dl + bias);
+            if constexpr (SP) {
+                lg_[v] = logistic_f32(dl + bias);         // kept: formed from the step, it would have the step's absolute error
+                dl = softplus_f32(dl + bias);
+            }
             dl_[v] = ok ? dl : 0.0f;
             xe_[v] = ok && rm[v] == 0u ? raw_to_float(T{}, rx[v]) : 0.0f;        // select: nothing under the mask leaks
             float dyv = ok ? raw_to_float(T{}, ry[v]) : 0.0f;
@@ -205,7 +208,7 @@ __global__ __launch_bounds__(256) void scan2d_bwd_small_kernel(const BwdArgs p) 
             }
             if (in[v] && act) {
                 float dd = fmaf(xe_[v], S2, S1);
-                if constexpr (SP) { dd *= dsoftplus_from_value(dl_[v]); dBb += dd; }
+                if constexpr (SP) { dd *= lg_[v]; dBb += dd; }
                 store_elem(reinterpret_cast<T*>(p.ddelta) + map * HW + cell[v], dd);
                 store_elem(reinterpret_cast<T*>(p.dx) + map * HW + cell[v], rm[v] != 0u ? 0.0f : fmaf(dsk, dy_[v], dl_[v] * S2));
             }
