@@ -28,9 +28,15 @@ struct BwdKernels {
     // checkpoint sweep run by the shared-producer forward kernel in its checkpoint mode (FwdArgs), with its tiling
     void (*ckpt_fwd)(const FwdArgs) = nullptr;
     int cf_LG = 0, cf_K = 0, cf_NW = 0, cf_NG = 0, cf_waves = 0, cf_RPB = 0;
+    // maps of two column panels: both panels' checkpoints in one sweep of the shared-producer forward kernel's 512-column
+    // tiling (kWide*), which also leaves the row-scan states between them
+    void (*ckpt_wide)(const FwdArgs) = nullptr;
     // the same tiling as a forward pass that also writes the checkpoints (training step: scan2d_fwd_saving)
     void (*train_fwd)(const FwdArgs) = nullptr;
 };
+
+// The checkpoint sweep of maps that the main sweep takes in two panels of 256 columns.
+constexpr int kWideLG = 64, kWideK = 8, kWideNW = 1, kWideNG = 16, kWideWaves = 16, kWideRPB = 2;
 
 // Main sweeps that share the per-position work of a job through LDS: (LG, K, NW, NG, WAVES, RB) and the tiling
 // (LG, K, NW) of the checkpoint sweep that goes with them (same RB, 4 waves per workgroup for 16-lane groups,
@@ -69,9 +75,14 @@ inline BwdKernels lookup_bwd_shared_kernels(int LG, int K, int NW, int NG, int w
         if constexpr (SP && !CF)                                                                         \
             r.main_gate = fast ? scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, true, true, false, false, true>       \
                                : scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, false, true, false, false, true>;     \
-        if constexpr (!CF && lg == 64 && k == 4 && nw == 2)                                              \
+        if constexpr (!CF && lg == 64 && k == 4 && nw == 2) {                                            \
             r.main_panels = fast ? scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, true, SP, false, true>      \
                                  : scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, false, SP, false, true>;    \
+            if (W <= kWideLG * kWideK)                                                                   \
+                r.ckpt_wide = Elem<T>::kBytes == 2 && (W % 2) != 0                                       \
+                    ? scan2d_fwd_shared_kernel<T, kWideLG, kWideK, kWideNW, kWideNG, kWideWaves, kWideRPB, SP, Elem<T>::kBytes == 2, rb>     \
+                    : scan2d_fwd_shared_kernel<T, kWideLG, kWideK, kWideNW, kWideNG, kWideWaves, kWideRPB, SP, false, rb>;                   \
+        }                                                                                                \
         if constexpr (Elem<T>::kBytes == 2) {                                                            \
             r.ckpt_fwd = (W % 2) != 0 ? scan2d_fwd_shared_kernel<T, flg, fk, fnw, fng, fwv, frpb, SP, true, rb, CF>     \
                                       : scan2d_fwd_shared_kernel<T, flg, fk, fnw, fng, fwv, frpb, SP, false, rb, CF>;   \

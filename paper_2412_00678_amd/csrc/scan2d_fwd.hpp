@@ -61,6 +61,10 @@ struct FwdArgs {
     // checkpoint rows of LG*K floats in the lane order of the tiling, [K/4][LG][4]: every store instruction of a lane group
     // then writes 16 bytes x LG contiguously (the reader must have the same LG and K); 0: rows of W floats by column
     int ck_chunked = 0;
+    // checkpoint sweep of maps that the main sweep takes in panels of 256 columns: the row-scan states at the panels' right
+    // borders, [panel][maps][N][H], hc_panel floats per panel
+    float* hc = nullptr;
+    size_t hc_panel = 0;
     long long maps;      // Bt * Dc
     int Dc, H, W, N;
     int NG;              // lane groups per map = ceil(N / NW)

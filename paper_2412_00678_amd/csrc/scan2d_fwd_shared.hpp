@@ -84,6 +84,7 @@ template <typename T, int LG, int K, int NW, int NG, int WAVES, int RPB, bool SP
 __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const FwdArgs p) {
     static_assert(!SKEW || ((LG == 16 || LG == 64) && NW == 1 && CK == 0 && !CF && !UA), "skewed rows: 16- or 64-lane groups, one state per lane, forward, rows first");
     constexpr bool YOUT = CK == 0 || KEEPY;               // Cm, the sum over states and y are part of this instantiation
+    constexpr bool HCOUT = CK > 0 && !KEEPY && !CF && LG == 64 && K > 4;   // row-scan states at the borders of 256-column panels
     constexpr bool NOSCAN = CF && CK > 0 && !KEEPY;       // columns-first checkpoint sweep: the row scan feeds nothing
     static_assert(!UA || Elem<T>::kBytes == 2, "UA: bf16 rows on odd 2-byte boundaries");
     constexpr int XW = words_of<T, K>();
@@ -247,6 +248,9 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
     for (int s = 0; s < NW; ++s)
 #pragma unroll
         for (int j = 0; j < K; ++j) h[s][j] = 0.0f;            // h[-1, j] = 0
+    // HCOUT: the lanes whose last column is a panel's last one (and has a neighbour to its right)
+    const bool at_border = HCOUT && live && (l + 1) * K % 256 == 0 && (l + 1) * K < W;
+    float* const hcm = HCOUT ? p.hc + (at_border ? (size_t)((l + 1) * K / 256 - 1) * p.hc_panel : 0) + ((size_t)map * N + n0) * H : nullptr;
     float hrow[NW];                                            // SKEW: row state at this lane's last column, previous step
 #pragma unroll
     for (int s = 0; s < NW; ++s) hrow[s] = 0.0f;
@@ -350,6 +354,12 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
                 }
                 if constexpr (!NOSCAN && !SKEW) {
                     if constexpr (kDppApply) group_scan_nocarry<LG, SC>(P, Hh, cin); else group_scan<LG, SC>(P, Hh, cin);
+                }
+                if constexpr (HCOUT) {
+                    if (at_border && i < H) {
+#pragma unroll
+                        for (int t = 0; t < SC; ++t) hcm[(size_t)(s0 + t) * H + i] = Hh[t];
+                    }
                 }
 #pragma unroll
                 for (int t = 0; t < SC; ++t) {

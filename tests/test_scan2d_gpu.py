@@ -453,6 +453,14 @@ def test_backward_sweeps_at_the_edges_of_bands_and_tiles(s2d, Bt, Dc, H, W, dtyp
     check_bwd(s2d, wl.Workload("edge", Bt, Dc, 16, H, W, dtype, mask_frac=0.3, backward=True), seed=3)
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("Bt,Dc,H,W", [(2, 3, 1, 257), (1, 5, 2, 264), (2, 2, 3, 265), (1, 3, 6, 510), (1, 2, 5, 511), (2, 2, 4, 512), (1, 2, 5, 513)])
+def test_backward_of_two_column_panels_checkpointed_in_one_sweep(s2d, Bt, Dc, H, W, dtype):
+    """First and last widths, rows that fill a band of two or leave one over, with and without the softplus step; 513: three panels."""
+    check_bwd(s2d, wl.Workload("wide", Bt, Dc, 16, H, W, dtype, mask_frac=0.3, backward=True), seed=6)
+    test_backward_with_softplus_step_matches_oracle(s2d, (Bt, Dc, 16, H, W, dtype, 0.3), True)
+
+
 @pytest.mark.parametrize("W", [72, 75, 190])
 def test_backward_is_reproducible_and_ignores_garbage_under_the_mask(s2d, W):
     w = wl.Workload("brep", 2, 12, 16, 20, W, wl.F32, mask_frac=0.4, backward=True)
