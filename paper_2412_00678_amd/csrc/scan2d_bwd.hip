@@ -125,30 +125,47 @@ __global__ __launch_bounds__(256) void scan2d_bwd_step_kernel(const T* __restric
 // becomes the gradient of the raw projection, ddelta_raw = dstep / (1 + exp(-(raw + bias))), rounded once to
 // the storage type; its sum over the map's positions, taken from the stored values, goes to pbias (null: no
 // bias) in a fixed order (strided partial sums per thread, then a tree over the workgroup).
+// Bound: HBM.  A workgroup per map, because the sum is one per map; a slide's few hundred maps are a workgroup per compute
+// unit, so each brings 16 wavefronts and takes 4 elements per load (211x397 bf16, 256 maps: 4 wavefronts and single
+// elements 196 us, this 67).  Any alignment: maps of odd size start on odd elements.
+constexpr int kChainThreads = 1024;
 template <typename T>
-__global__ __launch_bounds__(256) void scan2d_bwd_chain_kernel(const float* __restrict__ dstep, const T* __restrict__ raw,
-                                                               const float* __restrict__ bias, T* __restrict__ ddelta_raw,
-                                                               float* __restrict__ pbias, size_t HW, int Dc) {
-    __shared__ float sh[256];
+__global__ __launch_bounds__(kChainThreads) void scan2d_bwd_chain_kernel(const float* __restrict__ dstep, const T* __restrict__ raw,
+                                                                         const float* __restrict__ bias, T* __restrict__ ddelta_raw,
+                                                                         float* __restrict__ pbias, size_t HW, int Dc) {
+    __shared__ float sh[kChainThreads];
     const size_t map = blockIdx.x;
     const float b = bias != nullptr ? bias[map % Dc] : 0.0f;
     const float* dd = dstep + map * HW;
     const T* src = raw + map * HW;
     T* dst = ddelta_raw + map * HW;
     float acc = 0.0f;
-    for (size_t e = threadIdx.x; e < HW; e += 256) {
-        float t;
-        if constexpr (Elem<T>::kBytes == 4) t = __uint_as_float(elem_bits(src + e));
-        else t = __uint_as_float(elem_bits(src + e) << 16);
-        const float v = dd[e] * logistic_f32(t + b);
-        store_elem(dst + e, v);
-        if constexpr (Elem<T>::kBytes == 4) acc += v;
-        else acc += __uint_as_float(f32_to_bf16_bits(v) << 16);
+    auto stored = [](uint32_t bits) { return Elem<T>::kBytes == 4 ? __uint_as_float(bits) : __uint_as_float(bits << 16); };
+    const size_t groups = HW / 4;
+#pragma unroll 2
+    for (size_t g = threadIdx.x; g < groups; g += kChainThreads) {
+        constexpr int XW = words_of<T, 4>();
+        uint32_t r[XW], q[4], o[XW] = {};
+        load_words_any<XW>(src + 4 * g, r);
+        load_words_any<4>(dd + 4 * g, q);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t bits = to_elem_bits<T>(__uint_as_float(q[j]) * logistic_f32(get_elem<T, 4>(r, j) + b));
+            put_elem<T, 4>(o, j, bits);
+            acc += stored(bits);
+        }
+        store_words_any<XW>(dst + 4 * g, o);
+    }
+    const size_t e = 4 * groups + threadIdx.x;             // the last HW % 4 elements
+    if (e < HW) {
+        const uint32_t bits = to_elem_bits<T>(dd[e] * logistic_f32(stored(elem_bits(src + e)) + b));
+        store_elem(dst + e, stored(bits));
+        acc += stored(bits);
     }
     if (pbias == nullptr) return;                        // uniform over the grid
     sh[threadIdx.x] = acc;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
+    for (int w = kChainThreads / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
         __syncthreads();
     }
@@ -634,10 +651,10 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     if (pl.step_outside) {
         const float* dstep = reinterpret_cast<const float*>(ws + pl.off_step);
         if (d->dtype == SCAN2D_BF16)
-            hipLaunchKernelGGL(scan2d_bwd_chain_kernel<bf16_t>, dim3((unsigned)maps), dim3(256), 0, stream, dstep,
+            hipLaunchKernelGGL(scan2d_bwd_chain_kernel<bf16_t>, dim3((unsigned)maps), dim3(kChainThreads), 0, stream, dstep,
                                static_cast<const bf16_t*>(delta), delta_bias, static_cast<bf16_t*>(ddelta), pbias, HW, d->Dc);
         else
-            hipLaunchKernelGGL(scan2d_bwd_chain_kernel<float>, dim3((unsigned)maps), dim3(256), 0, stream, dstep,
+            hipLaunchKernelGGL(scan2d_bwd_chain_kernel<float>, dim3((unsigned)maps), dim3(kChainThreads), 0, stream, dstep,
                                static_cast<const float*>(delta), delta_bias, static_cast<float*>(ddelta), pbias, HW, d->Dc);
     }
     launch_sums(d, pl, a, dBm, dCm, dA, dA_v, dDskip, softplus ? ddelta_bias : nullptr, pbias, stream);
