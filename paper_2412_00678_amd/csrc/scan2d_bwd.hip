@@ -125,10 +125,13 @@ __global__ __launch_bounds__(256) void scan2d_bwd_step_kernel(const T* __restric
 // becomes the gradient of the raw projection, ddelta_raw = dstep / (1 + exp(-(raw + bias))), rounded once to
 // the storage type; its sum over the map's positions, taken from the stored values, goes to pbias (null: no
 // bias) in a fixed order (strided partial sums per thread, then a tree over the workgroup).
-// Bound: HBM.  A workgroup per map, because the sum is one per map; a slide's few hundred maps are a workgroup per compute
-// unit, so each brings 16 wavefronts and takes 4 elements per load (211x397 bf16, 256 maps: 4 wavefronts and single
-// elements 196 us, this 67).  Any alignment: maps of odd size start on odd elements.
-constexpr int kChainThreads = 1024;
+// Bound: HBM.  A workgroup per map, because the sum is one per map, with 4 elements per load.  A slide's few hundred maps
+// are a workgroup per compute unit, so each brings 16 wavefronts (211x397 bf16, 256 maps: 4 wavefronts and single elements
+// 160 us, this 64); maps of a few elements per thread would wait for the barriers of its sum, so below 8192 elements it is 4
+// (us with 4 and 16 wavefronts: 4096 maps of 20x20 6.7 and 16.7, of 56x56 19.2 and 26.8, 1024 of 80x80 11.6 and 12.7, of
+// 100x100 23.5 and 22.5, 256 of 100x100 6.4 and 5.5).  Any alignment: maps of odd size start on odd elements.
+constexpr int kChainThreads = 1024;                        // the most
+inline int chain_threads(size_t HW) { return HW >= 8192 ? kChainThreads : 256; }      // a power of two, for the tree
 template <typename T>
 __global__ __launch_bounds__(kChainThreads) void scan2d_bwd_chain_kernel(const float* __restrict__ dstep, const T* __restrict__ raw,
                                                                          const float* __restrict__ bias, T* __restrict__ ddelta_raw,
@@ -142,8 +145,9 @@ __global__ __launch_bounds__(kChainThreads) void scan2d_bwd_chain_kernel(const f
     float acc = 0.0f;
     auto stored = [](uint32_t bits) { return Elem<T>::kBytes == 4 ? __uint_as_float(bits) : __uint_as_float(bits << 16); };
     const size_t groups = HW / 4;
+    const unsigned step = blockDim.x;
 #pragma unroll 2
-    for (size_t g = threadIdx.x; g < groups; g += kChainThreads) {
+    for (size_t g = threadIdx.x; g < groups; g += step) {
         constexpr int XW = words_of<T, 4>();
         uint32_t r[XW], q[4], o[XW] = {};
         load_words_any<XW>(src + 4 * g, r);
@@ -165,7 +169,7 @@ __global__ __launch_bounds__(kChainThreads) void scan2d_bwd_chain_kernel(const f
     if (pbias == nullptr) return;                        // uniform over the grid
     sh[threadIdx.x] = acc;
     __syncthreads();
-    for (int w = kChainThreads / 2; w > 0; w >>= 1) {
+    for (int w = (int)step / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
         __syncthreads();
     }
@@ -651,10 +655,10 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     if (pl.step_outside) {
         const float* dstep = reinterpret_cast<const float*>(ws + pl.off_step);
         if (d->dtype == SCAN2D_BF16)
-            hipLaunchKernelGGL(scan2d_bwd_chain_kernel<bf16_t>, dim3((unsigned)maps), dim3(kChainThreads), 0, stream, dstep,
+            hipLaunchKernelGGL(scan2d_bwd_chain_kernel<bf16_t>, dim3((unsigned)maps), dim3(chain_threads(HW)), 0, stream, dstep,
                                static_cast<const bf16_t*>(delta), delta_bias, static_cast<bf16_t*>(ddelta), pbias, HW, d->Dc);
         else
-            hipLaunchKernelGGL(scan2d_bwd_chain_kernel<float>, dim3((unsigned)maps), dim3(kChainThreads), 0, stream, dstep,
+            hipLaunchKernelGGL(scan2d_bwd_chain_kernel<float>, dim3((unsigned)maps), dim3(chain_threads(HW)), 0, stream, dstep,
                                static_cast<const float*>(delta), delta_bias, static_cast<float*>(ddelta), pbias, HW, d->Dc);
     }
     launch_sums(d, pl, a, dBm, dCm, dA, dA_v, dDskip, softplus ? ddelta_bias : nullptr, pbias, stream);

@@ -461,6 +461,13 @@ def test_backward_of_two_column_panels_checkpointed_in_one_sweep(s2d, Bt, Dc, H,
     test_backward_with_softplus_step_matches_oracle(s2d, (Bt, Dc, 16, H, W, dtype, 0.3), True)
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("H,W,N", [(1, 17, 5), (20, 20, 8), (31, 264, 16), (32, 256, 8), (33, 257, 16)])
+def test_softplus_chain_rule_outside_the_sweeps(s2d, H, W, N, dtype):
+    """Maps below, at and above the size from which a map gets 16 wavefronts, with 0 to 3 elements behind the last four."""
+    test_backward_with_softplus_step_matches_oracle(s2d, (2, 3, N, H, W, dtype, 0.3), True)
+
+
 @pytest.mark.parametrize("W", [72, 75, 190])
 def test_backward_is_reproducible_and_ignores_garbage_under_the_mask(s2d, W):
     w = wl.Workload("brep", 2, 12, 16, 20, W, wl.F32, mask_frac=0.4, backward=True)
