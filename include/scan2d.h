@@ -253,8 +253,10 @@ int scan2d_bwd_variants(const scan2d_desc* desc,
  *   scan2d_saved_bytes(desc)  : size of that buffer; 0 when this shape has no saving forward (then pass saved = NULL:
  *                               the two calls below are exactly scan2d_fwd and scan2d_bwd).  It exists for
  *                               desc.flags == 0, N = 16 and maps of at most 192 columns with more rows than one band.
- *   scan2d_fwd_saving(...)    : scan2d_fwd that also writes `saved` ([Bt*Dc][bands][N][W] fp32, device memory,
- *                               16-byte aligned, at least scan2d_saved_bytes(desc) bytes: SCAN2D_ERR_WORKSPACE_SMALL)
+ *   scan2d_fwd_saving(...)    : scan2d_fwd that also writes `saved` ([Bt*Dc][bands][N][row] fp32, rows of W or, for some
+ *                               widths, of a padded number of columns; device memory, 16-byte aligned, at least
+ *                               scan2d_saved_bytes(desc) bytes: SCAN2D_ERR_WORKSPACE_SMALL.  The size can include
+ *                               bytes behind the last row that the backward reads and does not use)
  *   scan2d_bwd_saved(...)     : scan2d_bwd without its checkpoint sweep, reading `saved` (not modified)
  * y and the gradients are those of scan2d_fwd / scan2d_bwd up to the order of the fp32 sums over states (the saving
  * forward has one fixed tiling).  Workspaces as for scan2d_fwd / scan2d_bwd.  desc.flags must be 0 (SCAN2D_ERR_BAD_FLAGS).

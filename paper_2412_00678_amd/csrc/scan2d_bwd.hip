@@ -438,7 +438,9 @@ bool saving_plan(const scan2d_desc* d, BwdPlan* pl) {
 size_t bwd_saved_bytes(const scan2d_desc* d) {
     BwdPlan pl;
     if (!saving_plan(d, &pl)) return 0;
-    return align_up((size_t)d->Bt * d->Dc * pl.nb * d->N * (pl.ck_chunked ? (size_t)pl.LG * pl.K : (size_t)d->W) * sizeof(float));
+    const size_t rows = align_up((size_t)d->Bt * d->Dc * pl.nb * d->N * (pl.ck_chunked ? (size_t)pl.LG * pl.K : (size_t)d->W) * sizeof(float));
+    // rows by column: the lane across the row end reads all of its K columns, behind the last row up to 4 (K - 1) bytes
+    return rows + (!pl.ck_chunked && d->W % pl.K != 0 ? 256 : 0);
 }
 
 int fwd_saving_launch(const scan2d_desc* d, const void* x, const void* delta, const float* A, const void* Bm, const void* Cm,

@@ -346,7 +346,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             rawd[v] = elem_bits(at_byte(dm, o * (uint32_t)Elem<DT>::kBytes));
             rawy[v] = elem_bits(at_byte(dym, o * EB));
         }
-        // the checkpoint (band 0 starts from zero and reads what band 1 reads); past the row end: the next row or the region behind
+        // the checkpoint (band 0 starts from zero and reads what band 1 reads); past the row end: the next row, or what lies
+        // behind the checkpoints (workspace: the next region; a caller's buffer: the spare bytes of bwd_saved_bytes)
         const float* ck = p.ck + (map * p.nb + min(max(band, 1), p.nb - 1)) * N * ck_row;
         const float* Am = p.A + (map - (size_t)b * p.Dc) * N;
 #pragma unroll

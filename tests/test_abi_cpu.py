@@ -188,6 +188,28 @@ def test_backward_plans_cover_every_shape_the_forward_accepts(lib):
                         assert f["workspace"] <= ck_max + part_max + Bt * Dc * (N + 2) * 4 + tail + carries + 7 * 256, where
 
 
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "bf16"])
+def test_saved_buffer_covers_every_checkpoint_read(lib, dtype):
+    """The backward's lanes read whole groups of K columns of a checkpoint row; rows by column are W floats apart, so the
+    lane across the end of the very last row reads up to K - 1 floats behind it."""
+    seen = set()
+    for Bt, Dc, H in ((2, 5, 37), (1, 2, 64), (1, 1, 9)):
+        for W in range(1, 193):
+            d = lib.Desc(Bt, Dc, H, W, 16, dtype, 0)
+            have = lib.saved_bytes(d)
+            if have == 0:
+                continue
+            f = plan(lib, d, lib.PASS_BWD)
+            K, rows = f["K"], Bt * Dc * f["bands"] * 16
+            padded = -(-(rows * f["LG"] * K * 4) // 256) * 256
+            if have >= padded:                                 # rows in lane order: LG * K floats each
+                continue
+            last = (rows - 1) * W + (W - 1) // K * K + K       # floats up to the end of the last read
+            assert have >= 4 * last, (dtype, Bt, Dc, H, W, f)
+            seen.add(K)
+    assert seen == {4, 8, 12}
+
+
 def test_benchmark_configurations_take_the_intended_forms(lib):
     f = plan(lib, lib.Desc(1, 256, 256, 256, 16, 1, 0), lib.PASS_FWD)
     # one map per compute unit: one state per lane on 16 wavefronts (four per SIMD); with more maps than compute units
