@@ -136,6 +136,39 @@ struct Workspace {
     }
 };
 
+// The tensors a caller hands over for the outputs, held until the call has returned: an iterable may make its items as it
+// goes, and then nothing else keeps them.
+struct Given {
+    PyObject* item[6] = {};               // owned
+    Given() = default;
+    Given(const Given&) = delete;
+    ~Given() { for (PyObject* o : item) Py_XDECREF(o); }
+    // out[0] .. out[n - 1], none of them None
+    void index(PyObject* out, int n, const char* text) {
+        for (int i = 0; i < n; ++i) {
+            PyObject* key = PyLong_FromLong(i);
+            if (key == nullptr) throw Raised{};
+            item[i] = PyObject_GetItem(out, key);
+            Py_DECREF(key);
+            if (item[i] == nullptr) throw Raised{};
+            if (item[i] == Py_None) raise(PyExc_ValueError, text);
+        }
+    }
+    // the n items of an iterable
+    void unpack(PyObject* out, int n, const char* text) {
+        PyObject* t = PySequence_Tuple(out);
+        if (t == nullptr) throw Raised{};
+        const bool all = PyTuple_GET_SIZE(t) == n;
+        for (int i = 0; all && i < n; ++i) {
+            item[i] = PyTuple_GET_ITEM(t, i);
+            Py_INCREF(item[i]);
+        }
+        Py_DECREF(t);
+        if (!all) raise(PyExc_ValueError, text);
+    }
+    PyObject* operator[](int i) const { return item[i]; }
+};
+
 // An output: the caller's tensor, checked, or a new one.
 struct Out {
     PyObject* o;                          // owned
@@ -233,14 +266,9 @@ PyObject* scan_fwd_gated(Args a) {        // x, delta_raw, delta_bias, A, Bm, Cm
 PyObject* scan_bwd(Args a) {              // x, delta, A, Bm, Cm, Dskip, mask, dy, workspace, flags, out
     const Scan s(a[0], a[1], "delta", a[2], a[3], a[4], a[5], a[6], flags_of(a[9]));
     const void* dy = s.map(a[7], "dy");
-    PyObject* given[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    Given given;
     if (a[10] != Py_None) {
-        PyObject* t = PySequence_Tuple(a[10]);
-        if (t == nullptr) throw Raised{};
-        const bool six = PyTuple_GET_SIZE(t) == 6;
-        for (int i = 0; six && i < 6; ++i) given[i] = PyTuple_GET_ITEM(t, i);   // `out` itself keeps them alive
-        Py_DECREF(t);
-        if (!six) raise(PyExc_ValueError, "out: expected six tensors");
+        given.unpack(a[10], 6, "out: expected six tensors");
         const char* const names[] = {"dx", "ddelta", "dA", "dBm", "dCm"};
         for (int i = 0; i < 5; ++i)
             if (given[i] == Py_None) raise(PyExc_ValueError, std::string(names[i]) + " is required");
@@ -295,14 +323,8 @@ PyObject* block_xproj(Args a) {           // x, Wx, Wdt, N, out
     const Map m(a[0], "x", N, 0);
     const void *x = need(a[0], "x", m.t, {m.Bt, m.C, m.H, m.W}), *Wx = need(a[1], "Wx", m.t, {R + 2 * N, m.C});
     const float* Wdt = needf(a[2], "Wdt", {m.C, R});
-    PyObject* given[3] = {nullptr, nullptr, nullptr};
-    if (a[4] != Py_None)
-        for (int i = 0; i < 3; ++i) {
-            given[i] = PySequence_GetItem(a[4], i);
-            if (given[i] == nullptr) throw Raised{};
-            Py_DECREF(given[i]);                           // `out` itself keeps it alive
-            if (given[i] == Py_None) raise(PyExc_ValueError, "out: expected three tensors");
-        }
+    Given given;
+    if (a[4] != Py_None) given.index(a[4], 3, "out: expected three tensors");
     Out dr(given[0], "delta_raw", m, m.t, {m.Bt, m.C, m.H, m.W}), B(given[1], "Bm", m, m.t, {m.Bt, N, m.H, m.W}),
         C(given[2], "Cm", m, m.t, {m.Bt, N, m.H, m.W});
     check_rc(unlocked(scan2d_block_xproj, &m.d, (int)R, x, Wx, Wdt, dr.p, B.p, C.p, stream()), "scan2d_block_xproj");
@@ -342,14 +364,8 @@ PyObject* block_attn_pool(Args a) {       // h, V, w, mask, out
     const void *h = need(a[0], "h", m.t, {m.Bt, m.C, m.H, m.W}), *V = need(a[1], "V", m.t, {D, m.C});
     const float* w = needf(a[2], "w", {D});
     const uint8_t* mask = static_cast<uint8_t*>(maybe(a[3], "mask", at::kByte, {m.Bt, m.H, m.W}));
-    PyObject* given[2] = {nullptr, nullptr};
-    if (a[4] != Py_None)
-        for (int i = 0; i < 2; ++i) {
-            given[i] = PySequence_GetItem(a[4], i);
-            if (given[i] == nullptr) throw Raised{};
-            Py_DECREF(given[i]);
-            if (given[i] == Py_None) raise(PyExc_ValueError, "out: expected two tensors");
-        }
+    Given given;
+    if (a[4] != Py_None) given.index(a[4], 2, "out: expected two tensors");
     Out z(given[0], "z", m, at::kFloat, {m.Bt, m.C}), attn(given[1], "attn", m, at::kFloat, {m.Bt, m.H, m.W});
     check_rc(unlocked(scan2d_block_attn_pool, &m.d, (int)D, h, V, w, mask, attn.f(), z.f(), stream()), "scan2d_block_attn_pool");
     if (a[4] != Py_None) {

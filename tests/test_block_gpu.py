@@ -532,3 +532,31 @@ def test_attn_pool_of_a_bag_whose_scores_are_all_minus_infinity(s2d, P):
     mask[0, 0, 1] = 1
     z, attn = s2d.block_attn_pool(h, V, w, mask)
     assert float(attn[0, 0, 1]) == 0.0 and int(torch.isnan(attn).sum()) == P - 1 and bool(torch.isnan(z).all())
+
+
+def test_block_outputs_of_any_indexable_object(s2d):
+    """`out` is indexed once per tensor; its items may exist only while the call holds them."""
+    import torch
+    Dc = N = 8                                            # one shape for the step, B and C
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x, Wx, Wdt = (torch.randn(s, device="cuda", generator=g) for s in ((1, Dc, 5, 7), (2 + 2 * N, Dc), (Dc, 2)))
+    V, w = torch.randn((16, Dc), device="cuda", generator=g), torch.randn(16, device="cuda", generator=g)
+
+    class OnAccess:
+        def __init__(self, like):
+            self.like, self.made = like, []
+
+        def __getitem__(self, i):
+            t = torch.empty_like(self.like[i])
+            self.made.append(t.data_ptr())
+            return t
+
+    want = s2d.block_xproj(x, Wx, Wdt, N)
+    for out in (torch.empty((3, 1, Dc, 5, 7), device="cuda"), {k: torch.empty_like(t) for k, t in enumerate(want)}, [torch.empty_like(t) for t in want]):
+        got = s2d.block_xproj(x, Wx, Wdt, N, out=out)
+        assert got is out and all(torch.equal(got[k], want[k]) for k in range(3))
+    lazy = OnAccess(want)
+    assert s2d.block_xproj(x, Wx, Wdt, N, out=lazy) is lazy and len(lazy.made) == 3
+    pooled = s2d.block_attn_pool(x, V, w)
+    lazy = OnAccess(pooled)
+    assert s2d.block_attn_pool(x, V, w, out=lazy) is lazy and len(lazy.made) == 2

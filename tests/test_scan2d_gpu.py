@@ -1221,3 +1221,20 @@ def test_binding_refuses_what_does_not_fit(s2d, wrong):
     if wrong == "rank":
         with pytest.raises(ValueError):
             s2d.scan2d_fwd(bad, bad, A, B, B)
+
+
+@pytest.mark.parametrize("form", ["tuple", "list", "generator", "map"])
+def test_backward_writes_into_the_tensors_of_any_iterable(s2d, form):
+    """`out` may make its items as they are taken: nothing but the call itself then holds them."""
+    import torch
+    w = wl.Workload("out", 1, 3, 16, 9, 21, wl.F32, mask_frac=0.3, backward=True)
+    d = s2d.to_device(wl.make_inputs(w, seed=3), wl.F32)
+    args = (d["x"], d["delta"], d["A"], d["Bm"], d["Cm"], d["Dskip"], d["mask"], d["dy"])
+    want = s2d.scan2d_bwd(*args)
+    make = lambda: {"tuple": tuple(torch.empty_like(t) for t in want), "list": [torch.empty_like(t) for t in want],
+                    "generator": (torch.empty_like(t) for t in want), "map": map(torch.empty_like, want)}[form]
+    for _ in range(3):
+        got = s2d.scan2d_bwd(*args, out=make())
+        assert all(torch.equal(g, r) for g, r in zip(got, want))
+    with pytest.raises(ValueError):
+        s2d.scan2d_bwd(*args, out=(torch.empty_like(t) for t in want[:5]))
