@@ -487,7 +487,7 @@ PyMODINIT_FUNC PyInit__scan2d_py() {
     PyObject* m = PyModule_Create(&module);
     if (m == nullptr) return nullptr;
     Py_INCREF(&CallType);
-    if (PyModule_AddObject(m, "Call", reinterpret_cast<PyObject*>(&CallType)) < 0) {
+    if (PyModule_AddObject(m, "Call", reinterpret_cast<PyObject*>(&CallType)) < 0 || PyModule_AddIntConstant(m, "MOST_ARGUMENTS", kMostArgs) < 0) {
         Py_DECREF(m);
         return nullptr;
     }

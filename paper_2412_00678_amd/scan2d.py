@@ -209,13 +209,23 @@ def scan2d_fwd(x, delta, A, Bm, Cm, Dskip=None, mask=None, y=None, workspace=Non
     return _native.scan2d_fwd(x, delta, A, Bm, Cm, Dskip, mask, y, workspace, flags)
 
 
+def _fits_registers(fn, args) -> bool:
+    """Whether a call of fn(*args, stream) is integers and addresses only, which the extension passes on as they are."""
+    types = getattr(fn, "argtypes", None)
+    return (types is not None and len(types) == len(args) + 1 and len(types) <= _native.MOST_ARGUMENTS
+            and not any(t in (ctypes.c_float, ctypes.c_double) for t in types) and all(a is None or isinstance(a, int) for a in args))
+
+
 class Prepared:
     """An entry point with its arguments marshalled once.  Calling the object enqueues the same call again on torch's
     current stream: same tensors (their contents may change between calls), same workspace.  For loops that issue
     one short call after another, where checking and converting a dozen arguments costs more than the kernel."""
 
     def __init__(self, fn, name, args, keep):
-        self._call = _native.Call(ctypes.cast(fn, ctypes.c_void_p).value, args)
+        if _fits_registers(fn, args):
+            self._call = _native.Call(ctypes.cast(fn, ctypes.c_void_p).value, tuple(args))
+        else:                                                                    # converted by ctypes on every call
+            self._call = lambda: fn(*args, _stream_ptr())
         self._name, self._keep = name, keep                                      # keep: the tensors stay alive
 
     def __call__(self):
@@ -402,7 +412,7 @@ LAYER_NORM, RMS_NORM = 0, 1
 
 def block_norm(x, gamma, beta=None, eps=1e-5, kind=LAYER_NORM, out=None):
     """Layer norm or RMS norm over the channels of every position of x [Bt][C][H][W]; gamma, beta: [C] fp32."""
-    return _native.block_norm(x, gamma, beta, eps, kind, out)
+    return _native.block_norm(x, gamma, beta, float(eps), int(kind), out)
 
 
 def block_attn_pool(h, V, w, mask=None, out=None):

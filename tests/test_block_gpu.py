@@ -560,3 +560,21 @@ def test_block_outputs_of_any_indexable_object(s2d):
     pooled = s2d.block_attn_pool(x, V, w)
     lazy = OnAccess(pooled)
     assert s2d.block_attn_pool(x, V, w, out=lazy) is lazy and len(lazy.made) == 2
+
+
+def test_norm_converts_its_numbers_and_prepared_takes_ctypes_arguments(s2d):
+    import ctypes
+    import torch
+    x, gamma = torch.randn((1, 8, 5, 7), device="cuda"), torch.rand(8, device="cuda") + 0.5
+    want = s2d.block_norm(x, gamma, None, 1.0, s2d.RMS_NORM)
+    assert torch.equal(s2d.block_norm(x, gamma, None, np.float64(1), np.float64(s2d.RMS_NORM)), want)
+    desc, out = s2d.Desc(1, 8, 5, 7, 1, s2d.F32, 0), torch.zeros_like(x)
+    p = lambda t: t.data_ptr()
+    for eps in (1, 1.0, ctypes.c_float(1)):               # a float parameter does not travel with the integers
+        s2d.Prepared(s2d.lib.scan2d_block_norm, "scan2d_block_norm", (ctypes.byref(desc), s2d.RMS_NORM, eps, p(x), p(gamma), None, p(out)), (desc, x, gamma, out))()
+        assert torch.equal(out, want)
+        out.zero_()
+    W = torch.randn((6, 8), device="cuda")
+    lin = torch.zeros((1, 6, 5, 7), device="cuda")
+    s2d.Prepared(s2d.lib.scan2d_block_linear, "scan2d_block_linear", [ctypes.byref(desc), 6, p(x), p(W), None, None, p(lin)], (desc, x, W, lin))()
+    assert torch.equal(lin, s2d.block_linear(x, W))
