@@ -116,14 +116,15 @@ template <typename T> constexpr int contract_step() { return Elem<T>::kBytes == 
 // `in`: the batch item's map, wave-uniform; s: first position this lane reads; W: row 0, wave-uniform, ldw channels per
 // row; this lane supplies rows min(o0 + 16 ot + n, rows - 1).  DEPTH steps are in flight ahead of the products.
 // TAIL: the channels are not whole steps (a flag, because the element-wise loads of the last ones take many registers).
-// 32-bit byte offsets per lane: 25 rows of positions and the whole of W stay below 2^32 bytes (checked on the host).
-template <typename T, int NOT, int DEPTH, bool TAIL>
+// 32-bit byte offsets per lane: the whole of W stays below 2^32 bytes, and so do the rows of positions between a lane's
+// address and the uniform base (contract_narrow; checked on the host).  WIDE: maps where the latter does not hold.
+template <typename T, int NOT, int DEPTH, bool TAIL, bool WIDE = false>
 __device__ __forceinline__ void contract(const T* __restrict__ in, uint32_t P, uint32_t s, const T* __restrict__ W, int ldw, int rows,
                                          int o0, int cbeg, int cend, f32x4 (&acc)[NOT][4]) {
     constexpr int EB = Elem<T>::kBytes, KS = contract_step<T>(), KL = KS / 4;        // channels per lane and step
     constexpr int BW = words_of<T, 4>();                                            // dwords of 4 positions
     const int l = threadIdx.x & 63, g = l >> 4, n = l & 15;
-    const uint32_t boff = ((uint32_t)(KL * g) * P + s) * EB;
+    const std::conditional_t<WIDE, uint64_t, uint32_t> boff = ((std::conditional_t<WIDE, uint64_t, uint32_t>)(KL * g) * P + s) * EB;
     uint32_t aoff[NOT];
 #pragma unroll
     for (int ot = 0; ot < NOT; ++ot) aoff[ot] = ((uint32_t)min(o0 + 16 * ot + n, rows - 1) * (uint32_t)ldw + (uint32_t)(KL * g)) * EB;
@@ -131,7 +132,10 @@ __device__ __forceinline__ void contract(const T* __restrict__ in, uint32_t P, u
     auto load = [&](int buf, int c0) {
         const char* bb = reinterpret_cast<const char*>(in + (size_t)c0 * P);
 #pragma unroll
-        for (int e = 0; e < KL; ++e) load_words_at<BW>(bb + (size_t)e * P * EB, boff, braw[buf][e]);
+        for (int e = 0; e < KL; ++e) {
+            if constexpr (WIDE) load_words_any<BW>(bb + (size_t)e * P * EB + boff, braw[buf][e]);
+            else load_words_at<BW>(bb + (size_t)e * P * EB, boff, braw[buf][e]);
+        }
         const char* aa = reinterpret_cast<const char*>(W + c0);
 #pragma unroll
         for (int ot = 0; ot < NOT; ++ot) load_words_at<4>(aa, aoff[ot], araw[buf][ot]);
@@ -209,9 +213,13 @@ __device__ __forceinline__ void contract(const T* __restrict__ in, uint32_t P, u
     }
 }
 
-// Whether the 32-bit lane offsets of contract() reach everything.
+// Whether contract() takes the call: at least one group of positions, W within 32-bit offsets.  (Maps have fewer than 2^27
+// positions.)
 inline bool contract_fits(long long P, long long wrows, long long ldw, int elem_bytes) {
-    return P >= 4 && P <= (1LL << 25) && wrows * ldw * elem_bytes < (1LL << 32) - 64;
+    return P >= 4 && P < (1LL << 27) && wrows * ldw * elem_bytes < (1LL << 32) - 64;
 }
+// Whether 32-bit lane offsets reach the positions too: lane group 3 stands 24 (bf16) or 12 (fp32) rows behind the uniform
+// base and reads one row on.  85.9 and 82.6 million positions; beyond, the lanes carry 64-bit offsets (WIDE).
+inline bool contract_narrow(long long P, int elem_bytes) { return (elem_bytes == 2 ? 25 : 13) * P * elem_bytes < (1LL << 32) - 64; }
 
 }  // namespace scan2d

@@ -8,7 +8,7 @@
 // The four wavefronts of a workgroup, and the workgroups that follow it on the same XCD, take the other output channels
 // of the same positions, so `in` comes from HBM once and from L1 / L2 afterwards.  Bound: HBM for bf16 (the products of
 // 128 -> 256 channels are 4.3 GFLOP beside 50 MB), the fp32 matrix rate for fp32.
-// scan2d_linear_any_kernel: one thread per output, for maps of fewer than 4 positions or beyond 2^25.
+// scan2d_linear_any_kernel: one thread per output, for maps of fewer than 4 positions or 4 GB of weights.
 #include "scan2d_block.hpp"
 
 #include <algorithm>
@@ -24,7 +24,7 @@ struct LinArgs {
     long long ptiles, P, waves;     // tiles of 64 positions per batch item, positions per map, wavefronts (pieces) with work
 };
 
-template <typename T, int NOT, int DEPTH, bool TAIL>
+template <typename T, int NOT, int DEPTH, bool TAIL, bool WIDE = false>
 __global__ __launch_bounds__(256) void scan2d_linear_kernel(const LinArgs p) {
     const long long per = gridDim.x / kXcds;               // the grid is a multiple of 8: workgroups of one XCD follow each other
     const long long wg = (long long)(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
@@ -43,8 +43,8 @@ __global__ __launch_bounds__(256) void scan2d_linear_kernel(const LinArgs p) {
     for (int ot = 0; ot < NOT; ++ot)
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    contract<T, NOT, DEPTH, TAIL>(static_cast<const T*>(p.in) + (size_t)b * p.Cin * P, P, pos.s, static_cast<const T*>(p.Wt), p.Cin, p.Cout, o0,
-                            0, p.Cin, acc);
+    contract<T, NOT, DEPTH, TAIL, WIDE>(static_cast<const T*>(p.in) + (size_t)b * p.Cin * P, P, pos.s, static_cast<const T*>(p.Wt), p.Cin, p.Cout, o0,
+                                  0, p.Cin, acc);
 
     const T* res = static_cast<const T*>(p.res);
     T* out = static_cast<T*>(p.out);
@@ -282,12 +282,12 @@ __global__ __launch_bounds__(256) void scan2d_linear_any_kernel(const LinArgs p)
     store_elem(static_cast<T*>(p.out) + idx, acc);
 }
 
-template <typename T, int NOT, int DEPTH>
+template <typename T, int NOT, int DEPTH, bool WIDE = false>
 int launch(LinArgs a, hipStream_t stream) {
     a.ogroups = (a.Cout + 16 * NOT - 1) / (16 * NOT);
     const long long wgs = (a.ptiles * a.Bt + 1) / 2 * ((a.ogroups + 1) / 2), grid = (wgs + kXcds - 1) / kXcds * kXcds;
     if (grid > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
-    auto kernel = a.Cin % contract_step<T>() == 0 ? scan2d_linear_kernel<T, NOT, DEPTH, false> : scan2d_linear_kernel<T, NOT, DEPTH, true>;
+    auto kernel = a.Cin % contract_step<T>() == 0 ? scan2d_linear_kernel<T, NOT, DEPTH, false, WIDE> : scan2d_linear_kernel<T, NOT, DEPTH, true, WIDE>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, stream, a);
     return SCAN2D_OK;
 }
@@ -297,6 +297,7 @@ int launch(LinArgs a, hipStream_t stream) {
 template <typename T>
 int launch_sized(const LinArgs& a, hipStream_t stream) {
     const long long tiles = a.ptiles * a.Bt, o16 = (a.Cout + 15) / 16;
+    if (!contract_narrow(a.P, Elem<T>::kBytes)) return launch<T, 4, 2, true>(a, stream);     // more than 82 million positions
     if constexpr (Elem<T>::kBytes == 2) {
         if (tiles >= 512 && o16 >= 4 && a.Cin % 32 == 0 && a.Cin <= 256) {
             LinArgs r = a;                                 // two wavefronts per tile until there are four per SIMD

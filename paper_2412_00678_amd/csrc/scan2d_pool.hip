@@ -3,8 +3,8 @@
 // Three kernels, no workspace (attn holds the scores in between):
 //   scan2d_pool_scores_kernel  : the scores.  V . h is a dense contraction (D x M x positions), so it runs on the matrix
 //                                cores (scan2d_contract.hpp); tanh, the product with w and the sum over the D hidden
-//                                units are its epilogue.  scan2d_pool_scores_any_kernel: maps of fewer than 4 positions
-//                                or beyond 2^25.
+//                                units are its epilogue.  scan2d_pool_scores_any_kernel: maps of fewer than 4
+//                                positions or 4 GB of weights.
 //   scan2d_pool_softmax_kernel : per batch item, max and sum of exp over the bag in a fixed order, then the weights.
 //   scan2d_pool_sum_kernel     : z[b][m], one workgroup per channel, fixed order.
 #include "scan2d_block.hpp"
@@ -31,7 +31,7 @@ __device__ __forceinline__ float fast_tanh(float v) {          // 1 - 2 / (1 + e
 
 // A workgroup of four wavefronts per tile of 64 positions; wavefront v takes hidden units 32 v .. 32 v + 31, the parts of
 // a score meet in LDS and are added in wavefront order.
-template <typename T, bool TAIL>
+template <typename T, bool TAIL, bool WIDE = false>
 __global__ __launch_bounds__(256) void scan2d_pool_scores_kernel(const PoolArgs p) {
     __shared__ float part[4][64];
     const int tid = threadIdx.x, l = tid & 63, g = l >> 4, n = l & 15;
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void scan2d_pool_scores_kernel(const PoolArgs 
         for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
             for (int t = 0; t < 4; ++t) acc[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        contract<T, 2, 2, TAIL>(static_cast<const T*>(p.h) + (size_t)b * p.M * P, P, pos.s, static_cast<const T*>(p.V), p.M, p.D, d0, 0, p.M, acc);
+        contract<T, 2, 2, TAIL, WIDE>(static_cast<const T*>(p.h) + (size_t)b * p.M * P, P, pos.s, static_cast<const T*>(p.V), p.M, p.D, d0, 0, p.M, acc);
 #pragma unroll
         for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
@@ -278,7 +278,8 @@ int block_attn_pool_launch(const scan2d_desc* d, int D, const void* h, const voi
     const dim3 g1((unsigned)((fits ? tiles : a.P) * d->Bt)), g2((unsigned)d->Bt), g3((unsigned)d->Dc, (unsigned)d->Bt);
     using Kernel = void (*)(const PoolArgs);
     Kernel scores, soft;
-    if (fits && bf16) scores = a.M % 32 == 0 ? scan2d_pool_scores_kernel<bf16_t, false> : scan2d_pool_scores_kernel<bf16_t, true>;
+    if (fits && !contract_narrow(a.P, bf16 ? 2 : 4)) scores = bf16 ? scan2d_pool_scores_kernel<bf16_t, true, true> : scan2d_pool_scores_kernel<float, true, true>;
+    else if (fits && bf16) scores = a.M % 32 == 0 ? scan2d_pool_scores_kernel<bf16_t, false> : scan2d_pool_scores_kernel<bf16_t, true>;
     else if (fits) scores = a.M % 16 == 0 ? scan2d_pool_scores_kernel<float, false> : scan2d_pool_scores_kernel<float, true>;
     else scores = bf16 ? scan2d_pool_scores_any_kernel<bf16_t> : scan2d_pool_scores_any_kernel<float>;
     if (a.P < 4) soft = scan2d_pool_softmax_any_kernel<false>;

@@ -14,7 +14,7 @@
 // scan2d_xproj_wave_kernel, bf16 from kWaveTiles tiles on: each wavefront does all of this for 64 positions of its own.
 // Bound: HBM (read x, write delta_raw).  256 channels, R = 8, N = 16, bf16: 256x256 22.5 us (3.2 TB/s; split rows 28.4),
 // 181x181 15.7 us (a wavefront each: 22.9), 57x83 10.9 us; 512 channels, R = 16, fp32: 128x200 37.0 us.
-// scan2d_xproj_any_kernel: one workgroup per position, for maps of fewer than 4 positions or beyond 2^25.
+// scan2d_xproj_any_kernel: one workgroup per position, for maps of fewer than 4 positions or 4 GB of weights.
 #include "scan2d_block.hpp"
 
 #include "scan2d_contract.hpp"
@@ -153,8 +153,8 @@ __device__ __forceinline__ void step_rows(const XprojArgs& p, int b, const LaneP
 }
 template <int KR> constexpr int step_ahead() { return KR <= 4 ? 4 : 1; }      // blocks of 16 rows whose weights are in flight
 
-// KR: low-rank rows per lane group, 4 KR >= R
-template <typename T, int KR, bool TAIL>
+// KR: low-rank rows per lane group, 4 KR >= R.  TAIL, WIDE: of contract(), fp32 only
+template <typename T, int KR, bool TAIL, bool WIDE>
 __global__ __launch_bounds__(256, 2) void scan2d_xproj_kernel(const XprojArgs p) {
     constexpr bool CHAIN = Elem<T>::kBytes == 2;
     __shared__ float part[CHAIN ? 1 : 4][kRowBlocks * 16][64];
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256, 2) void scan2d_xproj_kernel(const XprojArgs p)
             for (int mb = 0; mb < kRowBlocks; ++mb)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) acc[mb][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            contract<T, kRowBlocks, 2, TAIL>(x, P, pos.s, static_cast<const T*>(p.Wx), Dc, M, m0, cbeg, cend, acc);
+            contract<T, kRowBlocks, 2, TAIL, WIDE>(x, P, pos.s, static_cast<const T*>(p.Wx), Dc, M, m0, cbeg, cend, acc);
             if (m0 > 0) __syncthreads();                   // the sums of the previous rows have been read
 #pragma unroll
             for (int mb = 0; mb < kRowBlocks; ++mb)
@@ -300,12 +300,12 @@ __global__ __launch_bounds__(256) void scan2d_xproj_any_kernel(const XprojArgs p
     }
 }
 
-template <typename T, bool TAIL>
+template <typename T, bool TAIL, bool WIDE = false>
 void launch(const XprojArgs& a, int Bt, hipStream_t stream) {
     const dim3 grid((unsigned)(a.tiles * Bt));
-    if (a.R <= 8) hipLaunchKernelGGL((scan2d_xproj_kernel<T, 2, TAIL>), grid, dim3(256), 0, stream, a);
-    else if (a.R <= 16) hipLaunchKernelGGL((scan2d_xproj_kernel<T, 4, TAIL>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((scan2d_xproj_kernel<T, 16, TAIL>), grid, dim3(256), 0, stream, a);
+    if (a.R <= 8) hipLaunchKernelGGL((scan2d_xproj_kernel<T, 2, TAIL, WIDE>), grid, dim3(256), 0, stream, a);
+    else if (a.R <= 16) hipLaunchKernelGGL((scan2d_xproj_kernel<T, 4, TAIL, WIDE>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((scan2d_xproj_kernel<T, 16, TAIL, WIDE>), grid, dim3(256), 0, stream, a);
 }
 
 }  // namespace
@@ -329,7 +329,8 @@ int block_xproj_launch(const scan2d_desc* d, int R, const void* x, const void* W
             if (R <= 8) hipLaunchKernelGGL(scan2d_xproj_wave_kernel<2>, grid, dim3(256), 0, stream, a);
             else if (R <= 16) hipLaunchKernelGGL(scan2d_xproj_wave_kernel<4>, grid, dim3(256), 0, stream, a);
             else hipLaunchKernelGGL(scan2d_xproj_wave_kernel<16>, grid, dim3(256), 0, stream, a);
-        } else if (bf16) launch<bf16_t, false>(a, d->Bt, stream);
+        } else if (bf16) launch<bf16_t, false>(a, d->Bt, stream);      // 13 rows of positions within 32-bit offsets: any map
+        else if (!contract_narrow(a.P, 4)) launch<float, true, true>(a, d->Bt, stream);
         else if (a.Dc % contract_step<float>() == 0) launch<float, false>(a, d->Bt, stream);
         else launch<float, true>(a, d->Bt, stream);
     } else {

@@ -578,3 +578,51 @@ def test_norm_converts_its_numbers_and_prepared_takes_ctypes_arguments(s2d):
     lin = torch.zeros((1, 6, 5, 7), device="cuda")
     s2d.Prepared(s2d.lib.scan2d_block_linear, "scan2d_block_linear", [ctypes.byref(desc), 6, p(x), p(W), None, None, p(lin)], (desc, x, W, lin))()
     assert torch.equal(lin, s2d.block_linear(x, W))
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("H,W", [(5793, 5793), (9280, 9281)])
+def test_layers_on_the_matrix_cores_for_the_largest_maps(s2d, H, W, dtype):
+    """33.6 and 86.1 million positions: beyond the second size the lanes of a contraction carry 64-bit offsets.  Linear layer,
+    projections and aggregator against sums in 64 bits at sampled positions, and, where their element-wise kernels would
+    take the call, ten times their rate per position and more is lost: the time stays in proportion to a map of 4 million."""
+    import torch
+    tt = {wl.F32: torch.float32, wl.BF16: torch.bfloat16}[dtype]
+    C, N, R, D = 32, 1, 3, 16
+    g = torch.Generator(device="cuda").manual_seed(8)
+    r = lambda *s, scale=1.0, dt=torch.float32: (torch.randn(s, device="cuda", generator=g, dtype=dt) * scale)
+    Wl, Wx, Wdt, V, w = r(5, C, scale=C ** -0.5).to(tt), r(R + 2 * N, C, scale=C ** -0.5).to(tt), r(C, R), r(D, C, scale=C ** -0.5).to(tt), r(D)
+
+    def passes(h, wd):
+        x = r(1, C, h, wd, dt=tt)
+        calls = {"linear": lambda: s2d.block_linear(x, Wl), "xproj": lambda: s2d.block_xproj(x, Wx, Wdt, N), "pool": lambda: s2d.block_attn_pool(x, V, w)}
+        out, us = {}, {}
+        for name, call in calls.items():
+            out[name] = call()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            us[name] = a.elapsed_time(b) / (h * wd)
+        return x, out, us
+
+    us_small = passes(2048, 2048)[2]
+    x, out, us = passes(H, W)
+    P = H * W
+    at = torch.cat([torch.arange(0, 130), torch.arange(P // 2 - 65, P // 2 + 65), torch.arange(P - 130, P)]).cuda()
+    col = lambda t: t.reshape(t.shape[1], P)[:, at].double()
+    xs = col(x)
+    low = Wx.double() @ xs
+    assert rel_err(col(out["linear"]).cpu().numpy(), (Wl.double() @ xs).cpu().numpy()) <= TOL_BLOCK[dtype]
+    raw, Bm, Cm = out["xproj"]
+    for got, want in ((raw, Wdt.double() @ low[:R]), (Bm, low[R:R + N]), (Cm, low[R + N:])):
+        assert rel_err(col(got).cpu().numpy(), want.cpu().numpy()) <= TOL_BLOCK[dtype]
+    z, attn = out["pool"]
+    s = w.double() @ torch.tanh(V.double() @ xs)
+    a = attn.reshape(P)[at].double()
+    np.testing.assert_allclose(torch.log(a / a[0]).cpu().numpy(), (s - s[0]).cpu().numpy(), atol=1e-4)
+    # a thread adds up to P / 1024 weights in a row in fp32
+    assert bool(torch.isfinite(z).all()) and abs(float(attn.double().sum()) - 1.0) <= P / 1024 * 2.0 ** -24 + 1e-6
+    for name in us:
+        assert us[name] <= 4 * us_small[name], (name, us, us_small)
