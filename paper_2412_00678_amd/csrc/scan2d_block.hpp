@@ -4,9 +4,34 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "../../include/scan2d.h"
 
 namespace scan2d {
+
+// A launch holds fewer than 2^32 threads; of a larger one only a part runs, and no error is reported.
+inline bool launch_fits(long long workgroups, int threads) { return workgroups * threads < (1LL << 32); }
+
+// f(desc, first item) for all batch items at once, or, where it refuses so many (SCAN2D_ERR_BAD_SHAPE, nothing enqueued),
+// for the halves.
+template <typename F>
+int by_items(const scan2d_desc& d, F f, int first = 0) {
+    const int rc = f(d, (size_t)first);
+    if (rc != SCAN2D_ERR_BAD_SHAPE || d.Bt == 1) return rc;
+    scan2d_desc half = d;
+    half.Bt = d.Bt / 2;
+    const int rc0 = by_items(half, f, first);
+    if (rc0 != SCAN2D_OK) return rc0;
+    half.Bt = d.Bt - d.Bt / 2;
+    return by_items(half, f, first + d.Bt / 2);
+}
+// `items` batch items of `each` bytes behind p (null stays null).
+template <typename P>
+P* item_at(P* p, size_t items, size_t each) {
+    using Byte = std::conditional_t<std::is_const_v<P>, const char, char>;
+    return p == nullptr ? nullptr : reinterpret_cast<P*>(reinterpret_cast<Byte*>(p) + items * each);
+}
 
 // Depth-wise convolution + SiLU; SCAN2D_ERR_BAD_SHAPE for a filter shape outside the documented range.
 int block_conv_silu_launch(const scan2d_desc* d, const scan2d_conv_shape* cs, const void* u, const float* w, const float* bias,

@@ -286,7 +286,7 @@ template <typename T, int NOT, int DEPTH, bool WIDE = false>
 int launch(LinArgs a, hipStream_t stream) {
     a.ogroups = (a.Cout + 16 * NOT - 1) / (16 * NOT);
     const long long wgs = (a.ptiles * a.Bt + 1) / 2 * ((a.ogroups + 1) / 2), grid = (wgs + kXcds - 1) / kXcds * kXcds;
-    if (grid > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+    if (!launch_fits(grid, 256)) return SCAN2D_ERR_BAD_SHAPE;
     auto kernel = a.Cin % contract_step<T>() == 0 ? scan2d_linear_kernel<T, NOT, DEPTH, false, WIDE> : scan2d_linear_kernel<T, NOT, DEPTH, true, WIDE>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, stream, a);
     return SCAN2D_OK;
@@ -305,7 +305,7 @@ int launch_sized(const LinArgs& a, hipStream_t stream) {
             const int oblocks = (int)((o16 + r.ogroups - 1) / r.ogroups);
             r.waves = tiles * r.ogroups;
             const long long grid = ((r.waves + 3) / 4 + kXcds - 1) / kXcds * kXcds;
-            if (grid > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+            if (!launch_fits(grid, 256)) return SCAN2D_ERR_BAD_SHAPE;
             if (a.Cin <= 128) hipLaunchKernelGGL(scan2d_linear_resident_kernel<4>, dim3((unsigned)grid), dim3(256), 0, stream, r, oblocks);
             else hipLaunchKernelGGL(scan2d_linear_resident_kernel<8>, dim3((unsigned)grid), dim3(256), 0, stream, r, oblocks);
             return SCAN2D_OK;
@@ -332,10 +332,7 @@ int launch_sized(const LinArgs& a, hipStream_t stream) {
     return launch<T, 1, 4>(a, stream);
 }
 
-}  // namespace
-
-int block_linear_launch(const scan2d_desc* d, int Cout, const void* in, const void* Wt, const float* bias, const void* residual,
-                        void* out, hipStream_t stream) {
+int launch_linear(const scan2d_desc* d, int Cout, const void* in, const void* Wt, const float* bias, const void* residual, void* out, hipStream_t stream) {
     if (Cout < 1) return SCAN2D_ERR_BAD_SHAPE;
     LinArgs a;
     a.in = in; a.Wt = Wt; a.bias = bias; a.res = residual; a.out = out;
@@ -349,12 +346,22 @@ int block_linear_launch(const scan2d_desc* d, int Cout, const void* in, const vo
         rc = bf16 ? launch_sized<bf16_t>(a, stream) : launch_sized<float>(a, stream);
     } else {
         const long long blocks = ((long long)d->Bt * Cout * a.P + 255) / 256;
-        if (blocks > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+        if (!launch_fits(blocks, 256)) return SCAN2D_ERR_BAD_SHAPE;
         if (bf16) hipLaunchKernelGGL(scan2d_linear_any_kernel<bf16_t>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
         else hipLaunchKernelGGL(scan2d_linear_any_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
     }
     if (rc != SCAN2D_OK) return rc;
     return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
+}
+
+}  // namespace
+
+int block_linear_launch(const scan2d_desc* d, int Cout, const void* in, const void* Wt, const float* bias, const void* residual,
+                        void* out, hipStream_t stream) {
+    const size_t row = (size_t)d->H * d->W * (d->dtype == SCAN2D_BF16 ? 2 : 4), each = row * Cout;
+    return by_items(*d, [&](const scan2d_desc& q, size_t b) {
+        return launch_linear(&q, Cout, item_at(in, b, row * d->Dc), Wt, bias, item_at(residual, b, each), item_at(out, b, each), stream);
+    });
 }
 
 }  // namespace scan2d

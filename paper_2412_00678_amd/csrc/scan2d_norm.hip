@@ -194,10 +194,7 @@ __global__ __launch_bounds__(256) void scan2d_norm_any_kernel(const NormArgs p) 
     }
 }
 
-}  // namespace
-
-int block_norm_launch(const scan2d_desc* d, int kind, float eps, const void* in, const float* gamma, const float* beta, void* out,
-                      hipStream_t stream) {
+int launch_norm(const scan2d_desc* d, int kind, float eps, const void* in, const float* gamma, const float* beta, void* out, hipStream_t stream) {
     if ((kind != 0 && kind != 1) || !(eps >= 0.0f)) return SCAN2D_ERR_BAD_SHAPE;
     NormArgs a;
     a.in = in; a.gamma = gamma; a.beta = beta; a.out = out;
@@ -207,7 +204,7 @@ int block_norm_launch(const scan2d_desc* d, int kind, float eps, const void* in,
     (void)hipGetLastError();
     if (a.P >= 4 && a.P < (1LL << 31) && a.C <= 512) {
         const long long blocks = (a.P + 63) / 64 * d->Bt;
-        if (blocks > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+        if (!launch_fits(blocks, 256)) return SCAN2D_ERR_BAD_SHAPE;
         using Kernel = void (*)(const NormArgs);
         Kernel k;
         if (a.C <= 64) k = bf16 ? scan2d_norm_kernel<bf16_t, 2, 8, 8> : scan2d_norm_kernel<float, 4, 16, 4>;
@@ -220,7 +217,7 @@ int block_norm_launch(const scan2d_desc* d, int kind, float eps, const void* in,
     const bool vec = a.P % 4 == 0;
     a.groups = vec ? a.P / 4 : a.P;
     const long long blocks = (a.groups + kNormGroups - 1) / kNormGroups * d->Bt;
-    if (blocks > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+    if (!launch_fits(blocks, 256)) return SCAN2D_ERR_BAD_SHAPE;
     if (bf16) {
         if (vec) hipLaunchKernelGGL((scan2d_norm_any_kernel<bf16_t, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
         else hipLaunchKernelGGL((scan2d_norm_any_kernel<bf16_t, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
@@ -229,6 +226,14 @@ int block_norm_launch(const scan2d_desc* d, int kind, float eps, const void* in,
         else hipLaunchKernelGGL((scan2d_norm_any_kernel<float, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
     }
     return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
+}
+
+}  // namespace
+
+int block_norm_launch(const scan2d_desc* d, int kind, float eps, const void* in, const float* gamma, const float* beta, void* out,
+                      hipStream_t stream) {
+    const size_t each = (size_t)d->Dc * d->H * d->W * (d->dtype == SCAN2D_BF16 ? 2 : 4);
+    return by_items(*d, [&](const scan2d_desc& q, size_t b) { return launch_norm(&q, kind, eps, item_at(in, b, each), gamma, beta, item_at(out, b, each), stream); });
 }
 
 }  // namespace scan2d

@@ -261,18 +261,14 @@ __global__ __launch_bounds__(kSoftThreads) void scan2d_pool_sum_kernel(const Poo
     if (tid == 0) p.z[(size_t)b * p.M + m] = acc;
 }
 
-}  // namespace
-
-int block_attn_pool_launch(const scan2d_desc* d, int D, const void* h, const void* V, const float* w, const uint8_t* mask,
-                           float* attn, float* z, hipStream_t stream) {
-    if (D < 1 || D > kPoolRows) return SCAN2D_ERR_BAD_SHAPE;
+int launch_pool(const scan2d_desc* d, int D, const void* h, const void* V, const float* w, const uint8_t* mask, float* attn, float* z, hipStream_t stream) {
     PoolArgs a;
     a.h = h; a.V = V; a.w = w; a.mask = mask; a.attn = attn; a.z = z;
     a.M = d->Dc; a.D = D; a.Bt = d->Bt;
     a.P = (long long)d->H * d->W;
     const long long tiles = (a.P + 63) / 64;
     const bool bf16 = d->dtype == SCAN2D_BF16, fits = contract_fits(a.P, D, a.M, bf16 ? 2 : 4);
-    if ((fits ? tiles : a.P) * d->Bt > 2147483647LL || d->Bt > 65535) return SCAN2D_ERR_BAD_SHAPE;
+    if (!launch_fits((fits ? tiles : a.P) * d->Bt, fits ? 256 : 64)) return SCAN2D_ERR_BAD_SHAPE;
     a.tiles = (int)tiles;
     (void)hipGetLastError();
     const dim3 g1((unsigned)((fits ? tiles : a.P) * d->Bt)), g2((unsigned)d->Bt), g3((unsigned)d->Dc, (unsigned)d->Bt);
@@ -292,6 +288,17 @@ int block_attn_pool_launch(const scan2d_desc* d, int D, const void* h, const voi
     if (bf16) hipLaunchKernelGGL(scan2d_pool_sum_kernel<bf16_t>, g3, dim3(kSoftThreads), 0, stream, a);
     else hipLaunchKernelGGL(scan2d_pool_sum_kernel<float>, g3, dim3(kSoftThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
+}
+
+}  // namespace
+
+int block_attn_pool_launch(const scan2d_desc* d, int D, const void* h, const void* V, const float* w, const uint8_t* mask,
+                           float* attn, float* z, hipStream_t stream) {
+    if (D < 1 || D > kPoolRows || d->Bt > 65535) return SCAN2D_ERR_BAD_SHAPE;
+    const size_t P = (size_t)d->H * d->W, each = P * d->Dc * (d->dtype == SCAN2D_BF16 ? 2 : 4);
+    return by_items(*d, [&](const scan2d_desc& q, size_t b) {
+        return launch_pool(&q, D, item_at(h, b, each), V, w, item_at(mask, b, P), item_at(attn, b, 4 * P), item_at(z, b, 4 * (size_t)d->Dc), stream);
+    });
 }
 
 }  // namespace scan2d

@@ -308,10 +308,7 @@ void launch(const XprojArgs& a, int Bt, hipStream_t stream) {
     else hipLaunchKernelGGL((scan2d_xproj_kernel<T, 16, TAIL, WIDE>), grid, dim3(256), 0, stream, a);
 }
 
-}  // namespace
-
-int block_xproj_launch(const scan2d_desc* d, int R, const void* x, const void* Wx, const float* Wdt, void* delta_raw, void* Bm,
-                       void* Cm, hipStream_t stream) {
+int launch_xproj(const scan2d_desc* d, int R, const void* x, const void* Wx, const float* Wdt, void* delta_raw, void* Bm, void* Cm, hipStream_t stream) {
     if (R < 1 || R > 64) return SCAN2D_ERR_BAD_SHAPE;
     const bool bf16 = d->dtype == SCAN2D_BF16;
     XprojArgs a;
@@ -320,11 +317,12 @@ int block_xproj_launch(const scan2d_desc* d, int R, const void* x, const void* W
     a.P = (long long)d->H * d->W;
     const long long tiles = (a.P + 63) / 64;
     const bool fits = contract_fits(a.P, R + 2 * d->N, d->Dc, bf16 ? 2 : 4);
-    if ((fits ? tiles : a.P) * d->Bt > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+    const bool wave = fits && bf16 && tiles * d->Bt >= kWaveTiles;
+    if (!launch_fits(wave ? (tiles * d->Bt + 3) / 4 : (fits ? tiles : a.P) * d->Bt, 256)) return SCAN2D_ERR_BAD_SHAPE;
     a.tiles = (int)tiles; a.Bt = d->Bt;
     (void)hipGetLastError();
     if (fits) {
-        if (bf16 && tiles * d->Bt >= kWaveTiles) {
+        if (wave) {
             const dim3 grid((unsigned)((tiles * d->Bt + 3) / 4));
             if (R <= 8) hipLaunchKernelGGL(scan2d_xproj_wave_kernel<2>, grid, dim3(256), 0, stream, a);
             else if (R <= 16) hipLaunchKernelGGL(scan2d_xproj_wave_kernel<4>, grid, dim3(256), 0, stream, a);
@@ -339,6 +337,16 @@ int block_xproj_launch(const scan2d_desc* d, int R, const void* x, const void* W
         else hipLaunchKernelGGL(scan2d_xproj_any_kernel<float>, grid, dim3(256), 0, stream, a);
     }
     return hipGetLastError() == hipSuccess ? SCAN2D_OK : SCAN2D_ERR_LAUNCH_FAILED;
+}
+
+}  // namespace
+
+int block_xproj_launch(const scan2d_desc* d, int R, const void* x, const void* Wx, const float* Wdt, void* delta_raw, void* Bm,
+                       void* Cm, hipStream_t stream) {
+    const size_t row = (size_t)d->H * d->W * (d->dtype == SCAN2D_BF16 ? 2 : 4);
+    return by_items(*d, [&](const scan2d_desc& q, size_t b) {
+        return launch_xproj(&q, R, item_at(x, b, row * d->Dc), Wx, Wdt, item_at(delta_raw, b, row * d->Dc), item_at(Bm, b, row * d->N), item_at(Cm, b, row * d->N), stream);
+    });
 }
 
 }  // namespace scan2d

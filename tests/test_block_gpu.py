@@ -626,3 +626,27 @@ def test_layers_on_the_matrix_cores_for_the_largest_maps(s2d, H, W, dtype):
     assert bool(torch.isfinite(z).all()) and abs(float(attn.double().sum()) - 1.0) <= P / 1024 * 2.0 ** -24 + 1e-6
     for name in us:
         assert us[name] <= 4 * us_small[name], (name, us, us_small)
+
+
+def test_layers_on_more_positions_than_one_launch_has_threads_for(s2d):
+    """2.3e9 and 1.2e9 positions: a launch of 2 or 4 threads per position would hold more than 2^32, of which only a part
+    runs.  First and last positions of every batch item against plain torch."""
+    import torch
+    H, W = 11585, 11584
+    P = H * W
+    at = torch.cat([torch.arange(0, 70), torch.arange(P - 70, P)]).cuda()
+    col = lambda t: t.reshape(t.shape[0], t.shape[1], P)[:, :, at].float()
+    x = torch.randn((17, 1, H, W), device="cuda", dtype=torch.bfloat16)
+    out = s2d.block_linear(x, torch.full((1, 1), 2.0, device="cuda", dtype=torch.bfloat16))
+    assert torch.equal(col(out), 2.0 * col(x))
+    x, out = x[:9], out[:9]
+    out.zero_()
+    s2d.block_norm(x, torch.ones(1, device="cuda"), None, 1.0, s2d.RMS_NORM, out=out)
+    assert rel_err(col(out).cpu().numpy(), (col(x) / (col(x) ** 2 + 1).sqrt()).cpu().numpy()) <= TOL_BLOCK[wl.BF16]
+    z, attn = s2d.block_attn_pool(x, torch.ones((1, 1), device="cuda", dtype=torch.bfloat16), torch.ones(1, device="cuda"))
+    a, s = attn.reshape(9, P)[:, at], torch.tanh(col(x)[:, 0])
+    assert rel_err(torch.log(a / a[:, :1]).cpu().numpy(), (s - s[:, :1]).cpu().numpy()) <= 1e-4
+    x = x.float()
+    three = torch.tensor([[1.0], [2.0], [4.0]], device="cuda")
+    raw, Bm, Cm = s2d.block_xproj(x, three, torch.full((1, 1), 3.0, device="cuda"), 1)
+    assert all(torch.equal(col(got), k * col(x)) for got, k in ((raw, 3.0), (Bm, 2.0), (Cm, 4.0)))
