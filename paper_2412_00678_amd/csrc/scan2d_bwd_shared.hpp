@@ -565,6 +565,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         asm volatile("" ::: "memory");
         // ---- scans 3 and 4, bottom row of the band first
         float ga[NW][K], dAb[NW];
+        const int rows = H - r0;                           // of this band inside the map
 #pragma unroll
         for (int s = 0; s < NW; ++s) {
             dAb[s] = 0.0f;
@@ -659,6 +660,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             }
             Part::put(part + (size_t)(r * WAVES + wave) * Part::kRow, lane, s1, s2);
             __builtin_amdgcn_sched_barrier(0);
+            if (r > 0) {                                   // rows past H come first and add nothing to dA (0 * infinity would be NaN)
+#pragma unroll
+                for (int s = 0; s < NW; ++s) dAb[s] = r < rows ? dAb[s] : 0.0f;
+            }
         }
 #pragma unroll
         for (int s = 0; s < NW; ++s) {

@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void scan2d_bwd_small_kernel(const BwdArgs p) 
 #pragma unroll
         for (int q = HM / 4 - 1; q >= 0; --q) {
             if (4 * q < H) {
-                float dl[4], dxe[4], a[4], g3[4], gag[4], P[4], Q[4], qin[4], ar[4], s1[4], s2[4];
+                float dl[4], dxe[4], a[4], g3[4], gag[4], P[4], Q[4], qin[4], ar[4], t[4], s1[4], s2[4];
 #pragma unroll
                 for (int e = 3; e >= 0; --e) {
                     const int i = 4 * q + e;
@@ -178,19 +178,25 @@ __global__ __launch_bounds__(256) void scan2d_bwd_small_kernel(const BwdArgs p) 
                 for (int e = 0; e < 4; ++e) {
                     const int i = 4 * q + e;
                     const float qv = fmaf(ar[e], qin[e], g3[e]);                   // scan 4: q[i,j]
-                    const float t = fmaf(a[e] * qv, hhl[i], gag[e] * hprev[i]);    // gradient of the decay, times the decay
-                    dAb = fmaf(t, dl[e], dAb);
+                    t[e] = fmaf(a[e] * qv, hhl[i], gag[e] * hprev[i]);             // gradient of the decay, times the decay
                     dBacc[i] = fmaf(qv, dxe[e], dBacc[i]);
-                    s1[e] = t * An;
+                    s1[e] = t[e] * An;
                     s2[e] = qv * Bv[i];
                 }
+                if (4 * q + 3 >= H) {                     // rows past H add nothing to dA (0 * infinity would be NaN); once per map
+#pragma unroll
+                    for (int e = 1; e < 4; ++e)
+                        if (4 * q + e >= H) asm volatile("v_mov_b32 %0, 0" : "=v"(t[e]));
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dAb = fmaf(t[e], dl[e], dAb);
 #pragma unroll
                 for (int e = 0; e < 4; e += 2)
                     part[wave][2 * q + e / 2][lane] = row_pairs_sum(halves_sum(s1[e], s2[e]), halves_sum(s1[e + 1], s2[e + 1]));
             }
         }
         {
-            const float tot = row_sum16(dAb);
+            const float tot = row_sum16(l < W ? dAb : 0.0f);
             if (l == 0 && state && act) p.pA[map * N + n] = tot;
         }
         __syncthreads();

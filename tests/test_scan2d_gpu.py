@@ -1238,3 +1238,20 @@ def test_backward_writes_into_the_tensors_of_any_iterable(s2d, form):
         assert all(torch.equal(g, r) for g, r in zip(got, want))
     with pytest.raises(ValueError):
         s2d.scan2d_bwd(*args, out=(torch.empty_like(t) for t in want[:5]))
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("H,W", [(14, 14), (13, 16), (16, 9), (37, 56), (5, 128), (7, 192), (5, 256), (3, 260), (5, 512)])
+def test_infinity_in_the_last_cell_of_a_map_stays_out_of_dA(s2d, H, W, dtype):
+    """B of the last cell reaches the state of that cell only, behind which no decay is applied: dA does not depend on it,
+    and only that cell's gradients of x and delta do.  (Rows that do not fill a band, lanes past the last column.)"""
+    import torch
+    w = wl.Workload("last", 2, 3, 16, H, W, dtype, backward=True)
+    d = s2d.to_device(wl.make_inputs(w, seed=12), dtype)
+    args = lambda: (d["x"], d["delta"], d["A"], d["Bm"], d["Cm"], d["Dskip"], d["mask"], d["dy"])
+    want = s2d.scan2d_bwd(*args())
+    d["Bm"][:, ::3, -1, -1] = float("inf")
+    got = s2d.scan2d_bwd(*args())
+    assert torch.equal(got[2], want[2])
+    for k in (0, 1):
+        assert torch.equal(got[k].flatten(2)[..., :-1], want[k].flatten(2)[..., :-1])
