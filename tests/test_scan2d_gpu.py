@@ -1255,3 +1255,27 @@ def test_infinity_in_the_last_cell_of_a_map_stays_out_of_dA(s2d, H, W, dtype):
     assert torch.equal(got[2], want[2])
     for k in (0, 1):
         assert torch.equal(got[k].flatten(2)[..., :-1], want[k].flatten(2)[..., :-1])
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("H,W", [(6, 300), (5, 512), (4, 530)])
+def test_column_panels_beside_a_column_whose_state_overflows(s2d, H, W, dtype):
+    """Columns 40, 43, 255 and 281 collect 3e38 per row and overflow; the decay of the column behind each is exp(-200) = 0,
+    so nothing of it reaches the other columns: their gradients are those of ordinary inputs, to the bit."""
+    import torch
+    w = wl.Workload("over", 1, 2, 16, H, W, dtype, backward=True)
+    d = s2d.to_device(wl.make_inputs(w, seed=13), dtype)
+    cols = [40, 43, 255, 281]
+    d["A"].fill_(-1.0)
+    d["delta"].fill_(1e-3)
+    d["delta"][..., [c + 1 for c in cols]] = 200.0
+    d["Bm"][..., cols] = 3e21
+    d["dy"].mul_(1e-3)                                   # the gradients themselves stay far from overflow
+    out = []
+    for big in (1.0, 1e20):
+        d["x"][..., cols] = big
+        out.append(s2d.scan2d_bwd(d["x"], d["delta"], d["A"], d["Bm"], d["Cm"], d["Dskip"], d["mask"], d["dy"]))
+    assert not bool(torch.isfinite(out[1][4][..., cols]).all())             # dC: the states did overflow
+    others = [j for j in range(W) if j not in cols]
+    assert bool(torch.isfinite(out[0][1]).all()) and torch.equal(out[1][0], out[0][0])
+    assert torch.equal(out[1][1][..., others], out[0][1][..., others])
