@@ -263,7 +263,7 @@ LINEAR_CASES = [
     (1, 128, 256, 16, 32, wl.BF16, True, False), (2, 64, 128, 8, 16, wl.F32, False, False), (1, 256, 128, 16, 24, wl.BF16, True, True),
     (1, 36, 50, 5, 12, wl.F32, True, True), (3, 100, 130, 7, 20, wl.BF16, False, True), (1, 4, 1, 2, 2, wl.F32, True, False),
     (1, 512, 300, 3, 44, wl.BF16, True, False), (2, 96, 192, 56, 56, wl.BF16, False, False), (1, 160, 96, 20, 52, wl.F32, True, True),
-    # neither H*W nor the channel count a multiple of 4: the kernel with one thread per output
+    # neither H*W nor the channel count a multiple of 4, and a map of one position: the kernel with one thread per output
     (2, 37, 19, 5, 7, wl.BF16, True, True), (1, 30, 64, 3, 9, wl.F32, True, False), (1, 64, 10, 1, 1, wl.F32, False, True),
 ]
 
@@ -417,8 +417,7 @@ def test_whole_block_forward_matches_the_oracle_chain(s2d, shape):
 def test_whole_block_and_aggregator_replay_from_a_hip_graph(s2d, dtype):
     """The layers around the scan only enqueue kernels on the caller's stream (no allocation, no memset, no
     synchronisation), so a whole block forward plus the aggregator can be captured; every replay equals the eager
-    result bit for bit, also after the inputs changed and eager work ran in between.  fp32 takes the linear kernel
-    that needs more than 64 KB of dynamic LDS (the attribute is raised once, outside the capture)."""
+    result bit for bit, also after the inputs changed and eager work ran in between."""
     import torch
     Bt, Dm, N, H, W, R = 2, 32, 16, 16, 32, 4
     Dc = 2 * Dm
@@ -506,9 +505,29 @@ def test_xproj_with_ragged_channels_and_positions(s2d, Bt, Dc, N, H, W, R, dtype
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("bias", [True, False], ids=["b", "nb"])
+@pytest.mark.parametrize("res", [True, False], ids=["r", "nr"])
 @pytest.mark.parametrize("Bt,Cin,Cout,H,W", [(1, 33, 17, 1, 5), (2, 31, 47, 5, 13), (1, 64, 96, 181, 183), (2, 96, 40, 129, 130), (1, 128, 80, 7, 4681)])
-def test_linear_with_ragged_channels_and_many_positions(s2d, Bt, Cin, Cout, H, W, dtype):
-    test_linear_matches_oracle(s2d, (Bt, Cin, Cout, H, W, dtype, True, True))
+def test_linear_with_ragged_channels_and_many_positions(s2d, Bt, Cin, Cout, H, W, res, bias, dtype):
+    """From 512 tiles of 64 positions on, bf16 holds its positions in registers (two wavefronts per tile) and fp32 streams
+    pieces through one workgroup per compute unit, with instantiations for the residual and a stand-in for a missing bias."""
+    test_linear_matches_oracle(s2d, (Bt, Cin, Cout, H, W, dtype, bias, res))
+
+
+@pytest.mark.parametrize("res", [True, False], ids=["r", "nr"])
+def test_linear_with_one_wavefront_per_tile(s2d, res):
+    """bf16 from 4096 tiles of 64 positions on."""
+    test_linear_matches_oracle(s2d, (1, 32, 49, 512, 513, wl.BF16, not res, res))
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("Bt,C,H,W", [(1, 37, 1, 1), (3, 20, 1, 2), (2, 64, 3, 1)])
+def test_layers_on_maps_of_fewer_than_four_positions(s2d, Bt, C, H, W, dtype):
+    """The element-wise kernels of the linear layer, the projections and the aggregator."""
+    for bias in (False, True):
+        test_linear_matches_oracle(s2d, (Bt, C, 19, H, W, dtype, bias, not bias))
+    test_xproj_matches_oracle(s2d, (Bt, C, 16, H, W, dtype, 5))
+    test_attn_pool_matches_oracle(s2d, (Bt, C, H, W, dtype, 128, 0.0))
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])

@@ -1279,3 +1279,23 @@ def test_column_panels_beside_a_column_whose_state_overflows(s2d, H, W, dtype):
     others = [j for j in range(W) if j not in cols]
     assert bool(torch.isfinite(out[0][1]).all()) and torch.equal(out[1][0], out[0][0])
     assert torch.equal(out[1][1][..., others], out[0][1][..., others])
+
+
+# Bt, Dc, N, H, W, channels per workgroup
+SMALL_CHANNEL_GROUPS = [(8, 128, 16, 14, 14, 2), (9, 129, 16, 14, 14, 2), (13, 119, 16, 7, 7, 3), (16, 129, 8, 12, 16, 2), (32, 131, 4, 7, 9, 2)]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("form", ["plain", "softplus", "gated"])
+@pytest.mark.parametrize("Bt,Dc,N,H,W,GS", SMALL_CHANNEL_GROUPS, ids=lambda v: str(v))
+def test_backward_of_small_maps_with_several_channels_per_workgroup(s2d, Bt, Dc, N, H, W, GS, form, dtype):
+    """A workgroup handles GS channels in turn (whole groups and a ragged last one), states on one, two and four wavefronts;
+    the channel groups' partial sums are added by 16 threads per element."""
+    plan = s2d.describe_plan(s2d.Desc(Bt, Dc, H, W, N, dtype, 0), s2d.PASS_BWD)
+    assert "form=small " in plan and f" GS={GS} " in plan, plan
+    if form == "plain":
+        check_bwd(s2d, wl.Workload("small", Bt, Dc, N, H, W, dtype, mask_frac=0.3, backward=True), seed=16)
+    elif form == "softplus":
+        test_backward_with_softplus_step_matches_oracle(s2d, (Bt, Dc, N, H, W, dtype, 0.3), True)
+    else:
+        test_gated_backward_matches_oracle(s2d, (Bt, Dc, N, H, W, dtype, 0.3))
