@@ -326,9 +326,9 @@ int scan2d_block_attn_pool(const scan2d_desc* desc, int D, const void* h, const 
  *   out : [Bt][Cout][H][W] storage type (written; out == in is refused with SCAN2D_ERR_BAD_SHAPE).
  *   The product runs on the matrix cores (inputs as stored, fp32 accumulation); bias and residual are added in fp32
  *   and the sum is rounded once.  The input projection of a block is two calls, one per half of its rows, so that
- *   both halves are tensors of their own.  Cout >= 1 (else SCAN2D_ERR_BAD_SHAPE); any Cin, any H*W (multiples of 4
- *   take the fast path).  desc.N and desc.flags are not used.  Device pointers, 16-byte aligned; asynchronous on
- *   `stream`; no workspace.
+ *   both halves are tensors of their own.  Cout >= 1 (else SCAN2D_ERR_BAD_SHAPE); any Cin, any H*W (maps of fewer than
+ *   4 positions are computed element by element).  desc.N and desc.flags are not used.  Device pointers, 16-byte
+ *   aligned; asynchronous on `stream`; no workspace.
  */
 int scan2d_block_linear(const scan2d_desc* desc, int Cout, const void* in, const void* Wt, const float* bias,
                         const void* residual, void* out, void* stream);

@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void scan2d_bwd_step_kernel(const T* __restric
 // bias) in a fixed order (strided partial sums per thread, then a tree over the workgroup).
 // Bound: HBM.  A workgroup per map, because the sum is one per map, with 4 elements per load.  A slide's few hundred maps
 // are a workgroup per compute unit, so each brings 16 wavefronts (211x397 bf16, 256 maps: 4 wavefronts and single elements
-// 160 us, this 64); maps of a few elements per thread would wait for the barriers of its sum, so below 8192 elements it is 4
+// 161 us, this 68); maps of a few elements per thread would wait for the barriers of its sum, so below 8192 elements it is 4
 // (us with 4 and 16 wavefronts: 4096 maps of 20x20 6.7 and 16.7, of 56x56 19.2 and 26.8, 1024 of 80x80 11.6 and 12.7, of
 // 100x100 23.5 and 22.5, 256 of 100x100 6.4 and 5.5).  Any alignment: maps of odd size start on odd elements.
 constexpr int kChainThreads = 1024;                        // the most
@@ -223,9 +223,11 @@ struct BwdPlan {
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Tilings whose shared-producer main sweep is the default: measured 10-30 % faster than the plain one for 16-lane
-// groups (56x56 bf16 x 6144 maps: 1.41 -> 1.08 ms; 128x192 fp32 x 2048 maps: 3.63 -> 2.86 ms); slower for wave-wide
-// groups on 16 waves, where the 128-register budget makes it spill (256x256 bf16: 2.0 -> 3.0 ms).
+// Tilings whose shared-producer main sweep is the default.  Whole backward, us, plain -> shared: (16,4) 56x56 bf16, 6144
+// maps 1417 -> 719; (16,8) 128x128 bf16, 1024 maps 1407 -> 787; (16,12) 128x192 fp32, 2048 maps 3730 -> 2047; (64,4) on 8
+// waves, 256 maps of 256x256 bf16 2646 -> 1456, fp32 2484 -> 1579.  The other shared tilings run by the tuning override
+// only: (64,4) on 16 waves takes 1501 and 1695 on the last two (plain 2191 and 2014), (32,4) 1427 on the first and 760 on
+// the second, (32,6) 2496 on the third.
 bool shared_by_default(int LG, int K, int NW) { return LG == 16 || (LG == 64 && K == 4 && NW == 2); }
 
 }  // namespace
@@ -277,7 +279,8 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     else { LG = 64; K = 4; }
     // maps wider than the widest tiling (and, beyond 16 states, wider than 256 columns: the band arrays of four
     // states per lane and 16 waves fill the LDS) are swept in panels of 256 columns
-    // (measured faster than the 8- and 16-column tilings from 257 columns on: 512x512 bf16 x 256 maps 9.97 -> 8.74 ms)
+    // (faster than the 8- and 16-column tilings from 257 columns on; 256 maps, us: 300x300 fp32 3070 against 4709, 400x400
+    // bf16 4315 against 6657, 512x512 bf16 5757 against 9535, 600x600 bf16 11180 against 26660)
     if (W > 256 || av) { LG = 64; K = 4; pl.panels = (W + 255) / 256; }
     int force_waves = 0, force_gs = 0, want_shared = -1;
     if (tb.n >= 1) {                                             // tuning aid: LG,K[,WAVES[,GS[,shared]]]
@@ -298,8 +301,8 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     if (LG == 16) { waves = 4; NW = N <= 16 ? 1 : 4; }
     else if (LG == 32) { waves = 8; NW = 1; }
     else if (N <= 16 && K == 16) { waves = 4; NW = 4; }     // widest maps: LDS bounds the workgroup size
-    // (one panel of 16 states: two states per lane on 8 waves with the shared-producer main sweep, measured 13 % faster
-    // than 16 waves of one state that each repeat the per-position work: 256 maps of 256x256 bf16 2.11 -> 1.83 ms)
+    // (one panel of 16 states: two states per lane on 8 waves with the shared-producer main sweep, 256 maps of 256x256 bf16
+    // 1456 us, against 2191 on 16 waves of one state that each repeat the per-position work)
     else if (N == 16 && K == 4 && !av && want_shared != 0 && force_waves != 16) { waves = 8; NW = 2; }
     else if (N <= 16 && K == 4 && force_waves != 8) { waves = 16; NW = 1; }
     else if (N <= 16) { waves = 8; NW = 2; }

@@ -1,7 +1,9 @@
 // The launch plans a thread has used last.  Choosing a plan ranks dozens of kernel variants (5 us for a forward, with
 // the workspace query 15 to 30 us per call: more than the kernels of a small map take) and depends on the descriptor, a
 // few flags, the device and the tuning overrides only.  Each thread keeps its own few (no lock, bounded, gone with the
-// thread); they hold no device memory.
+// thread); they hold no device memory.  A forward shape takes up to four of the sixteen entries (the workspace query ranks
+// with and without the softplus step and aligned mask rows), a backward shape one per form: a loop over more than four
+// grids ranks again on every call.
 #pragma once
 
 #include <hip/hip_runtime.h>
