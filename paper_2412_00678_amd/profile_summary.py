@@ -2,6 +2,7 @@
 
     python -m paper_2412_00678_amd.profile_summary commands RUNS   # prints the rocprofv3 command lines, one per run
     python -m paper_2412_00678_amd.profile_summary write RUNS      # reads RUNS/*, writes profiles/*.md and profiles/traffic.json
+    python -m paper_2412_00678_amd.profile_summary case NAME N     # runs a listed case of perf/cases.py N times (traced by `commands`)
 
 `commands` prints one shell line per run (kernel trace, FETCH_SIZE, WRITE_SIZE and issue counters, each a run
 of its own, plus the copy-kernel runs that calibrate the two size counters); run them on the GPU from /tmp with
@@ -29,6 +30,10 @@ COPY_KIB = 1048576.0             # roofprobe --copy moves 2^30 bytes each way pe
 TRACE_STEPS = {1: "--steps 300 --warmup 200", 2: "--steps 300 --warmup 200", 3: "--steps 200 --warmup 100", 4: "--steps 40 --warmup 20"}
 PMC_STEPS = {1: "--steps 20 --warmup 4", 2: "--steps 20 --warmup 4", 3: "--steps 12 --warmup 4", 4: "--steps 8 --warmup 4"}
 
+# listed cases of perf/cases.py that bench.py has no workload for, with the passes to trace
+CASES = (("train_14x14_fp32_b8", 300), ("train_gated_56x56_bf16_b32", 60), ("train_gated_211x397_bf16_mask", 30), ("block_14x14_bf16_b8", 200),
+         ("slide_57x83_bf16_mask", 200), ("slide_127x201_fp32_mask", 100))
+
 
 def runs():
     out = []
@@ -50,6 +55,8 @@ def runs():
         b = f"python3 bench.py --no-cpu --block --workload {w} --steps 150 --warmup 100"
         out.append((f"trace_producers_{w}", "--kernel-trace --stats", b, f"trace_producers_{w}.json"))
         out.append((f"plain_producers_{w}", None, b, f"plain_producers_{w}.json"))
+    for name, passes in CASES:
+        out.append((f"trace_case_{name}", "--kernel-trace --stats", f"python3 ./paper_2412_00678_amd/profile_summary.py case {name} {passes}", None))
     out.append(("fetch_copy", "--pmc FETCH_SIZE", "./paper_2412_00678_amd/roofprobe --copy 5", None))
     out.append(("write_copy", "--pmc WRITE_SIZE", "./paper_2412_00678_amd/roofprobe --copy 5", None))
     return out
@@ -98,8 +105,8 @@ def short(name: str) -> str:
     return n
 
 
-def kernel_table(runs_dir, name):
-    rows = query(db_path(runs_dir, name), "select name,total_calls,total_duration,average,percentage from top_kernels")
+def kernel_table(runs_dir, name, like="%"):
+    rows = query(db_path(runs_dir, name), "select name,total_calls,total_duration,average,percentage from top_kernels where name like ?", (like,))
     out = ["| kernel | calls | total (us) | average (us) | % |", "|---|---|---|---|---|"]
     for n, calls, total, avg, pct in rows:
         out.append(f"| `{short(n)[:110]}` | {calls} | {total:.1f} | {avg:.2f} | {pct:.2f} |")
@@ -205,7 +212,7 @@ def raw_counter_table(runs_dir, name):
 
 # sources that the recorded workloads (scan2d_fwd / scan2d_bwd on the benchmark configurations) do not run: the probe
 # and the layers around the scan
-NOT_IN_DIGEST = ("roofprobe", "scan2d_block", "scan2d_pool", "scan2d_linear", "scan2d_norm")
+NOT_IN_DIGEST = ("roofprobe", "scan2d_block", "scan2d_contract", "scan2d_xproj", "scan2d_pool", "scan2d_linear", "scan2d_norm")
 
 
 def kernel_source_digest() -> str:
@@ -403,7 +410,32 @@ the matrix cores' rate: it is bound by the bytes of x and delta_raw):
 """ + "\n".join(rows) + "\n")
 
 
+def run_case(name, passes):
+    """`passes` passes of a listed case over two states in turn, as a program's loop over its data would run them."""
+    sys.path.insert(0, ROOT)
+    import torch
+    from perf import cases
+    case = next(c for c in cases.listed() if c["name"] == name)
+    states = [cases.prepare(case, seed) for seed in (1, 2)]
+    torch.cuda.synchronize()
+    for k in range(passes):
+        cases.run(states[k % 2])
+    torch.cuda.synchronize()
+
+
+def write_cases(runs_dir, by_name):
+    with open(os.path.join(PROFILES, "scan2d_listed_cases.md"), "w") as f:
+        f.write("# Kernels of the listed cases of `perf/cases.py` that bench.py has no workload for\n\n"
+                "Each run makes two states and passes over them in turn; kernels of torch make the inputs.  Averages are under the tracer.\n")
+        for name, passes in CASES:
+            run = f"trace_case_{name}"
+            f.write(f"\n## {name}, {passes} passes\n\n`{shown(by_name[run])}`\n\n{kernel_table(runs_dir, run, '%scan2d%')}\n")
+
+
 def main(argv):
+    if len(argv) == 4 and argv[1] == "case":
+        run_case(argv[2], int(argv[3]))
+        return 0
     if len(argv) != 3 or argv[1] not in ("commands", "write"):
         print(__doc__, file=sys.stderr)
         return 2
@@ -415,6 +447,7 @@ def main(argv):
         return 0
     write(runs_dir)
     write_producers(runs_dir, {r[0]: r for r in runs()})
+    write_cases(runs_dir, {r[0]: r for r in runs()})
     return 0
 
 
