@@ -39,6 +39,8 @@
  * with 32-bit lane offsets); any H, W >= 1 in the forward and in the backward (maps wider than
  * one lane-group panel are swept panel by panel and need workspace for the carries between the
  * panels, see scan2d_workspace_bytes).  Shapes outside these limits return SCAN2D_ERR_BAD_SHAPE.
+ * A launch holds fewer than 2^32 threads: the scans take Bt * Dc < 2^22 maps in a call whatever their
+ * shape (not checked); the layers around them split larger calls by batch items.
  */
 #ifndef SCAN2D_H_
 #define SCAN2D_H_
