@@ -87,8 +87,12 @@ __device__ __forceinline__ float group_sum_last(float v) {
 template <int LG, int S>
 __device__ __forceinline__ void group_scan_left_any(float* P, float* Q, float* C) {
     if constexpr (LG == 32) {
-        static_assert(S <= 2, "half-wave groups: one or two recurrences");
-        if constexpr (S == 1) {
+        if constexpr (S == 4) {
+            asm volatile("s_nop 1\n\t"
+                         SCAN2D_S4_STEP(SCAN2D_SHL(1)) SCAN2D_S4_STEP(SCAN2D_SHL(2))
+                         SCAN2D_S4_STEP(SCAN2D_SHL(4)) SCAN2D_S4_STEP(SCAN2D_SHL(8))
+                         : "+v"(Q[0]), "+v"(Q[1]), "+v"(Q[2]), "+v"(Q[3]), "+v"(P[0]), "+v"(P[1]), "+v"(P[2]), "+v"(P[3]));
+        } else if constexpr (S == 1) {
             asm volatile("s_nop 1\n\t"
                          SCAN2D_S1_STEP(SCAN2D_SHL(1)) SCAN2D_S1_STEP(SCAN2D_SHL(2))
                          SCAN2D_S1_STEP(SCAN2D_SHL(4)) SCAN2D_S1_STEP(SCAN2D_SHL(8))
@@ -207,6 +211,14 @@ constexpr bool bwd_bc_in_registers() { return 2 * RB * NW * words_of<T, (K + 3) 
 template <int K, int NW>
 constexpr int bwd_decay_rows() { return K * NW >= 12 ? 2 : 0; }
 
+// Rows of a band whose row scans run together (the column recurrence alone ties the rows of a map to each other).  A lone
+// scan is a chain of dependent lane movements with wait states between them; four of them side by side need none.  Where
+// all rows of a band are scanned together their decays also stay in registers from the rebuild to the reverse sweep.  Only
+// where that leaves two wavefronts per SIMD, i.e. up to 16 cells per lane (56x56 bf16 with step and gate, 6144 maps: 722
+// instructions per band and channel became 631, the sweep 528 -> 501 us).
+template <int K, int NW, int RB, bool MP>
+constexpr int bwd_rows_per_scan() { return !MP && K * NW * RB <= 16 ? RB : 1; }
+
 // Dynamic LDS layout (floats), TH = workgroup threads, SLOTS = TH / LG, JPW = SLOTS / NG, GS channels:
 //   part [RB][WAVES][PartRow::kRow]    the wavefronts' sums over their states of the current (band, channel)
 //   pp   [JPW][RB][3][PANEL]           the per-position values of the current (band, channel): step, step * x, dy
@@ -244,6 +256,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
     static_assert(bwd_decay_rows<K, NW>() == 0 || K % 4 == 0, "decays move in pieces of four");
     constexpr bool BCR = bwd_bc_in_registers<T, K, NW, RB>();
     constexpr int ALR = bwd_decay_rows<K, NW>();
+    constexpr int RS = bwd_rows_per_scan<K, NW, RB, MP>();
+    constexpr bool AREG = RS == RB;
+    static_assert(RB % RS == 0 && (!AREG || ALR == 0), "whole scans per band, decays in one place");
+    static_assert(RS == 1 || BCR, "rows scanned together have their Bm and Cm at hand");
     // SP: p.delta is the raw projection.  Single-panel instantiations (SPIN) apply the softplus where the cells are
     // produced and the chain rule where ddelta is summed (the logistic factor comes from the step kept in LDS), so
     // ddelta receives the gradient of the raw projection directly; the column-panel instantiations read the step from a
@@ -519,48 +535,61 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         // (decay product, state) pair that the lanes scan, then from the state that enters the lane - as many
         // multiply-adds as adding the carry to stored partial results, without the arrays that hold them
         float hprev[RB][NW][K], hhl[RECOMP ? 1 : RB][NW][K];
+        float ak[AREG ? RB : 1][NW][K], Prow[RB][NW];      // decays (AREG) and per lane their product over its columns
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            if constexpr (!BCR) {                          // row 0 is there: from the band's first request, then from the row sweep
-                if (r + 1 < RB) load_B((r + 1) % BR, r0 + r + 1);
-                else load_C(r % BR, r0 + r);
-            }
-            float dl[K], dxe[K], a[NW][K], u[NW][K], P[NW], Hh[NW], cin[NW];
-            lds_read_k<LG, K>(ppj + r * PP_ROW, l, dl);
-            lds_read_k<LG, K>(ppj + r * PP_ROW + PANEL, l, dxe);
+        for (int rb = 0; rb < RB; rb += RS) {
+            float a[RS][NW][K], u[RS][NW][K], P[RS * NW], Hh[RS * NW], cin[RS * NW];
 #pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                const uint32_t* Br = bB[r % BR][s];
-#pragma unroll
-                for (int j = 0; j < K; ++j) {
-                    a[s][j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
-                    if (r < ALR && j % 4 == 3) *reinterpret_cast<float4*>(aL + ((r * NW * K + s * K + j - 3) / 4 * THREADS + tid) * 4) = make_float4(a[s][j - 3], a[s][j - 2], a[s][j - 1], a[s][j]);
-                    u[s][j] = dxe[j] * get_elem<T, K>(Br, j);
-                    if constexpr (CF) {
-                        hprev[r][s][j] = hcur[s][j];                                   // v[i-1,j]
-                        u[s][j] = hcur[s][j] = fmaf(a[s][j], hcur[s][j], u[s][j]);
-                    }
-                    P[s] = j == 0 ? a[s][0] : P[s] * a[s][j];
-                    Hh[s] = j == 0 ? u[s][0] : fmaf(a[s][j], Hh[s], u[s][j]);
+            for (int r = rb; r < rb + RS; ++r) {
+                if constexpr (!BCR) {                      // row 0 is there: from the band's first request, then from the row sweep
+                    if (r + 1 < RB) load_B((r + 1) % BR, r0 + r + 1);
+                    else load_C(r % BR, r0 + r);
                 }
-                if constexpr (MP) Hh[s] = fmaf(P[s], hcv[r][s], Hh[s]);                // state entering from the panel to the left
-            }
-            group_scan<LG, NW>(P, Hh, cin);
+                float dl[K], dxe[K];
+                lds_read_k<LG, K>(ppj + r * PP_ROW, l, dl);
+                lds_read_k<LG, K>(ppj + r * PP_ROW + PANEL, l, dxe);
 #pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                float left = cin[s];                       // hhor[i, j-1] (CF: h[i, j-1])
-                if constexpr (MP) left += hcv[r][s];       // one of them is 0
+                for (int s = 0; s < NW; ++s) {
+                    const uint32_t* Br = bB[r % BR][s];
+                    const int q = (r - rb) * NW + s;
+                    float (&ar)[K] = a[r - rb][s], (&ur)[K] = u[r - rb][s];
 #pragma unroll
-                for (int j = 0; j < K; ++j) {
-                    if constexpr (!RECOMP) hhl[r][s][j] = left;
-                    if (!CF || j + 1 < K) left = fmaf(a[s][j], left, u[s][j]);
-                    if constexpr (!CF) {
-                        hprev[r][s][j] = hcur[s][j];
-                        hcur[s][j] = fmaf(a[s][j], hcur[s][j], left);
+                    for (int j = 0; j < K; ++j) {
+                        ar[j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
+                        if (r < ALR && j % 4 == 3) *reinterpret_cast<float4*>(aL + ((r * NW * K + s * K + j - 3) / 4 * THREADS + tid) * 4) = make_float4(ar[j - 3], ar[j - 2], ar[j - 1], ar[j]);
+                        if constexpr (AREG) ak[r][s][j] = ar[j];
+                        ur[j] = dxe[j] * get_elem<T, K>(Br, j);
+                        if constexpr (CF) {
+                            hprev[r][s][j] = hcur[s][j];                               // v[i-1,j]
+                            ur[j] = hcur[s][j] = fmaf(ar[j], hcur[s][j], ur[j]);
+                        }
+                        P[q] = j == 0 ? ar[0] : P[q] * ar[j];
+                        Hh[q] = j == 0 ? ur[0] : fmaf(ar[j], Hh[q], ur[j]);
                     }
+                    Prow[r][s] = P[q];
+                    if constexpr (MP) Hh[q] = fmaf(P[q], hcv[r][s], Hh[q]);            // state entering from the panel to the left
                 }
             }
-            __builtin_amdgcn_sched_barrier(0);             // rows stay apart: merged, their temporaries would not fit the registers
+            group_scan<LG, RS * NW>(P, Hh, cin);
+#pragma unroll
+            for (int r = rb; r < rb + RS; ++r) {
+#pragma unroll
+                for (int s = 0; s < NW; ++s) {
+                    const float (&ar)[K] = a[r - rb][s], (&ur)[K] = u[r - rb][s];
+                    float left = cin[(r - rb) * NW + s];   // hhor[i, j-1] (CF: h[i, j-1])
+                    if constexpr (MP) left += hcv[r][s];   // one of them is 0
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {
+                        if constexpr (!RECOMP) hhl[r][s][j] = left;
+                        if (!CF || j + 1 < K) left = fmaf(ar[j], left, ur[j]);
+                        if constexpr (!CF) {
+                            hprev[r][s][j] = hcur[s][j];
+                            hcur[s][j] = fmaf(ar[j], hcur[s][j], left);
+                        }
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);             // steps stay apart: merged, their temporaries would not fit the registers
         }
 
         // the compiler would keep step, step * x and the decays of all rows from here to the reverse sweep (3 RB NW K registers)
@@ -575,94 +604,108 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             for (int j = 0; j < K; ++j) ga[s][j] = gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j];
         }
 #pragma unroll
-        for (int r = RB - 1; r >= 0; --r) {
-            if constexpr (!BCR) {
-                if (r > 0) { load_B((r - 1) % BR, r0 + r - 1); load_C((r - 1) % BR, r0 + r - 1); }
-            }
-            const float* prow = ppj + r * PP_ROW;
-            float dl[K], dxe[K], dyv[K], s1[K], s2[K], a[NW][K], g[NW][K], P[NW], Q[NW], qin[NW], edge[NW];
-            lds_read_k<LG, K>(prow, l, dl);
-            lds_read_k<LG, K>(prow + PANEL, l, dxe);
-            lds_read_k<LG, K>(prow + 2 * PANEL, l, dyv);
+        for (int rt = RB - 1; rt >= 0; rt -= RS) {         // RS rows per scan, the topmost rt - RS + 1
+            float a[RS][NW][K], g[RS][NW][K], gr[RS][NW][K], P[RS * NW], Q[RS * NW], qin[RS * NW];     // gr: a * g (CF: of this row's q)
 #pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                const uint32_t* Cr = bC[r % BR][s];
-                if (r < ALR) {
-#pragma unroll
-                    for (int j = 0; j < K; j += 4) {
-                        const float4 v = *reinterpret_cast<const float4*>(aL + ((r * NW * K + s * K + j) / 4 * THREADS + tid) * 4);
-                        a[s][j] = v.x; a[s][j + 1] = v.y; a[s][j + 2] = v.z; a[s][j + 3] = v.w;
-                    }
+            for (int d = 0; d < RS; ++d) {
+                const int r = rt - d;
+                if constexpr (!BCR) {
+                    if (r > 0) { load_B((r - 1) % BR, r0 + r - 1); load_C((r - 1) % BR, r0 + r - 1); }
                 }
+                const float* prow = ppj + r * PP_ROW;
+                float dl[K], dxe[K], dyv[K];
+                if constexpr (!AREG) lds_read_k<LG, K>(prow, l, dl);
+                if constexpr (CF) lds_read_k<LG, K>(prow + PANEL, l, dxe);
+                lds_read_k<LG, K>(prow + 2 * PANEL, l, dyv);
 #pragma unroll
-                for (int j = 0; j < K; ++j) {
-                    if (r >= ALR) a[s][j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
-                    float hv;
-                    if constexpr (CF) {                // v[i,j], then h[i,j]
-                        hv = fmaf(a[s][j], hprev[r][s][j], dxe[j] * get_elem<T, K>(bB[r % BR][s], j));
-                        hv = fmaf(a[s][j], hhl[r][s][j], hv);
-                    } else {                           // h[i,j] is what the row below started from
-                        hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
-                    }
-                    dCacc[r][s][j] = fmaf(dyv[j], hv, dCacc[r][s][j]);
-                    const float Cv = get_elem<T, K>(Cr, j);
-                    if constexpr (CF) {
-                        g[s][j] = dyv[j] * Cv;
-                    } else {
-                        g[s][j] = fmaf(dyv[j], Cv, ga[s][j]);                                       // scan 3
-                        ga[s][j] = a[s][j] * g[s][j];
-                    }
-                }
-                // scan 4: q[j] = g[j] + a[j+1] * q[j+1]
-                edge[s] = from_right_any<LG>(a[s][0]);
-                if constexpr (MP) g[s][K - 1] += qcv[r][s];        // a*q entering from the panel to the right (last lane)
-                P[s] = edge[s];
-                Q[s] = g[s][K - 1];
+                for (int s = 0; s < NW; ++s) {
+                    const uint32_t* Cr = bC[r % BR][s];
+                    float (&ar)[K] = a[d][s];
+                    if (r < ALR) {
 #pragma unroll
-                for (int j = K - 2; j >= 0; --j) {
-                    Q[s] = fmaf(a[s][j + 1], Q[s], g[s][j]);
-                    P[s] *= a[s][j + 1];
-                }
-            }
-            group_scan_left_any<LG, NW>(P, Q, qin);
-#pragma unroll
-            for (int s = 0; s < NW; ++s) {
-                float q = qin[s], first = 0.0f;                    // first: hhor[i,j-1] of the lane's first column
-                const auto hh = [&](int j) {                       // hhor[i,j]
-                    const float hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
-                    return fmaf(-a[s][j], hprev[r][s][j], hv);
-                };
-                if constexpr (RECOMP) first = from_left_any<LG>(hh(K - 1));
-#pragma unroll
-                for (int j = K - 1; j >= 0; --j) {
-                    q = fmaf(j == K - 1 ? edge[s] : a[s][j + 1], q, g[s][j]);
-                    const float aq = a[s][j] * q;
-                    if constexpr (MP) {
-                        if (j == 0) put_elem_at(make_rsrc(p.qc_out + map * N * H, p.qc_out != nullptr ? (size_t)N * H * 4 : 0), (uint32_t)(n0 + s) * H + r0 + r,
-                                                l == 0 && act && r0 + r < H, aq, float{});
+                        for (int j = 0; j < K; j += 4) {
+                            const float4 v = *reinterpret_cast<const float4*>(aL + ((r * NW * K + s * K + j) / 4 * THREADS + tid) * 4);
+                            ar[j] = v.x; ar[j + 1] = v.y; ar[j + 2] = v.z; ar[j + 3] = v.w;
+                        }
                     }
-                    float left;                                    // hhor[i,j-1] (CF: h[i,j-1])
-                    if constexpr (RECOMP) left = j == 0 ? first : hh(j - 1);
-                    else left = hhl[r][s][j];
-                    float du = q;                                  // gradient of u
-                    if constexpr (CF) {
-                        du = q + ga[s][j];
-                        ga[s][j] = a[s][j] * du;
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {
+                        if constexpr (AREG) ar[j] = ak[r][s][j];
+                        else if (r >= ALR) ar[j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
+                        float hv;
+                        if constexpr (CF) {            // v[i,j], then h[i,j]
+                            hv = fmaf(ar[j], hprev[r][s][j], dxe[j] * get_elem<T, K>(bB[r % BR][s], j));
+                            hv = fmaf(ar[j], hhl[r][s][j], hv);
+                        } else {                       // h[i,j] is what the row below started from
+                            hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
+                        }
+                        dCacc[r][s][j] = fmaf(dyv[j], hv, dCacc[r][s][j]);
+                        const float Cv = get_elem<T, K>(Cr, j);
+                        if constexpr (CF) {
+                            g[d][s][j] = dyv[j] * Cv;
+                        } else {
+                            g[d][s][j] = fmaf(dyv[j], Cv, ga[s][j]);                                // scan 3
+                            ga[s][j] = ar[j] * g[d][s][j];
+                        }
+                        gr[d][s][j] = CF ? ar[j] * g[d][s][j] : ga[s][j];
                     }
-                    const float t = fmaf(aq, left, ga[s][j] * hprev[r][s][j]);   // gradient of the decay, times the decay
-                    dAb[s] = fmaf(t, dl[j], dAb[s]);
-                    s1[j] = s == 0 ? t * An[s] : fmaf(t, An[s], s1[j]);
-                    const float Bv = get_elem<T, K>(bB[r % BR][s], j);
-                    s2[j] = s == 0 ? du * Bv : fmaf(du, Bv, s2[j]);
-                    dBacc[r][s][j] = fmaf(du, dxe[j], dBacc[r][s][j]);
+                    // scan 4: q[j] = g[j] + a[j+1] * q[j+1], run on aq[j] = a[j] * q[j] = a[j] * g[j] + a[j] * aq[j+1]: a * g is
+                    // there, and the lane's decay product is the one of the rebuild
+                    const int k = d * NW + s;
+                    P[k] = Prow[r][s];
+                    Q[k] = MP ? fmaf(ar[K - 1], qcv[r][s], gr[d][s][K - 1]) : gr[d][s][K - 1];      // MP: a*q entering from the right panel (last lane)
+#pragma unroll
+                    for (int j = K - 2; j >= 0; --j) Q[k] = fmaf(ar[j], Q[k], gr[d][s][j]);
                 }
             }
-            Part::put(part + (size_t)(r * WAVES + wave) * Part::kRow, lane, s1, s2);
+            group_scan_left_any<LG, RS * NW>(P, Q, qin);
+#pragma unroll
+            for (int d = 0; d < RS; ++d) {
+                const int r = rt - d;
+                float dl[K], dxe[K], s1[K], s2[K];
+                lds_read_k<LG, K>(ppj + r * PP_ROW, l, dl);
+                lds_read_k<LG, K>(ppj + r * PP_ROW + PANEL, l, dxe);
+#pragma unroll
+                for (int s = 0; s < NW; ++s) {
+                    const float (&ar)[K] = a[d][s];
+                    float aq = qin[d * NW + s], first = 0.0f;      // first: hhor[i,j-1] of the lane's first column
+                    if constexpr (MP) aq += qcv[r][s];             // one of them is 0
+                    const auto hh = [&](int j) {                   // hhor[i,j]
+                        const float hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
+                        return fmaf(-ar[j], hprev[r][s][j], hv);
+                    };
+                    if constexpr (RECOMP) first = from_left_any<LG>(hh(K - 1));
+#pragma unroll
+                    for (int j = K - 1; j >= 0; --j) {
+                        const float q = g[d][s][j] + aq;
+                        aq = fmaf(ar[j], aq, gr[d][s][j]);
+                        if constexpr (MP) {
+                            if (j == 0) put_elem_at(make_rsrc(p.qc_out + map * N * H, p.qc_out != nullptr ? (size_t)N * H * 4 : 0), (uint32_t)(n0 + s) * H + r0 + r,
+                                                    l == 0 && act && r0 + r < H, aq, float{});
+                        }
+                        float left;                                // hhor[i,j-1] (CF: h[i,j-1])
+                        if constexpr (RECOMP) left = j == 0 ? first : hh(j - 1);
+                        else left = hhl[r][s][j];
+                        float du = q, gv = gr[d][s][j];            // gradient of u; gv: a * (what the column recurrence adds)
+                        if constexpr (CF) {
+                            du = q + ga[s][j];
+                            gv = ga[s][j] = ar[j] * du;
+                        }
+                        const float t = fmaf(aq, left, gv * hprev[r][s][j]);       // gradient of the decay, times the decay
+                        dAb[s] = fmaf(t, dl[j], dAb[s]);
+                        s1[j] = s == 0 ? t * An[s] : fmaf(t, An[s], s1[j]);
+                        const float Bv = get_elem<T, K>(bB[r % BR][s], j);
+                        s2[j] = s == 0 ? du * Bv : fmaf(du, Bv, s2[j]);
+                        dBacc[r][s][j] = fmaf(du, dxe[j], dBacc[r][s][j]);
+                    }
+                }
+                Part::put(part + (size_t)(r * WAVES + wave) * Part::kRow, lane, s1, s2);
+                if (r > 0) {                               // rows past H come first and add nothing to dA (0 * infinity would be NaN)
+#pragma unroll
+                    for (int s = 0; s < NW; ++s) dAb[s] = r < rows ? dAb[s] : 0.0f;
+                }
+            }
             __builtin_amdgcn_sched_barrier(0);
-            if (r > 0) {                                   // rows past H come first and add nothing to dA (0 * infinity would be NaN)
-#pragma unroll
-                for (int s = 0; s < NW; ++s) dAb[s] = r < rows ? dAb[s] : 0.0f;
-            }
         }
 #pragma unroll
         for (int s = 0; s < NW; ++s) {
