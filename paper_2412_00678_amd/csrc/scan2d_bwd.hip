@@ -24,8 +24,8 @@ struct SumArgs {
     // partials whose rows are LG*K floats in the lane order of the main sweep, [K/4][LG][4] (K = 0: plain rows): element q
     // of a row is column (q / 4 % LG) * K + (q / (4 * LG)) * 4 + q % 4
     int W, LG, K;
-    // sums over batch items (Bt > 1): [Bt][n] -> [n]
-    struct Batch { const float* src; float* dst; int n; } batch[4];
+    // sums over batch items, or batch items and row segments: [items][n] -> [n]
+    struct Batch { const float* src; float* dst; int n, items; } batch[4];
 };
 
 // S threads per element split the channel groups (thread s: groups s, s + S, ...), 8 loads of each tensor in flight, and
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(S == 1 ? 256 : 64 * S) void scan2d_bwd_sums_kernel(
             if (t.dst == nullptr) continue;
             if (e >= 0 && e < t.n) {
                 float acc = 0.0f;
-                for (int b = 0; b < p.Bt; ++b) acc += t.src[(size_t)b * t.n + e];
+                for (int b = 0; b < t.items; ++b) acc += t.src[(size_t)b * t.n + e];
                 t.dst[e] = acc;
             }
             e -= t.n;
@@ -176,6 +176,98 @@ __global__ __launch_bounds__(kChainThreads) void scan2d_bwd_chain_kernel(const f
     if (threadIdx.x == 0) pbias[map] = sh[0];
 }
 
+// Row segments of the main sweep: what the reverse column recurrence g (a*g, the value the row above adds to) holds at the
+// first row of every segment but the topmost one, gk[map][segment - 1][n][column].  The recurrence of a column needs no
+// other column, so a lane takes one column and all 16 states of a map (the sweep's tilings have no other number) and walks
+// up the rows; same operations in the same order as the sweep, so the segments change no bit of it.  The step and (gated)
+// dy * SiLU(z) are formed as in the sweep; kGcStep reads the step itself from the step kernel's buffer.
+// Bound: vector issue (9 instructions per position, channel and state) and, with few maps, the loads of one row, which are
+// requested two rows ahead (256 maps of 211x397 bf16: 125 us).
+enum { kGcPlain = 0, kGcSoftplus = 1, kGcGated = 2, kGcStep = 3 };
+struct GcarryArgs {
+    const void* delta; const float* delta_bias; const float* A; const void* Cm; const void* dy; const void* z;
+    float* gk;
+    int Dc, H, W, S, seg_rows;
+    unsigned waves, cols;                                  // wavefronts in all; 64-column pieces of a map
+};
+constexpr int kGcStates = 16;
+template <typename T, int FORM>
+__global__ __launch_bounds__(256) void scan2d_bwd_gcarry_kernel(const GcarryArgs p) {
+    using DT = std::conditional_t<FORM == kGcStep, float, T>;
+    const unsigned id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    if (id >= p.waves) return;
+    constexpr int N = kGcStates;
+    const unsigned cb = id % p.cols;
+    const size_t map = id / p.cols, b = map / p.Dc;
+    const int c = (int)(map - b * p.Dc), H = p.H, W = p.W;
+    const size_t HW = (size_t)H * W;
+    const int col = (int)cb * 64 + (int)(threadIdx.x & 63u);
+    const uint32_t lcol = (uint32_t)min(col, W - 1);
+    const T* dym = static_cast<const T*>(p.dy) + map * HW;
+    const DT* dm = static_cast<const DT*>(p.delta) + map * HW;
+    const T* zm = static_cast<const T*>(p.z) + (FORM == kGcGated ? map * HW : 0);
+    const T* Cb = static_cast<const T*>(p.Cm) + b * N * HW;
+    const float bias = (FORM == kGcSoftplus || FORM == kGcGated) && p.delta_bias != nullptr ? p.delta_bias[c] : 0.0f;
+    float Ap[N], ga[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        Ap[s] = p.A[(size_t)c * N + s] * kLog2e;
+        ga[s] = 0.0f;
+    }
+    auto widen = [](uint32_t bits, auto tag) -> float { return Elem<decltype(tag)>::kBytes == 4 ? __uint_as_float(bits) : __uint_as_float(bits << 16); };
+    uint32_t rdy[2], rd[2], rz[2], rC[2][N];
+    auto request = [&](int k, int i) {
+        const uint32_t o = (uint32_t)max(i, 0) * (uint32_t)W + lcol;
+        rdy[k] = elem_bits(dym + o);
+        rd[k] = elem_bits(dm + o);
+        if constexpr (FORM == kGcGated) rz[k] = elem_bits(zm + o);
+#pragma unroll
+        for (int s = 0; s < N; ++s) rC[k][s] = elem_bits(Cb + (size_t)s * HW + o);
+    };
+    const int first = p.seg_rows;                          // the topmost row that is needed
+    request(0, H - 1);
+    request(1, H - 2);
+    int to_store = (H - 1) % p.seg_rows;                   // rows until the next segment's first row
+    int seg = (H - 1) / p.seg_rows;
+    for (int i = H - 1; i >= first; i -= 2) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (i - k < first) break;
+            float step = widen(rd[k], DT{});
+            if constexpr (FORM == kGcSoftplus || FORM == kGcGated) step = softplus_f32(step + bias);
+            float dyv = widen(rdy[k], T{});
+            if constexpr (FORM == kGcGated) {
+                const float zv = widen(rz[k], T{});
+                dyv = dyv * (zv * logistic_f32(zv));
+            }
+#pragma unroll
+            for (int s = 0; s < N; ++s) {
+                const float a = __builtin_amdgcn_exp2f(step * Ap[s]);
+                ga[s] = a * fmaf(dyv, widen(rC[k][s], T{}), ga[s]);
+            }
+            request(k, i - k - 2);
+            if (to_store == 0) {
+                float* dst = p.gk + (map * (p.S - 1) + seg - 1) * N * W;
+                if (col < W) {
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        dst[(size_t)s * W + col] = ga[s];
+                }
+                to_store = p.seg_rows;
+                --seg;
+            }
+            --to_store;
+        }
+    }
+}
+using GcarryKernel = void (*)(const GcarryArgs);
+template <typename T>
+GcarryKernel gcarry_kernel(int form) {
+    return form == kGcGated ? scan2d_bwd_gcarry_kernel<T, kGcGated>
+         : form == kGcSoftplus ? scan2d_bwd_gcarry_kernel<T, kGcSoftplus>
+         : form == kGcStep ? scan2d_bwd_gcarry_kernel<T, kGcStep> : scan2d_bwd_gcarry_kernel<T, kGcPlain>;
+}
+
 // Padded copies of the rows behind which the input tensors end (layout: TailRows in scan2d_bwd_kernels.hpp):
 // the last row of the last map of x, delta and dy, of the last state plane of Bm and Cm, and of the last
 // batch item's mask, each followed by 16 zeros.  The instantiations for widths that are not a multiple of
@@ -204,6 +296,8 @@ struct BwdPlan {
     bool small = false;                                    // one to four wavefronts per map, no bands (scan2d_bwd_small.hpp)
     int LG = 0, K = 0, NW = 0, waves = 0, RB = 0;
     int NG = 0, GS = 0, CG = 0, nb = 0;
+    int S = 1, seg_bands = 0;                              // row segments of the main sweep (scan2d_bwd_shared.hpp only), bands of each
+    size_t off_gk = 0;                                     // what enters a segment from below (S > 1): [maps][S-1][N][W]
     BwdKernels k;
     size_t lds_bytes = 0;
     int panels = 1;                                        // column panels of LG*K columns, one launch of each sweep per panel
@@ -282,8 +376,8 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     // (faster than the 8- and 16-column tilings from 257 columns on; 256 maps, us: 300x300 fp32 3070 against 4709, 400x400
     // bf16 4315 against 6657, 512x512 bf16 5757 against 9535, 600x600 bf16 11180 against 26660)
     if (W > 256 || av) { LG = 64; K = 4; pl.panels = (W + 255) / 256; }
-    int force_waves = 0, force_gs = 0, want_shared = -1;
-    if (tb.n >= 1) {                                             // tuning aid: LG,K[,WAVES[,GS[,shared]]]
+    int force_waves = 0, force_gs = 0, force_seg = 0, want_shared = -1;
+    if (tb.n >= 1) {                                             // tuning aid: LG,K[,WAVES[,GS[,shared[,segments]]]]
         const int eLG = tb.v[0], eK = tb.v[1], eW = tb.v[2], eG = tb.v[3];
         const int got = tb.n;
         if (got >= 2 && (eLG == 16 || eLG == 32 || eLG == 64) && eLG * eK >= W && W <= 1024 && (N <= 16 || W <= 256)) {
@@ -292,6 +386,7 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
         if (got >= 3) force_waves = eW;
         if (got >= 4) force_gs = eG;
         if (got >= 5) want_shared = tb.v[4];
+        if (got >= 6) force_seg = tb.v[5];
     }
     // states per lane and waves per workgroup: 16 lane groups of one DPP row with one state each;
     // wavefront-wide lane groups: 16 of them with one state each for 4 columns per lane (four waves
@@ -340,63 +435,99 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     pl.LG = LG; pl.K = K; pl.NW = NW; pl.waves = waves; pl.RB = pl.k.RB;
     pl.NG = (N + NW - 1) / NW;
     pl.nb = (d->H + pl.RB - 1) / pl.RB;
-    // channels a workgroup handles one after the other: bounded by the 160 KB of LDS; among the
-    // feasible counts take the one with the shortest critical path (rounds of resident workgroups
-    // - the runtime's occupancy figure for the kernel's registers and this much LDS, one per CU
-    // if it cannot be asked - times channels per workgroup), the larger count on a tie (fewer
-    // partial sums to write and add up)
+    // Channels a workgroup handles one after the other (bounded by the 160 KB of LDS) and row segments per map, by an
+    // estimate of the whole call in us:
+    //   * rounds of resident workgroups (the runtime's occupancy figure for the kernel's registers and this much LDS, one per
+    //     CU if it cannot be asked) times (band, channel) steps of a workgroup;
+    //   * the dBm / dCm partials, one per channel group, written here and read by the reduction;
+    //   * with segments, the pass in front of the sweep that forms what enters each from below.
+    // More channels mean fewer partials, more segments keep the chip busy all the same: one slide of 256 channels of 211x397
+    // bf16 has 256 maps, one for each CU, and without segments a partial per channel (us, one segment and now: the two panels'
+    // sweeps 1648 and 1041, the partials' sum 526 and 93, the pass in front 125; the whole training step 2931 and 1975).
+    // More than 8 channels: 6144 maps of 56x56 bf16 take 12 instead of 6, partials' sum 104 -> 42 us.
     const size_t T = (size_t)waves * 64;
     size_t fixed = 4 * T * K, per = T * ((size_t)NW * K + NW + 1);
     if (pl.shared) { fixed = pl.k.lds_fixed; per = pl.k.lds_per_channel; }
     const int gs_lds = (int)std::max<size_t>(1, (40960 - std::min<size_t>(fixed, 40960)) / per);
     const int JPW = slots / pl.NG;
-    const int gs_max = av ? 1 : std::min({gs_lds, 8, d->Dc});   // av: one channel per workgroup (its dA_v partial stays in registers)
-    int gs = 1;
-    long long best_path = -1;
+    const int gs_max = av ? 1 : std::min({gs_lds, 16, d->Dc});   // av: one channel per workgroup (its dA_v partial stays in registers)
+    const size_t maps = (size_t)d->Bt * d->Dc;
+    const bool tight = (size_t)LG * K * 15 <= (size_t)W * 16;
+    auto layout = [&](BwdPlan& q) {
+        size_t o = 0;
+        // the shared-producer forward kernel writes the checkpoints and the shared-producer main sweep reads them with the same
+        // lane tiling: rows of LG*K floats in lane order, so that both move whole 16-byte x LG pieces per instruction
+        // (only where the padding of the rows to LG*K columns costs less than 7 %)
+        q.ck_chunked = tight && q.shared && q.panels == 1 && q.k.ckpt_fwd != nullptr && N == q.k.cf_NG * q.k.cf_NW && q.k.cf_LG == LG &&
+                       q.k.cf_K == K && K % 4 == 0;
+        q.off_ck = o; o += align_up(maps * q.nb * N * (q.ck_chunked ? (size_t)LG * K : (size_t)W) * sizeof(float));
+        q.part_chunked = tight && q.shared && q.panels == 1 && q.CG > 1 && K % 4 == 0;
+        const size_t part_row = q.part_chunked ? (size_t)LG * K : (size_t)W;
+        const bool items = d->Bt * (long long)q.S > 1;         // dA, dDskip and the bias gradient: a row per (batch item, segment)
+        q.off_pB = o; o += q.CG > 1 ? align_up((size_t)d->Bt * q.CG * N * d->H * part_row * sizeof(float)) : 0;
+        q.off_pC = o; o += q.CG > 1 ? align_up((size_t)d->Bt * q.CG * N * d->H * part_row * sizeof(float)) : 0;
+        q.off_pA = o; o += items ? align_up(maps * q.S * N * sizeof(float)) : 0;
+        q.off_pD = o; o += items ? align_up(maps * q.S * sizeof(float)) : 0;
+        q.off_pb = o; o += align_up(maps * q.S * sizeof(float));
+        q.off_step = o; o += q.step_outside ? align_up(maps * (size_t)d->H * W * sizeof(float)) + 256 : 0;
+        q.off_tail = o; o += align_up((size_t)(W + 16) * (5 * (d->dtype == SCAN2D_BF16 ? 2 : 4) + 1));
+        if (av) { q.off_pAv = o; o += d->Bt > 1 ? align_up(maps * N * sizeof(float)) : 0; }
+        if (q.panels > 1) {
+            const size_t one = align_up(maps * N * (size_t)d->H * sizeof(float));
+            q.off_hc = o; o += (size_t)(q.panels - 1) * one;
+            q.off_qc = o; o += 2 * one;
+        }
+        q.off_gk = o; o += q.S > 1 ? align_up(maps * (q.S - 1) * N * W * sizeof(float)) : 0;
+        q.total = o;
+    };
+    auto set = [&](int gs, int segments) {
+        BwdPlan q = pl;
+        q.GS = gs;
+        q.CG = (d->Dc + gs - 1) / gs;
+        q.seg_bands = (q.nb + segments - 1) / segments;
+        q.S = (q.nb + q.seg_bands - 1) / q.seg_bands;
+        q.lds_bytes = (fixed + (size_t)gs * per) * sizeof(float);
+        layout(q);
+        return q;
+    };
+    const double units = (double)pl.RB * K * NW, cells = (double)d->N * d->H * W;      // of a step per lane; of a map
+    double best_us = -1.0;
+    size_t plain_total = 0;                                    // smallest workspace without segments
+    BwdPlan best;
     for (int g = 1; g <= gs_max; ++g) {
-        const long long jobs = (long long)d->Bt * ((d->Dc + g - 1) / g);
-        const long long wgs = (jobs + JPW - 1) / JPW;
         int per_cu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(pl.k.main), (int)T,
                                                          (fixed + (size_t)g * per) * sizeof(float)) != hipSuccess || per_cu < 1) {
             (void)hipGetLastError();
             per_cu = 1;
         }
-        const long long resident = 256LL * per_cu;
-        const long long path = ((wgs + resident - 1) / resident) * g;
-        if (best_path < 0 || path <= best_path) { best_path = path; gs = g; }
+        // (the pass in front counts its wavefronts in 32 bits)
+        const bool segs = pl.shared && !cf && N == kGcStates && (double)maps * ((W + 63) / 64) < 1073741824.0;
+        const int most = segs && pl.nb >= 4 ? std::min(16, pl.nb / 2) : 1;
+        int last = 0;
+        for (int segments = 1; segments <= std::max(1, most); ++segments) {
+            const BwdPlan q = set(g, segments);
+            if (q.S == last) continue;
+            last = q.S;
+            if (q.S == 1) plain_total = plain_total == 0 ? q.total : std::min(plain_total, q.total);
+            // what fits the scratch array of scan2d_bwd_static_scratch without segments has to fit it with them
+            else if (q.total > SCAN2D_STATIC_SCRATCH_BYTES && plain_total <= SCAN2D_STATIC_SCRATCH_BYTES) continue;
+            const double wgs = std::ceil((double)d->Bt * q.CG * q.S / JPW);
+            const double resident = 256.0 * per_cu, rounds = std::ceil(wgs / resident);
+            const double wps = std::min((double)per_cu, std::ceil(wgs / 256.0)) * waves / 4.0;
+            double us = rounds * g * q.seg_bands * pl.panels * units * 0.12 * (0.5 + 0.5 * std::max(1.0, wps));
+            if (q.CG > 1) us += 2.0 * d->Bt * q.CG * cells * 4.0 * (1.0 / 4.0e6 + 1.0 / 5.0e6);
+            if (q.S > 1) {
+                const double up = 1.0 - 1.0 / q.S;
+                us += 6.0 + std::max((double)maps * cells * up / 2.2e6, d->H * up * 0.3);
+            }
+            if (best_us < 0.0 || us < best_us * (1.0 - 1e-9) || (us <= best_us * (1.0 + 1e-9) && q.S == best.S)) { best_us = us; best = q; }
+        }
     }
-    if (force_gs >= 1 && force_gs <= gs_lds && force_gs <= d->Dc) gs = force_gs;
-    pl.GS = gs;
-    pl.CG = (d->Dc + gs - 1) / gs;
-    pl.lds_bytes = (fixed + (size_t)gs * per) * sizeof(float);
-    if (pl.lds_bytes > 160 * 1024) return false;
-    const size_t maps = (size_t)d->Bt * d->Dc;
-    size_t o = 0;
-    // the shared-producer forward kernel writes the checkpoints and the shared-producer main sweep reads them with the same
-    // lane tiling: rows of LG*K floats in lane order, so that both move whole 16-byte x LG pieces per instruction
-    // (only where the padding of the rows to LG*K columns costs less than 7 %)
-    const bool tight = (size_t)LG * K * 15 <= (size_t)W * 16;
-    pl.ck_chunked = tight && pl.shared && pl.panels == 1 && pl.k.ckpt_fwd != nullptr && N == pl.k.cf_NG * pl.k.cf_NW && pl.k.cf_LG == LG &&
-                    pl.k.cf_K == K && K % 4 == 0;
-    pl.off_ck = o; o += align_up(maps * pl.nb * N * (pl.ck_chunked ? (size_t)LG * K : (size_t)W) * sizeof(float));
-    pl.part_chunked = tight && pl.shared && pl.panels == 1 && pl.CG > 1 && K % 4 == 0;
-    const size_t part_row = pl.part_chunked ? (size_t)LG * K : (size_t)W;
-    pl.off_pB = o; o += pl.CG > 1 ? align_up((size_t)d->Bt * pl.CG * N * d->H * part_row * sizeof(float)) : 0;
-    pl.off_pC = o; o += pl.CG > 1 ? align_up((size_t)d->Bt * pl.CG * N * d->H * part_row * sizeof(float)) : 0;
-    pl.off_pA = o; o += d->Bt > 1 ? align_up(maps * N * sizeof(float)) : 0;
-    pl.off_pD = o; o += d->Bt > 1 ? align_up(maps * sizeof(float)) : 0;
-    pl.off_pb = o; o += align_up(maps * sizeof(float));
-    pl.off_step = o; o += pl.step_outside ? align_up(maps * (size_t)d->H * W * sizeof(float)) + 256 : 0;
-    pl.off_tail = o; o += align_up((size_t)(W + 16) * (5 * (d->dtype == SCAN2D_BF16 ? 2 : 4) + 1));
-    if (av) { pl.off_pAv = o; o += d->Bt > 1 ? align_up(maps * N * sizeof(float)) : 0; }
-    if (pl.panels > 1) {
-        const size_t one = align_up(maps * N * (size_t)d->H * sizeof(float));
-        pl.off_hc = o; o += (size_t)(pl.panels - 1) * one;
-        pl.off_qc = o; o += 2 * one;
-    }
-    pl.total = o;
-    *out = pl;
+    if (force_gs >= 1 && force_gs <= gs_lds && force_gs <= d->Dc) best = set(force_gs, 1);
+    if (force_seg >= 1 && pl.shared && !cf && N == kGcStates && maps < 1000000) best = set(best.GS, std::min(force_seg, best.nb));
+    if (best.lds_bytes > 160 * 1024) return false;
+    *out = best;
     return true;
 }
 
@@ -424,7 +555,7 @@ int bwd_check(const scan2d_desc* d, bool softplus, bool av) {
     const int MPW = (pl.waves * 64 / pl.LG) / pl.NG;
     const int ck_NG = (d->N + pl.k.ckpt_NW - 1) / pl.k.ckpt_NW;
     const int MPW1 = (pl.ck_waves * 64 / pl.ck_LG) / ck_NG;
-    const long long wg1 = (maps + MPW1 - 1) / MPW1, wg2 = ((long long)d->Bt * pl.CG + MPW - 1) / MPW;
+    const long long wg1 = (maps + MPW1 - 1) / MPW1, wg2 = ((long long)d->Bt * pl.CG * pl.S + MPW - 1) / MPW;
     if (wg1 > 2147483647LL || wg2 > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
     const long long chunks = ((long long)d->H * d->W + 1023) / 1024;
     if (pl.step_outside && chunks * maps > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
@@ -476,12 +607,12 @@ bool bwd_describe(const scan2d_desc* d, char* text, size_t text_bytes) {
     if (pl.small) wgs = small_wgs(d, pl);
     else {
         const int per_wg = (pl.waves * 64 / pl.LG) / pl.NG;
-        wgs = ((long long)d->Bt * pl.CG + per_wg - 1) / per_wg;
+        wgs = ((long long)d->Bt * pl.CG * pl.S + per_wg - 1) / per_wg;
     }
-    std::snprintf(text, text_bytes, "%sbwd form=%s LG=%d K=%d NW=%d waves=%d RB=%d GS=%d CG=%d bands=%d panels=%d wgs=%lld lds=%zu workspace=%zu",
+    std::snprintf(text, text_bytes, "%sbwd form=%s LG=%d K=%d NW=%d waves=%d RB=%d GS=%d CG=%d bands=%d panels=%d segments=%d wgs=%lld lds=%zu workspace=%zu",
                   (d->flags & SCAN2D_FLAG_COLUMNS_FIRST) != 0 ? "columns-first(in-kernel) " : "",
                   pl.small ? "small" : (pl.shared ? "banded-shared" : "banded"), pl.LG, pl.K, pl.NW, pl.waves, pl.RB, pl.GS, pl.CG, pl.nb,
-                  pl.panels, wgs, pl.lds_bytes, pl.total);
+                  pl.panels, pl.S, wgs, pl.lds_bytes, pl.total);
     return true;
 }
 
@@ -507,14 +638,15 @@ void launch_sums(const scan2d_desc* d, const BwdPlan& pl, const BwdArgs& a, floa
     const unsigned E = S == 1 ? 256 : 64, threads = S == 1 ? 256 : 64 * S;
     s.groups_wgs = pl.CG > 1 ? (unsigned)std::min<size_t>((total + E - 1) / E, 16384) : 0;
     size_t n = 0;
-    for (auto& t : s.batch) t = {nullptr, nullptr, 0};
-    if (d->Bt > 1) {
-        s.batch[0] = {a.pA, dA, d->Dc * d->N};
-        if (dDskip != nullptr) s.batch[1] = {a.pD, dDskip, d->Dc};
-        if (dbias != nullptr) s.batch[2] = {pbias, dbias, d->Dc};
-        if (dA_v != nullptr) s.batch[3] = {a.pAv, dA_v, d->Dc * d->N};
-        for (const auto& t : s.batch) n += (size_t)t.n;
+    for (auto& t : s.batch) t = {nullptr, nullptr, 0, 0};
+    const int items = d->Bt * pl.S, bias_items = pl.step_outside ? d->Bt : items;      // (the chain kernel sums whole maps)
+    if (items > 1) {
+        s.batch[0] = {a.pA, dA, d->Dc * d->N, items};
+        if (dDskip != nullptr) s.batch[1] = {a.pD, dDskip, d->Dc, items};
     }
+    if (bias_items > 1 && dbias != nullptr) s.batch[2] = {pbias, dbias, d->Dc, bias_items};
+    if (d->Bt > 1 && dA_v != nullptr) s.batch[3] = {a.pAv, dA_v, d->Dc * d->N, d->Bt};
+    for (const auto& t : s.batch) n += (size_t)t.n;
     const unsigned wgs = s.groups_wgs + (unsigned)((n + threads - 1) / threads);
     if (wgs == 0) return;
     if (S == 1) hipLaunchKernelGGL(scan2d_bwd_sums_kernel<1>, dim3(wgs), dim3(threads), 0, stream, s);
@@ -547,16 +679,19 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     a.ck = saved != nullptr ? const_cast<float*>(saved) : reinterpret_cast<float*>(ws + pl.off_ck);
     a.pB = pl.CG > 1 ? reinterpret_cast<float*>(ws + pl.off_pB) : dBm;   // one group: the partial is the result
     a.pC = pl.CG > 1 ? reinterpret_cast<float*>(ws + pl.off_pC) : dCm;
-    a.pA = d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pA) : dA;
-    a.pD = dDskip == nullptr ? nullptr : (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pD) : dDskip);
+    const bool items = d->Bt * (long long)pl.S > 1;
+    a.pA = items ? reinterpret_cast<float*>(ws + pl.off_pA) : dA;
+    a.pD = dDskip == nullptr ? nullptr : (items ? reinterpret_cast<float*>(ws + pl.off_pD) : dDskip);
     a.Bt = d->Bt; a.Dc = d->Dc; a.H = d->H; a.W = d->W; a.N = d->N;
     a.NG = pl.NG; a.GS = pl.GS; a.CG = pl.CG; a.nb = pl.nb;
+    a.S = pl.S; a.seg_bands = pl.seg_bands;
+    if (pl.S > 1) a.gk = reinterpret_cast<const float*>(ws + pl.off_gk);
     a.A_v = A_v;
     a.ck_chunked = pl.ck_chunked ? 1 : 0;
     a.part_chunked = pl.part_chunked ? 1 : 0;
     a.pAv = A_v == nullptr ? nullptr : (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pAv) : dA_v);
     // the sweeps that apply the softplus themselves also add up ddelta_raw per map
-    float* const pbias = softplus && ddelta_bias != nullptr ? (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pb) : ddelta_bias) : nullptr;
+    float* const pbias = softplus && ddelta_bias != nullptr ? ((pl.step_outside ? d->Bt > 1 : items) ? reinterpret_cast<float*>(ws + pl.off_pb) : ddelta_bias) : nullptr;
     if (!pl.step_outside) a.pBias = pbias;
 
     const long long maps = (long long)d->Bt * d->Dc;
@@ -573,7 +708,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     ac.NG = (d->N + pl.k.ckpt_NW - 1) / pl.k.ckpt_NW;
     const int MPW1 = (pl.ck_waves * 64 / pl.ck_LG) / ac.NG;
     const long long wg1 = (maps + MPW1 - 1) / MPW1;
-    const long long jobs = (long long)d->Bt * pl.CG;
+    const long long jobs = (long long)d->Bt * pl.CG * pl.S;
     const long long wg2 = (jobs + MPW - 1) / MPW;
     if (wg1 > 2147483647LL || wg2 > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
     (void)hipGetLastError();
@@ -601,6 +736,17 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
         else
             hipLaunchKernelGGL(scan2d_bwd_step_kernel<float>, dim3((unsigned)(chunks * maps)), dim3(256), 0, stream,
                                static_cast<const float*>(delta), delta_bias, step, HW, d->Dc, chunks);
+    }
+    if (pl.S > 1) {
+        GcarryArgs g;
+        g.delta = a.delta; g.delta_bias = delta_bias; g.A = A; g.Cm = Cm; g.dy = dy; g.z = z;
+        g.gk = reinterpret_cast<float*>(ws + pl.off_gk);
+        g.Dc = d->Dc; g.H = d->H; g.W = d->W; g.S = pl.S; g.seg_rows = pl.seg_bands * pl.RB;
+        g.cols = (unsigned)((d->W + 63) / 64);
+        g.waves = (unsigned)((unsigned long long)maps * g.cols);           // rank_plan: fits
+        const int form = pl.step_outside ? kGcStep : (z != nullptr ? kGcGated : (softplus ? kGcSoftplus : kGcPlain));
+        hipLaunchKernelGGL(d->dtype == SCAN2D_BF16 ? gcarry_kernel<bf16_t>(form) : gcarry_kernel<float>(form), dim3((g.waves + 3) / 4), dim3(256),
+                           0, stream, g);
     }
     if (pl.lds_bytes > 65536 && !allow_large_lds(reinterpret_cast<const void*>(pl.k.main), pl.lds_bytes)) return SCAN2D_ERR_LAUNCH_FAILED;
     // the checkpoint sweep by the shared-producer forward kernel (checkpoint mode): it computes the softplus step itself from

@@ -281,10 +281,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
     const int job_slot = wave / WPJ;
     const int sg = slot - job_slot * NG;
     const int tm = tid - job_slot * TMJ;                  // thread index inside the job
-    const long long groups = (long long)p.Bt * p.CG;
+    const long long groups = (long long)p.Bt * p.CG * p.S;
     const long long job = (long long)blockIdx.x * JPW + job_slot;
     const bool live = job < groups;
-    const int b = live ? (int)(job / p.CG) : 0, cg = live ? (int)(job % p.CG) : 0;
+    const int seg = live ? (int)(job % p.S) : 0;          // row segment: bands [band0, band0 + seg_bands), the last one's may lie past H
+    const int b = live ? (int)(job / p.S / p.CG) : 0, cg = live ? (int)(job / p.S % p.CG) : 0;
+    const int band0 = seg * p.seg_bands;
     const int c_first = cg * GS;
     const int nch = live ? min(GS, p.Dc - c_first) : 0;
 
@@ -313,8 +315,13 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
     const float* const partj = part + (size_t)job_slot * WPJ * Part::kRow;
 
     for (int ch = 0; ch < GS; ++ch) {
+        const bool below = seg + 1 < p.S && ch < nch;      // g below the map is 0
+        const float* gk = p.gk + (((size_t)b * p.Dc + c_first + ch) * (p.S - 1) + seg) * N * W;
 #pragma unroll
-        for (int e = 0; e < NW * K; ++e) gaL[((size_t)ch * THREADS + tid) * (NW * K) + e] = 0.0f;   // g below the map is 0
+        for (int s = 0; s < NW; ++s)
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j] = below && j < nv ? gk[(size_t)(n0 + s) * W + col0 + j] : 0.0f;
         if (l == LG - 1) {
 #pragma unroll
             for (int s = 0; s < NW; ++s) dAL[((size_t)ch * SLOTS + slot) * NW + s] = 0.0f;
@@ -700,10 +707,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
                     }
                 }
                 Part::put(part + (size_t)(r * WAVES + wave) * Part::kRow, lane, s1, s2);
-                if (r > 0) {                               // rows past H come first and add nothing to dA (0 * infinity would be NaN)
+                // rows past H come first and add nothing to dA (0 * infinity would be NaN)
 #pragma unroll
-                    for (int s = 0; s < NW; ++s) dAb[s] = r < rows ? dAb[s] : 0.0f;
-                }
+                for (int s = 0; s < NW; ++s) dAb[s] = r < rows ? dAb[s] : 0.0f;
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -743,10 +749,11 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         }
     };
 
-    request(p.nb - 1, 0);
-    load_band(p.nb - 1);
-    for (int band = p.nb - 1; band >= 0; --band) {
-        store_band(band + 1);                              // of the band below (first: rows past H, nothing is stored)
+    request(band0 + p.seg_bands - 1, 0);
+    load_band(band0 + p.seg_bands - 1);
+    for (int k = p.seg_bands - 1; k >= 0; --k) {
+        const int band = band0 + k;
+        store_band(k + 1 < p.seg_bands ? band + 1 : p.nb); // of the band below (first: rows past H, nothing is stored)
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
@@ -759,7 +766,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         for (int ch = 1; ch < GS; ++ch) sweep(band, ch);
         load_band(max(band - 1, 0));
     }
-    store_band(0);
+    store_band(band0);
 
     // dA[b,c,n]: already summed over the lane group; dDskip[b,c] and the bias gradient: the sums over the job's wavefronts,
     // in index order
@@ -769,7 +776,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
 #pragma unroll
             for (int s = 0; s < NW; ++s)
             {
-                float* dst = p.pA + ((size_t)b * p.Dc + c_first + ch) * N + n0 + s;
+                float* dst = p.pA + (((size_t)b * p.S + seg) * p.Dc + c_first + ch) * N + n0 + s;
                 const float v = dAL[((size_t)ch * SLOTS + slot) * NW + s];
                 *dst = (MP && p.accum) ? *dst + v : v;             // panels are launched one after the other
             }
@@ -781,7 +788,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             for (int ch = 0; ch < nch; ++ch) {
                 float acc = 0.0f;
                 for (int w = 0; w < WPJ; ++w) acc += dDL[(ch * WAVES + job_slot * WPJ + w) * 2 + tm];
-                float* dst = base + (size_t)b * p.Dc + c_first + ch;
+                float* dst = base + ((size_t)b * p.S + seg) * p.Dc + c_first + ch;
                 *dst = (MP && p.accum) ? *dst + acc : acc;
             }
         }

@@ -4,7 +4,7 @@
 //   SCAN2D_FWD_VARIANT = LG,K,NW,WAVES[,RPB]     force a variant of the plain forward kernel
 //   SCAN2D_FWD_SHARED  = LG,K,NW,WAVES,RPB[,SKEW] force a variant of the shared-producer forward kernel (SKEW = 1: its
 //                        skewed-row tilings; "0" alone = never use that form)
-//   SCAN2D_BWD_VARIANT = LG,K[,WAVES[,GS]]       force a variant of the banded backward
+//   SCAN2D_BWD_VARIANT = LG,K[,WAVES[,GS[,SHARED[,SEGMENTS]]]]  force a variant of the banded backward
 #pragma once
 
 #include <atomic>

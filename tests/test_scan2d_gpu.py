@@ -1299,3 +1299,45 @@ def test_backward_of_small_maps_with_several_channels_per_workgroup(s2d, Bt, Dc,
         test_backward_with_softplus_step_matches_oracle(s2d, (Bt, Dc, N, H, W, dtype, 0.3), True)
     else:
         test_gated_backward_matches_oracle(s2d, (Bt, Dc, N, H, W, dtype, 0.3))
+
+
+# Row segments of the banded backward: a segment starts its reverse column recurrence from what a pass in front of the sweep
+# has formed with the sweep's own operations, so at the same channels per workgroup everything but the sums over a whole map
+# (dA, dDskip, the bias gradient: another order) is bit for bit what one segment per map gives.
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("form", ["plain", "softplus", "gated"])
+@pytest.mark.parametrize("variant,segments,shape", [
+    ("16,4,4,2,1", 2, (1, 5, 16, 57)), ("16,4,4,3,1", 5, (2, 7, 18, 64)), ("16,8,4,1,1", 3, (1, 3, 41, 121)), ("16,12,4,2,1", 4, (2, 3, 30, 190)),
+    ("64,4,8,2,1", 3, (1, 3, 11, 255)), ("64,4,8,2,-1", 4, (2, 3, 23, 397)), ("64,4,8,1,-1", 2, (1, 2, 9, 777))],
+    ids=lambda v: v if isinstance(v, str) else ("x".join(map(str, v)) if isinstance(v, tuple) else f"{v}seg"))
+def test_backward_row_segments(s2d, variant, segments, shape, form, dtype):
+    import torch
+    Bt, Dc, H, W = shape
+    d = s2d.to_device(wl.make_inputs(wl.Workload("bseg", Bt, Dc, 16, H, W, dtype, mask_frac=0.3, backward=True), seed=21), dtype)
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    z = torch.randn(d["x"].shape, device="cuda:0", generator=g).to(d["x"].dtype)
+    bias = torch.randn(Dc, device="cuda:0", generator=g) * 0.1
+
+    def grads(seg):
+        with s2d.forced_variant(s2d.TUNE_BWD, f"{variant},{seg}"):
+            plan = s2d.describe_plan(s2d.Desc(Bt, Dc, H, W, 16, dtype, 0), s2d.PASS_BWD)
+            assert f"segments={seg} " in plan, plan
+            a = (d["A"], d["Bm"], d["Cm"], d["Dskip"], d["mask"])
+            if form == "plain":
+                names, out = ("dx", "ddelta", "dA", "dBm", "dCm", "dDskip"), s2d.scan2d_bwd(d["x"], d["delta"], *a, d["dy"])
+            elif form == "softplus":
+                names, out = ("dx", "ddelta", "dbias", "dA", "dBm", "dCm", "dDskip"), s2d.scan2d_bwd_softplus(d["x"], d["delta"], bias, *a, d["dy"])
+            else:
+                names = ("dx", "ddelta", "dbias", "dA", "dBm", "dCm", "dDskip", "dz")
+                out = s2d.scan2d_bwd_softplus_gated(d["x"], d["delta"], bias, *a, z, d["x"], d["dy"])
+        torch.cuda.synchronize()
+        return dict(zip(names, out))
+
+    one, many = grads(1), grads(segments)
+    for k, v in one.items():
+        if k in ("dA", "dDskip", "dbias"):
+            # fp32 sums of up to H * W terms in two orders: a few units in the last place of the sum of magnitudes, which
+            # for these inputs is within 100 times the largest entry
+            assert (many[k] - v).abs().max() <= 100 * 2.0 ** -23 * v.abs().max(), k
+        else:
+            assert torch.equal(many[k], v), k
