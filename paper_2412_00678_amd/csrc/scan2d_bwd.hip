@@ -180,10 +180,10 @@ __global__ __launch_bounds__(kChainThreads) void scan2d_bwd_chain_kernel(const f
 // first row of every segment but the topmost one, gk[map][segment - 1][n][column].  The recurrence of a column needs no
 // other column, so a lane takes one column and all 16 states of a map (the sweep's tilings have no other number) and walks
 // up the rows; same operations in the same order as the sweep, so the segments change no bit of it.  The step and (gated)
-// dy * SiLU(z) are formed as in the sweep; kGcStep reads the step itself from the step kernel's buffer.
+// dy * SiLU(z) are formed as in the sweep.
 // Bound: vector issue (9 instructions per position, channel and state) and, with few maps, the loads of one row, which are
 // requested two rows ahead (256 maps of 211x397 bf16: 125 us).
-enum { kGcPlain = 0, kGcSoftplus = 1, kGcGated = 2, kGcStep = 3 };
+enum { kGcPlain = 0, kGcSoftplus = 1, kGcGated = 2 };
 struct GcarryArgs {
     const void* delta; const float* delta_bias; const float* A; const void* Cm; const void* dy; const void* z;
     float* gk;
@@ -193,7 +193,6 @@ struct GcarryArgs {
 constexpr int kGcStates = 16;
 template <typename T, int FORM>
 __global__ __launch_bounds__(256) void scan2d_bwd_gcarry_kernel(const GcarryArgs p) {
-    using DT = std::conditional_t<FORM == kGcStep, float, T>;
     const unsigned id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     if (id >= p.waves) return;
     constexpr int N = kGcStates;
@@ -204,10 +203,10 @@ __global__ __launch_bounds__(256) void scan2d_bwd_gcarry_kernel(const GcarryArgs
     const int col = (int)cb * 64 + (int)(threadIdx.x & 63u);
     const uint32_t lcol = (uint32_t)min(col, W - 1);
     const T* dym = static_cast<const T*>(p.dy) + map * HW;
-    const DT* dm = static_cast<const DT*>(p.delta) + map * HW;
+    const T* dm = static_cast<const T*>(p.delta) + map * HW;
     const T* zm = static_cast<const T*>(p.z) + (FORM == kGcGated ? map * HW : 0);
     const T* Cb = static_cast<const T*>(p.Cm) + b * N * HW;
-    const float bias = (FORM == kGcSoftplus || FORM == kGcGated) && p.delta_bias != nullptr ? p.delta_bias[c] : 0.0f;
+    const float bias = FORM != kGcPlain && p.delta_bias != nullptr ? p.delta_bias[c] : 0.0f;
     float Ap[N], ga[N];
 #pragma unroll
     for (int s = 0; s < N; ++s) {
@@ -233,8 +232,8 @@ __global__ __launch_bounds__(256) void scan2d_bwd_gcarry_kernel(const GcarryArgs
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             if (i - k < first) break;
-            float step = widen(rd[k], DT{});
-            if constexpr (FORM == kGcSoftplus || FORM == kGcGated) step = softplus_f32(step + bias);
+            float step = widen(rd[k], T{});
+            if constexpr (FORM != kGcPlain) step = softplus_f32(step + bias);
             float dyv = widen(rdy[k], T{});
             if constexpr (FORM == kGcGated) {
                 const float zv = widen(rz[k], T{});
@@ -264,8 +263,7 @@ using GcarryKernel = void (*)(const GcarryArgs);
 template <typename T>
 GcarryKernel gcarry_kernel(int form) {
     return form == kGcGated ? scan2d_bwd_gcarry_kernel<T, kGcGated>
-         : form == kGcSoftplus ? scan2d_bwd_gcarry_kernel<T, kGcSoftplus>
-         : form == kGcStep ? scan2d_bwd_gcarry_kernel<T, kGcStep> : scan2d_bwd_gcarry_kernel<T, kGcPlain>;
+         : form == kGcSoftplus ? scan2d_bwd_gcarry_kernel<T, kGcSoftplus> : scan2d_bwd_gcarry_kernel<T, kGcPlain>;
 }
 
 // Padded copies of the rows behind which the input tensors end (layout: TailRows in scan2d_bwd_kernels.hpp):
@@ -304,8 +302,9 @@ struct BwdPlan {
     size_t off_hc = 0, off_qc = 0;                         // carries between panels: [panels-1][maps][N][H] and [2][maps][N][H]
     bool shared = false;                                   // main sweep of scan2d_bwd_shared.hpp
     int ck_LG = 0, ck_waves = 0;                           // lane tiling of the checkpoint sweep
-    bool step_outside = false;                             // softplus step written by a kernel of its own (banded form)
-    size_t off_step = 0;                                   // the step [maps][H][W] fp32 (step_outside only), 256 spare bytes behind it
+    bool step_outside = false;                             // softplus step written by a kernel of its own (plain main sweep)
+    bool step_for_ckpt = false;                            // the same for the checkpoint sweep alone (more than two column panels)
+    size_t off_step = 0;                                   // the step [maps][H][W] fp32 (either of them), 256 spare bytes behind it
     bool fast = true;                                      // W is a multiple of the columns per lane
     size_t off_tail = 0;                                   // padded copies of the tensors' last rows (TailRows)
     size_t off_ck = 0, off_pB = 0, off_pC = 0, off_pA = 0, off_pD = 0, off_pb = 0, total = 0;   // pb: bias-gradient partials
@@ -405,7 +404,6 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     const int slots = waves * 64 / LG;
     if ((N + NW - 1) / NW > slots) return false;
     const bool fast = (W % K) == 0;                          // otherwise: the instantiations that treat the row end
-    pl.step_outside = sp;
     pl.fast = fast;
     // the main sweep that shares the per-position work through LDS, where it exists for this tiling (N = NG * NW)
     // (its kernels take column panels too; their 32-bit offsets span one item's state planes)
@@ -415,7 +413,7 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
                                              : bwd_shared_kernels_f32_cf(LG, K, NW, N / NW, waves, W, sp);
         else ks = d->dtype == SCAN2D_BF16 ? bwd_shared_kernels_bf16(LG, K, NW, N / NW, waves, W, sp)
                                           : bwd_shared_kernels_f32(LG, K, NW, N / NW, waves, W, sp);
-        if (pl.panels > 1) ks.main = ks.main_panels;              // column panels: the instantiation that takes them, if any
+        if (pl.panels > 1) { ks.main = ks.main_panels; ks.main_gate = ks.main_panels_gate; }      // column panels: the instantiations that take them, if any
         if (ks.main != nullptr && (want_shared == 1 || shared_by_default(LG, K, NW))) pl.k = ks;
     }
     if (cf && pl.k.main == nullptr) return false;
@@ -427,9 +425,10 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
         pl.k = d->dtype == SCAN2D_BF16 ? bwd_kernels_bf16(LG, K, NW, waves, fast, sp) : bwd_kernels_f32(LG, K, NW, waves, fast, sp);
     if (pl.k.main == nullptr) return false;
     pl.shared = pl.k.shared;
-    // the single-panel shared-producer sweeps apply the softplus and its chain rule themselves (their checkpoint sweep,
-    // the shared-producer forward kernel, computes the step from the raw projection too)
-    if (pl.shared && pl.panels == 1 && pl.k.ckpt_fwd != nullptr && N == pl.k.cf_NG * pl.k.cf_NW) pl.step_outside = false;
+    // the shared-producer sweeps apply the softplus and its chain rule themselves (their checkpoint sweep, the shared-producer
+    // forward kernel, computes the step from the raw projection too; the plain checkpoint sweep of many panels reads it)
+    pl.step_outside = sp && !pl.shared;
+    pl.step_for_ckpt = sp && pl.shared && pl.panels > 1 && pl.k.ckpt_wide == nullptr;
     pl.fast = fast && pl.k.ckpt_fast;                        // false: the padded copies of the tensors' last rows are needed
     pl.ck_LG = pl.k.ckpt_LG; pl.ck_waves = pl.k.ckpt_waves;
     pl.LG = LG; pl.K = K; pl.NW = NW; pl.waves = waves; pl.RB = pl.k.RB;
@@ -469,7 +468,7 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
         q.off_pA = o; o += items ? align_up(maps * q.S * N * sizeof(float)) : 0;
         q.off_pD = o; o += items ? align_up(maps * q.S * sizeof(float)) : 0;
         q.off_pb = o; o += align_up(maps * q.S * sizeof(float));
-        q.off_step = o; o += q.step_outside ? align_up(maps * (size_t)d->H * W * sizeof(float)) + 256 : 0;
+        q.off_step = o; o += q.step_outside || q.step_for_ckpt ? align_up(maps * (size_t)d->H * W * sizeof(float)) + 256 : 0;
         q.off_tail = o; o += align_up((size_t)(W + 16) * (5 * (d->dtype == SCAN2D_BF16 ? 2 : 4) + 1));
         if (av) { q.off_pAv = o; o += d->Bt > 1 ? align_up(maps * N * sizeof(float)) : 0; }
         if (q.panels > 1) {
@@ -515,7 +514,7 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
             const double wgs = std::ceil((double)d->Bt * q.CG * q.S / JPW);
             const double resident = 256.0 * per_cu, rounds = std::ceil(wgs / resident);
             const double wps = std::min((double)per_cu, std::ceil(wgs / 256.0)) * waves / 4.0;
-            double us = rounds * g * q.seg_bands * pl.panels * units * 0.12 * (0.5 + 0.5 * std::max(1.0, wps));
+            double us = rounds * pl.panels * (5.0 + g * q.seg_bands * units * 0.12 * (0.5 + 0.5 * std::max(1.0, wps)));
             if (q.CG > 1) us += 2.0 * d->Bt * q.CG * cells * 4.0 * (1.0 / 4.0e6 + 1.0 / 5.0e6);
             if (q.S > 1) {
                 const double up = 1.0 - 1.0 / q.S;
@@ -558,7 +557,7 @@ int bwd_check(const scan2d_desc* d, bool softplus, bool av) {
     const long long wg1 = (maps + MPW1 - 1) / MPW1, wg2 = ((long long)d->Bt * pl.CG * pl.S + MPW - 1) / MPW;
     if (wg1 > 2147483647LL || wg2 > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
     const long long chunks = ((long long)d->H * d->W + 1023) / 1024;
-    if (pl.step_outside && chunks * maps > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+    if ((pl.step_outside || pl.step_for_ckpt) && chunks * maps > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
     return SCAN2D_OK;
 }
 
@@ -618,7 +617,7 @@ bool bwd_describe(const scan2d_desc* d, char* text, size_t text_bytes) {
 
 bool bwd_gate_in_sweep(const scan2d_desc* d) {
     BwdPlan pl;
-    return d->flags == 0u && make_plan(d, &pl, true, false) && (pl.small || (pl.shared && pl.panels == 1 && !pl.step_outside)) &&
+    return d->flags == 0u && make_plan(d, &pl, true, false) && (pl.small || pl.shared) &&
            pl.k.main_gate != nullptr;
 }
 
@@ -664,7 +663,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     BwdPlan pl;
     if (!make_plan(d, &pl, softplus, A_v != nullptr)) return SCAN2D_ERR_BAD_SHAPE;
     if (z != nullptr) {                                        // the output gate's backward inside the main sweep
-        if (!softplus || y_scan == nullptr || dz == nullptr || pl.k.main_gate == nullptr || !(pl.small || (pl.shared && pl.panels == 1 && !pl.step_outside)))
+        if (!softplus || y_scan == nullptr || dz == nullptr || pl.k.main_gate == nullptr || !(pl.small || pl.shared))
             return SCAN2D_ERR_BAD_SHAPE;
         pl.k.main = pl.k.main_gate;
     }
@@ -705,6 +704,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     }
     const int MPW = (pl.waves * 64 / pl.LG) / pl.NG;
     BwdArgs ac = a;                                            // the checkpoint sweep may hold more states per lane
+    if (pl.step_for_ckpt) ac.delta = ws + pl.off_step;
     ac.NG = (d->N + pl.k.ckpt_NW - 1) / pl.k.ckpt_NW;
     const int MPW1 = (pl.ck_waves * 64 / pl.ck_LG) / ac.NG;
     const long long wg1 = (maps + MPW1 - 1) / MPW1;
@@ -726,7 +726,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
                                static_cast<const float*>(delta), static_cast<const float*>(dy), static_cast<const float*>(Bm),
                                static_cast<const float*>(Cm), mask, reinterpret_cast<float*>(ws + pl.off_tail), r1, r2, r3, d->W);
     }
-    if (pl.step_outside) {
+    if (pl.step_outside || pl.step_for_ckpt) {
         const unsigned chunks = (unsigned)((HW + 1023) / 1024);
         if ((long long)chunks * maps > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
         float* step = reinterpret_cast<float*>(ws + pl.off_step);
@@ -744,7 +744,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
         g.Dc = d->Dc; g.H = d->H; g.W = d->W; g.S = pl.S; g.seg_rows = pl.seg_bands * pl.RB;
         g.cols = (unsigned)((d->W + 63) / 64);
         g.waves = (unsigned)((unsigned long long)maps * g.cols);           // rank_plan: fits
-        const int form = pl.step_outside ? kGcStep : (z != nullptr ? kGcGated : (softplus ? kGcSoftplus : kGcPlain));
+        const int form = z != nullptr ? kGcGated : (softplus ? kGcSoftplus : kGcPlain);
         hipLaunchKernelGGL(d->dtype == SCAN2D_BF16 ? gcarry_kernel<bf16_t>(form) : gcarry_kernel<float>(form), dim3((g.waves + 3) / 4), dim3(256),
                            0, stream, g);
     }

@@ -225,7 +225,7 @@ constexpr int bwd_rows_per_scan() { return !MP && K * NW * RB <= 16 ? RB : 1; }
 //   aL   [ALR][NW*K/4][TH][4]          the decays of the band's first ALR rows in the current channel, each thread its own
 //   gaL  [GS][TH][NW*K]               a[i+1,j]*g[i+1,j] of every channel, kept between bands
 //   dAL  [GS][SLOTS][NW]              dA of every channel, accumulated over the bands
-//   dDL  [GS][WAVES][2]               dDskip and (SPIN) the bias gradient of every channel per wavefront, likewise
+//   dDL  [GS][WAVES][2]               dDskip and (SP) the bias gradient of every channel per wavefront, likewise
 template <int LG, int K, int NW, int NG, int WAVES, int RB>
 constexpr size_t bwd_shared_lds_fixed() {                  // floats that do not depend on GS
     constexpr size_t TH = WAVES * 64, JPW = TH / LG / NG;
@@ -244,7 +244,7 @@ constexpr size_t bwd_shared_lds_per_channel() { return (size_t)WAVES * 64 * NW *
 template <typename T, int LG, int K, int NW, int NG, int WAVES, int RB, bool FAST, bool SP, bool CF = false, bool MP = false, bool GATE = false>
 __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kernel(const BwdArgs p) {
     static_assert(!MP || !CF, "column panels: rows first only");
-    static_assert(!GATE || (SP && !MP), "the gate goes with the softplus step, single panel");
+    static_assert(!GATE || SP, "the gate goes with the softplus step");
     constexpr bool RECOMP = !CF && !MP;
     const int cb = MP ? p.cb : 0;                         // first column of this launch's panel
     constexpr int THREADS = WAVES * 64, SLOTS = THREADS / LG, JPW = SLOTS / NG, PANEL = LG * K, TMJ = NG * LG;
@@ -260,12 +260,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
     constexpr bool AREG = RS == RB;
     static_assert(RB % RS == 0 && (!AREG || ALR == 0), "whole scans per band, decays in one place");
     static_assert(RS == 1 || BCR, "rows scanned together have their Bm and Cm at hand");
-    // SP: p.delta is the raw projection.  Single-panel instantiations (SPIN) apply the softplus where the cells are
-    // produced and the chain rule where ddelta is summed (the logistic factor comes from the step kept in LDS), so
-    // ddelta receives the gradient of the raw projection directly; the column-panel instantiations read the step from a
-    // buffer a kernel of its own has filled (fp32, p.delta) and write the step's gradient back over it.
-    constexpr bool SPIN = SP && !MP;
-    using DT = std::conditional_t<SP && !SPIN, float, T>;               // element type of what p.delta holds
+    // SP: p.delta is the raw projection.  The softplus is applied where the cells are produced and the chain rule where
+    // ddelta is summed (the logistic factor comes from the step kept in LDS), so ddelta receives the gradient of the raw
+    // projection directly.
     constexpr int PP_ROW = 3 * PANEL, PP_JOB = RB * PP_ROW;
     extern __shared__ float lds[];
     const int GS = p.GS;
@@ -359,7 +356,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
     auto request = [&](int band, int ch) {
         const size_t map = map_of(ch);
         const T* xm = reinterpret_cast<const T*>(p.x) + map * HW;
-        const DT* dm = reinterpret_cast<const DT*>(p.delta) + map * HW;
+        const T* dm = reinterpret_cast<const T*>(p.delta) + map * HW;
         const T* dym = reinterpret_cast<const T*>(p.dy) + map * HW;
         const T* zm = reinterpret_cast<const T*>(p.z) + map * HW;          // GATE only
         const T* ysm = reinterpret_cast<const T*>(p.y_scan) + map * HW;    // GATE only
@@ -368,7 +365,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             const uint32_t o = (uint32_t)min(band * RB + cell_r[v], H - 1) * (uint32_t)W + (uint32_t)min(cb + cell_c[v], W - 1);
             if constexpr (GATE) { rawz[v] = elem_bits(at_byte(zm, o * EB)); raws[v] = elem_bits(at_byte(ysm, o * EB)); }
             rawx[v] = elem_bits(at_byte(xm, o * EB));
-            rawd[v] = elem_bits(at_byte(dm, o * (uint32_t)Elem<DT>::kBytes));
+            rawd[v] = elem_bits(at_byte(dm, o * EB));
             rawy[v] = elem_bits(at_byte(dym, o * EB));
         }
         // the checkpoint (band 0 starts from zero and reads what band 1 reads); past the row end: the next row, or what lies
@@ -483,7 +480,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         const bool act = ch < nch;
         const size_t map = map_of(ch);                     // idle iterations re-read a valid channel
         const int c = (int)(map - (size_t)b * p.Dc);
-        const float dbc = (SPIN && p.delta_bias != nullptr) ? p.delta_bias[c] : 0.0f;
+        const float dbc = (SP && p.delta_bias != nullptr) ? p.delta_bias[c] : 0.0f;
         float An[NW], Ap[NW], hcv[MP ? RB : 1][NW], qcv[MP ? RB : 1][NW];
 #pragma unroll
         for (int s = 0; s < NW; ++s) {
@@ -497,13 +494,13 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         const float dsk = p.Dskip != nullptr ? p.Dskip[c] : 0.0f;
 
         // ---- produce the per-position values of this (band, channel)
-        float xe[CT], dDb = 0.0f, dBb = 0.0f;              // dBb (SPIN): sum of the ddelta_raw this thread stores
+        float xe[CT], dDb = 0.0f, dBb = 0.0f;              // dBb (SP): sum of the ddelta_raw this thread stores
 #pragma unroll
         for (int v = 0; v < CT; ++v) {
             const bool in = cell_ok[v] && act && r0 + cell_r[v] < H;
             const bool m = rawm[v] != 0u;
-            float dl = widen(rawd[v], DT{});
-            if constexpr (SPIN) dl = softplus_f32(dl + dbc);
+            float dl = widen(rawd[v], T{});
+            if constexpr (SP) dl = softplus_f32(dl + dbc);
             dl = in ? dl : 0.0f;
             xe[v] = (in && !m) ? widen(rawx[v], T{}) : 0.0f;         // select: nothing under the mask leaks
             float dyv = in ? widen(rawy[v], T{}) : 0.0f;
@@ -734,12 +731,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             const float dl = cell[0], dyv = cell[2 * PANEL];
             const uint32_t o = (uint32_t)(r0 + cell_r[v]) * (uint32_t)W + (uint32_t)(cb + cell_c[v]);
             float dd = fmaf(xe[v], sB, sA);
-            if constexpr (SP && !SPIN)         // over the step of this cell, which nobody reads again
-                put_elem_at(make_rsrc(reinterpret_cast<const float*>(p.delta) + map * HW, HW * 4), o, in, dd, float{});
-            else {
-                if constexpr (SPIN) { dd = in ? dd * dsoftplus_from_value(dl) : 0.0f; dBb += dd; }
-                put_elem_at(make_rsrc(reinterpret_cast<T*>(p.ddelta) + map * HW, HW * EB), o, in, dd, T{});
-            }
+            if constexpr (SP) { dd = in ? dd * dsoftplus_from_value(dl) : 0.0f; dBb += dd; }
+            put_elem_at(make_rsrc(reinterpret_cast<T*>(p.ddelta) + map * HW, HW * EB), o, in, dd, T{});
             // skip term; exactly +0 under the mask
             put_elem_at(make_rsrc(reinterpret_cast<T*>(p.dx) + map * HW, HW * EB), o, in, rawm[v] != 0u ? 0.0f : fmaf(dsk, dyv, dl * sB), T{});
         }
@@ -783,7 +776,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         }
     }
     if (tm < 2) {
-        float* const base = tm == 0 ? p.pD : (SPIN ? p.pBias : nullptr);
+        float* const base = tm == 0 ? p.pD : (SP ? p.pBias : nullptr);
         if (base != nullptr) {
             for (int ch = 0; ch < nch; ++ch) {
                 float acc = 0.0f;

@@ -24,6 +24,7 @@ struct BwdKernels {
     bool shared = false;                  // main sweep of scan2d_bwd_shared.hpp
     size_t lds_fixed = 0, lds_per_channel = 0;   // its LDS in floats: fixed + per channel that a job handles in turn
     BwdKernel main_panels = nullptr;      // its instantiation that takes column panels (wave-wide tiling of two states per lane)
+    BwdKernel main_panels_gate = nullptr; // that one with the output gate's backward inside
     BwdKernel main_gate = nullptr;        // its instantiation with the output gate's backward inside (softplus step, rows first)
     // checkpoint sweep run by the shared-producer forward kernel in its checkpoint mode (FwdArgs), with its tiling
     void (*ckpt_fwd)(const FwdArgs) = nullptr;
@@ -78,6 +79,9 @@ inline BwdKernels lookup_bwd_shared_kernels(int LG, int K, int NW, int NG, int w
         if constexpr (!CF && lg == 64 && k == 4 && nw == 2) {                                            \
             r.main_panels = fast ? scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, true, SP, false, true>      \
                                  : scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, false, SP, false, true>;    \
+            if constexpr (SP)                                                                            \
+                r.main_panels_gate = fast ? scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, true, true, false, true, true>    \
+                                          : scan2d_bwd_shared_kernel<T, lg, k, nw, ng, wv, rb, false, true, false, true, true>;  \
             if (W <= kWideLG * kWideK)                                                                   \
                 r.ckpt_wide = Elem<T>::kBytes == 2 && (W % 2) != 0                                       \
                     ? scan2d_fwd_shared_kernel<T, kWideLG, kWideK, kWideNW, kWideNG, kWideWaves, kWideRPB, SP, Elem<T>::kBytes == 2, rb>     \
