@@ -469,7 +469,7 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
                                 uint32_t bits[VEC >= 2 ? VEC / 2 : 1];
 #pragma unroll
                                 for (int e = 0; e < VEC / 2; ++e)
-                                    bits[e] = f32_to_bf16_bits(val[2 * e]) | (f32_to_bf16_bits(val[2 * e + 1]) << 16);
+                                    bits[e] = pack_bf16x2(val[2 * e], val[2 * e + 1]);
                                 store_words<(VEC >= 2 ? VEC / 2 : 1)>(reinterpret_cast<uint32_t*>(dst), bits);
                             } else {
 #pragma unroll
