@@ -7,7 +7,8 @@
 // scan2d_linear_kernel: a wavefront owns 64 positions x 16 NOT output channels (scan2d_contract.hpp); no LDS, no barrier.
 // The four wavefronts of a workgroup, and the workgroups that follow it on the same XCD, take the other output channels
 // of the same positions, so `in` comes from HBM once and from L1 / L2 afterwards.  Bound: HBM for bf16 (the products of
-// 128 -> 256 channels are 4.3 GFLOP beside 50 MB), the fp32 matrix rate for fp32.
+// 128 -> 256 channels are 4.3 GFLOP beside 50 MB), the matrix rate for fp32.
+// scan2d_linear_resident_kernel (bf16), scan2d_linear_split_kernel and scan2d_linear_stream_kernel (fp32): large maps.
 // scan2d_linear_any_kernel: one thread per output, for maps of fewer than 4 positions or 4 GB of weights.
 #include "scan2d_block.hpp"
 
@@ -16,6 +17,7 @@
 #include "scan2d_contract.hpp"
 
 namespace scan2d {
+bool allow_large_lds(const void* kernel, size_t bytes);   // scan2d_api.hip
 namespace {
 
 struct LinArgs {
@@ -265,6 +267,202 @@ __global__ __launch_bounds__(256, 1) void scan2d_linear_stream_kernel(const LinA
     }
 }
 
+// fp32 as sums of bf16: x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1) and x3 the rest, which has at most 8 bits, so the
+// sum is x itself.  Of a product's nine terms the six largest are formed, on v_mfma_f32_16x16x32_bf16 (16 times the fp32
+// matrix rate); the other three are below 2^-23 of it, typically 2^-26.
+struct Split { uint32_t part[3]; };                        // of two values, packed
+__device__ __forceinline__ Split split_bf16(float a, float b) {
+    Split s;
+    s.part[0] = pack_bf16x2(a, b);
+    a -= __uint_as_float(s.part[0] << 16);
+    b -= __uint_as_float(s.part[0] & 0xffff0000u);
+    s.part[1] = pack_bf16x2(a, b);
+    a -= __uint_as_float(s.part[1] << 16);
+    b -= __uint_as_float(s.part[1] & 0xffff0000u);
+    s.part[2] = pack_bf16x2(a, b);
+    return s;
+}
+
+// fp32, enough work for every SIMD, input channels in whole steps of 64: the layer as bf16 products (split_bf16).  A workgroup
+// (one per compute unit) splits its 16 NOT rows of Wt once and keeps them in LDS as MFMA operands; its 8 wavefronts walk over
+// pieces of 32 positions, whose channels they split on the way: a step of 32 channels is split beside the products of the
+// step before it (4 vector slots per product pass), its loads a step earlier still, across the end of one piece into the next.
+// The largest terms have accumulators of their own: theirs is the rounding that counts, once per 32 channels.
+// What is not finite in one of the parts (an infinity, a value that rounds to one) is not finite in the result, and what is so
+// small that its last part is lost gives a tiny result: a piece with such a result is formed again from fp32 products.
+// Bound: the matrix pipe (half its time in use) and the clock under it: 256 -> 512 channels at 24576 positions take 43 us, with
+// all operands zero 37 us (scan2d_linear_stream_kernel 57 and 54 us).  Error against 64 bits, 2-norm: 0.9e-7 (2.9e-7).
+constexpr int kSplitWaves = 8;
+template <int NOT, bool RES>
+__global__ __launch_bounds__(kSplitWaves * 64, 2) void scan2d_linear_split_kernel(const LinArgs p) {
+    extern __shared__ u32x4_t wl[];                        // [steps][NOT][3][64 lanes], then the bias
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t slices = (uint32_t)p.ogroups, groups = gridDim.x / slices;
+    const uint32_t wg = (blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+    const uint32_t slice = wg % slices, group = wg / slices;
+    if (group >= groups) return;                           // the grid is a multiple of 8, not of the slices
+    const int l = threadIdx.x & 63, g = l >> 4, n = l & 15;
+    const int Cin = p.Cin, steps = Cin / 32, o0 = (int)slice * 16 * NOT;
+    const uint32_t P = (uint32_t)p.P, ptiles = (uint32_t)p.ptiles, items = (uint32_t)p.waves, stride = groups * kSplitWaves;
+
+    // four fragments' loads at a time (past the last one it is loaded again)
+    for (int f0 = wv; f0 < steps * NOT; f0 += 4 * kSplitWaves) {
+        uint32_t r[4][8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int f = min(f0 + u * kSplitWaves, steps * NOT - 1), k = f / NOT, ot = f - k * NOT;
+            load_words_any<8>(static_cast<const float*>(p.Wt) + (size_t)min(o0 + 16 * ot + n, p.Cout - 1) * Cin + 32 * k + 8 * g, r[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int f = f0 + u * kSplitWaves;
+            if (f >= steps * NOT) break;
+            Split s[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] = split_bf16(__uint_as_float(r[u][2 * e]), __uint_as_float(r[u][2 * e + 1]));
+#pragma unroll
+            for (int q = 0; q < 3; ++q) wl[(f * 3 + q) * 64 + l] = u32x4_t{s[0].part[q], s[1].part[q], s[2].part[q], s[3].part[q]};
+        }
+    }
+    float* const bl = reinterpret_cast<float*>(wl + steps * NOT * 3 * 64);   // bias of the 16 NOT output channels
+    if (threadIdx.x < 16 * NOT) bl[threadIdx.x] = p.bias != nullptr ? p.bias[min(o0 + (int)threadIdx.x, p.Cout - 1)] : 0.0f;
+    __syncthreads();
+
+    struct Piece { const char* in; uint32_t boff, p0; int b; };
+    auto piece = [&](uint32_t item) {
+        Piece w;
+        w.b = (int)(item / ptiles);
+        w.p0 = (item - (uint32_t)w.b * ptiles) * 32u;
+        w.in = reinterpret_cast<const char*>(static_cast<const float*>(p.in) + (size_t)w.b * Cin * P);
+        w.boff = ((uint32_t)(8 * g) * P + LanePos<2>(w.p0, n, P).s) * 4u;
+        return w;
+    };
+    uint32_t raw[2][8][2];
+    u32x4_t x[2][2][3];
+    f32x4 acc[NOT][2], low[NOT][2];                        // sums of x1 w1; of the other terms
+    const uint32_t first = group + groups * wv;            // the last round's pieces spread over the groups, then over the SIMDs
+    if (first >= items) return;
+    Piece cur = piece(first), next = cur;
+    auto load = [&](int buf, int k) {                      // step k of this piece, or of the next one behind its end (steps >= 4)
+        const bool over = k >= steps;
+        const char* bb = (over ? next.in : cur.in) + (size_t)(over ? k - steps : k) * 128u * P;
+        const uint32_t off = over ? next.boff : cur.boff;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) load_words_at<2>(bb + (size_t)e * P * 4u, off, raw[buf][e]);
+    };
+    auto split_pair = [&](int buf, int pair) {             // two channels of one of the lane's two positions
+        const int t = pair / 4, e = pair % 4;
+        const Split s = split_bf16(__uint_as_float(raw[buf][2 * e][t]), __uint_as_float(raw[buf][2 * e + 1][t]));
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[buf][t][q][e] = s.part[q];
+    };
+    u32x4_t wr[2][3];                                      // a block of 16 output channels ahead
+    auto load_w = [&](int buf, int block) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) wr[buf][q] = wl[(block * 3 + q) * 64 + l];
+    };
+    // The products of step k beside the split of the step behind it, in pieces that the scheduler may not merge: left to
+    // itself it puts chains of dependent products together and the operands' reads in front of their use.
+    auto step = [&](int buf, int k) {
+        int pair = 0;
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot) {
+            const int at = (buf * NOT + ot) & 1;
+            load_w(at ^ 1, ot + 1 < NOT ? k * NOT + ot + 1 : (k + 1 < steps ? (k + 1) * NOT : 0));
+            const auto term = [&](f32x4 (&to)[2], int wq, int xq) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    to[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[at][wq]), __builtin_bit_cast(bf16x8, x[buf][t][xq]), to[t], 0, 0, 0);
+            };
+#pragma unroll
+            for (int part = 0; part < 3; ++part) {
+                if (part == 0) { term(low[ot], 2, 0); term(acc[ot], 0, 0); }
+                else if (part == 1) { term(low[ot], 0, 2); term(low[ot], 1, 1); }
+                else { term(low[ot], 1, 0); term(low[ot], 0, 1); }
+#pragma unroll
+                for (; pair < ((ot * 3 + part + 1) * 8 + 3 * NOT - 1) / (3 * NOT); ++pair) split_pair(buf ^ 1, pair);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    const float* res = static_cast<const float*>(p.res);
+    float* out = static_cast<float*>(p.out);
+
+    load(0, 0);
+    load(1, 1);
+    load_w(0, 0);
+#pragma unroll
+    for (int pair = 0; pair < 8; ++pair) split_pair(0, pair);
+    load(0, 2);
+    for (uint32_t item = first; item < items; item += stride) {
+        next = piece(min(item + stride, items - 1));
+        const LanePos<2> pos(cur.p0, n, P);
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[ot][t] = low[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k = 0; k < steps; k += 2) {
+            step(0, k);
+            load(1, k + 3);
+            step(1, k + 1);
+            load(0, k + 4);
+        }
+        float size = 0.0f;
+        uint32_t add[RES ? NOT : 1][4][2];
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[ot][t] += low[ot][t];
+        if constexpr (RES) {                               // into the registers of `low`
+#pragma unroll
+            for (int ot = 0; ot < NOT; ++ot) {
+                const int r0 = min(o0 + 16 * ot, p.Cout - 1);      // uniform; the lane's rows follow it
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    load_words_at<2>(res + ((size_t)cur.b * p.Cout + r0) * P, ((uint32_t)min(4 * g + i, p.Cout - 1 - r0) * P + pos.s) * 4u, add[ot][i]);
+            }
+        }
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) size += fabsf(acc[ot][t][i]);
+        // finite, and not so small that parts of 2^-133 count (values below 2^-90 have lost up to 2^-43 of themselves)
+        if (__any(!(size <= 3.402823466e38f) || (size > 0.0f && size < 8e-28f))) {
+#pragma unroll
+            for (int ot = 0; ot < NOT; ++ot)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) acc[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int c = g; c < Cin; c += 4) {
+                const float* in = static_cast<const float*>(p.in) + ((size_t)cur.b * Cin + c) * P + pos.s;
+#pragma unroll
+                for (int ot = 0; ot < NOT; ++ot) {
+                    const float w = static_cast<const float*>(p.Wt)[(size_t)min(o0 + 16 * ot + n, p.Cout - 1) * Cin + c];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) acc[ot][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, in[t], acc[ot][t], 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int ot = 0; ot < NOT; ++ot) {
+            const f32x4 bias = *reinterpret_cast<const f32x4*>(bl + 16 * ot + 4 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int o = o0 + 16 * ot + 4 * g + i;
+                float v[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    v[t] = p.bias != nullptr ? acc[ot][t][i] + bias[i] : acc[ot][t][i];
+                    if constexpr (RES) v[t] += __uint_as_float(add[ot][i][t]);
+                }
+                if (o < p.Cout) pos.store(out + ((size_t)cur.b * p.Cout + o) * P, v);
+            }
+        }
+        cur = next;
+    }
+}
+
 // Any shape: one thread per output, channels in ascending order.
 template <typename T>
 __global__ __launch_bounds__(256) void scan2d_linear_any_kernel(const LinArgs p) {
@@ -312,6 +510,37 @@ int launch_sized(const LinArgs& a, hipStream_t stream) {
         }
     }
     if constexpr (Elem<T>::kBytes == 4) {
+        // bf16 products (us, split and fp32 products: 256 -> 512 channels at 25527 positions 47 and 65..74, at 8192 18 and 23;
+        // 512 -> 256 at 25527 48..52 and 68..79; 128 -> 256 at 16384 13.5 and 14.0, at 8192 9.7 and 8.5: the line lies between
+        // the last two, in pieces of 32 positions x 16 outputs x 32 channels).  LDS holds 32 rows of Wt up to 768 channels.
+        const long long pieces = (a.P + 31) / 32 * a.Bt;
+        if (a.Cin % 64 == 0 && a.Cin >= 128 && a.Cin <= 768 && 25 * a.P * 4 < (1LL << 32) && pieces * o16 * (a.Cin / 32) >= 18000 &&
+            pieces < (1LL << 30) && o16 <= 512) {
+            // 16 NOT output channels per workgroup, as many as its LDS holds: the fewest rounds of SIMDs, in products and
+            // the work of splitting the inputs
+            const auto cost = [&](long long n) {
+                const long long slices = (o16 + n - 1) / n, groups = 256 / slices;
+                if (a.Cin / 32 * n * 3072 > 150 * 1024 || groups < 1) return 1LL << 40;
+                return (pieces + groups * 4 - 1) / (groups * 4) * (192 * n + 150);
+            };
+            int n = 2;
+            for (int k = 3; k <= 4; ++k)
+                if (cost(k) <= cost(n)) n = k;
+            if (cost(n) < (1LL << 40)) {
+                LinArgs r = a;
+                r.ogroups = (int)((o16 + n - 1) / n);
+                r.ptiles = (a.P + 31) / 32;
+                r.waves = pieces;
+                using Kernel = void (*)(const LinArgs);
+                const Kernel k = n == 4 ? (a.res ? scan2d_linear_split_kernel<4, true> : scan2d_linear_split_kernel<4, false>)
+                               : n == 3 ? (a.res ? scan2d_linear_split_kernel<3, true> : scan2d_linear_split_kernel<3, false>)
+                                        : (a.res ? scan2d_linear_split_kernel<2, true> : scan2d_linear_split_kernel<2, false>);
+                const size_t lds = (size_t)a.Cin / 32 * n * 3072 + (size_t)n * 64;
+                if (lds > 65536 && !allow_large_lds(reinterpret_cast<const void*>(k), lds)) return SCAN2D_ERR_LAUNCH_FAILED;
+                hipLaunchKernelGGL(k, dim3(256), dim3(kSplitWaves * 64), lds, stream, r);
+                return SCAN2D_OK;
+            }
+        }
         // 16 NOT output channels per piece: the fewest rounds of 1024 wavefronts, counted in their products
         const auto cost = [&](long long n) { return (tiles * ((o16 + n - 1) / n) + 1023) / 1024 * n; };
         if (a.Cin % 64 == 0 && tiles * o16 >= 2048 && tiles * o16 < (1LL << 30)) {

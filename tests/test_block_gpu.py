@@ -669,3 +669,51 @@ def test_layers_on_more_positions_than_one_launch_has_threads_for(s2d):
     three = torch.tensor([[1.0], [2.0], [4.0]], device="cuda")
     raw, Bm, Cm = s2d.block_xproj(x, three, torch.full((1, 1), 3.0, device="cuda"), 1)
     assert all(torch.equal(col(got), k * col(x)) for got, k in ((raw, 3.0), (Bm, 2.0), (Cm, 4.0)))
+
+
+# fp32 linear layers as sums of bf16 products: channels of Wt in LDS (4, 3 and 2 blocks of 16 rows per workgroup), output
+# channels off the 16 grid, positions off the grid of 32, several batch items, bias and residual.
+@pytest.mark.parametrize("Bt,Cin,Cout,P,with_bias,with_res", [
+    (1, 128, 256, 10007, False, False), (2, 192, 200, 4099, True, False), (1, 512, 256, 3721, True, True), (3, 768, 130, 1023, False, True),
+    (1, 256, 510, 4731, False, True), (5, 320, 33, 3333, True, True), (1, 128, 16, 150001, False, False)])
+def test_linear_fp32_as_bf16_products(s2d, Bt, Cin, Cout, P, with_bias, with_res):
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(Cin + Cout)
+    x = torch.randn((Bt, Cin, 1, P), device="cuda:0", generator=g)
+    W = torch.randn((Cout, Cin), device="cuda:0", generator=g) * Cin ** -0.5
+    bias = torch.randn(Cout, device="cuda:0", generator=g) if with_bias else None
+    res = torch.randn((Bt, Cout, 1, P), device="cuda:0", generator=g) if with_res else None
+    got = s2d.block_linear(x, W, bias, res).double().reshape(Bt, Cout, P)
+    X = x.double().reshape(Bt, Cin, P)
+    ref = torch.stack([W.double() @ X[b] for b in range(Bt)])
+    size = torch.stack([W.double().abs() @ X[b].abs() for b in range(Bt)])
+    if with_bias:
+        ref += bias.double()[:, None]
+        size += bias.double().abs()[:, None]
+    if with_res:
+        ref += res.double().reshape(ref.shape)
+        size += res.double().abs().reshape(ref.shape)
+    # dropped terms below 2^-22 of a product, then a rounding of the large sum per 32 channels, of the small one, bias and residual
+    assert ((got - ref).abs() <= (2.0 ** -22 + (Cin / 32 + 4) * 2.0 ** -24) * size).all()
+
+
+def test_linear_fp32_as_bf16_products_beyond_their_range(s2d):
+    """Infinities, NaN, values that round to infinity in bf16 and values near the smallest normal ones give what fp32 products give."""
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(8)
+    P, Cin, Cout = 12000, 128, 256
+    x = torch.randn((1, Cin, 1, P), device="cuda:0", generator=g)
+    W = torch.randn((Cout, Cin), device="cuda:0", generator=g) * 0.01
+    x[0, 5, 0, 77], x[0, 7, 0, 3001], x[0, 9, 0, 9000] = float("inf"), float("nan"), 3.3999e38
+    x[0, :, 0, 6000] = 0
+    x[0, :, 0, 4000:4064] *= 1e-36
+    W[3, :] = 0
+    W[7, 5] = 0
+    got = s2d.block_linear(x, W).reshape(Cout, P)
+    ref = (W.double() @ x.double().reshape(Cin, P))
+    f = ref.float()
+    assert torch.equal(torch.isnan(got), torch.isnan(f)) and torch.equal(torch.isinf(got), torch.isinf(f))
+    ok = torch.isfinite(f)
+    size = (W.double().abs() @ x.double().abs().reshape(Cin, P))
+    assert ((got.double() - ref).abs()[ok] <= ((2.0 ** -22 + 136 * 2.0 ** -24) * size + 1e-44)[ok]).all()
+    assert (got[:, 6000] == 0).all()
