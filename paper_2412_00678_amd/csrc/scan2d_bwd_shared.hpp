@@ -540,6 +540,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         // multiply-adds as adding the carry to stored partial results, without the arrays that hold them
         float hprev[RB][NW][K], hhl[RECOMP ? 1 : RB][NW][K];
         float ak[AREG ? RB : 1][NW][K], Prow[RB][NW];      // decays (AREG) and per lane their product over its columns
+        // Rows scanned one by one (AHEAD): the next row's values are read from LDS in front of the current row's work.  One
+        // wavefront per SIMD has nothing else to put beside that latency, eight times per band and channel.
+        constexpr bool AHEAD = RS == 1;
+        float dlq[AHEAD ? 2 : 1][K], dxq[AHEAD ? 2 : 1][K];
+        if constexpr (AHEAD) {
+            lds_read_k<LG, K>(ppj, l, dlq[0]);
+            lds_read_k<LG, K>(ppj + PANEL, l, dxq[0]);
+        }
 #pragma unroll
         for (int rb = 0; rb < RB; rb += RS) {
             float a[RS][NW][K], u[RS][NW][K], P[RS * NW], Hh[RS * NW], cin[RS * NW];
@@ -549,9 +557,13 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
                     if (r + 1 < RB) load_B((r + 1) % BR, r0 + r + 1);
                     else load_C(r % BR, r0 + r);
                 }
-                float dl[K], dxe[K];
-                lds_read_k<LG, K>(ppj + r * PP_ROW, l, dl);
-                lds_read_k<LG, K>(ppj + r * PP_ROW + PANEL, l, dxe);
+                float (&dl)[K] = dlq[AHEAD ? r % 2 : 0], (&dxe)[K] = dxq[AHEAD ? r % 2 : 0];
+                const int rr = AHEAD ? r + 1 : r;          // the row read here
+                if (rr < RB) {
+                    lds_read_k<LG, K>(ppj + rr * PP_ROW, l, dlq[AHEAD ? rr % 2 : 0]);
+                    lds_read_k<LG, K>(ppj + rr * PP_ROW + PANEL, l, dxq[AHEAD ? rr % 2 : 0]);
+                    if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+                }
 #pragma unroll
                 for (int s = 0; s < NW; ++s) {
                     const uint32_t* Br = bB[r % BR][s];
@@ -607,6 +619,15 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
 #pragma unroll
             for (int j = 0; j < K; ++j) ga[s][j] = gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j];
         }
+        // what a row's first half needs (AHEAD: read one row ahead): dy and, where the decays are formed again, the step
+        float dln[K], dyn[K];
+        const auto first_half = [&](int r) {
+            if constexpr (!AREG) {
+                if (r >= ALR) lds_read_k<LG, K>(ppj + r * PP_ROW, l, dln);
+            }
+            lds_read_k<LG, K>(ppj + r * PP_ROW + 2 * PANEL, l, dyn);
+        };
+        if constexpr (AHEAD) first_half(RB - 1);
 #pragma unroll
         for (int rt = RB - 1; rt >= 0; rt -= RS) {         // RS rows per scan, the topmost rt - RS + 1
             float a[RS][NW][K], g[RS][NW][K], gr[RS][NW][K], P[RS * NW], Q[RS * NW], qin[RS * NW];     // gr: a * g (CF: of this row's q)
@@ -617,10 +638,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
                     if (r > 0) { load_B((r - 1) % BR, r0 + r - 1); load_C((r - 1) % BR, r0 + r - 1); }
                 }
                 const float* prow = ppj + r * PP_ROW;
-                float dl[K], dxe[K], dyv[K];
-                if constexpr (!AREG) lds_read_k<LG, K>(prow, l, dl);
+                float dxe[K];
+                if constexpr (!AHEAD) first_half(r);
                 if constexpr (CF) lds_read_k<LG, K>(prow + PANEL, l, dxe);
-                lds_read_k<LG, K>(prow + 2 * PANEL, l, dyv);
 #pragma unroll
                 for (int s = 0; s < NW; ++s) {
                     const uint32_t* Cr = bC[r % BR][s];
@@ -635,7 +655,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
 #pragma unroll
                     for (int j = 0; j < K; ++j) {
                         if constexpr (AREG) ar[j] = ak[r][s][j];
-                        else if (r >= ALR) ar[j] = __builtin_amdgcn_exp2f(dl[j] * Ap[s]);
+                        else if (r >= ALR) ar[j] = __builtin_amdgcn_exp2f(dln[j] * Ap[s]);
                         float hv;
                         if constexpr (CF) {            // v[i,j], then h[i,j]
                             hv = fmaf(ar[j], hprev[r][s][j], dxe[j] * get_elem<T, K>(bB[r % BR][s], j));
@@ -643,12 +663,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
                         } else {                       // h[i,j] is what the row below started from
                             hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
                         }
-                        dCacc[r][s][j] = fmaf(dyv[j], hv, dCacc[r][s][j]);
+                        dCacc[r][s][j] = fmaf(dyn[j], hv, dCacc[r][s][j]);
                         const float Cv = get_elem<T, K>(Cr, j);
                         if constexpr (CF) {
-                            g[d][s][j] = dyv[j] * Cv;
+                            g[d][s][j] = dyn[j] * Cv;
                         } else {
-                            g[d][s][j] = fmaf(dyv[j], Cv, ga[s][j]);                                // scan 3
+                            g[d][s][j] = fmaf(dyn[j], Cv, ga[s][j]);                                // scan 3
                             ga[s][j] = ar[j] * g[d][s][j];
                         }
                         gr[d][s][j] = CF ? ar[j] * g[d][s][j] : ga[s][j];
@@ -661,6 +681,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
 #pragma unroll
                     for (int j = K - 2; j >= 0; --j) Q[k] = fmaf(ar[j], Q[k], gr[d][s][j]);
                 }
+            }
+            if constexpr (AHEAD) {
+                if (rt > 0) first_half(rt - 1);
             }
             group_scan_left_any<LG, RS * NW>(P, Q, qin);
 #pragma unroll
