@@ -24,8 +24,10 @@ struct SumArgs {
     // partials whose rows are LG*K floats in the lane order of the main sweep, [K/4][LG][4] (K = 0: plain rows): element q
     // of a row is column (q / 4 % LG) * K + (q / (4 * LG)) * 4 + q % 4
     int W, LG, K;
-    // sums over batch items, or batch items and row segments: [items][n] -> [n]
-    struct Batch { const float* src; float* dst; int n, items; } batch[4];
+    // sums over batch items, [Bt][n] -> [n], or with S > 1 over batch items and row segments: element e = c * per + k of n is
+    // the sum over items b and segments s of src[(b * n / per + c) * map + s * seg + k]
+    int S, seg;
+    struct Batch { const float* src; float* dst; int n, per; long long map; } batch[4];
 };
 
 // S threads per element split the channel groups (thread s: groups s, s + S, ...), 8 loads of each tensor in flight, and
@@ -44,7 +46,13 @@ __global__ __launch_bounds__(S == 1 ? 256 : 64 * S) void scan2d_bwd_sums_kernel(
             if (t.dst == nullptr) continue;
             if (e >= 0 && e < t.n) {
                 float acc = 0.0f;
-                for (int b = 0; b < t.items; ++b) acc += t.src[(size_t)b * t.n + e];
+                if (p.S == 1) {
+                    for (int b = 0; b < p.Bt; ++b) acc += t.src[(size_t)b * t.n + e];
+                } else {
+                    const int c = (int)e / t.per, k = (int)e - c * t.per, channels = t.n / t.per;
+                    for (int b = 0; b < p.Bt; ++b)
+                        for (int s = 0; s < p.S; ++s) acc += t.src[((size_t)b * channels + c) * t.map + s * p.seg + k];
+                }
                 t.dst[e] = acc;
             }
             e -= t.n;
@@ -177,7 +185,7 @@ __global__ __launch_bounds__(kChainThreads) void scan2d_bwd_chain_kernel(const f
 }
 
 // Row segments of the main sweep: what the reverse column recurrence g (a*g, the value the row above adds to) holds at the
-// first row of every segment but the topmost one, gk[map][segment - 1][n][column].  The recurrence of a column needs no
+// first row of every segment but the topmost one (left where BwdArgs says).  The recurrence of a column needs no
 // other column, so a lane takes one column and all 16 states of a map (the sweep's tilings have no other number) and walks
 // up the rows; same operations in the same order as the sweep, so the segments change no bit of it.  The step and (gated)
 // dy * SiLU(z) are formed as in the sweep.
@@ -186,8 +194,8 @@ __global__ __launch_bounds__(kChainThreads) void scan2d_bwd_chain_kernel(const f
 enum { kGcPlain = 0, kGcSoftplus = 1, kGcGated = 2 };
 struct GcarryArgs {
     const void* delta; const float* delta_bias; const float* A; const void* Cm; const void* dy; const void* z;
-    float* gk;
-    int Dc, H, W, S, seg_rows;
+    float* pB; float* pC;
+    int Dc, H, W, S, seg_rows, GS, CG, part_row;
     unsigned waves, cols;                                  // wavefronts in all; 64-column pieces of a map
 };
 constexpr int kGcStates = 16;
@@ -246,11 +254,12 @@ __global__ __launch_bounds__(256) void scan2d_bwd_gcarry_kernel(const GcarryArgs
             }
             request(k, i - k - 2);
             if (to_store == 0) {
-                float* dst = p.gk + (map * (p.S - 1) + seg - 1) * N * W;
+                const int ch = c % p.GS;                   // of its job, which reads it for segment seg - 1
+                float* dst = (ch < p.seg_rows ? p.pB : p.pC) + (b * p.CG + c / p.GS) * N * H * p.part_row + (size_t)((seg - 1) * p.seg_rows + ch % p.seg_rows) * p.part_row;
                 if (col < W) {
 #pragma unroll
                     for (int s = 0; s < N; ++s)
-                        dst[(size_t)s * W + col] = ga[s];
+                        dst[(size_t)s * H * p.part_row + col] = ga[s];
                 }
                 to_store = p.seg_rows;
                 --seg;
@@ -295,7 +304,6 @@ struct BwdPlan {
     int LG = 0, K = 0, NW = 0, waves = 0, RB = 0;
     int NG = 0, GS = 0, CG = 0, nb = 0;
     int S = 1, seg_bands = 0;                              // row segments of the main sweep (scan2d_bwd_shared.hpp only), bands of each
-    size_t off_gk = 0;                                     // what enters a segment from below (S > 1): [maps][S-1][N][W]
     BwdKernels k;
     size_t lds_bytes = 0;
     int panels = 1;                                        // column panels of LG*K columns, one launch of each sweep per panel
@@ -319,9 +327,8 @@ size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 // Tilings whose shared-producer main sweep is the default.  Whole backward, us, plain -> shared: (16,4) 56x56 bf16, 6144
 // maps 1417 -> 719; (16,8) 128x128 bf16, 1024 maps 1407 -> 787; (16,12) 128x192 fp32, 2048 maps 3730 -> 2047; (64,4) on 8
 // waves, 256 maps of 256x256 bf16 2646 -> 1456, fp32 2484 -> 1579.  The other shared tilings run by the tuning override
-// only: (64,4) on 16 waves takes 1501 and 1695 on the last two (plain 2191 and 2014), (32,4) 1427 on the first and 760 on
-// the second, (32,6) 2496 on the third.
-bool shared_by_default(int LG, int K, int NW) { return LG == 16 || (LG == 64 && K == 4 && NW == 2); }
+// only: (64,4) on 16 waves takes 1501 and 1695 on the last two (plain 2191 and 2014), (32,6) 2496 on the third.
+bool shared_by_default(int LG, int K, int NW) { return LG == 16 || (LG == 32 && K == 4) || (LG == 64 && K == 4 && NW == 2); }
 
 }  // namespace
 bool allow_large_lds(const void* kernel, size_t bytes);   // scan2d_api.hip
@@ -364,6 +371,10 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     }
     int LG, K;
     if (W <= 64) { LG = 16; K = 4; }
+    // half-wave groups of 4 columns: two wavefronts per SIMD and all rows of a band in one scan, where 8 columns per lane leave
+    // one wavefront per SIMD (us, (16,8) and (32,4): 2048 maps of 128x128 bf16 1271 and 1176, fp32 1415 and 1220; 1024 of 100x100
+    // bf16 593 and 507; 256 of 57x83 160 and 145; with 8 and 16 maps there is no difference, 8 of 200x127 242 and 253)
+    else if (W <= 128 && N == 16 && !cf && !av && (long long)d->Bt * d->Dc >= 32 && (double)N * d->H * 128.0 * 4.0 < 2147483648.0) { LG = 32; K = 4; }
     else if (W <= 128) { LG = 16; K = 8; }
     else if (W <= 192 && N <= 16) { LG = 16; K = 12; }         // 12 columns x 4 states per lane would not fit the registers
     else if (W <= 256) { LG = 64; K = 4; }
@@ -462,12 +473,11 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
         q.off_ck = o; o += align_up(maps * q.nb * N * (q.ck_chunked ? (size_t)LG * K : (size_t)W) * sizeof(float));
         q.part_chunked = tight && q.shared && q.panels == 1 && q.CG > 1 && K % 4 == 0;
         const size_t part_row = q.part_chunked ? (size_t)LG * K : (size_t)W;
-        const bool items = d->Bt * (long long)q.S > 1;         // dA, dDskip and the bias gradient: a row per (batch item, segment)
         q.off_pB = o; o += q.CG > 1 ? align_up((size_t)d->Bt * q.CG * N * d->H * part_row * sizeof(float)) : 0;
         q.off_pC = o; o += q.CG > 1 ? align_up((size_t)d->Bt * q.CG * N * d->H * part_row * sizeof(float)) : 0;
-        q.off_pA = o; o += items ? align_up(maps * q.S * N * sizeof(float)) : 0;
-        q.off_pD = o; o += items ? align_up(maps * q.S * sizeof(float)) : 0;
-        q.off_pb = o; o += align_up(maps * q.S * sizeof(float));
+        q.off_pA = o; o += d->Bt > 1 ? align_up(maps * N * sizeof(float)) : 0;
+        q.off_pD = o; o += d->Bt > 1 ? align_up(maps * sizeof(float)) : 0;
+        q.off_pb = o; o += align_up(maps * sizeof(float));
         q.off_step = o; o += q.step_outside || q.step_for_ckpt ? align_up(maps * (size_t)d->H * W * sizeof(float)) + 256 : 0;
         q.off_tail = o; o += align_up((size_t)(W + 16) * (5 * (d->dtype == SCAN2D_BF16 ? 2 : 4) + 1));
         if (av) { q.off_pAv = o; o += d->Bt > 1 ? align_up(maps * N * sizeof(float)) : 0; }
@@ -476,7 +486,6 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
             q.off_hc = o; o += (size_t)(q.panels - 1) * one;
             q.off_qc = o; o += 2 * one;
         }
-        q.off_gk = o; o += q.S > 1 ? align_up(maps * (q.S - 1) * N * W * sizeof(float)) : 0;
         q.total = o;
     };
     auto set = [&](int gs, int segments) {
@@ -490,9 +499,9 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
         return q;
     };
     const double units = (double)pl.RB * K * NW, cells = (double)d->N * d->H * W;      // of a step per lane; of a map
-    double best_us = -1.0;
-    size_t plain_total = 0;                                    // smallest workspace without segments
-    BwdPlan best;
+    double best_us = -1.0, fit_us = -1.0;
+    long long plain_path = -1;
+    BwdPlan best, fit, plain;                                  // the best; the best within the scratch array; the shortest without segments
     for (int g = 1; g <= gs_max; ++g) {
         int per_cu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(pl.k.main), (int)T,
@@ -500,17 +509,15 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
             (void)hipGetLastError();
             per_cu = 1;
         }
-        // (the pass in front counts its wavefronts in 32 bits)
+        // at most 15 segments: their sums lie in one row of a map's checkpoints, 18 of at least 16 * 17 floats each; what
+        // enters them in their own rows of the partial sums.  (The pass in front counts its wavefronts in 32 bits.)
         const bool segs = pl.shared && !cf && N == kGcStates && (double)maps * ((W + 63) / 64) < 1073741824.0;
-        const int most = segs && pl.nb >= 4 ? std::min(16, pl.nb / 2) : 1;
+        const int most = segs ? std::max(1, std::min(15, pl.nb / 2)) : 1;
         int last = 0;
-        for (int segments = 1; segments <= std::max(1, most); ++segments) {
+        for (int segments = 1; segments <= most; ++segments) {
             const BwdPlan q = set(g, segments);
-            if (q.S == last) continue;
+            if (q.S == last || (q.S > 1 && g > 2 * q.seg_bands * q.RB)) continue;
             last = q.S;
-            if (q.S == 1) plain_total = plain_total == 0 ? q.total : std::min(plain_total, q.total);
-            // what fits the scratch array of scan2d_bwd_static_scratch without segments has to fit it with them
-            else if (q.total > SCAN2D_STATIC_SCRATCH_BYTES && plain_total <= SCAN2D_STATIC_SCRATCH_BYTES) continue;
             const double wgs = std::ceil((double)d->Bt * q.CG * q.S / JPW);
             const double resident = 256.0 * per_cu, rounds = std::ceil(wgs / resident);
             const double wps = std::min((double)per_cu, std::ceil(wgs / 256.0)) * waves / 4.0;
@@ -520,12 +527,20 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
                 const double up = 1.0 - 1.0 / q.S;
                 us += 6.0 + std::max((double)maps * cells * up / 2.2e6, d->H * up * 0.3);
             }
-            if (best_us < 0.0 || us < best_us * (1.0 - 1e-9) || (us <= best_us * (1.0 + 1e-9) && q.S == best.S)) { best_us = us; best = q; }
+            const auto better = [&](double than, const BwdPlan& p) {
+                return than < 0.0 || us < than * (1.0 - 1e-9) || (us <= than * (1.0 + 1e-9) && q.S == p.S);
+            };
+            if (better(best_us, best)) { best_us = us; best = q; }
+            if (q.total <= SCAN2D_STATIC_SCRATCH_BYTES && better(fit_us, fit)) { fit_us = us; fit = q; }
+            if (q.S == 1 && g <= 8 && (plain_path < 0 || (long long)rounds * g <= plain_path)) { plain_path = (long long)rounds * g; plain = q; }
         }
     }
+    // scan2d_bwd_static_scratch takes what fits its array with the fewest rounds of workgroups and up to 8 channels each;
+    // such a shape has to fit it with the plan chosen here too
+    if (best.total > SCAN2D_STATIC_SCRATCH_BYTES && plain.total <= SCAN2D_STATIC_SCRATCH_BYTES) best = fit;
     if (force_gs >= 1 && force_gs <= gs_lds && force_gs <= d->Dc) best = set(force_gs, 1);
-    if (force_seg >= 1 && pl.shared && !cf && N == kGcStates && maps < 1000000) best = set(best.GS, std::min(force_seg, best.nb));
-    if (best.lds_bytes > 160 * 1024) return false;
+    if (force_seg >= 1 && pl.shared && !cf && N == kGcStates && maps < 1000000) best = set(best.GS, std::min({force_seg, best.nb, 15}));
+    if (best.lds_bytes > 160 * 1024 || (best.S > 1 && best.GS > 2 * best.seg_bands * best.RB)) return false;
     *out = best;
     return true;
 }
@@ -637,14 +652,14 @@ void launch_sums(const scan2d_desc* d, const BwdPlan& pl, const BwdArgs& a, floa
     const unsigned E = S == 1 ? 256 : 64, threads = S == 1 ? 256 : 64 * S;
     s.groups_wgs = pl.CG > 1 ? (unsigned)std::min<size_t>((total + E - 1) / E, 16384) : 0;
     size_t n = 0;
-    for (auto& t : s.batch) t = {nullptr, nullptr, 0, 0};
-    const int items = d->Bt * pl.S, bias_items = pl.step_outside ? d->Bt : items;      // (the chain kernel sums whole maps)
-    if (items > 1) {
-        s.batch[0] = {a.pA, dA, d->Dc * d->N, items};
-        if (dDskip != nullptr) s.batch[1] = {a.pD, dDskip, d->Dc, items};
+    for (auto& t : s.batch) t = {nullptr, nullptr, 0, 1, 0};
+    s.S = pl.S; s.seg = a.sum_seg;
+    if (d->Bt > 1 || pl.S > 1) {
+        s.batch[0] = {a.pA, dA, d->Dc * d->N, d->N, a.sum_map};
+        if (dDskip != nullptr) s.batch[1] = {a.pD, dDskip, d->Dc, 1, a.sum_map1};
+        if (dbias != nullptr) s.batch[2] = {pbias, dbias, d->Dc, 1, a.sum_map1};      // (plain sweeps: one segment, summed by the chain kernel)
+        if (dA_v != nullptr) s.batch[3] = {a.pAv, dA_v, d->Dc * d->N, d->N, a.sum_map};
     }
-    if (bias_items > 1 && dbias != nullptr) s.batch[2] = {pbias, dbias, d->Dc, bias_items};
-    if (d->Bt > 1 && dA_v != nullptr) s.batch[3] = {a.pAv, dA_v, d->Dc * d->N, d->Bt};
     for (const auto& t : s.batch) n += (size_t)t.n;
     const unsigned wgs = s.groups_wgs + (unsigned)((n + threads - 1) / threads);
     if (wgs == 0) return;
@@ -678,19 +693,25 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     a.ck = saved != nullptr ? const_cast<float*>(saved) : reinterpret_cast<float*>(ws + pl.off_ck);
     a.pB = pl.CG > 1 ? reinterpret_cast<float*>(ws + pl.off_pB) : dBm;   // one group: the partial is the result
     a.pC = pl.CG > 1 ? reinterpret_cast<float*>(ws + pl.off_pC) : dCm;
-    const bool items = d->Bt * (long long)pl.S > 1;
-    a.pA = items ? reinterpret_cast<float*>(ws + pl.off_pA) : dA;
-    a.pD = dDskip == nullptr ? nullptr : (items ? reinterpret_cast<float*>(ws + pl.off_pD) : dDskip);
+    a.pA = d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pA) : dA;
+    a.pD = dDskip == nullptr ? nullptr : (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pD) : dDskip);
+    a.sum_map = d->N; a.sum_map1 = 1; a.sum_seg = 0;
+    if (pl.S > 1) {                                            // N, 1 and 1 floats per segment in the checkpoint row of band 0
+        float* row = reinterpret_cast<float*>(ws + pl.off_ck);
+        a.sum_map = a.sum_map1 = (long long)pl.nb * d->N * (pl.ck_chunked ? pl.LG * pl.K : d->W);
+        a.sum_seg = d->N + 2;
+        a.pA = row;
+        a.pD = dDskip != nullptr ? row + d->N : nullptr;
+    }
     a.Bt = d->Bt; a.Dc = d->Dc; a.H = d->H; a.W = d->W; a.N = d->N;
     a.NG = pl.NG; a.GS = pl.GS; a.CG = pl.CG; a.nb = pl.nb;
     a.S = pl.S; a.seg_bands = pl.seg_bands;
-    if (pl.S > 1) a.gk = reinterpret_cast<const float*>(ws + pl.off_gk);
     a.A_v = A_v;
     a.ck_chunked = pl.ck_chunked ? 1 : 0;
     a.part_chunked = pl.part_chunked ? 1 : 0;
     a.pAv = A_v == nullptr ? nullptr : (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pAv) : dA_v);
     // the sweeps that apply the softplus themselves also add up ddelta_raw per map
-    float* const pbias = softplus && ddelta_bias != nullptr ? ((pl.step_outside ? d->Bt > 1 : items) ? reinterpret_cast<float*>(ws + pl.off_pb) : ddelta_bias) : nullptr;
+    float* const pbias = softplus && ddelta_bias != nullptr ? (pl.S > 1 ? a.pA + d->N + 1 : (d->Bt > 1 ? reinterpret_cast<float*>(ws + pl.off_pb) : ddelta_bias)) : nullptr;
     if (!pl.step_outside) a.pBias = pbias;
 
     const long long maps = (long long)d->Bt * d->Dc;
@@ -740,7 +761,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
     if (pl.S > 1) {
         GcarryArgs g;
         g.delta = a.delta; g.delta_bias = delta_bias; g.A = A; g.Cm = Cm; g.dy = dy; g.z = z;
-        g.gk = reinterpret_cast<float*>(ws + pl.off_gk);
+        g.pB = a.pB; g.pC = a.pC; g.GS = pl.GS; g.CG = pl.CG; g.part_row = pl.part_chunked ? pl.LG * pl.K : d->W;
         g.Dc = d->Dc; g.H = d->H; g.W = d->W; g.S = pl.S; g.seg_rows = pl.seg_bands * pl.RB;
         g.cols = (unsigned)((d->W + 63) / 64);
         g.waves = (unsigned)((unsigned long long)maps * g.cols);           // rank_plan: fits

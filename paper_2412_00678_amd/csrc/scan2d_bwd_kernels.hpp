@@ -51,23 +51,28 @@ struct BwdArgs {
                          // kernel puts the columns back in place)
     float* pB; float* pC; // [Bt][CG][N][H][W] partial sums over the channels of one group
     const void* tail;    // padded copies of the rows behind which the tensors end (instantiations without FAST)
-    float* pA;           // [Bt][S][Dc][N]
-    float* pD;           // [Bt][S][Dc]
+    float* pA;           // [Bt][Dc][N]
+    float* pD;           // [Bt][Dc]
     // GATE instantiations of the shared-producer sweep only: the block's output gate inside the sweep
     const void* z = nullptr;        // gate branch, layout of x
     const void* y_scan = nullptr;   // the stored scan output, layout of x
     void* dz = nullptr;             // gradient of z, layout of x
-    float* pBias = nullptr; // [Bt][S][Dc] sums of ddelta_raw per map, written by the sweeps that apply the softplus themselves (or null)
+    float* pBias = nullptr; // [Bt][Dc] sums of ddelta_raw per map, written by the sweeps that apply the softplus themselves (or null)
     int Bt, Dc, H, W, N;
     int NG;              // lane groups per map
     int GS;              // channels a workgroup handles one after the other
     int CG;              // channel groups = ceil(Dc / GS)
     int nb;              // bands = ceil(H / RB)
     // Shared-producer main sweep: the bands of a map in S row segments of seg_bands bands, a job each.  A segment starts its
-    // reverse column recurrence from what scan2d_bwd_gcarry_kernel has left (gk [maps][S-1][N][W]: a*g of the first row of
-    // segment s+1 at index s), and pA / pD / pBias have a row per (batch item, segment).
+    // reverse column recurrence from what scan2d_bwd_gcarry_kernel has left: a*g of the first row of the segment below, for
+    // channel k of the job in row k of the segment in pB, beyond the segment's rows in pC.  The job's own partial sums go there
+    // later, nobody else's do.
     int S = 1, seg_bands = 0;
-    const float* gk = nullptr;
+    // Where that sweep's sums over the map go: map m, segment s, state n of dA at pA[m * sum_map + s * sum_seg + n], dDskip and
+    // the bias gradient at pD / pBias[m * sum_map1 + s * sum_seg].  One segment: [Bt][Dc][N] and [Bt][Dc]; several: in the row of
+    // the checkpoints that no band uses.
+    long long sum_map = 0, sum_map1 = 0;
+    int sum_seg = 0;
     // Maps wider than one lane-group panel are swept panel by panel (one launch each).  The row recurrences cross
     // the panel borders through carry buffers [maps][N][H]: the checkpoint sweeps run left to right and hand on the
     // row-end states hhor, the main sweeps run right to left and hand on a*q of their first column.

@@ -311,14 +311,17 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
     float* const ppj = pp + job_slot * PP_JOB;
     const float* const partj = part + (size_t)job_slot * WPJ * Part::kRow;
 
+    const uint32_t part_row = p.part_chunked ? (uint32_t)PANEL : (uint32_t)W;      // floats of a row of the partial sums
+    const size_t part_job = ((size_t)b * p.CG + cg) * N * H * part_row;
     for (int ch = 0; ch < GS; ++ch) {
+        const int seg_rows = p.seg_bands * RB;
         const bool below = seg + 1 < p.S && ch < nch;      // g below the map is 0
-        const float* gk = p.gk + (((size_t)b * p.Dc + c_first + ch) * (p.S - 1) + seg) * N * W;
+        const float* gk = (ch < seg_rows ? p.pB : p.pC) + part_job + (size_t)(seg * seg_rows + ch % seg_rows) * part_row;
 #pragma unroll
         for (int s = 0; s < NW; ++s)
 #pragma unroll
             for (int j = 0; j < K; ++j)
-                gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j] = below && j < nv ? gk[(size_t)(n0 + s) * W + col0 + j] : 0.0f;
+                gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j] = below && j < nv ? gk[(size_t)(n0 + s) * H * part_row + col0 + j] : 0.0f;
         if (l == LG - 1) {
 #pragma unroll
             for (int s = 0; s < NW; ++s) dAL[((size_t)ch * SLOTS + slot) * NW + s] = 0.0f;
@@ -435,10 +438,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
 
     float dBacc[RB][NW][K], dCacc[RB][NW][K];
     // The partial sums of a band over this workgroup's channels (past the last band: nothing).
-    const uint32_t part_row = p.part_chunked ? (uint32_t)PANEL : (uint32_t)W;
     const size_t part_bytes = (size_t)N * H * part_row * 4;
-    const rsrc_t rs_B = make_rsrc(p.pB + ((size_t)b * p.CG + cg) * N * H * part_row, part_bytes);
-    const rsrc_t rs_C = make_rsrc(p.pC + ((size_t)b * p.CG + cg) * N * H * part_row, part_bytes);
+    const rsrc_t rs_B = make_rsrc(p.pB + part_job, part_bytes);
+    const rsrc_t rs_C = make_rsrc(p.pC + part_job, part_bytes);
     auto store_band = [&](int band) {
         const uint32_t lane_at = p.part_chunked ? (uint32_t)l * 16u : (uint32_t)col0 * 4u, step = p.part_chunked ? LG * 16u : 16u;
         const bool whole = live && (p.part_chunked || nv == K);      // chunked: every lane stores; the reduction drops the columns past W
@@ -792,7 +794,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
 #pragma unroll
             for (int s = 0; s < NW; ++s)
             {
-                float* dst = p.pA + (((size_t)b * p.S + seg) * p.Dc + c_first + ch) * N + n0 + s;
+                float* dst = p.pA + ((size_t)b * p.Dc + c_first + ch) * p.sum_map + seg * p.sum_seg + n0 + s;
                 const float v = dAL[((size_t)ch * SLOTS + slot) * NW + s];
                 *dst = (MP && p.accum) ? *dst + v : v;             // panels are launched one after the other
             }
@@ -804,7 +806,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             for (int ch = 0; ch < nch; ++ch) {
                 float acc = 0.0f;
                 for (int w = 0; w < WPJ; ++w) acc += dDL[(ch * WAVES + job_slot * WPJ + w) * 2 + tm];
-                float* dst = base + ((size_t)b * p.S + seg) * p.Dc + c_first + ch;
+                float* dst = base + ((size_t)b * p.Dc + c_first + ch) * p.sum_map1 + seg * p.sum_seg;
                 *dst = (MP && p.accum) ? *dst + acc : acc;
             }
         }

@@ -94,7 +94,7 @@ inline BwdKernels lookup_bwd_shared_kernels(int LG, int K, int NW, int NG, int w
             r.ckpt_fwd = scan2d_fwd_shared_kernel<T, flg, fk, fnw, fng, fwv, frpb, SP, false, rb, CF>;   \
         }                                                                                                \
         r.cf_LG = flg; r.cf_K = fk; r.cf_NW = fnw; r.cf_NG = fng; r.cf_waves = fwv; r.cf_RPB = frpb;     \
-        if constexpr (!SP && !CF && lg == 16) {                                                          \
+        if constexpr (!SP && !CF && (lg == 16 || (lg == 32 && k == 4))) {                                                          \
             if constexpr (Elem<T>::kBytes == 2) {                                                        \
                 r.train_fwd = (W % 2) != 0 ? scan2d_fwd_shared_kernel<T, flg, fk, fnw, fng, fwv, frpb, false, true, rb, false, true>    \
                                            : scan2d_fwd_shared_kernel<T, flg, fk, fnw, fng, fwv, frpb, false, false, rb, false, true>;  \
