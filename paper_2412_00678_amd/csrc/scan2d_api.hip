@@ -178,24 +178,27 @@ bool fill_small(const scan2d_desc* d, int KS, bool sp, FwdChoice* out) {
     c.LG = 16; c.K = KS; c.NW = NW; c.waves = 4;
     c.exact = true; c.fast = false; c.multi = false;
     c.NG = 4; c.MPW = 4; c.panels = 1; c.RPB = 1; c.lds_bytes = 0;
-    c.kernel = d->dtype == SCAN2D_BF16 ? fwd_small_kernel_bf16(KS, NW, sp) : fwd_small_kernel_f32(KS, NW, sp);
+    c.kernel = d->dtype == SCAN2D_BF16 ? fwd_small_kernel_bf16(KS, NW, sp, false) : fwd_small_kernel_f32(KS, NW, sp, false);
     if (c.kernel == nullptr) return false;
     *out = c;
     return true;
 }
 
-// Few maps of at most 16 x 16 positions and 16 states: one workgroup per map, rows and columns as parallel scans
-// (scan2d_fwd_tile16.hip).  With many maps the kernel above wins: it repeats nothing and runs four maps per workgroup.
-#ifndef SCAN2D_TILE16_MAX_MAPS
-#define SCAN2D_TILE16_MAX_MAPS 1024
-#endif
+// Up to 6144 maps of at most 16 x 16 positions and 16 states: one workgroup per map, rows and columns as parallel scans
+// (scan2d_fwd_tile16.hip), several channels per workgroup beyond the 1024 maps that the chip holds at once.  Beyond 1024 only
+// from 13 rows on: the kernel above costs a wavefront per row, this one the same whatever the map (gated, bf16, us, rows one by
+// one / tile: 2048 maps of 7x7 9.0 / 11.1, 10x10 11.3 / 11.5, 14x14 14.7 / 11.9; 4096 of 12x12 18.0 / 19.5, 14x14 25.9 / 19.7;
+// 256 maps of 14x14 9.7 / 4.5).
+constexpr long long kTileMostMaps = 6144, kTileAnyRows = 1024;
 bool fill_tile16(const scan2d_desc* d, bool sp, FwdChoice* out) {
-    if (d->H > 16 || d->W > 16 || d->N > 16 || (long long)d->Bt * d->Dc > SCAN2D_TILE16_MAX_MAPS) return false;
+    const long long maps = (long long)d->Bt * d->Dc;
+    if (d->H > 16 || d->W > 16 || d->N > 16 || maps > kTileMostMaps || (maps > kTileAnyRows && d->H < 13)) return false;
     FwdChoice c;
     c.LG = 16; c.K = 1; c.NW = d->N; c.waves = 4; c.sp = sp;
     c.exact = true; c.fast = false; c.multi = false; c.tile = true;
-    c.NG = 1; c.MPW = 1; c.panels = 1; c.RPB = 1; c.lds_bytes = 0;
-    c.kernel = fwd_tile16_kernel(d->dtype, sp);
+    c.NG = 1; c.panels = 1; c.RPB = 1; c.lds_bytes = 0;
+    c.MPW = (int)std::max(1LL, std::min({4LL, maps / 1024, (long long)d->Dc}));
+    c.kernel = fwd_tile16_kernel(d->dtype, sp, false, c.MPW == 1);
     *out = c;
     return true;
 }
@@ -263,6 +266,9 @@ double fwd_cost(const scan2d_desc* d, const FwdChoice& c) {
     const bool bf16 = d->dtype == SCAN2D_BF16;
     const double maps = (double)d->Bt * d->Dc;
     const double wgs = std::ceil(maps / c.MPW);
+    // eight rows per batch: twice the loads in flight where a compute unit has one workgroup; it would not hold more of them
+    // (64x64 fp32, us, 8 and 4 rows: 256 maps 14.4 and 15.8, 384 maps of 40x60 13.7 and 12.6)
+    if (c.shared && c.LG == 16 && c.RPB == 8 && wgs > 256.0) return 1e30;
     const double c_core = bf16 ? 10.5 : 8.5;
     // a lone recurrence pads its DPP wait states (16- and 32-lane scans; the wave-wide scan has enough steps of its own)
     const double c_scan = (c.LG == 64 ? 13.0 : (c.LG == 32 ? 12.0 : 9.0)) + (c.NW == 1 && c.LG != 64 ? 4.0 : 0.0);
@@ -326,11 +332,12 @@ int rank_fwd(const scan2d_desc* d, FwdChoice* out, bool sp, bool ma, bool cf) {
             fill_choice(d, LG, K, NW, waves, rpb, sp, ma, out))
             return SCAN2D_OK;
     }
-    // narrow maps: one column per lane up to 16 columns; two per lane up to 32 where the width rules out
-    // the unguarded wide loads of the 4-column variants (measured: twice as fast as their guarded form)
     if (fill_tile16(d, sp, out)) return SCAN2D_OK;
     if (d->W <= 16 && fill_small(d, 1, sp, out)) return SCAN2D_OK;
-    if (d->W <= 32 && d->W % 4 != 0 && fill_small(d, 2, sp, out)) return SCAN2D_OK;
+    // up to 8 states that no shared-producer tiling takes, rows off the 4-column grid: two columns per lane (2048 maps of 30x30,
+    // N = 5: 33 us against 40 in general form; with 12 states and more the general form wins, and the shared-producer tilings
+    // do by a factor: 256 maps of 25x30, N = 16: 9.0 us against 21.8)
+    if (d->W <= 32 && d->W % 4 != 0 && d->N <= 8 && d->N != 4 && d->N != 8 && fill_small(d, 2, sp, out)) return SCAN2D_OK;
     bool found = false;
     double best = 0.0;
     for (const V4& v : kFwdVariants) {
@@ -375,6 +382,12 @@ bool allow_large_lds(const void* kernel, size_t bytes) {
     return true;
 }
 namespace {
+
+// Workgroups of a forward launch: MPW maps each; the kernel for tiny maps takes MPW channels of one batch item.
+long long fwd_wgs(const scan2d_desc* d, const FwdChoice& c) {
+    if (c.tile) return (long long)d->Bt * ((d->Dc + c.MPW - 1) / c.MPW);
+    return ((long long)d->Bt * d->Dc + c.MPW - 1) / c.MPW;
+}
 
 // Workspace of the scan kernel itself: row-end states between column panels (wide maps).
 size_t fwd_workspace(const scan2d_desc* d, const FwdChoice& c) {
@@ -468,7 +481,7 @@ int fwd_check(const scan2d_desc* d, bool sp, bool has_mask, bool cf) {
     const int rc = choose_fwd(d, &ch, sp, !has_mask || (d->W % 4) == 0, cf);
     if (rc != SCAN2D_OK) return rc;
     const long long maps = (long long)d->Bt * d->Dc;
-    if ((maps + ch.MPW - 1) / ch.MPW > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
+    if (fwd_wgs(d, ch) > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
     const long long chunks = ((long long)d->H * d->W + 1023) / 1024;
     if (skip_bytes(d) > 0 && has_mask && chunks * maps > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
     return SCAN2D_OK;
@@ -535,12 +548,15 @@ int fwd_impl(const scan2d_desc* desc, const void* x, const void* delta, const fl
     a.maps = (long long)desc->Bt * desc->Dc;
     a.Dc = desc->Dc; a.H = desc->H; a.W = desc->W; a.N = desc->N;
     a.NG = ch.NG; a.MPW = ch.MPW; a.panels = ch.panels; a.RPB = ch.RPB;
-    const long long wgs = (a.maps + ch.MPW - 1) / ch.MPW;
+    const long long wgs = fwd_wgs(desc, ch);
     if (wgs > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
-    if (z != nullptr && y_gated != nullptr && softplus != 0 && ch.shared && !ch.cf && !ch.skew) {   // the gate in the same kernel
+    if (z != nullptr && y_gated != nullptr && softplus != 0 && !ch.cf && !ch.skew) {               // the gate in the same kernel
         const bool ua = desc->dtype == SCAN2D_BF16 && (desc->W % 2) != 0;
-        const FwdKernel k = desc->dtype == SCAN2D_BF16 ? fwd_shared_kernel_gate_bf16(ch.LG, ch.K, ch.NW, ch.NG, ch.waves, ch.RPB, ua)
-                                                       : fwd_shared_kernel_gate_f32(ch.LG, ch.K, ch.NW, ch.NG, ch.waves, ch.RPB);
+        FwdKernel k = nullptr;
+        if (ch.tile) k = fwd_tile16_kernel(desc->dtype, true, true, false);
+        else if (ch.K < 4 && a.maps <= 4096) k = desc->dtype == SCAN2D_BF16 ? fwd_small_kernel_bf16(ch.K, ch.NW, true, true) : fwd_small_kernel_f32(ch.K, ch.NW, true, true);
+        else if (ch.shared) k = desc->dtype == SCAN2D_BF16 ? fwd_shared_kernel_gate_bf16(ch.LG, ch.K, ch.NW, ch.NG, ch.waves, ch.RPB, ua)
+                                                           : fwd_shared_kernel_gate_f32(ch.LG, ch.K, ch.NW, ch.NG, ch.waves, ch.RPB);
         if (k != nullptr) {
             ch.kernel = k;
             a.z = z; a.y_gated = y_gated;

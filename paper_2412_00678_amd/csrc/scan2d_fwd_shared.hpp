@@ -55,6 +55,13 @@ __device__ __forceinline__ void carry_apply(float* hl, const float* pl, const fl
     }
 }
 
+// Rows whose row scans run together: they depend on each other through the column recurrence only, and a lone scan of a
+// 16-lane group is a chain of dependent lane movements with wait states between them.  One state per lane is the tiling of
+// few maps, where a SIMD has a wavefront or two and the chain of the rows is the run time; tilings with more states per lane
+// scan those together.
+template <int LG, int K, int NW, int RPB, bool SKEW>
+constexpr int fwd_rows_per_scan() { return LG <= 32 && NW == 1 && !SKEW ? (K == 4 && RPB % 4 == 0 ? 4 : (RPB % 2 == 0 ? 2 : 1)) : 1; }
+
 // UA (bf16 only): rows of odd width; Bm/Cm rows then start on odd 2-byte boundaries every other row and
 // are shifted into place where they are unpacked, as in the plain form.
 // CK > 0: the checkpoint sweep of the backward pass instead of the forward pass.  The recurrences are the same;
@@ -97,6 +104,7 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
     constexpr int NV = CT / VEC, VPR = PANEL / VEC;
     constexpr int SC = (NW < 4 ? NW : (K >= 12 ? 2 : 4));
     static_assert(NW % SC == 0, "state chunking");
+    constexpr int RS = fwd_rows_per_scan<LG, K, NW, RPB, SKEW>();
     constexpr int PP_ROW = 2 * PANEL, PP_MAP = RPB * PP_ROW, PP_BUF = MPW * PP_MAP;
     constexpr int YP_ROW = SLOTS * PANEL, YP_BUF = RPB * YP_ROW;
     extern __shared__ float smem[];
@@ -218,7 +226,7 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
     // ---- Bm / Cm: ring of raw registers, PDS rows ahead
     constexpr int XWR = XW + (UA ? 1 : 0);
     constexpr int SSET = 2 * NW * XWR;
-    constexpr int PDS = (4 * SSET <= kPrefetchBudgetS && RPB % 4 == 0) ? 4 : (2 * SSET <= kPrefetchBudgetS ? 2 : 1);
+    constexpr int PDS = RPB == 8 && LG == 16 ? 8 : (4 * SSET <= kPrefetchBudgetS && RPB % 4 == 0) ? 4 : (2 * SSET <= kPrefetchBudgetS ? 2 : 1);
     const int col0 = l * K;
     const uint32_t lcol = col0 < W ? (uint32_t)col0 : 0u;      // lanes past the last column mirror lane 0
     uint32_t rB[PDS][NW][XWR], rC[PDS][NW][XWR];
@@ -275,7 +283,7 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
     request(min(1, nbatch - 1));
     __syncthreads();
 
-    float dlq[2][K], dxq[2][K];
+    float dlq[2 * RS][K], dxq[2 * RS][K];
     auto fetch_row = [&](int buf, int r, int set) {
         const float* row = pp + buf * PP_BUF + map_slot * PP_MAP + r * PP_ROW + l * 4;
 #pragma unroll
@@ -286,11 +294,116 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
             dxq[set][4 * j4] = d.x; dxq[set][4 * j4 + 1] = d.y; dxq[set][4 * j4 + 2] = d.z; dxq[set][4 * j4 + 3] = d.w;
         }
     };
-    fetch_row(0, 0, 0);
+#pragma unroll
+    for (int d = 0; d < RS; ++d) fetch_row(0, d, d);
 
     for (int bt = 0; bt < nbatch; ++bt) {
         const int buf = bt & 1;
         const int row0 = bt * RPB;
+        // partial sums over this lane group's states and, where the row closes a band, the checkpoint
+        const auto finish_row = [&](int r, const float* yacc) {
+            const int i = row0 + r;
+            if constexpr (YOUT) {
+                float* mine = ypart + buf * YP_BUF + r * YP_ROW + slot * PANEL + l * 4;
+#pragma unroll
+                for (int j4 = 0; j4 < K / 4; ++j4)
+                    *reinterpret_cast<float4*>(mine + j4 * (LG * 4)) =
+                        make_float4(yacc[4 * j4], yacc[4 * j4 + 1], yacc[4 * j4 + 2], yacc[4 * j4 + 3]);
+            }
+            if constexpr (CK > 0) {
+                if ((i + 1) % CK == 0 && i + 1 < H && live) {             // h[i] enters band (i+1)/CK
+                    const int band = (i + 1) / CK;
+#pragma unroll
+                    for (int s = 0; s < NW; ++s) {
+                        if (p.ck_chunked) {                            // every lane of the group writes, also past the last column
+                            float* dst = p.ck + (((size_t)map * p.nb + band) * N + n0 + s) * PANEL + l * 4;
+#pragma unroll
+                            for (int j4 = 0; j4 < K / 4; ++j4)
+                                *reinterpret_cast<float4*>(dst + j4 * (LG * 4)) =
+                                    make_float4(h[s][4 * j4], h[s][4 * j4 + 1], h[s][4 * j4 + 2], h[s][4 * j4 + 3]);
+                            continue;
+                        }
+                        float* dst = p.ck + (((size_t)map * p.nb + band) * N + n0 + s) * W + col0;
+                        if (col0 + K <= W) {
+                            uint32_t bits[K];
+#pragma unroll
+                            for (int j = 0; j < K; ++j) bits[j] = __float_as_uint(h[s][j]);
+                            store_words<K>(reinterpret_cast<uint32_t*>(dst), bits);
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < K; ++j)
+                                if (col0 + j < W) dst[j] = h[s][j];
+                        }
+                    }
+                }
+            }
+        };
+        if constexpr (RS > 1) {
+#pragma unroll
+            for (int rb = 0; rb < RPB; rb += RS) {
+                float a[RS][K], hl[RS][K], pl[RS][K], P[RS], Hh[RS], cin[RS];
+                constexpr int half = RS;                   // register sets: RS rows at hand, RS requested
+                const int at = (rb / RS) % 2 * half;
+                if (rb + RS < RPB) {
+#pragma unroll
+                    for (int d = 0; d < RS; ++d) fetch_row(buf, rb + RS + d, half - at + d);
+                }
+#pragma unroll
+                for (int d = 0; d < RS; ++d) {
+                    const int r = rb + d, i = row0 + r, SS = r % PDS;
+                    const float (&dl)[K] = dlq[at + d], (&dx)[K] = dxq[at + d];
+#pragma unroll
+                    for (int j = 0; j < K; ++j) a[d][j] = __builtin_amdgcn_exp2f(dl[j] * Ap[0]);
+                    uint32_t uB[XW];
+                    unpacks(rB[SS][0], 0, (uint32_t)min(i, H - 1) * (uint32_t)W, uB);
+                    if constexpr (CF) {
+#pragma unroll
+                        for (int j = 0; j < K; ++j) h[0][j] = fmaf(a[d][j], h[0][j], dx[j] * get_elem<T, K>(uB, j));
+                        hl[d][0] = h[0][0];
+                    } else {
+                        hl[d][0] = dx[0] * get_elem<T, K>(uB, 0);
+                    }
+                    pl[d][0] = a[d][0];
+                    if constexpr (!NOSCAN) {
+#pragma unroll
+                        for (int j = 1; j < K; ++j) {
+                            hl[d][j] = fmaf(a[d][j], hl[d][j - 1], CF ? h[0][j] : dx[j] * get_elem<T, K>(uB, j));
+                            pl[d][j] = pl[d][j - 1] * a[d][j];
+                        }
+                        P[d] = pl[d][K - 1];
+                        Hh[d] = hl[d][K - 1];
+                    }
+                    // CF: the sum over the states reads h of this row
+                    if constexpr (CF && NOSCAN) {
+                        const float none[K] = {};
+                        __builtin_amdgcn_sched_barrier(0x7CF);
+                        lds(rsB, 0, (uint32_t)min(i + PDS, H - 1) * (uint32_t)W, rB[SS][0]);
+                        finish_row(r, none);
+                        continue;
+                    }
+                    __builtin_amdgcn_sched_barrier(0x7CF);         // (see the other form below)
+                    lds(rsB, 0, (uint32_t)min(i + PDS, H - 1) * (uint32_t)W, rB[SS][0]);
+                }
+                if constexpr (!NOSCAN) {
+                    group_scan<LG, RS>(P, Hh, cin);
+#pragma unroll
+                    for (int d = 0; d < RS; ++d) {
+                        const int r = rb + d, i = row0 + r, SS = r % PDS;
+                        uint32_t uC[XW];
+                        if constexpr (YOUT) unpacks(rC[SS][0], 0, (uint32_t)min(i, H - 1) * (uint32_t)W, uC);
+                        float yacc[K];
+#pragma unroll
+                        for (int j = 0; j < K; ++j) {
+                            const float hh = j == K - 1 ? Hh[d] : fmaf(pl[d][j], cin[d], hl[d][j]);     // Eq. 5
+                            if constexpr (!CF) fma_inplace(h[0][j], a[d][j], hh);                       // Eq. 6
+                            if constexpr (YOUT) yacc[j] = get_elem<T, K>(uC, j) * (CF ? hh : h[0][j]);
+                        }
+                        if constexpr (YOUT) lds(rsC, 0, (uint32_t)min(i + PDS, H - 1) * (uint32_t)W, rC[SS][0]);
+                        finish_row(r, yacc);
+                    }
+                }
+            }
+        } else {
 #pragma unroll
         for (int r = 0; r < RPB; ++r) {
             const int i = row0 + r;
@@ -383,47 +496,16 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
                     if constexpr (YOUT) lds(rsC, s, nxt, rC[SS][s]);
                 }
             }
-            if constexpr (YOUT) {
-                float* mine = ypart + buf * YP_BUF + r * YP_ROW + slot * PANEL + l * 4;
-#pragma unroll
-                for (int j4 = 0; j4 < K / 4; ++j4)
-                    *reinterpret_cast<float4*>(mine + j4 * (LG * 4)) =
-                        make_float4(yacc[4 * j4], yacc[4 * j4 + 1], yacc[4 * j4 + 2], yacc[4 * j4 + 3]);
-            }
-            if constexpr (CK > 0) {
-                if ((i + 1) % CK == 0 && i + 1 < H && live) {             // h[i] enters band (i+1)/CK
-                    const int band = (i + 1) / CK;
-#pragma unroll
-                    for (int s = 0; s < NW; ++s) {
-                        if (p.ck_chunked) {                            // every lane of the group writes, also past the last column
-                            float* dst = p.ck + (((size_t)map * p.nb + band) * N + n0 + s) * PANEL + l * 4;
-#pragma unroll
-                            for (int j4 = 0; j4 < K / 4; ++j4)
-                                *reinterpret_cast<float4*>(dst + j4 * (LG * 4)) =
-                                    make_float4(h[s][4 * j4], h[s][4 * j4 + 1], h[s][4 * j4 + 2], h[s][4 * j4 + 3]);
-                            continue;
-                        }
-                        float* dst = p.ck + (((size_t)map * p.nb + band) * N + n0 + s) * W + col0;
-                        if (col0 + K <= W) {
-                            uint32_t bits[K];
-#pragma unroll
-                            for (int j = 0; j < K; ++j) bits[j] = __float_as_uint(h[s][j]);
-                            store_words<K>(reinterpret_cast<uint32_t*>(dst), bits);
-                        } else {
-#pragma unroll
-                            for (int j = 0; j < K; ++j)
-                                if (col0 + j < W) dst[j] = h[s][j];
-                        }
-                    }
-                }
-            }
+            finish_row(r, yacc);
+        }
         }
         // the next batch's cells: produced before the barrier (its LDS buffer was last read one batch ago,
         // before the previous barrier), then the loads of the batch after that are requested
         produce(buf ^ 1, bt + 1);
         request(min(bt + 2, nbatch - 1));
         __syncthreads();
-        fetch_row(buf ^ 1, 0, 0);
+#pragma unroll
+        for (int d = 0; d < RS; ++d) fetch_row(buf ^ 1, d, d);
         // sums over the lane groups of the cells this thread produced, skip term, one rounding, store
         if (YOUT && live) {
             const float* ybase = ypart + buf * YP_BUF + (slot - sg) * PANEL;

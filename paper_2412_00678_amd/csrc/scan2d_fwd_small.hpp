@@ -19,7 +19,8 @@ namespace scan2d {
 __device__ __forceinline__ float raw_to_float(float, uint32_t bits) { return __uint_as_float(bits); }
 __device__ __forceinline__ float raw_to_float(bf16_t, uint32_t bits) { return __uint_as_float(bits << 16); }
 
-template <typename T, int KS, int NW, int PD, bool SP = false>
+// GATE: the output gate in the same kernel (p.z, p.y_gated; p.y only if it is wanted), as in scan2d_fwd_shared.hpp.
+template <typename T, int KS, int NW, int PD, bool SP, bool GATE>
 __global__ __launch_bounds__(256) void scan2d_fwd_small_kernel(const FwdArgs p) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l = lane & 15, g = lane >> 4;
@@ -39,6 +40,8 @@ __global__ __launch_bounds__(256) void scan2d_fwd_small_kernel(const FwdArgs p) 
     const T* xm = reinterpret_cast<const T*>(p.x) + (size_t)map * HW;
     const T* dm = reinterpret_cast<const T*>(p.delta) + (size_t)map * HW;
     T* ym = reinterpret_cast<T*>(p.y) + (size_t)map * HW;
+    const T* zm = reinterpret_cast<const T*>(p.z) + (size_t)map * HW;             // GATE only
+    T* ygm = reinterpret_cast<T*>(p.y_gated) + (size_t)map * HW;                  // GATE only
     const uint8_t* mm = p.mask ? p.mask + (size_t)b * HW : nullptr;
     const T* Bs[NW];
     const T* Cs[NW];
@@ -56,7 +59,7 @@ __global__ __launch_bounds__(256) void scan2d_fwd_small_kernel(const FwdArgs p) 
     const float dbias = (SP && p.delta_bias != nullptr) ? p.delta_bias[c] : 0.0f;   // SP: delta = softplus(raw + bias)
 
     // ring of raw registers: row i waits in slot i % PD
-    uint32_t rx[PD][KS], rd[PD][KS], rm[PD][KS], rB[PD][NW][KS], rC[PD][NW][KS];
+    uint32_t rx[PD][KS], rd[PD][KS], rm[PD][KS], rz[GATE ? PD : 1][KS], rB[PD][NW][KS], rC[PD][NW][KS];
     auto request = [&](int slot, int i) {
         const size_t ro = (size_t)i * W;
 #pragma unroll
@@ -64,6 +67,7 @@ __global__ __launch_bounds__(256) void scan2d_fwd_small_kernel(const FwdArgs p) 
             rx[slot][k] = elem_bits(xm + ro + lc[k]);
             rd[slot][k] = elem_bits(dm + ro + lc[k]);
             rm[slot][k] = mm ? (uint32_t)mm[ro + lc[k]] : 0u;
+            if constexpr (GATE) rz[slot][k] = elem_bits(zm + ro + lc[k]);
         }
 #pragma unroll
         for (int s = 0; s < NW; ++s)
@@ -82,7 +86,7 @@ __global__ __launch_bounds__(256) void scan2d_fwd_small_kernel(const FwdArgs p) 
         for (int r = 0; r < PD; ++r) {
             const int i = i0 + r;
             if (i < H) {                                  // uniform
-                float dl[KS], xe[KS], dxe[KS], yacc[KS], Bv[NW][KS], Cv[NW][KS];
+                float dl[KS], xe[KS], dxe[KS], yacc[KS], gate[KS], Bv[NW][KS], Cv[NW][KS];
 #pragma unroll
                 for (int k = 0; k < KS; ++k) {
                     dl[k] = raw_to_float(T{}, rd[r][k]);
@@ -90,6 +94,10 @@ __global__ __launch_bounds__(256) void scan2d_fwd_small_kernel(const FwdArgs p) 
                     xe[k] = rm[r][k] != 0u ? 0.0f : raw_to_float(T{}, rx[r][k]);
                     dxe[k] = dl[k] * xe[k];
                     yacc[k] = dsk * xe[k];
+                    if constexpr (GATE) {
+                        const float zv = raw_to_float(T{}, rz[r][k]);
+                        gate[k] = zv * logistic_f32(zv);
+                    }
                 }
 #pragma unroll
                 for (int s = 0; s < NW; ++s)
@@ -136,7 +144,10 @@ __global__ __launch_bounds__(256) void scan2d_fwd_small_kernel(const FwdArgs p) 
                     float v = yacc[k];
                     v += __shfl_xor(v, 16);
                     v += __shfl_xor(v, 32);
-                    if (g == 0 && in[k]) store_elem(ym + (size_t)i * W + col[k], v);
+                    if (g == 0 && in[k]) {
+                        if (!GATE || p.y != nullptr) store_elem(ym + (size_t)i * W + col[k], v);
+                        if constexpr (GATE) store_elem(ygm + (size_t)i * W + col[k], v * gate[k]);
+                    }
                 }
             }
         }

@@ -42,6 +42,7 @@ using FwdKernel = void (*)(const FwdArgs);
     X(64, 4, 2, 8, 8, 4) X(64, 4, 2, 8, 8, 8) X(64, 4, 1, 16, 16, 4)                      \
     /* 257 to 1024 columns */ X(64, 8, 1, 16, 16, 2) X(64, 8, 2, 8, 8, 2) X(64, 12, 2, 8, 8, 2) X(64, 16, 2, 8, 8, 2) \
     X(16, 12, 1, 16, 4, 4) X(16, 12, 2, 8, 4, 2) X(16, 8, 1, 16, 4, 4) X(16, 8, 2, 8, 4, 2) \
+    /* few maps */ X(16, 4, 1, 16, 4, 8) X(32, 4, 1, 16, 8, 4) X(32, 4, 2, 8, 4, 4)          \
     X(16, 4, 1, 16, 4, 4) X(16, 4, 2, 8, 4, 4) X(16, 4, 4, 4, 4, 4) X(16, 4, 8, 2, 4, 4)   \
     /* N = 8 */ X(64, 4, 1, 8, 8, 4) X(16, 4, 1, 8, 4, 4) X(16, 4, 2, 4, 4, 4) X(16, 8, 1, 8, 4, 4) X(16, 12, 1, 8, 4, 4) \
     /* N = 4 */ X(64, 4, 1, 4, 4, 4) X(16, 4, 1, 4, 4, 4) X(16, 8, 1, 4, 4, 4)             \
@@ -101,19 +102,19 @@ inline FwdKernel lookup_fwd_kernel_unaligned_mask(int LG, int K, int NW, int wav
 FwdKernel fwd_kernel_av_f32();
 FwdKernel fwd_kernel_av_bf16();
 
-// Narrow maps (W <= 32): KS columns per lane, NW = states per lane group of the wave's four.
-FwdKernel fwd_small_kernel_f32(int KS, int NW, bool sp);
+// Narrow maps (W <= 32): KS columns per lane, NW = states per lane group of the wave's four (KS = 2: up to 16 states).
+FwdKernel fwd_small_kernel_f32(int KS, int NW, bool sp, bool gate);
 // maps of at most 16 x 16 positions and 16 states, one workgroup per map, both recurrences as parallel scans
 // (scan2d_fwd_tile16.hip)
-FwdKernel fwd_tile16_kernel(int dtype, bool sp);
-FwdKernel fwd_small_kernel_bf16(int KS, int NW, bool sp);
+FwdKernel fwd_tile16_kernel(int dtype, bool sp, bool gate, bool one);      // gate: softplus step and output gate; one: one channel per workgroup
+FwdKernel fwd_small_kernel_bf16(int KS, int NW, bool sp, bool gate);
 
-template <typename T, bool SP>
+template <typename T, bool SP, bool GATE>
 inline FwdKernel lookup_fwd_small_kernel(int KS, int NW) {
 #define SCAN2D_X(ks, nw, pd) \
-    if (KS == ks && NW == nw) return scan2d_fwd_small_kernel<T, ks, nw, pd, SP>;
+    if (KS == ks && NW == nw) return scan2d_fwd_small_kernel<T, ks, nw, pd, SP, GATE>;
     SCAN2D_X(1, 1, 4) SCAN2D_X(1, 2, 4) SCAN2D_X(1, 4, 4) SCAN2D_X(1, 8, 2) SCAN2D_X(1, 16, 2)
-    SCAN2D_X(2, 1, 4) SCAN2D_X(2, 2, 4) SCAN2D_X(2, 4, 4) SCAN2D_X(2, 8, 2) SCAN2D_X(2, 16, 1)
+    SCAN2D_X(2, 1, 4) SCAN2D_X(2, 2, 4) SCAN2D_X(2, 4, 4)
 #undef SCAN2D_X
     return nullptr;
 }
