@@ -269,6 +269,7 @@ double fwd_cost(const scan2d_desc* d, const FwdChoice& c) {
     // eight rows per batch: twice the loads in flight where a compute unit has one workgroup; it would not hold more of them
     // (64x64 fp32, us, 8 and 4 rows: 256 maps 14.4 and 15.8, 384 maps of 40x60 13.7 and 12.6)
     if (c.shared && c.LG == 16 && c.RPB == 8 && wgs > 256.0) return 1e30;
+    if (c.shared && c.LG == 32 && d->W <= 64) return 1e30;                           // half of the lanes past the map
     const double c_core = bf16 ? 10.5 : 8.5;
     // a lone recurrence pads its DPP wait states (16- and 32-lane scans; the wave-wide scan has enough steps of its own)
     const double c_scan = (c.LG == 64 ? 13.0 : (c.LG == 32 ? 12.0 : 9.0)) + (c.NW == 1 && c.LG != 64 ? 4.0 : 0.0);
@@ -295,7 +296,10 @@ double fwd_cost(const scan2d_desc* d, const FwdChoice& c) {
     double wps = std::min(std::min(occ, wg_cu * c.waves / 4.0), wgs * c.waves / 1024.0 / rounds);
     if (rounds > 1.0) wps = std::max(wps, 1.0);                                      // several rounds: SIMDs are never empty
     const double steps = (double)d->H * c.panels * row;                              // instructions of one wave
-    if (wps < 1.0) return steps * 8.0;                                               // a lone wave: its own critical path
+    if (wps < 1.0) {                                                                 // a lone wave: its own critical path
+        const double merged = c.shared && c.LG != 64 && c.NW == 1 ? 4.0 : 0.0;       // rows scanned together have no wait states
+        return (double)d->H * c.panels * (row - merged) * (c.shared ? 6.2 : 7.3);    // the scale of one wave per SIMD below
+    }
     // measured issue efficiencies: the plain kernels keep gaining up to four waves per SIMD, the shared-producer
     // kernels (fewer, longer dependent chains per row and an LDS hand-over) level off near 0.88 (256 maps of 256x256
     // bf16: one state per lane on 16 waves 124 us, two states per lane on 8 waves 133 us; with 512 maps 245 against 219 us)

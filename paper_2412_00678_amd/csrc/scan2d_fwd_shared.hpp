@@ -538,7 +538,10 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
                 if ((unsigned)i < (unsigned)H) {
                     float out[VEC];
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) out[e] = acc[e] + sk_cur[v * VEC + e];
+                    for (int e = 0; e < VEC; ++e) {        // never one multiply-add with the product behind sk_cur: the instantiations
+#pragma clang fp contract(off)                             // with and without the gate give the same bits
+                        out[e] = acc[e] + sk_cur[v * VEC + e];
+                    }
                     auto store_vec = [&](T* base, const float* val) {
                         T* dst = base + (size_t)i * W + cell_col[v];
                         if (cell_col[v] + VEC <= W) {

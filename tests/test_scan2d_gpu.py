@@ -1341,3 +1341,30 @@ def test_backward_row_segments(s2d, variant, segments, shape, form, dtype):
             assert (many[k] - v).abs().max() <= 100 * 2.0 ** -23 * v.abs().max(), k
         else:
             assert torch.equal(many[k], v), k
+
+
+# Forward forms for small and narrow maps: several channels of a batch item per workgroup (channels off the group grid), the
+# gate inside, half-wave groups, eight rows per batch (heights off it), one and several maps of a batch item.
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("Bt,Dc,N,H,W,form", [
+    (5, 411, 16, 13, 14, "tile16 "), (2, 1025, 7, 16, 16, "tile16 "), (300, 17, 4, 14, 3, "tile16 "), (3, 700, 16, 5, 9, "small "),
+    (1, 7, 5, 9, 30, "small "), (2, 3, 16, 5, 31, "shared LG=16 K=4 "), (1, 5, 16, 21, 64, "shared LG=16 K=4 "), (1, 3, 16, 8, 17, "shared LG=16 K=4 "),
+    (2, 130, 16, 6, 65, "shared LG=32 K=4 "), (1, 260, 16, 9, 127, "shared LG=32 K=4 ")])
+def test_forward_of_small_and_narrow_maps(s2d, Bt, Dc, N, H, W, form, dtype):
+    import torch
+    w = wl.Workload("narrow", Bt, Dc, N, H, W, dtype, mask_frac=0.3)
+    inp = _gated_inputs(w, seed=31)
+    plan = s2d.describe_plan(s2d.Desc(Bt, Dc, H, W, N, dtype, 0), s2d.PASS_FWD)
+    assert f"form={form}" in plan, plan
+    d = s2d.to_device(inp, dtype)
+    db = torch.from_numpy(inp["delta_bias"]).cuda()
+    a = (d["x"], d["delta"], db, d["A"], d["Bm"], d["Cm"], d["Dskip"], d["mask"])
+    ys, y = s2d.scan2d_fwd_softplus_gated(*a, d["z"])
+    _, y_only = s2d.scan2d_fwd_softplus_gated(*a, d["z"], want_y_scan=False)
+    plain = s2d.scan2d_fwd_softplus(*a)
+    torch.cuda.synchronize()
+    rys, ry = oracle.scan2d_fwd_softplus_gated(inp["x"], inp["delta"], inp["delta_bias"], inp["A"], inp["Bm"], inp["Cm"], inp["Dskip"],
+                                               inp["mask"], inp["z"], dtype=dtype)
+    assert rel_err(wl.to_float(s2d.to_host(ys), dtype), wl.to_float(rys, dtype)) <= TOL[dtype]
+    assert rel_err(wl.to_float(s2d.to_host(y), dtype), wl.to_float(ry, dtype)) <= TOL[dtype]
+    assert torch.equal(ys, plain) and torch.equal(y, y_only)
