@@ -498,6 +498,9 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
         layout(q);
         return q;
     };
+    // The segments' sums over the map, N + 2 floats each, lie in the checkpoints' row of a map's first band, which has at least
+    // N * W floats: 18 of 16 * W, so that maps below 17 columns take fewer than 15 segments (a single column none).
+    const int held = std::min(15, d->N * std::min(W, 17) / (d->N + 2));
     const double units = (double)pl.RB * K * NW, cells = (double)d->N * d->H * W;      // of a step per lane; of a map
     double best_us = -1.0, fit_us = -1.0;
     long long plain_path = -1;
@@ -509,10 +512,9 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
             (void)hipGetLastError();
             per_cu = 1;
         }
-        // at most 15 segments: their sums lie in one row of a map's checkpoints, 18 of at least 16 * 17 floats each; what
-        // enters them in their own rows of the partial sums.  (The pass in front counts its wavefronts in 32 bits.)
+        // What enters the segments lies in their own rows of the partial sums.  (The pass in front counts its wavefronts in 32 bits.)
         const bool segs = pl.shared && !cf && N == kGcStates && (double)maps * ((W + 63) / 64) < 1073741824.0;
-        const int most = segs ? std::max(1, std::min(15, pl.nb / 2)) : 1;
+        const int most = segs ? std::max(1, std::min(held, pl.nb / 2)) : 1;
         int last = 0;
         for (int segments = 1; segments <= most; ++segments) {
             const BwdPlan q = set(g, segments);
@@ -539,7 +541,7 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     // such a shape has to fit it with the plan chosen here too
     if (best.total > SCAN2D_STATIC_SCRATCH_BYTES && plain.total <= SCAN2D_STATIC_SCRATCH_BYTES) best = fit;
     if (force_gs >= 1 && force_gs <= gs_lds && force_gs <= d->Dc) best = set(force_gs, 1);
-    if (force_seg >= 1 && pl.shared && !cf && N == kGcStates && maps < 1000000) best = set(best.GS, std::min({force_seg, best.nb, 15}));
+    if (force_seg >= 1 && pl.shared && !cf && N == kGcStates && maps < 1000000) best = set(best.GS, std::max(1, std::min({force_seg, best.nb, held})));
     if (best.lds_bytes > 160 * 1024 || (best.S > 1 && best.GS > 2 * best.seg_bands * best.RB)) return false;
     *out = best;
     return true;

@@ -129,6 +129,18 @@ SWEEP_W = [1, 2, 3, 7, 13, 14, 15, 16, 17, 20, 28, 30, 31, 32, 33, 56, 60, 63, 6
 SWEEP_N = [1, 3, 4, 5, 8, 15, 16, 17, 24, 40, 63, 64]
 
 
+def test_row_segments_keep_their_sums_inside_one_checkpoint_row(lib):
+    """Each segment of the backward leaves N + 2 sums in the checkpoints' row of a map's first band, N * W floats at least."""
+    most = 0
+    for W in range(1, 40):
+        for H in (17, 64, 300, 1000):
+            for maps in ((1, 1), (1, 8), (1, 64), (3, 20)):
+                segments = plan(lib, lib.Desc(*maps, H, W, 16, 0, 0), lib.PASS_BWD).get("segments", 1)
+                assert segments == 1 or 18 * segments <= 16 * W, (maps, H, W, segments)
+                most = max(most, segments)
+    assert most == 15
+
+
 def test_every_shape_has_a_forward_plan_within_the_hardware_limits(lib):
     for dtype in (0, 1):
         for W in SWEEP_W:

@@ -1308,6 +1308,7 @@ def test_backward_of_small_maps_with_several_channels_per_workgroup(s2d, Bt, Dc,
 @pytest.mark.parametrize("form", ["plain", "softplus", "gated"])
 @pytest.mark.parametrize("variant,segments,shape", [
     ("16,4,4,2,1", 2, (1, 5, 16, 57)), ("16,4,4,3,1", 5, (2, 7, 18, 64)), ("16,8,4,1,1", 3, (1, 3, 41, 121)), ("16,12,4,2,1", 4, (2, 3, 30, 190)),
+    ("16,4,4,2,1", 8, (2, 3, 64, 10)), ("16,4,4,2,1", 2, (1, 3, 64, 3)),      # as many as the checkpoints' row holds the sums of
     ("64,4,8,2,1", 3, (1, 3, 11, 255)), ("64,4,8,2,-1", 4, (2, 3, 23, 397)), ("64,4,8,1,-1", 2, (1, 2, 9, 777))],
     ids=lambda v: v if isinstance(v, str) else ("x".join(map(str, v)) if isinstance(v, tuple) else f"{v}seg"))
 def test_backward_row_segments(s2d, variant, segments, shape, form, dtype):
