@@ -297,8 +297,10 @@ double fwd_cost(const scan2d_desc* d, const FwdChoice& c) {
     if (rounds > 1.0) wps = std::max(wps, 1.0);                                      // several rounds: SIMDs are never empty
     const double steps = (double)d->H * c.panels * row;                              // instructions of one wave
     if (wps < 1.0) {                                                                 // a lone wave: its own critical path
-        const double merged = c.shared && c.LG != 64 && c.NW == 1 ? 4.0 : 0.0;       // rows scanned together have no wait states
-        return (double)d->H * c.panels * (row - merged) * (c.shared ? 6.2 : 7.3);    // the scale of one wave per SIMD below
+        if (!c.shared) return steps * 8.0;        // several maps per workgroup leave compute units idle (128 maps of 35x305 bf16, N = 5,
+                                                  // us, one and three maps per workgroup: 46.7 and 103.6)
+        const double merged = c.LG != 64 && c.NW == 1 ? 4.0 : 0.0;       // rows scanned together have no wait states
+        return (double)d->H * c.panels * (row - merged) * 6.2;                       // the scale of one wave per SIMD below
     }
     // measured issue efficiencies: the plain kernels keep gaining up to four waves per SIMD, the shared-producer
     // kernels (fewer, longer dependent chains per row and an LDS hand-over) level off near 0.88 (256 maps of 256x256

@@ -448,7 +448,9 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     // Channels a workgroup handles one after the other (bounded by the 160 KB of LDS) and row segments per map, by an
     // estimate of the whole call in us:
     //   * rounds of resident workgroups (the runtime's occupancy figure for the kernel's registers and this much LDS, one per
-    //     CU if it cannot be asked) times (band, channel) steps of a workgroup;
+    //     CU if it cannot be asked) times (band, channel) steps of a workgroup.
+    //     The plain sweep repeats the per-position work in every lane group and takes about twice as long per step (with the
+    //     shared sweep's figure it got too many channels: 256 maps of 84x1174 fp32, N = 12, one and two channels 3704 and 4541);
     //   * the dBm / dCm partials, one per channel group, written here and read by the reduction;
     //   * with segments, the pass in front of the sweep that forms what enters each from below.
     // More channels mean fewer partials, more segments keep the chip busy all the same: one slide of 256 channels of 211x397
@@ -523,7 +525,7 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
             const double wgs = std::ceil((double)d->Bt * q.CG * q.S / JPW);
             const double resident = 256.0 * per_cu, rounds = std::ceil(wgs / resident);
             const double wps = std::min((double)per_cu, std::ceil(wgs / 256.0)) * waves / 4.0;
-            double us = rounds * pl.panels * (5.0 + g * q.seg_bands * units * 0.12 * (0.5 + 0.5 * std::max(1.0, wps)));
+            double us = rounds * pl.panels * (5.0 + g * q.seg_bands * units * (pl.shared ? 0.12 : 0.25) * (0.5 + 0.5 * std::max(1.0, wps)));
             if (q.CG > 1) us += 2.0 * d->Bt * q.CG * cells * 4.0 * (1.0 / 4.0e6 + 1.0 / 5.0e6);
             if (q.S > 1) {
                 const double up = 1.0 - 1.0 / q.S;
