@@ -17,7 +17,7 @@
 //             v_permlane32_swap / v_permlane16_swap, so that one value per column, tensor and WAVEFRONT goes to LDS;
 //   finish    the thread that produced a cell adds the wavefronts' parts in a fixed order, applies the factors that
 //             depend on the position (ddelta = first sum + x * second sum, dx = step * second sum + Dskip * dy, +0
-//             under the mask; softplus: the logistic factor from the step) and stores.
+//             under the mask; softplus: the logistic factor kept from produce) and stores.
 // What it replaced had a barrier and 2 NG LDS reads per column in every row: 128x192 fp32 waited 43 % of the time.
 // The row-scan states hhor[i,j-1] are not kept from the rebuild to the reverse sweep but formed again there from the
 // column states, which are kept anyway (RECOMP): Eq. 6 read backwards, hhor[i,j] = h[i,j] - a[i,j] * h[i-1,j].  The column
@@ -141,14 +141,6 @@ __device__ __forceinline__ float from_left_any(float v) {
     return r;
 }
 
-// d softplus(t) / dt from the softplus value itself: sp = log(1 + e^t), so the logistic function of t is 1 - e^(-sp).
-// Below 1/64 the difference loses digits and the series takes over (next term: sp^4 / 24, under 2e-7 of the value).
-__device__ __forceinline__ float dsoftplus_from_value(float sp) {
-    const float big = 1.0f - __builtin_amdgcn_exp2f(-sp * kLog2e);
-    const float small = sp * (1.0f - sp * (0.5f - sp * (1.0f / 6.0f)));
-    return sp < 0.015625f ? small : big;
-}
-
 template <typename P>
 __device__ __forceinline__ P* at_byte(P* base, uint32_t bytes) {
     using B = std::conditional_t<std::is_const_v<P>, const char, char>;
@@ -261,8 +253,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
     static_assert(RB % RS == 0 && (!AREG || ALR == 0), "whole scans per band, decays in one place");
     static_assert(RS == 1 || BCR, "rows scanned together have their Bm and Cm at hand");
     // SP: p.delta is the raw projection.  The softplus is applied where the cells are produced and the chain rule where
-    // ddelta is summed (the logistic factor comes from the step kept in LDS), so ddelta receives the gradient of the raw
-    // projection directly.
+    // ddelta is summed, so ddelta receives the gradient of the raw projection directly.
     constexpr int PP_ROW = 3 * PANEL, PP_JOB = RB * PP_ROW;
     extern __shared__ float lds[];
     const int GS = p.GS;
@@ -496,13 +487,15 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         const float dsk = p.Dskip != nullptr ? p.Dskip[c] : 0.0f;
 
         // ---- produce the per-position values of this (band, channel)
-        float xe[CT], dDb = 0.0f, dBb = 0.0f;              // dBb (SP): sum of the ddelta_raw this thread stores
+        // dlog (SP): d softplus(t) / dt of the raw projection, the logistic function.  It is kept from here: formed from the step,
+        // log(1 + e^t), it would have the absolute error of 1 + e^t (steps around softplus(-4): 3e-5 of the factor against 3e-7).
+        float xe[CT], dlog[SP ? CT : 1], dDb = 0.0f, dBb = 0.0f;       // dBb (SP): sum of the ddelta_raw this thread stores
 #pragma unroll
         for (int v = 0; v < CT; ++v) {
             const bool in = cell_ok[v] && act && r0 + cell_r[v] < H;
             const bool m = rawm[v] != 0u;
             float dl = widen(rawd[v], T{});
-            if constexpr (SP) dl = softplus_f32(dl + dbc);
+            if constexpr (SP) { dlog[v] = logistic_f32(dl + dbc); dl = softplus_f32(dl + dbc); }
             dl = in ? dl : 0.0f;
             xe[v] = (in && !m) ? widen(rawx[v], T{}) : 0.0f;         // select: nothing under the mask leaks
             float dyv = in ? widen(rawy[v], T{}) : 0.0f;
@@ -756,7 +749,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             const float dl = cell[0], dyv = cell[2 * PANEL];
             const uint32_t o = (uint32_t)(r0 + cell_r[v]) * (uint32_t)W + (uint32_t)(cb + cell_c[v]);
             float dd = fmaf(xe[v], sB, sA);
-            if constexpr (SP) { dd = in ? dd * dsoftplus_from_value(dl) : 0.0f; dBb += dd; }
+            if constexpr (SP) { dd = in ? dd * dlog[v] : 0.0f; dBb += dd; }
             put_elem_at(make_rsrc(reinterpret_cast<T*>(p.ddelta) + map * HW, HW * EB), o, in, dd, T{});
             // skip term; exactly +0 under the mask
             put_elem_at(make_rsrc(reinterpret_cast<T*>(p.dx) + map * HW, HW * EB), o, in, rawm[v] != 0u ? 0.0f : fmaf(dsk, dyv, dl * sB), T{});

@@ -637,6 +637,39 @@ def test_backward_with_softplus_step_matches_oracle(s2d, shape, with_bias):
             assert rel_err(s2d.to_host(got[k]).astype(np.float64), plain[j].astype(np.float64)) <= 2e-5, names[k]
 
 
+@pytest.mark.parametrize("gated", [False, True], ids=["softplus", "gated"])
+@pytest.mark.parametrize("Dc,H,W", [(2, 9, 14), (4, 10, 56), (32, 9, 121), (3, 7, 190), (3, 6, 256), (2, 9, 300), (2, 5, 600)])
+def test_softplus_derivative_of_small_steps(s2d, Dc, H, W, gated):
+    """The derivative of the softplus where the step is small (raw projections around -4 to -8), element by element.  With every
+    decay exp(-1e6 * step) = 0 (steps of 2e-4 and more) the gradient of the step is x * dy * sum_n B C, so that of the raw
+    projection is known in 64 bits.
+    Bound: the positive 16-term sums, their factors and x, at most 24 roundings of 2^-24; the exponential's argument, up to 16
+    after the change of base, is rounded to 2^-21 (3.3e-7), the exponential, the sum and the reciprocal to an ulp or two
+    each (4e-7)."""
+    import torch
+    r = np.random.default_rng(17)
+    N, shape, states = 16, (1, Dc, H, W), (1, 16, H, W)
+    pos = lambda s: r.uniform(0.5, 2.0, s).astype(np.float32)
+    x, dy, Bm, Cm = pos(shape), pos(shape), pos(states), pos(states)
+    raw = r.uniform(-8.0, -3.0, shape).astype(np.float32)
+    bias = r.uniform(-0.5, 0.5, Dc).astype(np.float32)
+    A, skip = np.full((Dc, N), -1e6, np.float32), np.zeros(Dc, np.float32)
+    a = [torch.from_numpy(v).cuda() for v in (x, raw, bias, A, Bm, Cm, skip)]
+    t = (raw + bias[None, :, None, None]).astype(np.float64)                # one fp32 sum, as in the kernels
+    want = x.astype(np.float64) * dy * (Bm.astype(np.float64) * Cm).sum(1, keepdims=True) / (1.0 + np.exp(-t))
+    if gated:                                                              # z = 32: SiLU(z) = 32 to the last bit
+        z = torch.full(shape, 32.0, device="cuda:0")
+        got = s2d.scan2d_bwd_softplus_gated(*a, None, z, z, torch.from_numpy(dy).cuda())
+        want *= 32.0
+    else:
+        got = s2d.scan2d_bwd_softplus(*a, None, torch.from_numpy(dy).cuda())
+    bound = 24 * 2.0 ** -24 + 3.3e-7 + 4e-7
+    err = np.abs(s2d.to_host(got[1]).astype(np.float64) - want) / want
+    assert err.max() <= bound, f"ddelta_raw: {err.max():.2e}"
+    sums = want.sum((0, 2, 3))
+    assert (np.abs(s2d.to_host(got[2]).astype(np.float64) - sums) / sums).max() <= bound + H * W * 2.0 ** -24
+
+
 # ------------------------------------------------------------------ output gate of the block
 
 def _gated_inputs(w, seed):
