@@ -283,19 +283,28 @@ __device__ __forceinline__ Split split_bf16(float a, float b) {
     return s;
 }
 
+// Largest / smallest magnitude so far (fmaxf and fminf would first quiet each value: one more instruction apiece).
+__device__ __forceinline__ void max3_abs(float& m, uint32_t a, uint32_t b) { asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b)); }
+__device__ __forceinline__ void min3_abs(float& m, float a, float b) { asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b)); }
+
 // fp32, enough work for every SIMD, input channels in whole steps of 64: the layer as bf16 products (split_bf16).  A workgroup
 // (one per compute unit) splits its 16 NOT rows of Wt once and keeps them in LDS as MFMA operands; its 8 wavefronts walk over
 // pieces of 32 positions, whose channels they split on the way: a step of 32 channels is split beside the products of the
 // step before it (4 vector slots per product pass), its loads a step earlier still, across the end of one piece into the next.
 // The largest terms have accumulators of their own: theirs is the rounding that counts, once per 32 channels.
-// What is not finite in one of the parts (an infinity, a value that rounds to one) is not finite in the result, and what is so
-// small that its last part is lost gives a tiny result: a piece with such a result is formed again from fp32 products.
+// Outside of bf16's range an output is formed again from fp32 products, each by its own row of Wt and its own position alone:
+//   * not finite: an infinity or NaN among its operands, a value that rounds to infinity in bf16, a sum that overflowed;
+//   * too small beside its operands: the parts of a value are exact down to 2^-133 (products and sums keep what is subnormal), so
+//     up to 2^-134 of each input and of each weight may be lost, and of the output up to 768 * 2^-134 * (X + W), X and W the largest
+//     magnitudes of its position and its row.  Where |output| >= 2^-96 (X + W), or X or W is 0, that is below 2^-28 of it.
+// A piece is tested as a whole first, by the smallest output of a position and the largest weight of the slice.
 // Bound: the matrix pipe (half its time in use) and the clock under it: 256 -> 512 channels at 24576 positions take 43 us, with
 // all operands zero 37 us (scan2d_linear_stream_kernel 57 and 54 us).  Error against 64 bits, 2-norm: 0.9e-7 (2.9e-7).
 constexpr int kSplitWaves = 8;
+constexpr float kMost = 3.402823466e38f, kSmall = 0x1p-96f;
 template <int NOT, bool RES>
 __global__ __launch_bounds__(kSplitWaves * 64, 2) void scan2d_linear_split_kernel(const LinArgs p) {
-    extern __shared__ u32x4_t wl[];                        // [steps][NOT][3][64 lanes], then the bias
+    extern __shared__ u32x4_t wl[];                        // [steps][NOT][3][64 lanes], then bias and largest weights
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t slices = (uint32_t)p.ogroups, groups = gridDim.x / slices;
     const uint32_t wg = (blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
@@ -305,6 +314,13 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void scan2d_linear_split_kerne
     const int Cin = p.Cin, steps = Cin / 32, o0 = (int)slice * 16 * NOT;
     const uint32_t P = (uint32_t)p.P, ptiles = (uint32_t)p.ptiles, items = (uint32_t)p.waves, stride = groups * kSplitWaves;
 
+    float* const bl = reinterpret_cast<float*>(wl + steps * NOT * 3 * 64);   // bias and largest weight of the 16 NOT output channels
+    float* const wmax = bl + 16 * NOT;
+    if (threadIdx.x < 16 * NOT) {
+        bl[threadIdx.x] = p.bias != nullptr ? p.bias[min(o0 + (int)threadIdx.x, p.Cout - 1)] : 0.0f;
+        wmax[threadIdx.x] = 0.0f;
+    }
+    __syncthreads();
     // four fragments' loads at a time (past the last one it is loaded again)
     for (int f0 = wv; f0 < steps * NOT; f0 += 4 * kSplitWaves) {
         uint32_t r[4][8];
@@ -322,11 +338,16 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void scan2d_linear_split_kerne
             for (int e = 0; e < 4; ++e) s[e] = split_bf16(__uint_as_float(r[u][2 * e]), __uint_as_float(r[u][2 * e + 1]));
 #pragma unroll
             for (int q = 0; q < 3; ++q) wl[(f * 3 + q) * 64 + l] = u32x4_t{s[0].part[q], s[1].part[q], s[2].part[q], s[3].part[q]};
+            uint32_t most = 0u;                            // magnitudes compare like their bits
+#pragma unroll
+            for (int e = 0; e < 8; ++e) most = max(most, r[u][e] & 0x7fffffffu);
+            atomicMax(reinterpret_cast<uint32_t*>(wmax) + 16 * (f % NOT) + n, most);
         }
     }
-    float* const bl = reinterpret_cast<float*>(wl + steps * NOT * 3 * 64);   // bias of the 16 NOT output channels
-    if (threadIdx.x < 16 * NOT) bl[threadIdx.x] = p.bias != nullptr ? p.bias[min(o0 + (int)threadIdx.x, p.Cout - 1)] : 0.0f;
     __syncthreads();
+    float wmost = 0.0f;
+#pragma unroll
+    for (int o = 0; o < 16 * NOT; ++o) wmost = fmaxf(wmost, wmax[o]);
 
     struct Piece { const char* in; uint32_t boff, p0; int b; };
     auto piece = [&](uint32_t item) {
@@ -350,8 +371,10 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void scan2d_linear_split_kerne
 #pragma unroll
         for (int e = 0; e < 8; ++e) load_words_at<2>(bb + (size_t)e * P * 4u, off, raw[buf][e]);
     };
-    auto split_pair = [&](int buf, int pair) {             // two channels of one of the lane's two positions
+    float xmax[2] = {0.0f, 0.0f};                          // largest magnitude split of the lane's two positions
+    auto split_pair = [&](int buf, int pair) {             // two channels of one of them
         const int t = pair / 4, e = pair % 4;
+        max3_abs(xmax[t], raw[buf][2 * e][t], raw[buf][2 * e + 1][t]);
         const Split s = split_bf16(__uint_as_float(raw[buf][2 * e][t]), __uint_as_float(raw[buf][2 * e + 1][t]));
 #pragma unroll
         for (int q = 0; q < 3; ++q) x[buf][t][q][e] = s.part[q];
@@ -401,13 +424,17 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void scan2d_linear_split_kerne
         for (int ot = 0; ot < NOT; ++ot)
 #pragma unroll
             for (int t = 0; t < 2; ++t) acc[ot][t] = low[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        float xm[2] = {0.0f, 0.0f};
         for (int k = 0; k < steps; k += 2) {
             step(0, k);
             load(1, k + 3);
+            if (k + 2 == steps) {                          // what follows belongs to the next piece
+                xm[0] = xmax[0]; xm[1] = xmax[1];
+                xmax[0] = xmax[1] = 0.0f;
+            }
             step(1, k + 1);
             load(0, k + 4);
         }
-        float size = 0.0f;
         uint32_t add[RES ? NOT : 1][4][2];
 #pragma unroll
         for (int ot = 0; ot < NOT; ++ot)
@@ -422,26 +449,54 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void scan2d_linear_split_kerne
                     load_words_at<2>(res + ((size_t)cur.b * p.Cout + r0) * P, ((uint32_t)min(4 * g + i, p.Cout - 1 - r0) * P + pos.s) * 4u, add[ot][i]);
             }
         }
+        bool again = false;
 #pragma unroll
-        for (int ot = 0; ot < NOT; ++ot)
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) size += fabsf(acc[ot][t][i]);
-        // finite, and not so small that parts of 2^-133 count (values below 2^-90 have lost up to 2^-43 of themselves)
-        if (__any(!(size <= 3.402823466e38f) || (size > 0.0f && size < 8e-28f))) {
+        for (int t = 0; t < 2; ++t) {
+            xm[t] = fmaxf(xm[t], __shfl_xor(xm[t], 16));   // the four lanes of a position hold 8 channels of every 32 each
+            xm[t] = fmaxf(xm[t], __shfl_xor(xm[t], 32));
+            float size = 0.0f, least = kMost;
 #pragma unroll
             for (int ot = 0; ot < NOT; ++ot)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) acc[ot][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            for (int c = g; c < Cin; c += 4) {
-                const float* in = static_cast<const float*>(p.in) + ((size_t)cur.b * Cin + c) * P + pos.s;
+                for (int i = 0; i < 4; i += 2) {
+                    size += fabsf(acc[ot][t][i]);
+                    size += fabsf(acc[ot][t][i + 1]);
+                    min3_abs(least, acc[ot][t][i], acc[ot][t][i + 1]);
+                }
+            again |= !((size <= kMost) & ((xm[t] == 0.0f) | (least >= fmaf(kSmall, xm[t], kSmall * wmost))));
+        }
+        if (__any(again)) {
+            uint32_t redo = 0u;                            // a bit per output of the lane
+#pragma unroll
+            for (int ot = 0; ot < NOT; ++ot) {
+                const f32x4 wm = *reinterpret_cast<const f32x4*>(wmax + 16 * ot + 4 * g);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float v = fabsf(acc[ot][t][i]);
+                        const bool good = (v <= kMost) & ((xm[t] == 0.0f) | (wm[i] == 0.0f) | (v >= fmaf(kSmall, xm[t], kSmall * wm[i])));
+                        redo |= good ? 0u : 1u << (8 * ot + 4 * t + i);
+                    }
+            }
+            if (__any(redo != 0u)) {
 #pragma unroll
                 for (int ot = 0; ot < NOT; ++ot) {
-                    const float w = static_cast<const float*>(p.Wt)[(size_t)min(o0 + 16 * ot + n, p.Cout - 1) * Cin + c];
+                    f32x4 full[2] = {};
+                    uint32_t row = (uint32_t)min(o0 + 16 * ot + n, p.Cout - 1);
+                    asm volatile("" : "+v"(row));          // the address is formed here: from in front of the loops it would hold registers there
+                    for (int c = 0; c < Cin; c += 4) {
+                        const float* in = static_cast<const float*>(p.in) + ((size_t)cur.b * Cin + c + g) * P + pos.s;
+                        const float w = static_cast<const float*>(p.Wt)[(size_t)row * Cin + c + g];
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) acc[ot][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, in[t], acc[ot][t], 0, 0, 0);
+                        for (int t = 0; t < 2; ++t) full[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, in[t], full[t], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[ot][t][i] = (redo >> (8 * ot + 4 * t + i) & 1u) != 0u ? full[t][i] : acc[ot][t][i];
                 }
+                load_w(0, 0);                              // again: its registers were needed here
             }
         }
 #pragma unroll
@@ -535,7 +590,7 @@ int launch_sized(const LinArgs& a, hipStream_t stream) {
                 const Kernel k = n == 4 ? (a.res ? scan2d_linear_split_kernel<4, true> : scan2d_linear_split_kernel<4, false>)
                                : n == 3 ? (a.res ? scan2d_linear_split_kernel<3, true> : scan2d_linear_split_kernel<3, false>)
                                         : (a.res ? scan2d_linear_split_kernel<2, true> : scan2d_linear_split_kernel<2, false>);
-                const size_t lds = (size_t)a.Cin / 32 * n * 3072 + (size_t)n * 64;
+                const size_t lds = (size_t)a.Cin / 32 * n * 3072 + (size_t)n * 128;
                 if (lds > 65536 && !allow_large_lds(reinterpret_cast<const void*>(k), lds)) return SCAN2D_ERR_LAUNCH_FAILED;
                 hipLaunchKernelGGL(k, dim3(256), dim3(kSplitWaves * 64), lds, stream, r);
                 return SCAN2D_OK;

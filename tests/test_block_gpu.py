@@ -717,3 +717,40 @@ def test_linear_fp32_as_bf16_products_beyond_their_range(s2d):
     size = (W.double().abs() @ x.double().abs().reshape(Cin, P))
     assert ((got.double() - ref).abs()[ok] <= ((2.0 ** -22 + 136 * 2.0 ** -24) * size + 1e-44)[ok]).all()
     assert (got[:, 6000] == 0).all()
+
+
+@pytest.mark.parametrize("Cin,Cout,with_res", [(128, 256, False), (256, 130, True), (512, 256, True)])
+def test_linear_fp32_small_and_huge_operands_beside_ordinary_ones(s2d, Cin, Cout, with_res):
+    """Single positions and rows of tiny values, tiny values beside huge weights, zero positions and rows, each next to ordinary
+    data: every output within the bound of its own products, and an ordinary output the same bits whatever the others hold."""
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(9)
+    P = 12001
+    x = torch.randn((1, Cin, 1, P), device="cuda:0", generator=g)
+    W = torch.randn((Cout, Cin), device="cuda:0", generator=g) * 0.1
+    res = torch.zeros((1, Cout, 1, P), device="cuda:0") if with_res else None
+    plain = s2d.block_linear(x, W, residual=res).reshape(Cout, P)
+    rows, cols = [3, 17, 40, 41, 70], [5, 64, 1000, 1001, 6000, P - 1]
+    x[0, :, 0, 5] *= 1e-36
+    x[0, :, 0, 64] *= 1e-30
+    x[0, :, 0, 1000] = 0
+    x[0, :, 0, 1001] = torch.where(torch.arange(Cin, device="cuda:0") % 7 == 0, x[0, :, 0, 1001] * 1e-41, 0)
+    x[0, :, 0, 6000] *= 1e-33
+    x[0, 1, 0, P - 1] = float("inf")
+    W[3] *= 1e-36
+    W[17] *= 1e-31
+    W[40] *= 1e37
+    W[41] = 0
+    W[70, 5:] *= 1e-38
+    got = s2d.block_linear(x, W, residual=res).reshape(Cout, P)
+    X = x.double().reshape(Cin, P)
+    ref, size = W.double() @ X, W.double().abs() @ X.abs()
+    ok = torch.isfinite(ref.float())
+    assert torch.equal(torch.isfinite(got), ok)
+    # products below 2^-22 of the largest aside (see above), a rounding per 4 channels at most, each also to the subnormals' 2^-149
+    bound = (2.0 ** -22 + (Cin / 4 + 4) * 2.0 ** -24) * size + (Cin + 4) * 2.0 ** -149
+    assert ((got.double() - ref).abs()[ok] <= bound[ok]).all()
+    assert (got[:, 1000] == 0).all() and (got[41, : P - 1] == 0).all()
+    keep_r = torch.tensor([r for r in range(Cout) if r not in rows], device="cuda:0")
+    keep_c = torch.tensor([c for c in range(P) if c not in cols], device="cuda:0")
+    assert torch.equal(got[keep_r][:, keep_c], plain[keep_r][:, keep_c])
