@@ -268,8 +268,9 @@ __global__ __launch_bounds__(256, 1) void scan2d_linear_stream_kernel(const LinA
 }
 
 // fp32 as sums of bf16: x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1) and x3 the rest, which has at most 8 bits, so the
-// sum is x itself.  Of a product's nine terms the six largest are formed, on v_mfma_f32_16x16x32_bf16 (16 times the fp32
-// matrix rate); the other three are below 2^-23 of it, typically 2^-26.
+// sum is x itself.  Of a product's nine terms all but x3 w3 are formed, on v_mfma_f32_16x16x32_bf16 (16 times the fp32
+// matrix rate); it is below 2^-33 of the product.  (Six terms take 43 us where eight take 51, but a sum of one large product is then
+// up to 1.1e-7 off, not 6.0e-8 as by fp32 products.)
 struct Split { uint32_t part[3]; };                        // of two values, packed
 __device__ __forceinline__ Split split_bf16(float a, float b) {
     Split s;
@@ -298,8 +299,8 @@ __device__ __forceinline__ void min3_abs(float& m, float a, float b) { asm("v_mi
 //     up to 2^-134 of each input and of each weight may be lost, and of the output up to 768 * 2^-134 * (X + W), X and W the largest
 //     magnitudes of its position and its row.  Where |output| >= 2^-96 (X + W), or X or W is 0, that is below 2^-28 of it.
 // A piece is tested as a whole first, by the smallest output of a position and the largest weight of the slice.
-// Bound: the matrix pipe (half its time in use) and the clock under it: 256 -> 512 channels at 24576 positions take 43 us, with
-// all operands zero 37 us (scan2d_linear_stream_kernel 57 and 54 us).  Error against 64 bits, 2-norm: 0.9e-7 (2.9e-7).
+// Bound: the matrix pipe (half its time in use) and the clock under it: 256 -> 512 channels at 24576 positions take 47 to 50 us, with
+// all operands zero 41 us (scan2d_linear_stream_kernel 55 and 53 us).  Error against 64 bits, 2-norm: 0.9e-7 (2.9e-7).
 constexpr int kSplitWaves = 8;
 constexpr float kMost = 3.402823466e38f, kSmall = 0x1p-96f;
 template <int NOT, bool RES>
@@ -398,12 +399,13 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void scan2d_linear_split_kerne
                     to[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[at][wq]), __builtin_bit_cast(bf16x8, x[buf][t][xq]), to[t], 0, 0, 0);
             };
 #pragma unroll
-            for (int part = 0; part < 3; ++part) {
-                if (part == 0) { term(low[ot], 2, 0); term(acc[ot], 0, 0); }
-                else if (part == 1) { term(low[ot], 0, 2); term(low[ot], 1, 1); }
+            for (int part = 0; part < 4; ++part) {
+                if (part == 0) { term(low[ot], 2, 1); term(acc[ot], 0, 0); }
+                else if (part == 1) { term(low[ot], 1, 2); term(low[ot], 2, 0); }
+                else if (part == 2) { term(low[ot], 0, 2); term(low[ot], 1, 1); }
                 else { term(low[ot], 1, 0); term(low[ot], 0, 1); }
 #pragma unroll
-                for (; pair < ((ot * 3 + part + 1) * 8 + 3 * NOT - 1) / (3 * NOT); ++pair) split_pair(buf ^ 1, pair);
+                for (; pair < ((ot * 4 + part + 1) * 8 + 4 * NOT - 1) / (4 * NOT); ++pair) split_pair(buf ^ 1, pair);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -565,23 +567,28 @@ int launch_sized(const LinArgs& a, hipStream_t stream) {
         }
     }
     if constexpr (Elem<T>::kBytes == 4) {
-        // bf16 products (us, split and fp32 products: 256 -> 512 channels at 25527 positions 47 and 65..74, at 8192 18 and 23;
-        // 512 -> 256 at 25527 48..52 and 68..79; 128 -> 256 at 16384 13.5 and 14.0, at 8192 9.7 and 8.5: the line lies between
-        // the last two, in pieces of 32 positions x 16 outputs x 32 channels).  LDS holds 32 rows of Wt up to 768 channels.
+        // 16 NOT output channels per piece: the fewest rounds of 1024 wavefronts, counted in their products
+        const auto cost = [&](long long n) { return (tiles * ((o16 + n - 1) / n) + 1023) / 1024 * n; };
+        const bool stream_form = a.Cin % 64 == 0 && tiles * o16 >= 2048 && tiles * o16 < (1LL << 30);
+        // bf16 products where an estimate of both forms in us says so, fitted to 344 shapes (128 to 768 -> 32 to 1024 channels, 800 to
+        // 40000 positions; mean error 3 to 4 %, and the chip's power moves the bf16 side by as much again: hence the 5 %).  By bf16
+        // and by fp32 products, us: 256 -> 512 channels at 25527 positions 50.8 and 64.0, at 8192 19.9 and 21.7, 384 -> 192 at 12000 19.9
+        // and 28.6; fp32 products win where a round or two of wavefronts is all there is: 384 -> 256 at 3200 11.1 and 9.8, 512 -> 128 at
+        // 8000 14.0 and 12.3.  LDS holds 32 rows of Wt up to 768 channels.
         const long long pieces = (a.P + 31) / 32 * a.Bt;
-        if (a.Cin % 64 == 0 && a.Cin >= 128 && a.Cin <= 768 && 25 * a.P * 4 < (1LL << 32) && pieces * o16 * (a.Cin / 32) >= 18000 &&
-            pieces < (1LL << 30) && o16 <= 512) {
-            // 16 NOT output channels per workgroup, as many as its LDS holds: the fewest rounds of SIMDs, in products and
-            // the work of splitting the inputs
-            const auto cost = [&](long long n) {
+        if (a.Cin % 64 == 0 && a.Cin >= 128 && a.Cin <= 768 && 25 * a.P * 4 < (1LL << 32) && pieces < (1LL << 30) && o16 <= 512 && tiles * o16 < (1LL << 30)) {
+            const double m = (double)(stream_form ? std::min(cost(2), cost(4)) : cost(1));
+            const double fp32_us = 2.7 + 0.75 * m + a.Cin * (0.0147 * m + 0.0014);
+            // 16 n output channels per workgroup, as many as its LDS holds: the fewest rounds of SIMDs, in products and the work of
+            // splitting the inputs
+            const auto rounds = [&](long long n) {
                 const long long slices = (o16 + n - 1) / n, groups = 256 / slices;
-                if (a.Cin / 32 * n * 3072 > 150 * 1024 || groups < 1) return 1LL << 40;
-                return (pieces + groups * 4 - 1) / (groups * 4) * (192 * n + 150);
+                return a.Cin / 32 * n * 3072 > 150 * 1024 || groups < 1 ? 1LL << 40 : (pieces + groups * 4 - 1) / (groups * 4);
             };
             int n = 2;
             for (int k = 3; k <= 4; ++k)
-                if (cost(k) <= cost(n)) n = k;
-            if (cost(n) < (1LL << 40)) {
+                if (rounds(k) * (256 * k + 150) <= rounds(n) * (256 * n + 150)) n = k;
+            if (2.6 + 0.97 * n + a.Cin * ((double)rounds(n) * (0.0053 * n + 0.0043) + 0.0018) < 0.95 * fp32_us) {
                 LinArgs r = a;
                 r.ogroups = (int)((o16 + n - 1) / n);
                 r.ptiles = (a.P + 31) / 32;
@@ -596,9 +603,7 @@ int launch_sized(const LinArgs& a, hipStream_t stream) {
                 return SCAN2D_OK;
             }
         }
-        // 16 NOT output channels per piece: the fewest rounds of 1024 wavefronts, counted in their products
-        const auto cost = [&](long long n) { return (tiles * ((o16 + n - 1) / n) + 1023) / 1024 * n; };
-        if (a.Cin % 64 == 0 && tiles * o16 >= 2048 && tiles * o16 < (1LL << 30)) {
+        if (stream_form) {
             LinArgs r = a;
             const bool four = cost(4) <= cost(2);
             r.ogroups = (int)((o16 + (four ? 3 : 1)) / (four ? 4 : 2));

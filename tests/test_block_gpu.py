@@ -719,7 +719,7 @@ def test_linear_fp32_as_bf16_products_beyond_their_range(s2d):
     assert (got[:, 6000] == 0).all()
 
 
-@pytest.mark.parametrize("Cin,Cout,with_res", [(128, 256, False), (256, 130, True), (512, 256, True)])
+@pytest.mark.parametrize("Cin,Cout,with_res", [(128, 256, False), (256, 510, True), (256, 200, False), (512, 256, True)])
 def test_linear_fp32_small_and_huge_operands_beside_ordinary_ones(s2d, Cin, Cout, with_res):
     """Single positions and rows of tiny values, tiny values beside huge weights, zero positions and rows, each next to ordinary
     data: every output within the bound of its own products, and an ordinary output the same bits whatever the others hold."""
@@ -754,3 +754,29 @@ def test_linear_fp32_small_and_huge_operands_beside_ordinary_ones(s2d, Cin, Cout
     keep_r = torch.tensor([r for r in range(Cout) if r not in rows], device="cuda:0")
     keep_c = torch.tensor([c for c in range(P) if c not in cols], device="cuda:0")
     assert torch.equal(got[keep_r][:, keep_c], plain[keep_r][:, keep_c])
+
+
+# 4, 3 and 2 blocks of 16 rows per workgroup; output channels off the 16 grid, positions off the grid of 32, several batch items.
+@pytest.mark.parametrize("Bt,Cin,Cout,P,with_res", [
+    (1, 128, 256, 12000, False), (1, 256, 512, 8192, False), (1, 512, 256, 9001, True), (2, 192, 200, 12001, True), (5, 320, 33, 13333, False),
+    (3, 768, 100, 12001, True)])
+def test_linear_fp32_one_large_product_per_output(s2d, Bt, Cin, Cout, P, with_res):
+    """Rows of Wt with one weight: every output is one product, rounded once - half an ulp, as by fp32 products (and 2^-8 of
+    another one for the sum of the small terms)."""
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(10)
+    x = torch.randn((Bt, Cin, 1, P), device="cuda:0", generator=g)
+    W = torch.zeros((Cout, Cin), device="cuda:0")
+    W[torch.arange(Cout), torch.arange(Cout) % Cin] = torch.rand(Cout, device="cuda:0", generator=g) + 1.0
+    res = torch.zeros((Bt, Cout, 1, P), device="cuda:0") if with_res else None
+    got = s2d.block_linear(x, W, torch.zeros(Cout, device="cuda:0") if with_res else None, res).double().reshape(Bt, Cout, P)
+    for b in range(Bt):
+        ref = W.double() @ x[b].double().reshape(Cin, P)
+        assert ((got[b] - ref).abs() <= (1.0 + 2.0 ** -7) * 2.0 ** -24 * ref.abs()).all()
+    # ordinary data: dropped terms of 2^-33, two roundings of the large sum per 32 channels (the matrix core drops what is below
+    # the last bit of the sum), a few at the end
+    W = torch.randn((Cout, Cin), device="cuda:0", generator=g) * Cin ** -0.5
+    got = s2d.block_linear(x, W, None, res).double().reshape(Bt, Cout, P)
+    for b in range(Bt):
+        X = x[b].double().reshape(Cin, P)
+        assert ((got[b] - W.double() @ X).abs() <= (2.0 ** -33 + (2 * Cin / 32 + 4) * 2.0 ** -24) * (W.double().abs() @ X.abs())).all()
