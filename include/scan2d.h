@@ -36,7 +36,9 @@
  * Thread safety: entry points may be called concurrently from several host threads.
  *
  * Limits of this version: 1 <= N <= 64; N*H*W < 2^27 (the kernels address one map's states
- * with 32-bit lane offsets); any H, W >= 1 in the forward and in the backward (maps wider than
+ * with 32-bit lane offsets; in the forward of maps wider than 32 columns the offsets span several maps, depending
+ * on the tiling: 68*N*H*W < 2^31 is taken by all, 20*N*H*W >= 2^31 by none); any H, W >= 1 within that
+ * in the forward and in the backward (maps wider than
  * one lane-group panel are swept panel by panel and need workspace for the carries between the
  * panels, see scan2d_workspace_bytes).  Shapes outside these limits return SCAN2D_ERR_BAD_SHAPE.
  * A launch holds fewer than 2^32 threads: the scans take Bt * Dc < 2^22 maps in a call whatever their

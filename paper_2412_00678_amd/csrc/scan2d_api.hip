@@ -359,7 +359,8 @@ int rank_fwd(const scan2d_desc* d, FwdChoice* out, bool sp, bool ma, bool cf) {
             const double cost = fwd_cost(d, c);
             if (!found || cost < best) { best = cost; *out = c; found = true; }
         }
-    return found ? SCAN2D_OK : SCAN2D_ERR_BAD_SHAPE;
+    // tall narrow maps whose states the lane offsets of the tilings above do not span: this kernel addresses each state by itself
+    return found || fill_small(d, 2, sp, out) ? SCAN2D_OK : SCAN2D_ERR_BAD_SHAPE;
 }
 
 int choose_fwd(const scan2d_desc* d, FwdChoice* out, bool sp = false, bool ma = true, bool cf = false) {

@@ -102,7 +102,7 @@ inline FwdKernel lookup_fwd_kernel_unaligned_mask(int LG, int K, int NW, int wav
 FwdKernel fwd_kernel_av_f32();
 FwdKernel fwd_kernel_av_bf16();
 
-// Narrow maps (W <= 32): KS columns per lane, NW = states per lane group of the wave's four (KS = 2: up to 16 states).
+// Narrow maps (W <= 32): KS columns per lane, NW = states per lane group of the wave's four (gate with KS = 2: up to 16 states).
 FwdKernel fwd_small_kernel_f32(int KS, int NW, bool sp, bool gate);
 // maps of at most 16 x 16 positions and 16 states, one workgroup per map, both recurrences as parallel scans
 // (scan2d_fwd_tile16.hip)
@@ -115,6 +115,7 @@ inline FwdKernel lookup_fwd_small_kernel(int KS, int NW) {
     if (KS == ks && NW == nw) return scan2d_fwd_small_kernel<T, ks, nw, pd, SP, GATE>;
     SCAN2D_X(1, 1, 4) SCAN2D_X(1, 2, 4) SCAN2D_X(1, 4, 4) SCAN2D_X(1, 8, 2) SCAN2D_X(1, 16, 2)
     SCAN2D_X(2, 1, 4) SCAN2D_X(2, 2, 4) SCAN2D_X(2, 4, 4)
+    if constexpr (!GATE) { SCAN2D_X(2, 8, 2) SCAN2D_X(2, 16, 1) }
 #undef SCAN2D_X
     return nullptr;
 }

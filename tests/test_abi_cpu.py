@@ -168,6 +168,18 @@ def test_every_shape_has_a_forward_plan_within_the_hardware_limits(lib):
                     assert f["workspace"] == lib.workspace_bytes(d, lib.PASS_FWD), where
 
 
+def test_tall_narrow_maps_have_a_forward_plan(lib):
+    """Up to the limit of N * H * W < 2^27, beyond what the 32-bit lane offsets of the wider tilings span."""
+    for dtype in (0, 1):
+        for maps in ((1, 1), (1, 8), (3, 300)):
+            for W in range(1, 33):
+                for N in (1, 5, 9, 12, 15, 16, 17, 33, 64):
+                    for part in (0.24, 0.5, 0.81, 1.0):
+                        d = lib.Desc(*maps, max(1, int(part * 134217727) // (N * W)), W, N, dtype, 0)
+                        f = plan(lib, d, lib.PASS_FWD)
+                        assert f["form"] != "small" or (W <= 16 * f["K"] and 4 * f["NW"] >= N and f["wgs"] == -(-maps[0] * maps[1] // 4)), (maps, W, N, f)
+
+
 def test_backward_plans_cover_every_shape_the_forward_accepts(lib):
     for dtype in (0, 1):
         for W in SWEEP_W:

@@ -160,7 +160,7 @@ VARIANT_CASES = [
     ("16,4,4", (1, 6, 16, 9, 61)), ("64,4,4", (1, 6, 16, 9, 203)), ("64,4,2", (1, 3, 4, 7, 777)),
     ("16,4,4", (1, 3, 16, 7, 150)), ("16,4,4", (1, 3, 10, 7, 150)), ("16,8,4", (1, 3, 10, 7, 128)),
     # narrow-map kernel with two columns per lane forced on a map that one column per lane would cover
-    ("16,2", (1, 5, 16, 9, 14)), ("16,1", (2, 3, 8, 9, 16)),
+    ("16,2", (1, 5, 16, 9, 14)), ("16,1", (2, 3, 8, 9, 16)), ("16,2", (2, 5, 20, 9, 29)), ("16,2", (1, 3, 64, 7, 30)),
 ]
 
 
@@ -169,6 +169,15 @@ VARIANT_CASES = [
 def test_every_kernel_variant(s2d, variant, shape, dtype):
     Bt, Dc, N, H, W = shape
     check_fwd(s2d, wl.Workload("var", Bt, Dc, N, H, W, dtype, mask_frac=0.25), seed=5, variant=variant)
+
+
+@pytest.mark.parametrize("dtype,shape", [(wl.F32, (1, 2, 9, 200000, 18)), (wl.BF16, (1, 1, 15, 100000, 30))], ids=["f32", "bf16"])
+def test_tall_narrow_maps(s2d, shape, dtype):
+    """Maps whose states the 32-bit lane offsets of the wider tilings do not span run in the narrow-map kernel."""
+    Bt, Dc, N, H, W = shape
+    plan = s2d.describe_plan(s2d.Desc(Bt, Dc, H, W, N, dtype, 0), s2d.PASS_FWD)
+    assert "form=small LG=16 K=2 " in plan, plan
+    check_fwd(s2d, wl.Workload("tall", Bt, Dc, N, H, W, dtype, mask_frac=0.25), seed=6)
 
 
 # The form whose lane groups share the per-position work through LDS: LG,K,NW,WAVES,RPB forced on shapes with
