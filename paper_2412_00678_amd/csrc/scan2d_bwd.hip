@@ -557,8 +557,11 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     // such a shape has to fit it with the plan chosen here too
     if (best.total > SCAN2D_STATIC_SCRATCH_BYTES && plain.total <= SCAN2D_STATIC_SCRATCH_BYTES) best = fit;
     if (force_gs >= 1 && force_gs <= gs_lds && force_gs <= d->Dc) best = set(force_gs, 1);
-    if (force_seg >= 1 && pl.shared && !cf && N == kGcStates && maps < 1000000) best = set(best.GS, std::max(1, std::min({force_seg, best.nb, held})));
-    if (best.lds_bytes > 160 * 1024 || (best.S > 1 && best.GS > 2 * best.seg_bands * best.RB)) return false;
+    if (force_seg >= 1 && pl.shared && !cf && N == kGcStates && maps < 1000000) {
+        const BwdPlan q = set(best.GS, std::max(1, std::min({force_seg, best.nb, held})));
+        if (q.S == 1 || q.GS <= 2 * q.seg_bands * q.RB) best = q;      // ignored where the segments' rows do not hold what enters them
+    }
+    if (best.lds_bytes > 160 * 1024) return false;
     *out = best;
     return true;
 }

@@ -141,6 +141,18 @@ def test_row_segments_keep_their_sums_inside_one_checkpoint_row(lib):
     assert most == 15
 
 
+@pytest.mark.parametrize("variant,shape", [("16,4,4,16,1,2", (1, 16, 8, 64)), ("16,4,4,12,1,8", (1, 16, 32, 64))])
+def test_forced_segments_that_do_not_fit_are_ignored(lib, variant, shape):
+    """Segments of fewer rows than hold what enters the channels of a job: the call takes the plan without them."""
+    Bt, Dc, H, W = shape
+    d = lib.Desc(Bt, Dc, H, W, 16, 0, 0)
+    with lib.forced_variant(lib.TUNE_BWD, variant.rsplit(",", 1)[0]):
+        one = plan(lib, d, lib.PASS_BWD)
+    with lib.forced_variant(lib.TUNE_BWD, variant):
+        assert plan(lib, d, lib.PASS_BWD) == one
+    assert one["GS"] == int(variant.split(",")[3]) and one["segments"] == 1
+
+
 def test_every_shape_has_a_forward_plan_within_the_hardware_limits(lib):
     for dtype in (0, 1):
         for W in SWEEP_W:
