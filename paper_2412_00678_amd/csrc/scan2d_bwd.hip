@@ -209,7 +209,7 @@ enum { kGcPlain = 0, kGcSoftplus = 1, kGcGated = 2 };
 struct GcarryArgs {
     const void* delta; const float* delta_bias; const float* A; const void* Cm; const void* dy; const void* z;
     float* pB; float* pC;
-    int Dc, H, W, S, seg_rows, GS, CG, part_row;
+    int Dc, H, W, seg_rows, GS, CG, part_row;
     unsigned waves, cols;                                  // wavefronts in all; 64-column pieces of a map
 };
 constexpr int kGcStates = 16;
@@ -783,7 +783,7 @@ int bwd_launch(const scan2d_desc* d, const void* x, const void* delta, const flo
         GcarryArgs g;
         g.delta = a.delta; g.delta_bias = delta_bias; g.A = A; g.Cm = Cm; g.dy = dy; g.z = z;
         g.pB = a.pB; g.pC = a.pC; g.GS = pl.GS; g.CG = pl.CG; g.part_row = pl.part_chunked ? pl.LG * pl.K : d->W;
-        g.Dc = d->Dc; g.H = d->H; g.W = d->W; g.S = pl.S; g.seg_rows = pl.seg_bands * pl.RB;
+        g.Dc = d->Dc; g.H = d->H; g.W = d->W; g.seg_rows = pl.seg_bands * pl.RB;
         g.cols = (unsigned)((d->W + 63) / 64);
         g.waves = (unsigned)((unsigned long long)maps * g.cols);           // rank_plan: fits
         const int form = z != nullptr ? kGcGated : (softplus ? kGcSoftplus : kGcPlain);

@@ -117,16 +117,6 @@ __device__ __forceinline__ void group_scan_left_any(float* P, float* Q, float* C
         group_scan_left<LG, S>(P, Q, C);
     }
 }
-// Value held by the lane to the right inside the lane group (0 for the group's last lane).
-template <int LG>
-__device__ __forceinline__ float from_right_any(float v) {
-    if constexpr (LG == 32) {
-        const float r = from_right<64>(v);
-        return (threadIdx.x & 31u) == 31u ? 0.0f : r;
-    } else {
-        return from_right<LG>(v);
-    }
-}
 
 // Value held by the lane to the left inside the lane group (0 for the group's first lane).
 template <int LG>
