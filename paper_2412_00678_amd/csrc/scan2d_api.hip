@@ -267,8 +267,10 @@ double fwd_cost(const scan2d_desc* d, const FwdChoice& c) {
     const double maps = (double)d->Bt * d->Dc;
     const double wgs = std::ceil(maps / c.MPW);
     // eight rows per batch: twice the loads in flight where a compute unit has one workgroup; it would not hold more of them
-    // (64x64 fp32, us, 8 and 4 rows: 256 maps 14.4 and 15.8, 384 maps of 40x60 13.7 and 12.6)
-    if (c.shared && c.LG == 16 && c.RPB == 8 && wgs > 256.0) return 1e30;
+    // (64x64 fp32, us, 8 and 4 rows: 256 maps 14.4 and 15.8, 384 maps of 40x60 13.7 and 12.6).  Whole batches run, so that heights
+    // just past one lose: a batch of eight takes 1.4 us and one of four 0.8 (256 maps of 9, 17, 26, 35 rows 5.7, 7.3, 8.3, 10.3
+    // and 4.8, 6.6, 8.1, 10.2 us; of 23, 32, 47, 56 rows 7.4, 8.5, 11.9, 12.7 and 7.7, 8.9, 12.7, 13.9)
+    if (c.shared && c.LG == 16 && c.RPB == 8 && (wgs > 256.0 || 7 * ((d->H + 7) / 8) + 2 >= 4 * ((d->H + 3) / 4))) return 1e30;
     if (c.shared && c.LG == 32 && d->W <= 64) return 1e30;                           // half of the lanes past the map
     const double c_core = bf16 ? 10.5 : 8.5;
     // a lone recurrence pads its DPP wait states (16- and 32-lane scans; the wave-wide scan has enough steps of its own)

@@ -267,6 +267,13 @@ def test_benchmark_configurations_take_the_intended_forms(lib):
     assert (b["form"], b["LG"], b["K"], b["NW"]) == ("banded-shared", 16, 12, 1) and b["wgs"] * b["GS"] >= 4 * 512 // 1
 
 
+@pytest.mark.parametrize("H,rows", [(1, 4), (9, 4), (12, 4), (17, 4), (26, 4), (35, 4), (23, 8), (32, 8), (47, 8), (64, 8)])
+def test_rows_per_batch_follow_the_height(lib, H, rows):
+    """Whole batches run: eight rows per batch only where that many rows are there."""
+    f = plan(lib, lib.Desc(1, 256, H, 60, 16, 0, 0), lib.PASS_FWD)
+    assert (f["form"], f["LG"], f["NW"], f["RPB"]) == ("shared", 16, 1, rows), f
+
+
 def test_wide_grids_take_the_shared_producer_forms(lib):
     # 257 to 1024 columns, 16 states, one map per compute unit: wave-wide groups with 8, 12 or 16 columns per lane
     for W, K in ((300, 8), (400, 8), (512, 8), (513, 12), (600, 12), (768, 12), (769, 16), (1000, 16), (1024, 16)):
