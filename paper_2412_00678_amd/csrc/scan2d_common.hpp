@@ -194,6 +194,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
+// The same bits by integer arithmetic, for one place where that is faster (scan2d_fwd_shared.hpp).
+__device__ __forceinline__ uint32_t f32_to_bf16_bits_int(float f) {
+    const uint32_t u = __float_as_uint(f);
+    const uint32_t r = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+    return ((u & 0x7fffffffu) > 0x7f800000u) ? ((u >> 16) | 0x40u) : r;
+}
+
 template <typename T> __device__ __forceinline__ uint32_t to_elem_bits(float f) {
     if constexpr (Elem<T>::kBytes == 4) return __float_as_uint(f);
     else return f32_to_bf16_bits(f);

@@ -102,6 +102,10 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
     static_assert(RPB % 2 == 0, "rows are read from LDS one ahead, two register sets");
     constexpr int VEC = CT % 4 == 0 ? 4 : (CT % 2 == 0 ? 2 : 1);
     constexpr int NV = CT / VEC, VPR = PANEL / VEC;
+    // bf16, four states per lane, four cells per vector: rounded by integer arithmetic, more instructions and yet faster on inputs
+    // that change from call to call (us, integer and v_cvt_pk_bf16_f32: 6144 maps of 56x56 134.0 and 135.5, 12288 of 21x40 112.0 and
+    // 114.5; 3072 of 64x64 82.0 and 82.3).  The other tilings gain 0.5 to 5 % by the instruction, this one with two cells 1 %.
+    constexpr bool INT_ROUND = Elem<T>::kBytes == 2 && NW == 4 && VEC == 4 && !GATE;
     constexpr int SC = (NW < 4 ? NW : (K >= 12 ? 2 : 4));
     static_assert(NW % SC == 0, "state chunking");
     constexpr int RS = fwd_rows_per_scan<LG, K, NW, RPB, SKEW>();
@@ -542,6 +546,10 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
 #pragma clang fp contract(off)                             // with and without the gate give the same bits
                         out[e] = acc[e] + sk_cur[v * VEC + e];
                     }
+                    auto store_cell = [](T* dst, float val) {
+                        if constexpr (INT_ROUND) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)f32_to_bf16_bits_int(val);
+                        else store_elem(dst, val);
+                    };
                     auto store_vec = [&](T* base, const float* val) {
                         T* dst = base + (size_t)i * W + cell_col[v];
                         if (cell_col[v] + VEC <= W) {
@@ -553,17 +561,19 @@ __global__ __launch_bounds__(WAVES * 64) void scan2d_fwd_shared_kernel(const Fwd
                             } else if (VEC >= 2 && (((size_t)i * W + cell_col[v]) & 1u) == 0u) {   // pairs on dword boundaries
                                 uint32_t bits[VEC >= 2 ? VEC / 2 : 1];
 #pragma unroll
-                                for (int e = 0; e < VEC / 2; ++e)
-                                    bits[e] = pack_bf16x2(val[2 * e], val[2 * e + 1]);
+                                for (int e = 0; e < VEC / 2; ++e) {
+                                    if constexpr (INT_ROUND) bits[e] = f32_to_bf16_bits_int(val[2 * e]) | (f32_to_bf16_bits_int(val[2 * e + 1]) << 16);
+                                    else bits[e] = pack_bf16x2(val[2 * e], val[2 * e + 1]);
+                                }
                                 store_words<(VEC >= 2 ? VEC / 2 : 1)>(reinterpret_cast<uint32_t*>(dst), bits);
                             } else {
 #pragma unroll
-                                for (int e = 0; e < VEC; ++e) store_elem(dst + e, val[e]);
+                                for (int e = 0; e < VEC; ++e) store_cell(dst + e, val[e]);
                             }
                         } else {
 #pragma unroll
                             for (int e = 0; e < VEC; ++e)
-                                if (cell_col[v] + e < W) store_elem(dst + e, val[e]);
+                                if (cell_col[v] + e < W) store_cell(dst + e, val[e]);
                         }
                     };
                     if constexpr (GATE) {
