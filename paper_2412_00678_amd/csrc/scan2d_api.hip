@@ -287,9 +287,13 @@ double fwd_cost(const scan2d_desc* d, const FwdChoice& c) {
     double row = c.K * c.NW * c_core + c.NW * c_scan + pos + (c.shared ? 8.0 : 35.0) + c_red;
     if (!c.fast) row *= 1.6;
     if (c.multi) row += 8.0 * c.NW;
-    // the instantiations that compute the step need one or two VGPRs more, which matters at the 256 boundary
+    // the instantiations that compute the step need one or two VGPRs more, which matters at the 256 boundary and, as registers are
+    // given out in eights, for the plain bf16 kernel of 8 states: 168 leave three wavefronts per SIMD, 170 two (4608 gated maps of
+    // 20x44: ranked with three it was chosen and took 78 us, where the shared-producer form takes 44).  In fp32 the counts rank better as
+    // they are: with the exact ones 12 of 122 gated shapes ran up to 1.35 times as fast and 5 up to 1.6 times as long.
     const V6 v6{c.LG, c.K, c.NW, c.NG, c.waves, c.RPB};
-    const double regs = (c.shared ? fwd_shared_regs(bf16, v6) : fwd_regs(bf16, c.K, c.NW)) + (c.sp ? 2 : 0);
+    double regs = (c.shared ? fwd_shared_regs(bf16, v6) : fwd_regs(bf16, c.K, c.NW)) + (c.sp ? 2 : 0);
+    if (bf16 && !c.shared) regs = std::ceil(regs / 8.0) * 8.0;
     const double occ = std::min(8.0, std::max(std::floor(512.0 / regs), c.waves / 4.0));
     double wg_cu = std::max(1.0, std::floor(occ * 4.0 / c.waves));                    // workgroups resident on a CU: registers ...
     if (c.lds_bytes > 0) wg_cu = std::min(wg_cu, std::max(1.0, std::floor(163840.0 / (double)c.lds_bytes)));   // ... and LDS
