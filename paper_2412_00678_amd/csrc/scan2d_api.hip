@@ -365,6 +365,15 @@ int rank_fwd(const scan2d_desc* d, FwdChoice* out, bool sp, bool ma, bool cf) {
             const double cost = fwd_cost(d, c);
             if (!found || cost < best) { best = cost; *out = c; found = true; }
         }
+    // 9 to 15 states, rows off the 4-column grid: two columns per lane, one wavefront per map, where that puts one of them on a SIMD at
+    // most and the general form needs two workgroups per compute unit (us per row, two columns / general: 0.65 / 0.55 at 40 and 256
+    // maps, 0.70 / 0.75 at 512, 0.70 / 0.90 at 640, 0.73 / 0.95 at 1024, 1.4 / 1.0 at 1280; 10 states 0.70 / 0.70 at 640; fp32, up to
+    // 9 rows: one state per lane is the faster one to 512), and for bf16 planes on odd boundaries (3072 maps of 25x25, N = 15: 63 us / 81)
+    if (found && !out->shared && d->W <= 32 && d->W % 4 != 0 && d->N > 8 && d->N < 16) {
+        const long long maps = (long long)d->Bt * d->Dc;
+        const bool odd = d->dtype == SCAN2D_BF16 && d->H > 9 && d->H % 2 != 0 && d->W % 2 != 0 && d->N % 2 != 0 && maps > 1280 && maps <= 4096;
+        if (odd || (out->NW == 1 ? maps > (d->H > 9 || d->dtype == SCAN2D_BF16 ? 256 : 512) : maps <= 1024 && maps > (d->N == 10 ? 768 : 512))) fill_small(d, 2, sp, out);
+    }
     // tall narrow maps whose states the lane offsets of the tilings above do not span: this kernel addresses each state by itself
     return found || fill_small(d, 2, sp, out) ? SCAN2D_OK : SCAN2D_ERR_BAD_SHAPE;
 }

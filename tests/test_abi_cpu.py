@@ -274,6 +274,15 @@ def test_rows_per_batch_follow_the_height(lib, H, rows):
     assert (f["form"], f["LG"], f["NW"], f["RPB"]) == ("shared", 16, 1, rows), f
 
 
+@pytest.mark.parametrize("maps,H,W,N,dtype,form", [
+    ((1, 256), 20, 19, 9, 0, "general"), ((1, 300), 20, 19, 9, 0, "small"), ((1, 300), 9, 19, 9, 0, "general"), ((1, 300), 9, 19, 9, 1, "small"),
+    ((4, 160), 30, 30, 12, 0, "small"), ((4, 256), 30, 30, 15, 1, "small"), ((4, 160), 20, 18, 10, 0, "general"), ((5, 256), 20, 18, 12, 0, "general"),
+    ((12, 256), 25, 25, 15, 1, "small"), ((12, 256), 25, 25, 15, 0, "general"), ((4, 160), 30, 28, 12, 0, "general"), ((4, 160), 30, 30, 16, 0, "shared")])
+def test_narrow_maps_of_nine_to_fifteen_states(lib, maps, H, W, N, dtype, form):
+    f = plan(lib, lib.Desc(*maps, H, W, N, dtype, 0), lib.PASS_FWD)
+    assert f["form"] == form and (form != "small" or (f["K"], f["NW"]) == (2, 4)), f
+
+
 def test_wide_grids_take_the_shared_producer_forms(lib):
     # 257 to 1024 columns, 16 states, one map per compute unit: wave-wide groups with 8, 12 or 16 columns per lane
     for W, K in ((300, 8), (400, 8), (512, 8), (513, 12), (600, 12), (768, 12), (769, 16), (1000, 16), (1024, 16)):
