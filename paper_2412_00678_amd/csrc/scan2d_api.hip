@@ -411,6 +411,16 @@ long long fwd_wgs(const scan2d_desc* d, const FwdChoice& c) {
     return ((long long)d->Bt * d->Dc + c.MPW - 1) / c.MPW;
 }
 
+// The gate inside the narrow-map kernels: it saves a launch and a pass over y, and makes each of the dependent rows longer.  Inside
+// and as a kernel of its own, us: 1024 maps of 17x16 bf16 8.3 and 9.7, of 30x11 11.2 and 11.9, of 40x11 (32 states) 31.8 and 30.9, of
+// 80x14 40.1 and 38.2; 4096 of 9x9 bf16 18.4 and 19.0, of 11x11 fp32 20.2 and 19.3, of 40x5 bf16 59.0 and 56.3; 3072 of 13x16 fp32,
+// 2 states, 8.0 and 9.8; two columns per lane: 1024 of 9x19 8.5 and 9.2, 16 of 22x30 15.2 and 12.9, 512 of 48x19 34.4 and 29.5.
+bool small_gate(const scan2d_desc* d, const FwdChoice& c) {
+    const long long maps = (long long)d->Bt * d->Dc;
+    if (c.K > 1) return d->H <= 14 && maps <= 2048;
+    return (d->H <= 32 && maps <= 2048) || ((d->dtype == SCAN2D_BF16 || d->N <= 8) && d->H <= 20 && maps <= 4096);
+}
+
 // Workspace of the scan kernel itself: row-end states between column panels (wide maps).
 size_t fwd_workspace(const scan2d_desc* d, const FwdChoice& c) {
     if (!c.multi) return 0;
@@ -576,7 +586,7 @@ int fwd_impl(const scan2d_desc* desc, const void* x, const void* delta, const fl
         const bool ua = desc->dtype == SCAN2D_BF16 && (desc->W % 2) != 0;
         FwdKernel k = nullptr;
         if (ch.tile) k = fwd_tile16_kernel(desc->dtype, true, true, false);
-        else if (ch.K < 4 && a.maps <= 4096) k = desc->dtype == SCAN2D_BF16 ? fwd_small_kernel_bf16(ch.K, ch.NW, true, true) : fwd_small_kernel_f32(ch.K, ch.NW, true, true);
+        else if (ch.K < 4 && small_gate(desc, ch)) k = desc->dtype == SCAN2D_BF16 ? fwd_small_kernel_bf16(ch.K, ch.NW, true, true) : fwd_small_kernel_f32(ch.K, ch.NW, true, true);
         else if (ch.shared) k = desc->dtype == SCAN2D_BF16 ? fwd_shared_kernel_gate_bf16(ch.LG, ch.K, ch.NW, ch.NG, ch.waves, ch.RPB, ua)
                                                            : fwd_shared_kernel_gate_f32(ch.LG, ch.K, ch.NW, ch.NG, ch.waves, ch.RPB);
         if (k != nullptr) {
