@@ -197,7 +197,11 @@ bool fill_tile16(const scan2d_desc* d, bool sp, FwdChoice* out) {
     c.LG = 16; c.K = 1; c.NW = d->N; c.waves = 4; c.sp = sp;
     c.exact = true; c.fast = false; c.multi = false; c.tile = true;
     c.NG = 1; c.panels = 1; c.RPB = 1; c.lds_bytes = 0;
+    // channels per workgroup: as many as keep 1024 workgroups, one more where that leaves a compute unit less to do (us: 12 x 256 maps,
+    // 1032 workgroups of three and 768 of four channels 15.0 and 13.1, 12 x 192 of 16x13 10.1 and 9.3; 14 x 256 stays at three, 16.2 and 16.0)
+    const auto work = [&](long long m) { return (d->Bt * ((d->Dc + m - 1) / m) + 255) / 256 * m; };
     c.MPW = (int)std::max(1LL, std::min({4LL, maps / 1024, (long long)d->Dc}));
+    if (maps > 1024 && c.MPW < 4 && c.MPW < d->Dc && work(c.MPW + 1) < work(c.MPW)) ++c.MPW;
     c.kernel = fwd_tile16_kernel(d->dtype, sp, false, c.MPW == 1);
     *out = c;
     return true;
@@ -803,10 +807,9 @@ extern "C" int scan2d_describe_plan(const scan2d_desc* desc, int pass, char* tex
         FwdChoice ch;
         rc = choose_fwd(desc, &ch, false, true, fused);
         if (rc != SCAN2D_OK) return rc;
-        const long long maps = (long long)desc->Bt * desc->Dc;
         std::snprintf(text, text_bytes, "%sfwd form=%s LG=%d K=%d NW=%d waves=%d RPB=%d NG=%d MPW=%d panels=%d fast=%d exact=%d wgs=%lld lds=%zu workspace=%zu",
                       fused ? "columns-first(in-kernel) " : "", ch.tile ? "tile16" : (ch.K < 4 ? "small" : (ch.skew ? "skew" : (ch.shared ? "shared" : "general"))), ch.LG, ch.K, ch.NW, ch.waves, ch.RPB, ch.NG, ch.MPW, ch.panels,
-                      (int)ch.fast, (int)ch.exact, (maps + ch.MPW - 1) / ch.MPW, ch.lds_bytes, fwd_workspace(desc, ch));
+                      (int)ch.fast, (int)ch.exact, fwd_wgs(desc, ch), ch.lds_bytes, fwd_workspace(desc, ch));
         return SCAN2D_OK;
     }
     if (pass == SCAN2D_PASS_BWD) return bwd_describe(desc, text, text_bytes) ? SCAN2D_OK : SCAN2D_ERR_BAD_SHAPE;

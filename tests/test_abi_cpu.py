@@ -283,6 +283,14 @@ def test_narrow_maps_of_nine_to_fifteen_states(lib, maps, H, W, N, dtype, form):
     assert f["form"] == form and (form != "small" or (f["K"], f["NW"]) == (2, 4)), f
 
 
+@pytest.mark.parametrize("maps,channels", [((8, 128), 1), ((9, 192), 1), ((8, 256), 2), ((12, 192), 3), ((3, 700), 3), ((9, 256), 2), ((12, 256), 4),
+                                           ((14, 256), 3), ((16, 256), 4), ((24, 256), 4)])
+def test_tiny_maps_channels_per_workgroup(lib, maps, channels):
+    """As many as keep 1024 workgroups, one more where a compute unit then has fewer channels to do."""
+    f = plan(lib, lib.Desc(*maps, 14, 14, 16, 0, 0), lib.PASS_FWD)
+    assert (f["form"], f["MPW"]) == ("tile16", channels) and f["wgs"] == maps[0] * -(-maps[1] // channels), f
+
+
 def test_wide_grids_take_the_shared_producer_forms(lib):
     # 257 to 1024 columns, 16 states, one map per compute unit: wave-wide groups with 8, 12 or 16 columns per lane
     for W, K in ((300, 8), (400, 8), (512, 8), (513, 12), (600, 12), (768, 12), (769, 16), (1000, 16), (1024, 16)):

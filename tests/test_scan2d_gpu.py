@@ -1390,7 +1390,7 @@ def test_backward_row_segments(s2d, variant, segments, shape, form, dtype):
 # gate inside, half-wave groups, eight rows per batch (heights off it), one and several maps of a batch item.
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("Bt,Dc,N,H,W,form", [
-    (5, 411, 16, 13, 14, "tile16 "), (2, 1025, 7, 16, 16, "tile16 "), (300, 17, 4, 14, 3, "tile16 "), (3, 700, 16, 5, 9, "small "),
+    (5, 411, 16, 13, 14, "tile16 "), (2, 1025, 7, 16, 16, "tile16 "), (300, 17, 4, 14, 3, "tile16 "), (3, 700, 16, 13, 14, "tile16 "), (3, 700, 16, 5, 9, "small "),
     (1, 7, 5, 9, 30, "small "), (2, 300, 13, 11, 19, "small LG=16 K=2 NW=4 "), (2, 3, 16, 33, 14, "small LG=16 K=1 "), (1, 5, 3, 15, 22, "small LG=16 K=2 "),
     (3, 700, 8, 12, 13, "small LG=16 K=1 "), (2, 3, 16, 5, 31, "shared LG=16 K=4 "), (1, 5, 16, 21, 64, "shared LG=16 K=4 "), (1, 3, 16, 8, 17, "shared LG=16 K=4 "),
     (2, 130, 16, 6, 65, "shared LG=32 K=4 "), (1, 260, 16, 9, 127, "shared LG=32 K=4 ")])
