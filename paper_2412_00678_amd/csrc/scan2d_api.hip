@@ -193,6 +193,9 @@ constexpr long long kTileMostMaps = 6144, kTileAnyRows = 1024;
 bool fill_tile16(const scan2d_desc* d, bool sp, FwdChoice* out) {
     const long long maps = (long long)d->Bt * d->Dc;
     if (d->H > 16 || d->W > 16 || d->N > 16 || maps > kTileMostMaps || (maps > kTileAnyRows && d->H < 13)) return false;
+    // whole rows of 16 columns favour the row walk (plain scan, us, rows one by one / tile: 8 x 512 maps of 14x16, N = 4 7.4 / 9.0, 32 x 192 of
+    // 13x16, N = 8 12.2 / 15.7, 8 x 256 of 14x16, N = 16 9.1 / 10.3; 6 x 256 of 13x16, N = 3 6.4 / 5.8, 24 x 256, N = 12 20.4 / 19.6)
+    if (!sp && d->W == 16 && (d->N <= 8 ? maps >= 2304 : d->N > 12 && d->H <= 14 && maps >= 2048)) return false;
     FwdChoice c;
     c.LG = 16; c.K = 1; c.NW = d->N; c.waves = 4; c.sp = sp;
     c.exact = true; c.fast = false; c.multi = false; c.tile = true;

@@ -291,6 +291,12 @@ def test_tiny_maps_channels_per_workgroup(lib, maps, channels):
     assert (f["form"], f["MPW"]) == ("tile16", channels) and f["wgs"] == maps[0] * -(-maps[1] // channels), f
 
 
+@pytest.mark.parametrize("maps,H,W,N,form", [((8, 512), 14, 16, 4, "small"), ((32, 192), 13, 16, 8, "small"), ((8, 256), 14, 16, 16, "small"),
+                                              ((8, 256), 16, 16, 16, "tile16"), ((6, 256), 13, 16, 3, "tile16"), ((24, 256), 13, 16, 12, "tile16"), ((8, 512), 14, 15, 4, "tile16")])
+def test_many_maps_of_whole_16_column_rows(lib, maps, H, W, N, form):
+    assert plan(lib, lib.Desc(*maps, H, W, N, 0, 0), lib.PASS_FWD)["form"] == form
+
+
 def test_wide_grids_take_the_shared_producer_forms(lib):
     # 257 to 1024 columns, 16 states, one map per compute unit: wave-wide groups with 8, 12 or 16 columns per lane
     for W, K in ((300, 8), (400, 8), (512, 8), (513, 12), (600, 12), (768, 12), (769, 16), (1000, 16), (1024, 16)):
