@@ -47,7 +47,14 @@ __global__ __launch_bounds__(S == 1 ? 256 : 64 * S) void scan2d_bwd_sums_kernel(
             if (e >= 0 && e < t.n) {
                 float acc = 0.0f;
                 if (p.S == 1) {
-                    for (int b = 0; b < p.Bt; ++b) acc += t.src[(size_t)b * t.n + e];
+                    for (int b = 0; b < p.Bt; b += 8) {    // in order; past the last item it is loaded again
+                        float v[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) v[u] = t.src[(size_t)min(b + u, p.Bt - 1) * t.n + e];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (b + u < p.Bt) acc += v[u];
+                    }
                 } else {
                     const int c = (int)e / t.per, k = (int)e - c * t.per, channels = t.n / t.per;
                     // one chain of loads of an item's segments each: requested eight at a time, added in the same order (32 batch

@@ -439,6 +439,12 @@ def test_backward_shared_producer_variants(s2d, variant, shape, dtype):
     check_bwd(s2d, w, seed=12, variant=variant)
 
 
+# Sums over batch items, eight requested at a time: below, at and past a multiple of eight, small and banded sweeps.
+@pytest.mark.parametrize("Bt,Dc,H,W", [(7, 3, 14, 14), (8, 2, 7, 9), (9, 3, 14, 14), (17, 3, 10, 20), (25, 2, 6, 70)])
+def test_backward_sums_over_batch_items(s2d, Bt, Dc, H, W):
+    check_bwd(s2d, wl.Workload("bsum", Bt, Dc, 16, H, W, wl.F32, mask_frac=0.3, backward=True), seed=Bt)
+
+
 # Maps wider than one lane-group panel (and, beyond 16 states, wider than 256 columns) are swept in panels of 256
 # columns with the row recurrences carried across the panel borders in both directions.
 @pytest.mark.parametrize("shape", [(1, 3, 16, 7, 1500, wl.F32, 0.3), (1, 2, 64, 6, 600, wl.BF16, 0.3), (2, 3, 32, 9, 300, wl.F32, 0.2),
