@@ -118,6 +118,17 @@ __device__ __forceinline__ void group_scan_left_any(float* P, float* Q, float* C
     }
 }
 
+// Value held by the lane to the right inside the lane group (0 for the group's last lane).
+template <int LG>
+__device__ __forceinline__ float from_right_any(float v) {
+    if constexpr (LG == 32) {
+        const float r = from_right<64>(v);
+        return (threadIdx.x & 31u) == 31u ? 0.0f : r;
+    } else {
+        return from_right<LG>(v);
+    }
+}
+
 // Value held by the lane to the left inside the lane group (0 for the group's first lane).
 template <int LG>
 __device__ __forceinline__ float from_left_any(float v) {
@@ -526,8 +537,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
         float hprev[RB][NW][K], hhl[RECOMP ? 1 : RB][NW][K];
         float ak[AREG ? RB : 1][NW][K], Prow[RB][NW];      // decays (AREG) and per lane their product over its columns
         // Rows scanned one by one (AHEAD): the next row's values are read from LDS in front of the current row's work.  One
-        // wavefront per SIMD has nothing else to put beside that latency, eight times per band and channel.
-        constexpr bool AHEAD = RS == 1;
+        // wavefront per SIMD has nothing else to put beside that latency, eight times per band and channel.  Columns first (ONCE) has
+        // no registers for that: every row's values are read in one place, and scan 4 runs on q itself (16 items of 96 channels of
+        // 21x146 bf16: 844 us the other way, and 800 bytes of scratch per lane; 599).
+        constexpr bool ONCE = CF && RS == 1, AHEAD = RS == 1 && !ONCE;
         float dlq[AHEAD ? 2 : 1][K], dxq[AHEAD ? 2 : 1][K];
         if constexpr (AHEAD) {
             lds_read_k<LG, K>(ppj, l, dlq[0]);
@@ -605,16 +618,18 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
             for (int j = 0; j < K; ++j) ga[s][j] = gaL[((size_t)ch * THREADS + tid) * (NW * K) + s * K + j];
         }
         // what a row's first half needs (AHEAD: read one row ahead): dy and, where the decays are formed again, the step
-        float dln[K], dyn[K];
+        float dln[K], dyn[K], dxn[K];                      // dxn (ONCE): step * x
         const auto first_half = [&](int r) {
             if constexpr (!AREG) {
-                if (r >= ALR) lds_read_k<LG, K>(ppj + r * PP_ROW, l, dln);
+                if (r >= ALR || ONCE) lds_read_k<LG, K>(ppj + r * PP_ROW, l, dln);
             }
             lds_read_k<LG, K>(ppj + r * PP_ROW + 2 * PANEL, l, dyn);
+            if constexpr (ONCE) lds_read_k<LG, K>(ppj + r * PP_ROW + PANEL, l, dxn);
         };
         if constexpr (AHEAD) first_half(RB - 1);
 #pragma unroll
         for (int rt = RB - 1; rt >= 0; rt -= RS) {         // RS rows per scan, the topmost rt - RS + 1
+            float edge[NW];                                // ONCE: the decay of the lane to the right
             float a[RS][NW][K], g[RS][NW][K], gr[RS][NW][K], P[RS * NW], Q[RS * NW], qin[RS * NW];     // gr: a * g (CF: of this row's q)
 #pragma unroll
             for (int d = 0; d < RS; ++d) {
@@ -623,9 +638,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
                     if (r > 0) { load_B((r - 1) % BR, r0 + r - 1); load_C((r - 1) % BR, r0 + r - 1); }
                 }
                 const float* prow = ppj + r * PP_ROW;
-                float dxe[K];
+                float dxr[K];
                 if constexpr (!AHEAD) first_half(r);
-                if constexpr (CF) lds_read_k<LG, K>(prow + PANEL, l, dxe);
+                if constexpr (CF && !ONCE) lds_read_k<LG, K>(prow + PANEL, l, dxr);
+                const float (&dxe)[K] = ONCE ? dxn : dxr;
 #pragma unroll
                 for (int s = 0; s < NW; ++s) {
                     const uint32_t* Cr = bC[r % BR][s];
@@ -656,11 +672,21 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
                             g[d][s][j] = fmaf(dyn[j], Cv, ga[s][j]);                                // scan 3
                             ga[s][j] = ar[j] * g[d][s][j];
                         }
-                        gr[d][s][j] = CF ? ar[j] * g[d][s][j] : ga[s][j];
+                        if constexpr (!ONCE) gr[d][s][j] = CF ? ar[j] * g[d][s][j] : ga[s][j];
                     }
                     // scan 4: q[j] = g[j] + a[j+1] * q[j+1], run on aq[j] = a[j] * q[j] = a[j] * g[j] + a[j] * aq[j+1]: a * g is
                     // there, and the lane's decay product is the one of the rebuild
                     const int k = d * NW + s;
+                    if constexpr (ONCE) {
+                        P[k] = edge[s] = from_right_any<LG>(ar[0]);
+                        Q[k] = g[d][s][K - 1];
+#pragma unroll
+                        for (int j = K - 2; j >= 0; --j) {
+                            Q[k] = fmaf(ar[j + 1], Q[k], g[d][s][j]);
+                            P[k] *= ar[j + 1];
+                        }
+                        continue;
+                    }
                     P[k] = Prow[r][s];
                     Q[k] = MP ? fmaf(ar[K - 1], qcv[r][s], gr[d][s][K - 1]) : gr[d][s][K - 1];      // MP: a*q entering from the right panel (last lane)
 #pragma unroll
@@ -674,13 +700,16 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
 #pragma unroll
             for (int d = 0; d < RS; ++d) {
                 const int r = rt - d;
-                float dl[K], dxe[K], s1[K], s2[K];
-                lds_read_k<LG, K>(ppj + r * PP_ROW, l, dl);
-                lds_read_k<LG, K>(ppj + r * PP_ROW + PANEL, l, dxe);
+                float dlr[K], dxr[K], s1[K], s2[K];
+                if constexpr (!ONCE) {
+                    lds_read_k<LG, K>(ppj + r * PP_ROW, l, dlr);
+                    lds_read_k<LG, K>(ppj + r * PP_ROW + PANEL, l, dxr);
+                }
+                const float (&dl)[K] = ONCE ? dln : dlr, (&dxe)[K] = ONCE ? dxn : dxr;
 #pragma unroll
                 for (int s = 0; s < NW; ++s) {
                     const float (&ar)[K] = a[d][s];
-                    float aq = qin[d * NW + s], first = 0.0f;      // first: hhor[i,j-1] of the lane's first column
+                    float aq = qin[d * NW + s], qr = aq, first = 0.0f;     // qr (ONCE): q to the right; first: hhor[i,j-1] of the lane's first column
                     if constexpr (MP) aq += qcv[r][s];             // one of them is 0
                     const auto hh = [&](int j) {                   // hhor[i,j]
                         const float hv = r == RB - 1 ? hcur[s][j] : hprev[r + 1 < RB ? r + 1 : r][s][j];
@@ -689,8 +718,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
                     if constexpr (RECOMP) first = from_left_any<LG>(hh(K - 1));
 #pragma unroll
                     for (int j = K - 1; j >= 0; --j) {
-                        const float q = g[d][s][j] + aq;
-                        aq = fmaf(ar[j], aq, gr[d][s][j]);
+                        float q;
+                        if constexpr (ONCE) {
+                            q = qr = fmaf(j == K - 1 ? edge[s] : ar[j + 1], qr, g[d][s][j]);
+                            aq = ar[j] * q;
+                        } else {
+                            q = g[d][s][j] + aq;
+                            aq = CF ? ar[j] * q : fmaf(ar[j], aq, gr[d][s][j]);
+                        }
                         if constexpr (MP) {
                             if (j == 0) put_elem_at(make_rsrc(p.qc_out + map * N * H, p.qc_out != nullptr ? (size_t)N * H * 4 : 0), (uint32_t)(n0 + s) * H + r0 + r,
                                                     l == 0 && act && r0 + r < H, aq, float{});
@@ -698,7 +733,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void scan2d_bwd_shared_kerne
                         float left;                                // hhor[i,j-1] (CF: h[i,j-1])
                         if constexpr (RECOMP) left = j == 0 ? first : hh(j - 1);
                         else left = hhl[r][s][j];
-                        float du = q, gv = gr[d][s][j];            // gradient of u; gv: a * (what the column recurrence adds)
+                        float du = q, gv = CF ? 0.0f : gr[d][s][j];     // gradient of u; gv: a * (what the column recurrence adds)
                         if constexpr (CF) {
                             du = q + ga[s][j];
                             gv = ga[s][j] = ar[j] * du;
