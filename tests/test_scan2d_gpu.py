@@ -874,6 +874,8 @@ CF_SHAPES = [
     # several maps per workgroup, a width whose backward needs column panels (transposed form; the forward stays in-kernel)
     (1, 2, 16, 33, 191, wl.BF16, 0.3), (2, 3, 16, 37, 50, wl.F32, 0.5), (1, 2, 32, 20, 40, wl.F32, 0.3), (1, 2, 64, 9, 30, wl.BF16, 0.3),
     (3, 7, 16, 56, 56, wl.BF16, 0.2), (1, 2, 16, 12, 300, wl.F32, 0.3),
+    # the tilings of 8 and of 12 columns per lane, whose rows are scanned one by one: whole and ragged
+    (2, 3, 16, 9, 104, wl.F32, 0.3), (1, 3, 16, 13, 121, wl.BF16, 0.3), (1, 5, 16, 10, 192, wl.BF16, 0.3), (2, 3, 16, 11, 147, wl.F32, 0.2),
 ]
 
 
@@ -906,6 +908,20 @@ def test_columns_first_forward_and_backward_match_oracle(s2d, shape):
         assert np.isfinite(gv).all(), name
         tol = TOL[dtype] if k < 2 else (1e-4 if dtype == wl.F32 else 2e-2)
         assert rel_err(gv, rv) <= tol, f"{name}: rel err {rel_err(gv, rv):.3e}"
+
+
+@pytest.mark.parametrize("H,W", [(9, 37), (9, 104), (13, 121), (10, 192), (11, 147)])
+def test_columns_first_backward_with_softplus_step_is_the_transposed_one(s2d, H, W):
+    import torch
+    inp = wl.make_inputs(wl.Workload("cfsp", 2, 3, 16, H, W, wl.F32, mask_frac=0.3, backward=True), seed=33)
+    d = s2d.to_device(inp, wl.F32)
+    bias = torch.linspace(-0.2, 0.2, 3, device="cuda:0")
+    tr = lambda t: t.transpose(-1, -2).contiguous()
+    got = s2d.scan2d_bwd_softplus(d["x"], d["delta"], bias, d["A"], d["Bm"], d["Cm"], d["Dskip"], d["mask"], d["dy"], flags=s2d.FLAG_COLUMNS_FIRST)
+    want = s2d.scan2d_bwd_softplus(tr(d["x"]), tr(d["delta"]), bias, d["A"], tr(d["Bm"]), tr(d["Cm"]), d["Dskip"], tr(d["mask"]), tr(d["dy"]))
+    for name, g, w in zip(("dx", "ddelta", "dbias", "dA", "dBm", "dCm", "dDskip"), got, want):
+        w = tr(w) if w.dim() == 4 else w
+        assert rel_err(s2d.to_host(g), s2d.to_host(w)) <= 1e-4, name           # two orders of fp32 sums
 
 
 def test_columns_first_with_identity_cells_softplus_and_gate(s2d):
