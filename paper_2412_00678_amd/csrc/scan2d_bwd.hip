@@ -478,6 +478,10 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
     // bf16 has 256 maps, one for each CU, and without segments a partial per channel (us, one segment and now: the two panels'
     // sweeps 1648 and 1041, the partials' sum 526 and 93, the pass in front 125; the whole training step 2931 and 1975).
     // More than 8 channels: 6144 maps of 56x56 bf16 take 12 instead of 6, partials' sum 104 -> 42 us.
+    // The constants are a fit to whole calls.  Checked for the shared sweep (0.12, 5.0, the partials' rates, the pass) on 1788 plans of 64
+    // shapes of 16 states, 20 to 400 a side: the one taken is 1.9 % slower than the best in the geometric mean, 15 % at most (32 items
+    // of 64 channels of 32x32: 16 channels in 4 segments 155 us, 4 in one 135).  For the plain sweep (0.28) on 486 plans of 70 shapes of 4 to
+    // 64 states: 0.3 %, 9 % at most, with 0.25; 4 x 192 maps of 47x47, 8 states, then took two channels and 243 us where one takes 200.
     const size_t T = (size_t)waves * 64;
     size_t fixed = 4 * T * K, per = T * ((size_t)NW * K + NW + 1);
     if (pl.shared) { fixed = pl.k.lds_fixed; per = pl.k.lds_per_channel; }
@@ -546,7 +550,7 @@ bool rank_plan(const scan2d_desc* d, BwdPlan* out, bool sp, bool av) {
             const double wgs = std::ceil((double)d->Bt * q.CG * q.S / JPW);
             const double resident = 256.0 * per_cu, rounds = std::ceil(wgs / resident);
             const double wps = std::min((double)per_cu, std::ceil(wgs / 256.0)) * waves / 4.0;
-            double us = rounds * pl.panels * (5.0 + g * q.seg_bands * units * (pl.shared ? 0.12 : 0.25) * (0.5 + 0.5 * std::max(1.0, wps)));
+            double us = rounds * pl.panels * (5.0 + g * q.seg_bands * units * (pl.shared ? 0.12 : 0.28) * (0.5 + 0.5 * std::max(1.0, wps)));
             if (q.CG > 1) us += 2.0 * d->Bt * q.CG * cells * 4.0 * (1.0 / 4.0e6 + 1.0 / 5.0e6);
             if (q.S > 1) {
                 const double up = 1.0 - 1.0 / q.S;
