@@ -394,7 +394,8 @@ int scan2d_describe_plan(const scan2d_desc* desc, int pass, char* text, size_t t
 
 /*
  * Test and tuning hook, not part of the paper's operator: forces a kernel variant for every later call of this
- * process (n = 0 clears the override).  kind 0: the plain forward kernels, values LG,K,NW,WAVES[,RPB];
+ * process (n = 0 clears the override).  kind 0: the plain forward kernels, values LG,K,NW,WAVES[,RPB],
+ * and with LG = 4 the forward kernel for many maps (K columns per block, the last value its wavefronts along the columns);
  * kind 1: the forward kernels that share the per-position work of a map through LDS, values LG,K,NW,WAVES,RPB[,SKEW]
  * (SKEW = 1: the tilings with skewed rows, which nothing else selects; the single value 0 = never use that form); kind 2: the banded backward, values
  * LG,K[,WAVES[,GS[,SHARED[,SEGMENTS]]]] (SHARED = 1 or 0: with or without the shared-producer main sweep, -1: as by default; SEGMENTS: of rows per map).

@@ -114,6 +114,7 @@ struct FwdChoice {
     bool cf = false;              // columns first inside the kernel
     bool skew = false;            // shared form with skewed rows: lane l of a group on row t - l, no scan across the lanes
     bool tile = false;            // one workgroup per map of at most 16 x 16 positions (scan2d_fwd_tile16.hip)
+    bool quads = false;           // eight channels per workgroup, channels and states along the lanes (scan2d_fwd_quads.hpp)
     FwdKernel kernel = nullptr;
 };
 
@@ -245,6 +246,62 @@ bool fill_shared(const scan2d_desc* d, int LG, int K, int NW, int waves, int RPB
     return true;
 }
 
+FwdKernel fwd_quads_kernel(int dtype, int K, bool sp, bool gate) {
+    return dtype == SCAN2D_BF16 ? fwd_quads_kernel_bf16(K, sp, gate) : fwd_quads_kernel_f32(K, sp, gate);
+}
+// Eight channels of a batch item per workgroup (scan2d_fwd_quads.hpp): two times `cols` wavefronts of four blocks of K or K - 1 columns.
+bool fill_quads(const scan2d_desc* d, int K, int cols, bool sp, FwdChoice* out) {
+    if (d->N != 16 || cols < 1 || cols > 4 || d->W > 4 * cols * K || d->W <= 4 * cols * (K - 1)) return false;
+    const long long wgs = (long long)d->Bt * ((d->Dc + 7) / 8);
+    if (wgs > 1 << 28) return false;
+    FwdChoice c;
+    c.LG = 4; c.K = K; c.NW = 4; c.waves = 2 * cols; c.sp = sp;
+    c.exact = true; c.fast = true; c.multi = false; c.quads = true;
+    c.NG = cols; c.MPW = (d->Dc + 7) / 8; c.panels = (int)wgs; c.RPB = 4;
+    c.kernel = fwd_quads_kernel(d->dtype, K, sp, false);
+    c.lds_bytes = fwd_quads_lds(K, cols);
+    if (c.kernel == nullptr || c.lds_bytes > 160 * 1024) return false;
+    *out = c;
+    return true;
+}
+
+// When that form is taken (16 states, from 13 to 64 columns, enough maps) and its blocks.  Below, us, the other forms' best / this one,
+// square maps, 128 or 192 channels; `sp`: with the softplus step and the gate.  It needs several workgroups per compute unit: a
+// wavefront's steps are chains through LDS and a barrier.  One column of wavefronts (K = W / 4) up to 32 columns:
+//   W = 14: 2048 maps bf16 10.7 / 12.6, 4608 23.4 / 19.5, 12288 59 / 32;  W = 17: 1536 maps sp 21.0 / 19.7, fp32 17.7 / 17.7, 2304 39 / 25
+//   W = 24: 2304 maps 32.0 / 30.5, sp 35.9 / 36.3, 3072 36.6 / 36.6, 4608 65 / 31;  W = 28: 4608 maps 76 / 38, fp32 48 / 38, sp 58 / 45
+//   (two columns, K = 4: 2304 maps 37.6 / 33.4, 3072 38.5 / 33.8, one column 37.7; 4608 43 and 38; 18 rows, 3072 maps, sp 31.0 / 31.9)
+// 33 to 64 columns, K = W / 8 on two columns of wavefronts, three workgroups per compute unit, or K = W / 4 on one, four (three from
+// K = 13 on), which has longer pieces of rows to read and waits longer for each (other / two / one):
+//   W = 48, maps 4608, 6144, 8192, 12288, 16384: bf16 129/84/96, 115/86/98, 144/114/107, 225/165/194, 301/218/209;
+//           bf16 sp 93/100/116, 129/108/115, 179/153/133, 259/218/238; fp32 80/84/94, 127/109/102, 168/146/115, 252/205/205; fp32 sp 117/138/117, 161/149/122
+//   W = 56, the same numbers of maps: bf16 150/106/123, 132/109/125, 175/152/211, 266/209/261; bf16 sp 113/130/145, 161/149/149, 212/202/247;
+//           fp32 119/129/128, 159/141/132, 220/186/216, 307/269/269; fp32 sp 155/182/149, 201/197/157, 272/262/250, 388/388/315
+//   W = 64: bf16 171/128/151, 155/135/155, 205/181/253; sp 139/172/196, 185/185/203; fp32 134/140/160, 177/150/165; sp 179/179/175, 222/193/180
+//   W = 36: bf16 sp 3456 maps 79/59, 4224 73/73; fp32 sp 94/55, 72/72; W = 53: bf16 4608 maps 187/102, sp 126/120
+// Wider maps gain nothing (96 columns, 3072 maps 217 / 213, sp 244 / 273; 128 columns 0.6 to 0.9 times as fast).
+bool choose_quads(const scan2d_desc* d, bool sp, FwdChoice* out) {
+    const int W = d->W;
+    if (d->N != 16 || W < 13 || W > 64 || d->H < 9) return false;
+    const int groups = (d->Dc + 7) / 8;
+    if (8 * groups - d->Dc > d->Dc / 8) return false;                                 // idle channels
+    const bool bf16 = d->dtype == SCAN2D_BF16;
+    const long long wgs = (long long)d->Bt * groups, layers = (wgs + 255) / 256;      // workgroups per compute unit
+    if (W <= 32) {
+        const int K = (W + 3) / 4;
+        if (W <= 16) return wgs >= 576 && d->H >= 13 && fill_quads(d, K, 1, sp, out);
+        if (wgs < (W <= 20 ? 288 : 384)) return false;
+        if (W > 24 && wgs < 512) return d->H >= 24 && fill_quads(d, 4, 2, sp, out);
+        return fill_quads(d, K, 1, sp, out);
+    }
+    const bool early = sp ? W <= 36 : (bf16 ? W <= 48 : W <= 40);                    // already with less than three layers
+    if (!(wgs > 640 || (early && wgs >= 432) || (bf16 && !sp && W <= 56 && wgs > 512))) return false;
+    bool one;
+    if (W <= 48) one = wgs > 640 && (bf16 ? layers % 4 == 0 : true);
+    else one = !bf16 && layers % 3 == 0 && (sp || W <= 56);
+    return one ? fill_quads(d, (W + 3) / 4, 1, sp, out) : fill_quads(d, (W + 7) / 8, 2, sp, out);
+}
+
 // VGPRs + AGPRs of the compiled forward kernels (more than 256 means one wave per SIMD), used only to rank
 // variants.  The table is generated by the build from the compiler's resource-usage remarks for exactly the
 // kernels that are linked into this library.
@@ -347,10 +404,12 @@ int rank_fwd(const scan2d_desc* d, FwdChoice* out, bool sp, bool ma, bool cf) {
         const int LG = tf.v[0], K = tf.v[1], NW = tf.v[2], waves = tf.n >= 4 ? tf.v[3] : 4, rpb = tf.n >= 5 ? tf.v[4] : 0;
         const int got = tf.n;
         if (got >= 2 && LG == 16 && (K == 1 || K == 2) && fill_small(d, K, sp, out)) return SCAN2D_OK;
+        if (got >= 4 && LG == 4 && fill_quads(d, K, waves, sp, out)) return SCAN2D_OK;
         if (got >= 3 && (LG == 16 || LG == 32 || LG == 64) && NW >= 1 && (waves == 4 || waves == 8 || waves == 16) &&
             fill_choice(d, LG, K, NW, waves, rpb, sp, ma, out))
             return SCAN2D_OK;
     }
+    if (choose_quads(d, sp, out)) return SCAN2D_OK;
     if (fill_tile16(d, sp, out)) return SCAN2D_OK;
     if (d->W <= 16 && fill_small(d, 1, sp, out)) return SCAN2D_OK;
     // up to 8 states that no shared-producer tiling takes, rows off the 4-column grid: two columns per lane (2048 maps of 30x30,
@@ -415,6 +474,7 @@ namespace {
 // Workgroups of a forward launch: MPW maps each; the kernel for tiny maps takes MPW channels of one batch item.
 long long fwd_wgs(const scan2d_desc* d, const FwdChoice& c) {
     if (c.tile) return (long long)d->Bt * ((d->Dc + c.MPW - 1) / c.MPW);
+    if (c.quads) return ((long long)c.panels + 7) / 8 * 8;               // a whole number per XCD; what is beyond the last one exits
     return ((long long)d->Bt * d->Dc + c.MPW - 1) / c.MPW;
 }
 
@@ -593,6 +653,7 @@ int fwd_impl(const scan2d_desc* desc, const void* x, const void* delta, const fl
         const bool ua = desc->dtype == SCAN2D_BF16 && (desc->W % 2) != 0;
         FwdKernel k = nullptr;
         if (ch.tile) k = fwd_tile16_kernel(desc->dtype, true, true, false);
+        else if (ch.quads) k = fwd_quads_kernel(desc->dtype, ch.K, true, true);
         else if (ch.K < 4 && small_gate(desc, ch)) k = desc->dtype == SCAN2D_BF16 ? fwd_small_kernel_bf16(ch.K, ch.NW, true, true) : fwd_small_kernel_f32(ch.K, ch.NW, true, true);
         else if (ch.shared) k = desc->dtype == SCAN2D_BF16 ? fwd_shared_kernel_gate_bf16(ch.LG, ch.K, ch.NW, ch.NG, ch.waves, ch.RPB, ua)
                                                            : fwd_shared_kernel_gate_f32(ch.LG, ch.K, ch.NW, ch.NG, ch.waves, ch.RPB);
@@ -811,7 +872,7 @@ extern "C" int scan2d_describe_plan(const scan2d_desc* desc, int pass, char* tex
         rc = choose_fwd(desc, &ch, false, true, fused);
         if (rc != SCAN2D_OK) return rc;
         std::snprintf(text, text_bytes, "%sfwd form=%s LG=%d K=%d NW=%d waves=%d RPB=%d NG=%d MPW=%d panels=%d fast=%d exact=%d wgs=%lld lds=%zu workspace=%zu",
-                      fused ? "columns-first(in-kernel) " : "", ch.tile ? "tile16" : (ch.K < 4 ? "small" : (ch.skew ? "skew" : (ch.shared ? "shared" : "general"))), ch.LG, ch.K, ch.NW, ch.waves, ch.RPB, ch.NG, ch.MPW, ch.panels,
+                      fused ? "columns-first(in-kernel) " : "", ch.tile ? "tile16" : ch.quads ? "quads" : (ch.K < 4 ? "small" : (ch.skew ? "skew" : (ch.shared ? "shared" : "general"))), ch.LG, ch.K, ch.NW, ch.waves, ch.RPB, ch.NG, ch.MPW, ch.panels,
                       (int)ch.fast, (int)ch.exact, fwd_wgs(desc, ch), ch.lds_bytes, fwd_workspace(desc, ch));
         return SCAN2D_OK;
     }

@@ -1,7 +1,8 @@
 // Tuning overrides of the dispatcher.  They start from the environment, read ONCE per process (first use),
 // and can afterwards only be changed through scan2d_debug_force_variant (a test hook): the entry points
 // themselves never call getenv.
-//   SCAN2D_FWD_VARIANT = LG,K,NW,WAVES[,RPB]     force a variant of the plain forward kernel
+//   SCAN2D_FWD_VARIANT = LG,K,NW,WAVES[,RPB]     force a variant of the plain forward kernel; LG = 4: of the kernel for many maps,
+//                        4,K,4,columns of wavefronts
 //   SCAN2D_FWD_SHARED  = LG,K,NW,WAVES,RPB[,SKEW] force a variant of the shared-producer forward kernel (SKEW = 1: its
 //                        skewed-row tilings; "0" alone = never use that form)
 //   SCAN2D_BWD_VARIANT = LG,K[,WAVES[,GS[,SHARED[,SEGMENTS]]]]  force a variant of the banded backward

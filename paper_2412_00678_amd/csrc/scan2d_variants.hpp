@@ -66,6 +66,13 @@ FwdKernel fwd_shared_kernel_bf16_cf(int LG, int K, int NW, int NG, int waves, in
 FwdKernel fwd_shared_kernel_gate_f32(int LG, int K, int NW, int NG, int waves, int RPB);
 FwdKernel fwd_shared_kernel_gate_bf16(int LG, int K, int NW, int NG, int waves, int RPB, bool ua);
 
+// Many maps, 16 states: eight channels per workgroup (scan2d_fwd_quads.hpp); columns per block.
+#define SCAN2D_FWD_QUADS_COLUMNS(X) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+// nullptr: not compiled
+FwdKernel fwd_quads_kernel_f32(int K, bool sp, bool gate);
+FwdKernel fwd_quads_kernel_bf16(int K, bool sp, bool gate);
+size_t fwd_quads_lds(int K, int cols);
+
 template <typename T, bool SP, bool UA, bool CF = false, bool GATE = false>
 inline FwdKernel lookup_fwd_shared_kernel(int LG, int K, int NW, int NG, int waves, int RPB) {
 #define SCAN2D_X(lg, k, nw, ng, wv, rpb) \

@@ -1434,3 +1434,65 @@ def test_forward_of_small_and_narrow_maps(s2d, Bt, Dc, N, H, W, form, dtype):
     assert rel_err(wl.to_float(s2d.to_host(ys), dtype), wl.to_float(rys, dtype)) <= TOL[dtype]
     assert rel_err(wl.to_float(s2d.to_host(y), dtype), wl.to_float(ry, dtype)) <= TOL[dtype]
     assert torch.equal(ys, plain) and torch.equal(y, y_only)
+
+
+# The forward kernel for many maps, eight channels per workgroup (blocks of K or K - 1 columns, four per wavefront): K and columns of
+# wavefronts forced at both ends of their widths, channels off the eights, heights off the batches of four and below the skew.
+QUADS_CASES = [(4, 1, (2, 9, 1, 13)), (4, 2, (1, 12, 9, 25)), (4, 4, (1, 7, 6, 64)), (5, 1, (3, 8, 5, 17)), (5, 3, (1, 5, 4, 59)), (6, 1, (2, 5, 3, 24)),
+               (6, 2, (1, 16, 11, 41)), (7, 1, (2, 4, 14, 28)), (7, 2, (2, 13, 13, 49)), (7, 2, (1, 8, 21, 56)), (7, 4, (1, 3, 18, 109)), (8, 1, (1, 9, 7, 29)),
+               (8, 2, (1, 8, 2, 64)), (8, 4, (1, 8, 17, 128)), (9, 1, (1, 8, 10, 33)), (10, 1, (2, 6, 9, 40)), (11, 1, (1, 8, 5, 43)), (12, 1, (1, 10, 13, 47)),
+               (12, 4, (1, 5, 11, 189)), (13, 1, (1, 8, 6, 52)), (14, 1, (2, 3, 9, 55)), (15, 1, (1, 8, 9, 57)), (16, 1, (1, 11, 10, 64))]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("K,cols,shape", QUADS_CASES, ids=[f"{k}-{c}-" + "x".join(map(str, s)) for k, c, s in QUADS_CASES])
+def test_forward_of_many_maps(s2d, K, cols, shape, dtype):
+    Bt, Dc, H, W = shape
+    with s2d.forced_variant(s2d.TUNE_FWD, f"4,{K},4,{cols}"):
+        plan = s2d.describe_plan(s2d.Desc(Bt, Dc, H, W, 16, dtype, 0), s2d.PASS_FWD)
+        assert f"form=quads LG=4 K={K} NW=4 waves={2 * cols} " in plan, plan
+        for mask in (0.3, 0.0):
+            check_fwd(s2d, wl.Workload("quads", Bt, Dc, 16, H, W, dtype, mask_frac=mask), seed=21)
+        test_forward_with_softplus_step_matches_oracle(s2d, (Bt, Dc, 16, H, W, dtype, 0.3), True)
+        test_gated_forward_matches_oracle(s2d, (Bt, Dc, 16, H, W, dtype, 0.3))
+        test_mask_is_bit_identical_to_prezeroed_x_and_blocks_garbage(s2d, H, W)
+
+
+# The sizes from which the dispatcher takes it, one below and one at each line of the rule.
+@pytest.mark.parametrize("Bt,Dc,H,W,dtype,sp,K", [
+    (48, 96, 13, 13, wl.F32, False, 4), (47, 96, 13, 13, wl.F32, False, 0), (48, 96, 12, 14, wl.BF16, False, 0), (24, 96, 9, 17, wl.BF16, True, 5),
+    (32, 96, 9, 21, wl.F32, True, 6), (32, 96, 24, 25, wl.BF16, False, 4), (32, 96, 23, 25, wl.BF16, False, 0), (43, 92, 9, 32, wl.F32, False, 8),
+    (36, 96, 9, 48, wl.BF16, False, 6), (36, 96, 9, 40, wl.F32, False, 5), (36, 96, 9, 36, wl.F32, True, 5), (36, 96, 9, 37, wl.BF16, True, 0),
+    (43, 96, 9, 56, wl.BF16, False, 7), (54, 96, 9, 44, wl.F32, False, 11), (86, 96, 9, 45, wl.BF16, True, 12), (54, 96, 9, 53, wl.F32, True, 14),
+    (54, 96, 9, 64, wl.F32, False, 8), (54, 97, 9, 64, wl.F32, False, 8), (300, 9, 9, 64, wl.F32, False, 0), (54, 96, 9, 65, wl.F32, False, 0)])
+def test_forward_of_many_maps_as_dispatched(s2d, Bt, Dc, H, W, dtype, sp, K):
+    import torch
+    if not sp:
+        plan = s2d.describe_plan(s2d.Desc(Bt, Dc, H, W, 16, dtype, 0), s2d.PASS_FWD)
+        assert (f"form=quads LG=4 K={K} " in plan) if K else ("form=quads" not in plan), plan
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    td = torch.float32 if dtype == wl.F32 else torch.bfloat16
+    draw = lambda *s: torch.randn(s, device="cuda:0", generator=g)
+    x, raw, z = (draw(Bt, Dc, H, W).to(td) for _ in range(3))
+    Bm, Cm = (draw(Bt, 16, H, W).to(td) for _ in range(2))
+    A, skip, bias = -(0.5 * draw(Dc, 16)).exp(), draw(Dc), draw(Dc)
+    mask = (draw(Bt, H, W) > 0.5).to(torch.uint8)
+    x.masked_fill_(mask.bool().unsqueeze(1), float("nan"))                      # nothing under the mask leaks
+    Bm[:, 3, H // 2, W // 2] = float("inf")                                     # beside an infinite input the same cells are not finite
+
+    def run():
+        if sp:
+            return s2d.scan2d_fwd_softplus_gated(x, raw, bias, A, Bm, Cm, skip, mask, z)
+        return (s2d.scan2d_fwd(x, torch.nn.functional.softplus(raw.float()).to(td), A, Bm, Cm, None, mask),)
+
+    got = run()
+    with s2d.forced_variant(s2d.TUNE_FWD, "16,4,4,4"):
+        want = run()
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        a, b = a.float(), b.float()
+        assert torch.equal(torch.isfinite(a), torch.isfinite(b))
+        a, b = torch.nan_to_num(a, posinf=0.0, neginf=0.0), torch.nan_to_num(b, posinf=0.0, neginf=0.0)
+        # fp32: sums of 16 terms in another order, at most 16 roundings of the largest; bf16: neighbouring values, which with eight
+        # significant bits lie up to 2^-7 of the value apart
+        assert (a - b).abs().max() <= (16 * 2.0 ** -24 * 16 if dtype == wl.F32 else 2.0 ** -7) * b.abs().max()
