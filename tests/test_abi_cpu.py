@@ -254,7 +254,8 @@ def test_benchmark_configurations_take_the_intended_forms(lib):
     f = plan(lib, lib.Desc(2, 256, 256, 256, 16, 1, 0), lib.PASS_FWD)
     assert (f["form"], f["LG"], f["K"], f["NW"], f["waves"]) == ("shared", 64, 4, 2, 8) and f["wgs"] == 512
     f = plan(lib, lib.Desc(32, 192, 56, 56, 16, 1, 0), lib.PASS_FWD)
-    assert f["form"] == "shared" and f["LG"] == 16 and f["K"] == 4 and f["fast"]
+    # 24 maps per compute unit: eight channels per workgroup, two wavefronts of four 7-column blocks
+    assert (f["form"], f["K"], f["waves"], f["wgs"]) == ("quads", 7, 4, 768) and f["fast"]
     f = plan(lib, lib.Desc(1, 256, 64, 64, 16, 0, 0), lib.PASS_FWD)
     assert (f["form"], f["LG"], f["K"], f["NW"]) == ("shared", 16, 4, 1)
     f = plan(lib, lib.Desc(1, 16, 16, 16, 4, 0, 0), lib.PASS_FWD)
@@ -262,7 +263,9 @@ def test_benchmark_configurations_take_the_intended_forms(lib):
     f = plan(lib, lib.Desc(8, 128, 14, 14, 16, 0, 0), lib.PASS_FWD)
     assert f["form"] == "tile16" and f["wgs"] == 1024
     f = plan(lib, lib.Desc(64, 128, 14, 14, 16, 0, 0), lib.PASS_FWD)
-    assert f["form"] == "small"                              # many of them: four maps per workgroup, row by row
+    assert (f["form"], f["K"]) == ("quads", 4)               # many of them
+    f = plan(lib, lib.Desc(64, 128, 12, 14, 16, 0, 0), lib.PASS_FWD)
+    assert f["form"] == "small"                              # with few rows: four maps per workgroup, row by row
     b = plan(lib, lib.Desc(4, 512, 128, 192, 16, 0, 0), lib.PASS_BWD)
     assert (b["form"], b["LG"], b["K"], b["NW"]) == ("banded-shared", 16, 12, 1) and b["wgs"] * b["GS"] >= 4 * 512 // 1
 
@@ -284,7 +287,7 @@ def test_narrow_maps_of_nine_to_fifteen_states(lib, maps, H, W, N, dtype, form):
 
 
 @pytest.mark.parametrize("maps,channels", [((8, 128), 1), ((9, 192), 1), ((8, 256), 2), ((12, 192), 3), ((3, 700), 3), ((9, 256), 2), ((12, 256), 4),
-                                           ((14, 256), 3), ((16, 256), 4), ((24, 256), 4)])
+                                           ((14, 256), 3), ((16, 256), 4), ((17, 256), 4)])
 def test_tiny_maps_channels_per_workgroup(lib, maps, channels):
     """As many as keep 1024 workgroups, one more where a compute unit then has fewer channels to do."""
     f = plan(lib, lib.Desc(*maps, 14, 14, 16, 0, 0), lib.PASS_FWD)
