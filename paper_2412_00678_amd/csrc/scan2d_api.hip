@@ -271,13 +271,15 @@ bool fill_quads(const scan2d_desc* d, int K, int cols, bool sp, FwdChoice* out) 
 //   W = 14: 2048 maps bf16 10.7 / 12.6, 4608 23.4 / 19.5, 12288 59 / 32;  W = 17: 1536 maps sp 21.0 / 19.7, fp32 17.7 / 17.7, 2304 39 / 25
 //   W = 24: 2304 maps 32.0 / 30.5, sp 35.9 / 36.3, 3072 36.6 / 36.6, 4608 65 / 31;  W = 28: 4608 maps 76 / 38, fp32 48 / 38, sp 58 / 45
 //   (two columns, K = 4: 2304 maps 37.6 / 33.4, 3072 38.5 / 33.8, one column 37.7; 4608 43 and 38; 18 rows, 3072 maps, sp 31.0 / 31.9)
-// 33 to 64 columns, K = W / 8 on two columns of wavefronts, three workgroups per compute unit, or K = W / 4 on one, four (three from
-// K = 13 on), which has longer pieces of rows to read and waits longer for each (other / two / one):
+// 33 to 64 columns, K = W / 8 on two columns of wavefronts, three workgroups per compute unit, or K = W / 4 on one, four, which reads
+// longer pieces of rows and has half of the skew, so that fewer of them leave the L2 half used, and waits longer for each (other / two / one):
 //   W = 48, maps 4608, 6144, 8192, 12288, 16384: bf16 129/84/96, 115/86/98, 144/114/107, 225/165/194, 301/218/209;
 //           bf16 sp 93/100/116, 129/108/115, 179/153/133, 259/218/238; fp32 80/84/94, 127/109/102, 168/146/115, 252/205/205; fp32 sp 117/138/117, 161/149/122
-//   W = 56, the same numbers of maps: bf16 150/106/123, 132/109/125, 175/152/211, 266/209/261; bf16 sp 113/130/145, 161/149/149, 212/202/247;
-//           fp32 119/129/128, 159/141/132, 220/186/216, 307/269/269; fp32 sp 155/182/149, 201/197/157, 272/262/250, 388/388/315
-//   W = 64: bf16 171/128/151, 155/135/155, 205/181/253; sp 139/172/196, 185/185/203; fp32 134/140/160, 177/150/165; sp 179/179/175, 222/193/180
+//   W = 56, the same numbers of maps: bf16 150/106/123, 132/109/125, 175/145/137, 266/209/248, 356/280/267; bf16 sp 113/130/145, 161/150/150,
+//           212/196/168, 310/285/300, 412/375/326; fp32 119/129/128, 159/141/132, 220/185/150, 307/269/264, 435/356/294; fp32 sp 155/182/149,
+//           201/197/157, 272/260/194, 388/388/328, 537/511/378
+//   W = 64: bf16 171/128/151, 155/135/155, 205/181/171, 303/255/307; sp 139/172/187, 185/183/193, 249/242/220; fp32 134/140/158, 177/149/162,
+//           240/203/181; fp32 sp 179/179/175, 222/190/182, 321/288/218, 432/371/364
 //   W = 36: bf16 sp 3456 maps 79/59, 4224 73/73; fp32 sp 94/55, 72/72; W = 53: bf16 4608 maps 187/102, sp 126/120
 // Wider maps gain nothing (96 columns, 3072 maps 217 / 213, sp 244 / 273; 128 columns 0.6 to 0.9 times as fast).
 bool choose_quads(const scan2d_desc* d, bool sp, FwdChoice* out) {
@@ -298,7 +300,7 @@ bool choose_quads(const scan2d_desc* d, bool sp, FwdChoice* out) {
     if (!(wgs > 640 || (early && wgs >= 432) || (bf16 && !sp && W <= 56 && wgs > 512))) return false;
     bool one;
     if (W <= 48) one = wgs > 640 && (bf16 ? layers % 4 == 0 : true);
-    else one = !bf16 && layers % 3 == 0 && (sp || W <= 56);
+    else one = layers % 4 == 0 || (!bf16 && layers % 3 == 0 && (sp || W <= 60));
     return one ? fill_quads(d, (W + 3) / 4, 1, sp, out) : fill_quads(d, (W + 7) / 8, 2, sp, out);
 }
 

@@ -69,15 +69,19 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 // LDS of a wavefront (floats): [4 rows][(K+1)/2 pairs of columns][16 (block, channel)] x (step, step * x) of both columns, replaced
 // by the sums over half of the state groups (both columns of one half, both of the other); 4 floats more per pair and 16 per row keep
-// neighbouring columns and rows in different banks.  Of two wavefronts with the same columns: [3 steps][Bm, Cm][ceil(K/4) columns]
-// [64 lanes] x 4 states.  Of a quad of channels:
+// neighbouring columns and rows in different banks.  Of two wavefronts with the same columns: [quad_sets steps][Bm, Cm]
+// [ceil(K/4) columns][64 lanes] x 4 states.  Of a quad of channels:
 // [2 steps] the row states at the blocks' right edges, a word per lane, one zero block in front.
 constexpr int kQuadPair = 68;
 template <int K> constexpr int quad_row() { return (K + 1) / 2 * kQuadPair + 16; }
 template <int K> constexpr int quad_bc() { return (K + 3) / 4 * 256; }
+// Steps of Bm and Cm in LDS: three where a step's are read into registers one step ahead.  From 13 columns on there are no registers
+// for that, and with two a compute unit holds four workgroups of two wavefronts instead of three.
+template <int K> constexpr bool quad_bc_ahead() { return K <= 12; }
+template <int K> constexpr int quad_sets() { return quad_bc_ahead<K>() ? 3 : 2; }
 constexpr int quad_carry(int cols) { return cols * 64 + 16; }
 template <int K> constexpr size_t quad_lds_bytes(int cols) {
-    return ((size_t)2 * 8 * quad_carry(cols) + (size_t)cols * (2 * 4 * quad_row<K>() + 6 * quad_bc<K>())) * sizeof(float);
+    return ((size_t)2 * 8 * quad_carry(cols) + (size_t)cols * (2 * 4 * quad_row<K>() + 2 * quad_sets<K>() * quad_bc<K>())) * sizeof(float);
 }
 
 // wavefronts per SIMD that the registers leave room for
@@ -97,7 +101,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
     constexpr int RV = SLOTS / 16;                                              // ... and the different rows among them
     constexpr int PW = 2;                                                       // dwords per pair (bf16: from the dword boundary below)
     constexpr bool AHEAD = K < 6 || (!GATE && K <= 8);     // a row's values read from LDS one step ahead, and Bm and Cm, where
-    constexpr bool BC_AHEAD = K <= 12;                     // there are registers for them
+    constexpr bool BC_AHEAD = quad_bc_ahead<K>();          // there are registers for them
+    constexpr int SETS = quad_sets<K>();
 
     // consecutive workgroups go to the eight XCDs in turn: each XCD takes a contiguous range, so that the channels of a batch item
     // find its Bm and Cm in one L2
@@ -114,8 +119,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
     const int ch = lane & 3, sg = (lane >> 2) & 3, blk = lane >> 4;
     const int cstride = quad_carry(cols);
     float4* const carry = reinterpret_cast<float4*>(smem) + quad * 2 * cstride;                 // [2][cols * 64 + 16]
-    float4* const bc = reinterpret_cast<float4*>(smem + 16 * cstride + wc * 6 * BC);            // [3][2][KQ][64]
-    float* const pp = smem + 16 * cstride + cols * 6 * BC + wave * 4 * PR;
+    float4* const bc = reinterpret_cast<float4*>(smem + 16 * cstride + wc * 2 * SETS * BC);     // [SETS][2][KQ][64]
+    float* const pp = smem + 16 * cstride + cols * 2 * SETS * BC + wave * 4 * PR;
 
     const int H = p.H, W = p.W;
     const size_t HW = (size_t)H * W;
@@ -218,7 +223,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
         }
     };
 
-    // ---- Bm or Cm of a step: requested three steps ahead, widened and handed over two steps ahead, read one step ahead
+    // ---- Bm or Cm of a step: requested three steps ahead, widened and handed over two steps ahead, read one step ahead (without
+    // BC_AHEAD: two, one, none)
     uint32_t slane[NS], raw[NS][BW], sh[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) slane[s] = ((uint32_t)(sg * NS + s) * (uint32_t)HW + (uint32_t)(col0 + min(ch * KQ, K - KQ))) * EB;
@@ -259,12 +265,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
         uint32_t raw0[NS][BW], sh0[NS], raw1[NS][BW], sh1[NS];
         request(0);
         request_bc(0, raw0, sh0);
-        request_bc(1, raw1, sh1);
-        request_bc(2, raw, sh);
+        if constexpr (BC_AHEAD) request_bc(1, raw1, sh1);
+        request_bc(SETS - 1, raw, sh);
         produce(0);
         request(min(1, batches - 1));
         hand_over(0, raw0, sh0);
-        hand_over(1, raw1, sh1);
+        if constexpr (BC_AHEAD) hand_over(1, raw1, sh1);
     }
     __syncthreads();
 
@@ -302,7 +308,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
             const int at = r & 1;
             if (!AHEAD || r == 0) take_row(r, at);
             if (AHEAD && r < 3) take_row(r + 1, at ^ 1);
-            if constexpr (BC_AHEAD) take_bc(set1, at ^ 1); else take_bc(3 - set1 - set2, at);
+            if constexpr (BC_AHEAD) take_bc(set1, at ^ 1); else take_bc(at, at);
             float y0 = 0.0f, hn[NS];
 #pragma unroll
             for (int j = 0; j < K; ++j) {
@@ -326,8 +332,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
             // a narrow block ends one column earlier
             carry[((r & 1) ^ 1) * cstride + wc * 64 + lane + 16] =
                 make_float4(full ? hh[0] : hn[0], full ? hh[1] : hn[1], full ? hh[2] : hn[2], full ? hh[3] : hn[3]);
-            hand_over(set2, raw, sh);
-            request_bc(t + 3, raw, sh);
+            hand_over(BC_AHEAD ? set2 : at ^ 1, raw, sh);
+            request_bc(t + SETS, raw, sh);
             const int set0 = 3 - set1 - set2;
             set1 = set2;
             set2 = set0;
