@@ -1463,7 +1463,7 @@ def test_forward_of_many_maps(s2d, K, cols, shape, dtype):
     (48, 96, 13, 13, wl.F32, False, 4), (47, 96, 13, 13, wl.F32, False, 0), (48, 96, 12, 14, wl.BF16, False, 0), (24, 96, 9, 17, wl.BF16, True, 5),
     (32, 96, 9, 21, wl.F32, True, 6), (32, 96, 24, 25, wl.BF16, False, 4), (32, 96, 23, 25, wl.BF16, False, 0), (43, 92, 9, 32, wl.F32, False, 8),
     (36, 96, 9, 48, wl.BF16, False, 6), (36, 96, 9, 40, wl.F32, False, 5), (36, 96, 9, 36, wl.F32, True, 5), (36, 96, 9, 37, wl.BF16, True, 0),
-    (43, 96, 9, 56, wl.BF16, False, 7), (54, 96, 9, 44, wl.F32, False, 11), (86, 96, 9, 45, wl.BF16, True, 12), (54, 96, 9, 53, wl.F32, True, 14), (70, 96, 9, 61, wl.BF16, True, 16), (70, 96, 9, 56, wl.BF16, False, 14),
+    (43, 96, 9, 56, wl.BF16, False, 7), (54, 96, 9, 44, wl.F32, False, 11), (86, 96, 9, 45, wl.BF16, True, 12), (54, 96, 9, 53, wl.F32, True, 14), (77, 96, 9, 61, wl.BF16, True, 16), (76, 96, 9, 59, wl.F32, True, 15), (70, 96, 9, 56, wl.BF16, False, 14),
     (54, 96, 9, 64, wl.F32, False, 8), (54, 97, 9, 64, wl.F32, False, 8), (300, 9, 9, 64, wl.F32, False, 0), (54, 96, 9, 65, wl.F32, False, 0)])
 def test_forward_of_many_maps_as_dispatched(s2d, Bt, Dc, H, W, dtype, sp, K):
     import torch
