@@ -278,9 +278,9 @@ bool fill_quads(const scan2d_desc* d, int K, int cols, bool sp, FwdChoice* out) 
 //   W = 56, the same numbers of maps: bf16 150/106/123, 132/109/125, 175/145/137, 266/209/248, 356/280/267; bf16 sp 113/130/145, 161/150/150,
 //           212/196/168, 310/285/300, 412/375/326; fp32 119/129/128, 159/141/132, 220/185/150, 307/269/264, 435/356/294; fp32 sp 155/182/149,
 //           201/197/157, 272/260/194, 388/388/328, 537/511/378
-//   W = 64: bf16 171/128/151, 155/135/155, 205/181/171, 303/255/307; sp 139/172/187, 185/183/193, 249/242/220; fp32 134/140/158, 177/149/162,
+//   W = 64: bf16 171/128/151, 155/135/155, 205/181/171, 303/255/307; sp 139/172/188, 180/175/191, 249/242/220; fp32 134/140/158, 177/149/162,
 //           240/203/181; fp32 sp 179/179/175, 222/190/182, 321/288/218, 432/371/364
-//   9216 maps: W = 56 bf16 sp 234/234/286, fp32 sp 291/308/290; W = 64 bf16 sp 272/285, fp32 sp 332/298/346
+//   9216 maps: W = 56 bf16 sp 234/234/286, fp32 sp 291/308/290; W = 64 bf16 sp 264/267, fp32 sp 332/298/346
 //   W = 36: bf16 sp 3456 maps 79/59, 4224 73/73; fp32 sp 94/55, 72/72; W = 53: bf16 4608 maps 187/102, sp 126/120
 // Wider maps gain nothing (96 columns, 3072 maps 217 / 213, sp 244 / 273; 128 columns 0.6 to 0.9 times as fast).
 bool choose_quads(const scan2d_desc* d, bool sp, FwdChoice* out) {
@@ -299,8 +299,9 @@ bool choose_quads(const scan2d_desc* d, bool sp, FwdChoice* out) {
     }
     const bool early = sp ? W <= 36 : (bf16 ? W <= 48 : W <= 40);                    // already with less than three layers
     if (!(wgs > 640 || (early && wgs >= 432) || (bf16 && !sp && W <= 56 && wgs > 512))) return false;
-    // bf16 with the step and the gate: beyond 56 columns it gains only where the last round of workgroups is nearly full as well
-    if (bf16 && sp && W > 56 && (wgs + 127) % 1024 >= 128) return false;
+    // bf16 with the step and the gate: beyond 56 columns it gains only with whole blocks (64 columns), whose pairs are stored as dwords, or
+    // where the last round of workgroups is nearly full
+    if (bf16 && sp && W > 56 && W % 8 != 0 && (wgs + 127) % 1024 >= 128) return false;
     bool one;
     if (W <= 48) one = wgs > 640 && (bf16 ? layers % 4 == 0 : true);
     else one = layers % 4 == 0 || (!bf16 && W <= 60 && (sp || layers % 3 == 0));

@@ -15,8 +15,16 @@
 //     rows that a block passes in four steps, two columns per lane with neighbouring columns in neighbouring lanes; the products go to
 //     LDS (private to the wavefront), the sums over the states come back in their place, and the lane that prepared a pair also
 //     stores its results.
-// Per (position, channel, state): two multiplies, an exponential and three multiply-adds, about 2.5 instructions of everything else.
-// What bounds it: vector issue.
+// Per (position, channel, state): two multiplies, an exponential and three multiply-adds, and 2.3 to 3.3 instructions of everything else
+// (6144 maps of 56x56 bf16: 9.3, where the shared-producer form needs 14.5).
+// What bounds it: with three wavefronts per SIMD vector issue (56x56 bf16 134 -> 111 us, the vector ALU at 78 % of the time; 28x28 67 ->
+// 38); in fp32 and with the gate the L2, which holds the lines that a block has begun until its neighbours have passed (56x56 bf16 gated
+// 157 -> 150; streaming hints on the stores make that 166, on the loads too 190); with one wavefront per SIMD the chain of a step, LDS,
+// seven columns one after the other and the barrier: 0.9 us where the instructions take 0.45.  x, the step and z by
+// elements instead of pairs: 6 % more; a first form in which every quad fetched Bm and Cm for itself, by unaligned loads: 215 us.
+// The backward pass's checkpoints do not come from here: a block's 28-byte pieces of their rows took longer to write than the
+// shared-producer form takes for all (saving forward of 56x56 bf16 297 us against 210), and in an order of this kernel's own
+// (185 us) the main sweep lost 20 to 37 us on gathering them.
 //
 // Blocks are K or K - 1 columns wide, the narrow ones first, so that K columns from a block's first are always inside the row and no
 // access is guarded; the last of a narrow block's K columns is its right neighbour's: its results are dropped.  Rows above and below
@@ -157,8 +165,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
     const auto e_ch = [](int e) { return e * RPI / 4; };
     const auto e_plane = [&](int e) { return (uint32_t)(min(c0 + e_ch(e), p.Dc - 1) - min(c0, p.Dc - 1)) * (uint32_t)HW * EB; };
     // neighbouring lanes take the blocks of one map row, which are in different steps of the batch: the four rows of a batch are seven
-    // runs of neighbouring columns instead of sixteen (with step = lane / SLOTS the pieces of a row were requested by different parts
-    // of a load, and the later ones waited for the line that the first had asked for)
+    // runs of neighbouring columns instead of sixteen (a sixth fewer cache accesses in all, bf16)
     int irow[RV];
     float* icell[RV];
 #pragma unroll
@@ -166,6 +173,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
         irow[v] = (v * RPI + lane / SLOTS + iblk) & 3;
         icell[v] = pp + irow[v] * PR + ij / 2 * kQuadPair + iblk * 16;
     }
+    // bf16, whole blocks of even width: every pair is a dword in memory (6144 maps of 64x64, gated, two 16-bit stores 182 us, one dword 173)
+    const bool dwords = EB == 2 && K % 2 == 0 && narrow == 0;
     float dsk[4], dbias[4];                                // uniform
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -368,8 +377,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
                     __builtin_amdgcn_raw_buffer_store_b32(both.x, rs, (here && iend == 1) ? at : none, e_plane(e), 0);
                 } else {
                     const uint32_t both = pack_bf16x2(val[0], val[1]);
-                    __builtin_amdgcn_raw_buffer_store_b16((short)both, rs, (here && iend > 0) ? at : none, e_plane(e), 0);
-                    __builtin_amdgcn_raw_buffer_store_b16((short)(both >> 16), rs, (here && iend > 1) ? at + 2u : none, e_plane(e), 0);
+                    if (dwords) {
+                        __builtin_amdgcn_raw_buffer_store_b32(both, rs, (here && iend > 0) ? at : none, e_plane(e), 0);
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b16((short)both, rs, (here && iend > 0) ? at : none, e_plane(e), 0);
+                        __builtin_amdgcn_raw_buffer_store_b16((short)(both >> 16), rs, (here && iend > 1) ? at + 2u : none, e_plane(e), 0);
+                    }
                 }
             };
             if (want_y) store(rsy, out);
