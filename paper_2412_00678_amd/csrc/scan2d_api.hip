@@ -810,7 +810,7 @@ extern "C" int scan2d_fwd_softplus_gated(const scan2d_desc* desc, const void* x,
                                          const uint8_t* mask, const void* z, void* y_scan, void* y, void* workspace,
                                          size_t workspace_bytes, void* stream) {
     if (!z || !y) return SCAN2D_ERR_NULL_POINTER;
-    if (!aligned16(z) || !aligned16(y_scan)) return SCAN2D_ERR_MISALIGNED;
+    if (!aligned16(z) || !aligned16(y_scan) || !aligned16(y)) return SCAN2D_ERR_MISALIGNED;
     void* ys = y_scan != nullptr ? y_scan : y;
     bool gated = false;
     const int rc = fwd_impl(desc, x, delta_raw, delta_bias, 1, A, Bm, Cm, Dskip, mask, ys, workspace, workspace_bytes, stream, z, y, &gated);

@@ -73,6 +73,15 @@ def test_misaligned_pointers_are_rejected_before_any_launch(lib):
         a = list(args)
         a[k] = bad
         assert lib.lib.scan2d_fwd(ctypes.byref(d), *a, None, 0, None) == -6
+    # the gated forward: x, delta_raw, delta_bias, A, Bm, Cm, Dskip, mask, z, y_scan, y, workspace; y_scan wanted and not
+    gated = lambda a: lib.lib.scan2d_fwd_softplus_gated(ctypes.byref(d), *a, 0, None)
+    for k in (0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11):
+        a = [ok] * 11 + [None]
+        a[k] = bad
+        assert gated(a) == -6, k
+        if k not in (9, 11):
+            a[9] = None
+            assert gated(a) == -6, k
 
 
 def test_workspace_query(lib):
