@@ -257,7 +257,7 @@ bool fill_quads(const scan2d_desc* d, int K, int cols, bool sp, FwdChoice* out) 
     FwdChoice c;
     c.LG = 4; c.K = K; c.NW = 4; c.waves = 2 * cols; c.sp = sp;
     c.exact = true; c.fast = true; c.multi = false; c.quads = true;
-    c.NG = cols; c.MPW = (d->Dc + 7) / 8; c.panels = (int)wgs; c.RPB = 4;
+    c.NG = 4; c.MPW = 8; c.panels = 1; c.RPB = 4;
     c.kernel = fwd_quads_kernel(d->dtype, K, sp, false);
     c.lds_bytes = fwd_quads_lds(K, cols);
     if (c.kernel == nullptr || c.lds_bytes > 160 * 1024) return false;
@@ -477,10 +477,11 @@ bool allow_large_lds(const void* kernel, size_t bytes) {
 }
 namespace {
 
-// Workgroups of a forward launch: MPW maps each; the kernel for tiny maps takes MPW channels of one batch item.
+// Workgroups of a forward launch: MPW maps each; the kernels for tiny and for many maps take MPW channels of one batch item.
 long long fwd_wgs(const scan2d_desc* d, const FwdChoice& c) {
-    if (c.tile) return (long long)d->Bt * ((d->Dc + c.MPW - 1) / c.MPW);
-    if (c.quads) return ((long long)c.panels + 7) / 8 * 8;               // a whole number per XCD; what is beyond the last one exits
+    const long long channels = (long long)d->Bt * ((d->Dc + c.MPW - 1) / c.MPW);
+    if (c.tile) return channels;
+    if (c.quads) return (channels + 7) / 8 * 8;                          // a whole number per XCD; what is beyond the last one exits
     return ((long long)d->Bt * d->Dc + c.MPW - 1) / c.MPW;
 }
 
@@ -653,6 +654,7 @@ int fwd_impl(const scan2d_desc* desc, const void* x, const void* delta, const fl
     a.maps = (long long)desc->Bt * desc->Dc;
     a.Dc = desc->Dc; a.H = desc->H; a.W = desc->W; a.N = desc->N;
     a.NG = ch.NG; a.MPW = ch.MPW; a.panels = ch.panels; a.RPB = ch.RPB;
+    if (ch.quads) { a.quad_cols = ch.waves / 2; a.quad_groups = (desc->Dc + ch.MPW - 1) / ch.MPW; a.quad_wgs = desc->Bt * a.quad_groups; }
     const long long wgs = fwd_wgs(desc, ch);
     if (wgs > 2147483647LL) return SCAN2D_ERR_BAD_SHAPE;
     if (z != nullptr && y_gated != nullptr && softplus != 0 && !ch.cf && !ch.skew) {               // the gate in the same kernel

@@ -71,6 +71,9 @@ struct FwdArgs {
     int MPW;             // maps per workgroup = (lane groups per workgroup) / NG, >= 1
     int panels;          // ceil(W / (LG * K))
     int RPB;             // rows between two workgroup barriers (1, 2, 4 or 8); sizes the dynamic LDS
+    // the kernel for many maps only (scan2d_fwd_quads.hpp): wavefronts along the columns (the workgroup has twice as many), workgroups
+    // per batch item, and their total (the grid is rounded up to a multiple of the eight XCDs)
+    int quad_cols = 0, quad_groups = 0, quad_wgs = 0;
 };
 
 // FAST (single-panel maps, any W): every lane reads its K columns with one wide buffer load per tensor.

@@ -95,8 +95,7 @@ template <int K> constexpr size_t quad_lds_bytes(int cols) {
 // wavefronts per SIMD that the registers leave room for
 template <int K> constexpr int quad_waves() { return K <= 4 ? 4 : (K <= 8 ? 3 : 2); }
 
-// GATE: as in scan2d_fwd_shared.hpp.  p.NG: wavefronts along the columns, the workgroup has twice as many; p.MPW: workgroups per
-// batch item, ceil(Dc / 8); p.panels: the total of workgroups (the grid is rounded up to a multiple of the eight XCDs).
+// GATE: as in scan2d_fwd_shared.hpp.
 template <typename T, int K, bool SP, bool GATE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<K>()))) void scan2d_fwd_quads_kernel(const FwdArgs p) {
     constexpr int N = 16, NS = 4;                          // states, states per lane
@@ -115,14 +114,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(quad_waves<
     // consecutive workgroups go to the eight XCDs in turn: each XCD takes a contiguous range, so that the channels of a batch item
     // find its Bm and Cm in one L2
     const int wg = (int)(blockIdx.x & 7u) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    if (wg >= p.panels) return;                            // uniform over the workgroup
-    const int b = wg / p.MPW;
+    if (wg >= p.quad_wgs) return;                            // uniform over the workgroup
+    const int b = wg / p.quad_groups;
 
     extern __shared__ float smem[];
-    const int cols = p.NG;
+    const int cols = p.quad_cols;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wc = wave >> 1, quad = wave & 1;             // place along the columns; quad of channels, and which of Bm, Cm it fetches
-    const int c0 = (wg - b * p.MPW) * 8 + quad * 4;        // may be past the last channel (Dc % 8 <= 4): nothing is stored then
+    const int c0 = (wg - b * p.quad_groups) * 8 + quad * 4;        // may be past the last channel (Dc % 8 <= 4): nothing is stored then
     const int lane = threadIdx.x & 63;
     const int ch = lane & 3, sg = (lane >> 2) & 3, blk = lane >> 4;
     const int cstride = quad_carry(cols);

@@ -265,6 +265,7 @@ def test_benchmark_configurations_take_the_intended_forms(lib):
     f = plan(lib, lib.Desc(32, 192, 56, 56, 16, 1, 0), lib.PASS_FWD)
     # 24 maps per compute unit: eight channels per workgroup, two wavefronts of four 7-column blocks
     assert (f["form"], f["K"], f["waves"], f["wgs"]) == ("quads", 7, 4, 768) and f["fast"]
+    assert (f["NG"], f["MPW"], f["panels"]) == (4, 8, 1)     # four state groups, eight maps per workgroup, one panel
     f = plan(lib, lib.Desc(1, 256, 64, 64, 16, 0, 0), lib.PASS_FWD)
     assert (f["form"], f["LG"], f["K"], f["NW"]) == ("shared", 16, 4, 1)
     f = plan(lib, lib.Desc(1, 16, 16, 16, 4, 0, 0), lib.PASS_FWD)
