@@ -92,7 +92,7 @@ enum { SCAN2D_FLAG_IDENTITY_CELLS = 1 };
  */
 enum { SCAN2D_FLAG_COLUMNS_FIRST = 2 };
 enum { SCAN2D_PASS_FWD = 0, SCAN2D_PASS_BWD = 1, SCAN2D_PASS_BWD_GATED = 2, SCAN2D_PASS_BWD_SOFTPLUS = 3,
-       SCAN2D_PASS_FWD_VARIANTS = 4, SCAN2D_PASS_BWD_VARIANTS = 5 };
+       SCAN2D_PASS_FWD_VARIANTS = 4, SCAN2D_PASS_BWD_VARIANTS = 5, SCAN2D_PASS_FWD_SOFTPLUS = 6 };
 
 typedef struct {
     int32_t  Bt, Dc, H, W, N;  /* batch, channels, grid height, grid width, states: all >= 1, N <= 64 */
@@ -374,7 +374,7 @@ int scan2d_bwd_static_scratch(const scan2d_desc* desc,
                               void* dx, void* ddelta, float* dA, float* dBm, float* dCm, float* dDskip,
                               void* stream);
 
-/* Bytes of workspace a call with this descriptor needs (pass = SCAN2D_PASS_FWD for the three forward
+/* Bytes of workspace a call with this descriptor needs (pass = SCAN2D_PASS_FWD or _FWD_SOFTPLUS for each of the three forward
  * calls, SCAN2D_PASS_BWD / _BWD_SOFTPLUS / _BWD_GATED for scan2d_bwd / _bwd_softplus / _bwd_softplus_gated).
  * Returns 0 for an invalid descriptor (the call itself then reports the error). */
 size_t scan2d_workspace_bytes(const scan2d_desc* desc, int pass);
@@ -387,7 +387,8 @@ size_t scan2d_workspace_bytes(const scan2d_desc* desc, int pass);
  * `text_bytes` bytes including the terminating 0).  The workspace figure is that of the scan kernels alone
  * (without the buffers of the gate, the identity cells and the columns-first order); with
  * SCAN2D_FLAG_COLUMNS_FIRST the text starts with "columns-first(in-kernel)" or with "columns-first(transposed)",
- * and the plan is then that of the transposed maps.  Touches no device memory and enqueues nothing.
+ * and the plan is then that of the transposed maps.  SCAN2D_PASS_FWD is the plan of scan2d_fwd and SCAN2D_PASS_FWD_SOFTPLUS that of
+ * scan2d_fwd_softplus and scan2d_fwd_softplus_gated, which may take other forms.  Touches no device memory and enqueues nothing.
  * Returns SCAN2D_OK, or the error code the corresponding call would return for this descriptor.
  */
 int scan2d_describe_plan(const scan2d_desc* desc, int pass, char* text, size_t text_bytes);

@@ -845,7 +845,7 @@ size_t variants_bwd_need(const scan2d_desc* d, bool av, bool pad);
 
 extern "C" size_t scan2d_workspace_bytes(const scan2d_desc* desc, int pass) {
     if (check_desc(desc) != SCAN2D_OK) return 0;
-    if (pass == SCAN2D_PASS_FWD) return fwd_need(desc);
+    if (pass == SCAN2D_PASS_FWD || pass == SCAN2D_PASS_FWD_SOFTPLUS) return fwd_need(desc);
     if (pass == SCAN2D_PASS_FWD_VARIANTS || pass == SCAN2D_PASS_BWD_VARIANTS) {   // enough for any combination of the variants
         if (desc->flags != 0u) return 0;
         size_t need = 0;
@@ -867,7 +867,8 @@ extern "C" int scan2d_describe_plan(const scan2d_desc* desc, int pass, char* tex
     int rc = check_desc(desc);
     if (rc != SCAN2D_OK) return rc;
     const bool bwd_pass = pass == SCAN2D_PASS_BWD || pass == SCAN2D_PASS_BWD_SOFTPLUS || pass == SCAN2D_PASS_BWD_GATED;
-    const bool fused = pass == SCAN2D_PASS_FWD ? fwd_fused_cf(desc) : (bwd_pass && bwd_fused_cf(desc, pass != SCAN2D_PASS_BWD));
+    const bool sp = pass == SCAN2D_PASS_FWD_SOFTPLUS, fwd_pass = pass == SCAN2D_PASS_FWD || sp;
+    const bool fused = fwd_pass ? fwd_fused_cf(desc) : (bwd_pass && bwd_fused_cf(desc, pass != SCAN2D_PASS_BWD));
     if (columns_first(desc) && !fused) {         // the plan of the kernels that run: those of the transposed maps
         const scan2d_desc t = swapped(desc);
         const int n = std::snprintf(text, text_bytes, "columns-first(transposed) ");
@@ -875,9 +876,9 @@ extern "C" int scan2d_describe_plan(const scan2d_desc* desc, int pass, char* tex
         return scan2d_describe_plan(&t, pass, text + n, text_bytes - (size_t)n);
     }
     if (pass == SCAN2D_PASS_BWD_SOFTPLUS || pass == SCAN2D_PASS_BWD_GATED) pass = SCAN2D_PASS_BWD;   // the same sweeps
-    if (pass == SCAN2D_PASS_FWD) {
+    if (fwd_pass) {
         FwdChoice ch;
-        rc = choose_fwd(desc, &ch, false, true, fused);
+        rc = choose_fwd(desc, &ch, sp, true, fused);
         if (rc != SCAN2D_OK) return rc;
         std::snprintf(text, text_bytes, "%sfwd form=%s LG=%d K=%d NW=%d waves=%d RPB=%d NG=%d MPW=%d panels=%d fast=%d exact=%d wgs=%lld lds=%zu workspace=%zu",
                       fused ? "columns-first(in-kernel) " : "", ch.tile ? "tile16" : ch.quads ? "quads" : (ch.K < 4 ? "small" : (ch.skew ? "skew" : (ch.shared ? "shared" : "general"))), ch.LG, ch.K, ch.NW, ch.waves, ch.RPB, ch.NG, ch.MPW, ch.panels,

@@ -323,3 +323,67 @@ def test_wide_grids_take_the_shared_producer_forms(lib):
     assert (b["form"], b["LG"], b["K"], b["NW"], b["waves"], b["panels"]) == ("banded-shared", 64, 4, 2, 8, 2)
     b = plan(lib, lib.Desc(1, 256, 400, 400, 8, 1, 0), lib.PASS_BWD)
     assert (b["form"], b["LG"], b["K"], b["panels"]) == ("banded", 64, 4, 2)
+
+
+# The kernel for many maps: one shape on each side of every line of its rule; `wgs` batch items of eight channels are as many workgroups.
+# K = 0: another form.  waves: two per column of wavefronts.
+MANY_MAPS = [
+    # 13 to 16 columns: 576 workgroups, 13 rows
+    ("both", 576, 13, 13, 4, 2), ("both", 575, 13, 13, 0, 0), ("both", 576, 12, 16, 0, 0), ("both", 576, 13, 16, 4, 2), ("both", 4096, 48, 12, 0, 0),
+    # from 17 columns on nine rows; to 20 columns 288 workgroups, to 24 columns 384
+    ("both", 288, 9, 17, 5, 2), ("both", 288, 8, 17, 0, 0), ("both", 287, 48, 17, 0, 0), ("both", 288, 48, 20, 5, 2), ("both", 383, 48, 21, 0, 0),
+    ("both", 384, 48, 21, 6, 2), ("both", 384, 9, 24, 6, 2),
+    # to 32 columns: two columns of wavefronts from 384 workgroups and 24 rows on, one from 512 workgroups on
+    ("both", 383, 48, 25, 0, 0), ("both", 384, 24, 25, 4, 4), ("both", 384, 23, 25, 0, 0), ("both", 511, 24, 32, 4, 4), ("both", 512, 23, 32, 8, 2),
+    ("both", 512, 48, 25, 7, 2),
+    # 33 to 48 columns: 641 workgroups, or 432 up to 48 columns in bf16, 40 in fp32 and 36 with the softplus step
+    ("both", 431, 48, 33, 0, 0), ("both", 432, 48, 33, 5, 4), ("both", 432, 48, 36, 5, 4), ("sp", 640, 48, 37, 0, 0), ("bf16", 432, 48, 37, 5, 4),
+    ("f32", 432, 48, 40, 5, 4), ("f32", 640, 48, 41, 0, 0), ("f32", 641, 48, 41, 11, 2), ("bf16", 432, 48, 48, 6, 4), ("bf16", 512, 48, 49, 0, 0),
+    # one column of wavefronts: in fp32 always, in bf16 where the last round of four workgroups per compute unit is more than three
+    # quarters full
+    ("f32 sp", 641, 48, 48, 12, 2), ("f32", 641, 48, 48, 12, 2), ("f32", 640, 48, 40, 5, 4), ("bf16 sp", 641, 48, 48, 6, 4), ("bf16 sp", 768, 48, 45, 6, 4),
+    ("bf16 sp", 769, 48, 45, 12, 2), ("bf16", 768, 48, 45, 6, 4), ("bf16", 769, 48, 45, 12, 2), ("bf16", 1024, 48, 33, 9, 2), ("bf16", 1025, 48, 33, 5, 4),
+    # 49 to 64 columns: 641 workgroups, 513 for the plain scan in bf16 up to 56 columns
+    ("bf16", 513, 48, 49, 7, 4), ("bf16", 513, 48, 56, 7, 4), ("bf16", 513, 48, 57, 0, 0), ("bf16", 640, 48, 64, 0, 0), ("bf16", 641, 48, 57, 8, 4),
+    ("f32", 640, 48, 49, 0, 0), ("f32", 1025, 48, 49, 7, 4), ("sp", 640, 48, 49, 0, 0), ("bf16 sp", 641, 48, 56, 7, 4),
+    # with the softplus step in bf16 beyond 56 columns: whole blocks or a last round that is nearly full
+    ("bf16 sp", 896, 48, 57, 0, 0), ("bf16 sp", 897, 48, 57, 15, 2), ("bf16 sp", 1024, 48, 63, 16, 2), ("bf16 sp", 1025, 48, 63, 0, 0),
+    ("bf16 sp", 641, 48, 64, 8, 4), ("bf16 sp", 1025, 48, 64, 8, 4),
+    # one column of wavefronts: the last round of four more than three quarters full; in fp32 up to 60 columns with the step always,
+    # without it also where a last round of three is more than two thirds full
+    ("both", 1024, 48, 64, 16, 2), ("bf16", 768, 48, 60, 8, 4), ("bf16", 769, 48, 60, 15, 2), ("f32 sp", 1025, 48, 60, 15, 2), ("f32 sp", 1025, 48, 61, 8, 4),
+    ("f32", 768, 48, 60, 15, 2), ("f32", 768, 48, 61, 8, 4), ("f32", 1281, 48, 60, 15, 2), ("f32", 1280, 48, 60, 8, 4), ("both", 4096, 48, 65, 0, 0),
+]
+
+
+@pytest.mark.parametrize("which,wgs,H,W,K,waves", MANY_MAPS, ids=["-".join(map(str, c[:4])) for c in MANY_MAPS])
+def test_many_maps_take_eight_channels_per_workgroup(lib, which, wgs, H, W, K, waves):
+    ways = [(dt, sp) for dt in (0, 1) for sp in (False, True)]
+    if which != "both":
+        dts = [0] if "f32" in which else [1] if "bf16" in which else [0, 1]
+        ways = [(dt, "sp" in which) for dt in dts]
+    for dt, sp in ways:
+        f = plan(lib, lib.Desc(wgs, 8, H, W, 16, dt, 0), lib.PASS_FWD_SOFTPLUS if sp else lib.PASS_FWD)
+        if K:
+            assert (f["form"], f["K"], f["waves"], f["wgs"]) == ("quads", K, waves, -(-wgs // 8) * 8), (dt, sp, f)
+            assert (f["NG"], f["MPW"], f["panels"], f["workspace"]) == (4, 8, 1, 0)
+            assert waves // 2 * 4 * (K - 1) < W <= waves // 2 * 4 * K
+        else:
+            assert f["form"] != "quads", (dt, sp, f)
+
+
+def test_many_maps_need_sixteen_states_and_few_idle_channels(lib):
+    form = lambda Bt, Dc, N=16, flags=0: plan(lib, lib.Desc(Bt, Dc, 28, 28, N, 1, flags), lib.PASS_FWD)["form"]
+    assert form(48, 96) == "quads" and form(48, 96, 15) != "quads" and form(48, 96, 17) != "quads"
+    # at most one channel in nine is idle
+    assert form(512, 15) == "quads" and form(512, 14) != "quads" and form(512, 9) != "quads" and form(1024, 7) != "quads" and form(300, 22) == "quads"
+    assert form(48, 96, 16, lib.FLAG_IDENTITY_CELLS) == "quads"
+
+
+def test_plans_with_and_without_the_softplus_step_are_told_apart(lib):
+    """The forms are ranked for each of them."""
+    d = lib.Desc(720, 8, 48, 60, 16, 1, 0)
+    assert plan(lib, d, lib.PASS_FWD)["form"] == "quads" and plan(lib, d, lib.PASS_FWD_SOFTPLUS)["form"] == "shared"
+    assert lib.workspace_bytes(d, lib.PASS_FWD_SOFTPLUS) == lib.workspace_bytes(d, lib.PASS_FWD)
+    assert lib.describe_plan(lib.Desc(2, 8, 20, 40, 16, 0, lib.FLAG_COLUMNS_FIRST), lib.PASS_FWD_SOFTPLUS).startswith("columns-first(in-kernel) fwd form=shared")
+    assert lib.describe_plan(lib.Desc(2, 8, 20, 40, 5, 0, lib.FLAG_COLUMNS_FIRST), lib.PASS_FWD_SOFTPLUS).startswith("columns-first(transposed) fwd")
