@@ -305,6 +305,11 @@ bool choose_quads(const scan2d_desc* d, bool sp, FwdChoice* out) {
     bool one;
     if (W <= 48) one = wgs > 640 && (bf16 ? layers % 4 == 0 : true);
     else one = layers % 4 == 0 || (!bf16 && W <= 60 && (sp || layers % 3 == 0));
+    // two columns of wavefronts take two batches of four rows more than the other forms, which round the rows up to such batches, or one
+    // where the height is one past a batch.  From 49 columns on that is too much of few rows (other / two, us: bf16 1400 workgroups of 10 x 60
+    // 57 / 71, 1489 of 11 x 62 62 / 69, 1028 of 15 x 62 61 / 70, 1320 of 19 x 58 89 / 95; fp32 1608 of 12 x 50 66 / 73; but bf16 of 9 rows
+    // 1.15, with the step and the gate 1.27 times as fast, geometric means, of 21 to 24 rows 1.2 and 1.17)
+    if (!one && W > 48 && d->H < 21 && d->H % 4 != 1) return false;
     return one ? fill_quads(d, (W + 3) / 4, 1, sp, out) : fill_quads(d, (W + 7) / 8, 2, sp, out);
 }
 
