@@ -303,7 +303,9 @@ bool choose_quads(const scan2d_desc* d, bool sp, FwdChoice* out) {
     // where the last round of workgroups is nearly full
     if (bf16 && sp && W > 56 && W % 8 != 0 && (wgs + 127) % 1024 >= 128) return false;
     bool one;
-    if (W <= 48) one = wgs > 640 && (bf16 ? layers % 4 == 0 : true);
+    // fp32: two columns of wavefronts are bound by the last of three workgroups where that is nearly alone (other / two / one, us: 544 of 43 x 35
+    // 100 / 107 / 81, with the step 120 / 138 / 99; 562 of 49 x 34, with the step, 138 / 150 / 108)
+    if (W <= 48) one = bf16 ? wgs > 640 && layers % 4 == 0 : wgs > 512;
     else one = layers % 4 == 0 || (!bf16 && W <= 60 && (sp || layers % 3 == 0));
     // two columns of wavefronts take two batches of four rows more than the other forms, which round the rows up to such batches, or one
     // where the height is one past a batch.  From 49 columns on that is too much of few rows (other / two, us: bf16 1400 workgroups of 10 x 60

@@ -339,9 +339,10 @@ MANY_MAPS = [
     # 33 to 48 columns: 641 workgroups, or 432 up to 48 columns in bf16, 40 in fp32 and 36 with the softplus step
     ("both", 431, 48, 33, 0, 0), ("both", 432, 48, 33, 5, 4), ("both", 432, 48, 36, 5, 4), ("sp", 640, 48, 37, 0, 0), ("bf16", 432, 48, 37, 5, 4),
     ("f32", 432, 48, 40, 5, 4), ("f32", 640, 48, 41, 0, 0), ("f32", 641, 48, 41, 11, 2), ("bf16", 432, 48, 48, 6, 4), ("bf16", 512, 48, 49, 0, 0),
-    # one column of wavefronts: in fp32 always, in bf16 where the last round of four workgroups per compute unit is more than three
+    # one column of wavefronts: in fp32 from 513 workgroups on, in bf16 where the last round of four workgroups per compute unit is more than three
     # quarters full
-    ("f32 sp", 641, 48, 48, 12, 2), ("f32", 641, 48, 48, 12, 2), ("f32", 640, 48, 40, 5, 4), ("bf16 sp", 641, 48, 48, 6, 4), ("bf16 sp", 768, 48, 45, 6, 4),
+    ("f32 sp", 641, 48, 48, 12, 2), ("f32", 641, 48, 48, 12, 2), ("f32", 640, 48, 40, 10, 2), ("f32 sp", 513, 48, 36, 9, 2), ("f32", 512, 48, 40, 5, 4),
+    ("bf16 sp", 641, 48, 48, 6, 4), ("bf16 sp", 768, 48, 45, 6, 4),
     ("bf16 sp", 769, 48, 45, 12, 2), ("bf16", 768, 48, 45, 6, 4), ("bf16", 769, 48, 45, 12, 2), ("bf16", 1024, 48, 33, 9, 2), ("bf16", 1025, 48, 33, 5, 4),
     # 49 to 64 columns: 641 workgroups, 513 for the plain scan in bf16 up to 56 columns
     ("bf16", 513, 48, 49, 7, 4), ("bf16", 513, 48, 56, 7, 4), ("bf16", 513, 48, 57, 0, 0), ("bf16", 640, 48, 64, 0, 0), ("bf16", 641, 48, 57, 8, 4),
