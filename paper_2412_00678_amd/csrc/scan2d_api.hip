@@ -307,6 +307,10 @@ bool choose_quads(const scan2d_desc* d, bool sp, FwdChoice* out) {
     // 100 / 107 / 81, with the step 120 / 138 / 99; 562 of 49 x 34, with the step, 138 / 150 / 108)
     if (W <= 48) one = bf16 ? wgs > 640 && layers % 4 == 0 : wgs > 512;
     else one = layers % 4 == 0 || (!bf16 && W <= 60 && (sp || layers % 3 == 0));
+    // bf16, just past three workgroups per compute unit: two columns start a second round for a few workgroups, one fills a quarter of its fourth (other /
+    // two / one, us: 804 of 32 x 62 78 / 96 / 91, 792 of 32 x 60 80 / 98 / 88, 816 of 42 x 60 104 / 124 / 114; with the step and the gate, of 56 x 10,
+    // 41 / 54 / 48, of 16 x 52 51 / 65 / 55)
+    if (bf16 && W > 48 && wgs > 768 && wgs <= 832) return false;
     // two columns of wavefronts take two batches of four rows more than the other forms, which round the rows up to such batches, or one
     // where the height is one past a batch.  From 49 columns on that is too much of few rows (other / two, us: bf16 1400 workgroups of 10 x 60
     // 57 / 71, 1489 of 11 x 62 62 / 69, 1028 of 15 x 62 61 / 70, 1320 of 19 x 58 89 / 95; fp32 1608 of 12 x 50 66 / 73; but bf16 of 9 rows

@@ -352,12 +352,15 @@ MANY_MAPS = [
     ("bf16 sp", 641, 48, 64, 8, 4), ("bf16 sp", 1025, 48, 64, 8, 4),
     # one column of wavefronts: the last round of four more than three quarters full; in fp32 up to 60 columns with the step always,
     # without it also where a last round of three is more than two thirds full
-    ("both", 1024, 48, 64, 16, 2), ("bf16", 768, 48, 60, 8, 4), ("bf16", 769, 48, 60, 15, 2), ("f32 sp", 1025, 48, 60, 15, 2), ("f32 sp", 1025, 48, 61, 8, 4),
+    ("both", 1024, 48, 64, 16, 2), ("bf16", 768, 48, 60, 8, 4), ("bf16", 832, 48, 60, 0, 0), ("bf16", 833, 48, 60, 15, 2), ("f32 sp", 1025, 48, 60, 15, 2), ("f32 sp", 1025, 48, 61, 8, 4),
     ("f32", 768, 48, 60, 15, 2), ("f32", 768, 48, 61, 8, 4), ("f32", 1281, 48, 60, 15, 2), ("f32", 1280, 48, 60, 8, 4), ("both", 4096, 48, 65, 0, 0),
     # two columns of wavefronts from 49 columns on: 21 rows, or 9, 13 and 17
     ("bf16", 641, 21, 57, 8, 4), ("bf16", 641, 20, 57, 0, 0), ("bf16 sp", 641, 18, 49, 0, 0), ("both", 1025, 17, 64, 8, 4), ("both", 1025, 16, 64, 0, 0),
     ("both", 1025, 13, 64, 8, 4), ("f32", 1281, 12, 61, 0, 0), ("f32", 1281, 9, 61, 8, 4), ("bf16", 641, 12, 48, 6, 4), ("f32 sp", 641, 12, 60, 15, 2),
     ("both", 1024, 10, 64, 16, 2),
+    # bf16 from 49 columns on: not just past three workgroups per compute unit
+    ("bf16", 768, 48, 49, 7, 4), ("bf16", 769, 48, 49, 0, 0), ("bf16 sp", 768, 48, 64, 8, 4), ("bf16 sp", 769, 48, 64, 0, 0), ("bf16 sp", 832, 48, 56, 0, 0),
+    ("bf16 sp", 833, 48, 56, 14, 2), ("bf16", 1800, 48, 56, 14, 2), ("f32", 769, 48, 60, 15, 2), ("bf16", 769, 48, 48, 12, 2),
 ]
 
 
