@@ -250,6 +250,7 @@ FwdKernel fwd_quads_kernel(int dtype, int K, bool sp, bool gate) {
     return dtype == SCAN2D_BF16 ? fwd_quads_kernel_bf16(K, sp, gate) : fwd_quads_kernel_f32(K, sp, gate);
 }
 // Eight channels of a batch item per workgroup (scan2d_fwd_quads.hpp): two times `cols` wavefronts of four blocks of K or K - 1 columns.
+// The rule below asks for one or two columns of wavefronts; three and four are for the tuning override, and for the tests that force them.
 bool fill_quads(const scan2d_desc* d, int K, int cols, bool sp, FwdChoice* out) {
     if (d->N != 16 || cols < 1 || cols > 4 || d->W > 4 * cols * K || d->W <= 4 * cols * (K - 1)) return false;
     const long long wgs = (long long)d->Bt * ((d->Dc + 7) / 8);

@@ -19,7 +19,7 @@
 // (6144 maps of 56x56 bf16: 9.3, where the shared-producer form needs 14.5).
 // What bounds it: with three wavefronts per SIMD vector issue (56x56 bf16 134 -> 111 us, the vector ALU at 78 % of the time; 28x28 67 ->
 // 38); in fp32 and with the gate the L2, which holds the lines that a block has begun until its neighbours have passed (56x56 bf16 gated
-// 157 -> 150; streaming hints on the stores make that 166, on the loads too 190); with one wavefront per SIMD the chain of a step, LDS,
+// 161 -> 150; streaming hints on the stores make that 166, on the loads too 190); with one wavefront per SIMD the chain of a step, LDS,
 // seven columns one after the other and the barrier: 0.9 us where the instructions take 0.45.  x, the step and z by
 // elements instead of pairs: 6 % more; a first form in which every quad fetched Bm and Cm for itself, by unaligned loads: 215 us.
 // The backward pass's checkpoints do not come from here: a block's 28-byte pieces of their rows took longer to write than the
@@ -92,7 +92,9 @@ template <int K> constexpr size_t quad_lds_bytes(int cols) {
     return ((size_t)2 * 8 * quad_carry(cols) + (size_t)cols * (2 * 4 * quad_row<K>() + 2 * quad_sets<K>() * quad_bc<K>())) * sizeof(float);
 }
 
-// wavefronts per SIMD that the registers leave room for
+// wavefronts per SIMD that the registers leave room for.  One instantiation does not fit: 16 columns, bf16, with the step and the gate, spills five
+// registers (24 bytes of scratch per lane); it is still the faster one where it is chosen (8192 maps of 64x64: 213 us, K = 8 on two columns of
+// wavefronts 228, the other forms 242).
 template <int K> constexpr int quad_waves() { return K <= 4 ? 4 : (K <= 8 ? 3 : 2); }
 
 // GATE: as in scan2d_fwd_shared.hpp.
